@@ -16,6 +16,7 @@
 #include "gemm_decode.h"
 #include "gemm_epilogue.h"
 #include "lds_dma.h"
+#include "scale_windows.h"
 
 #include <hip/hip_fp16.h>
 
@@ -149,7 +150,16 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(
 // swizzle with a period of 8 rows spent half of the LDS-active cycles on bank conflicts).
 // A wave-wide DMA instruction writes lane l to (uniform base) + 16 l, so the swizzle is applied
 // by choosing which global piece each lane fetches.
-template <int WM, int WN, int GM, int GN>
+//
+// How the stages get into LDS (MODE):
+//   COPIES   direct-to-LDS copies of whole 16-byte pieces; K' % 64 == 0, codes 16-byte and scale bytes 4-byte aligned;
+//   RAGGED   the same for any K' (a multiple of 16) from 256 on: rows of codes then start on 8-byte boundaries, which the
+//            copies take (they need dwords), and the scale bytes come as dword-aligned windows (scale_windows.h).  Pieces past
+//            the end of a row are fetched from further left and their blocks get scale 0; if only the second block of a
+//            piece is missing, the piece is the row's last two blocks and the scale of the first is 0.  The base of the scale
+//            bytes has to be 4-byte aligned;
+//   REGS     through registers, for what is left (short K', scale bytes at odd addresses), see below.
+template <int WM, int WN, int GM, int GN, int MODE = COPIES>
 struct StagedCfg {
     static constexpr int BM = 32 * WM * GM, BN = 32 * WN * GN;
     static constexpr int NT = 64 * GM * GN;              // threads
@@ -159,32 +169,36 @@ struct StagedCfg {
     // number of copies, which the counted waits rely on).
     static constexpr int NA = (BM * 4 + NT - 1) / NT, NW = (BN * 4 + NT - 1) / NT;
     static constexpr int NAS = (BM * 2 + NT - 1) / NT, NWS = (BN * 2 + NT - 1) / NT;
-    static constexpr int NDMA = NA + NW + NAS + NWS;
+    using Windows = ScaleWindows<BM, BN, NT, 8>;
+    static constexpr int NSW = MODE == RAGGED ? Windows::NS : 0;           // copies of windows come first
+    static constexpr int NDMA = NA + NW + (MODE == RAGGED ? NSW : NAS + NWS);
     static constexpr int A_CODES = 0;
     static constexpr int W_CODES = NA * NT * 16;
     static constexpr int A_SCALES = W_CODES + NW * NT * 16;
-    static constexpr int W_SCALES = A_SCALES + NAS * NT * 4;
-    static constexpr int STAGE_BYTES = W_SCALES + NWS * NT * 4;
+    static constexpr int W_SCALES = A_SCALES + (MODE == RAGGED ? Windows::DENSE_W : NAS * NT * 4);
+    static constexpr int WINDOWS = A_SCALES + Windows::DENSE_BYTES;
+    static constexpr int STAGE_BYTES = MODE == RAGGED ? WINDOWS + Windows::BYTES : W_SCALES + NWS * NT * 4;
     // Ring depth: a stage is fetched NSTAGE - 1 stages before it is computed (3 measured as good as 5).
     static constexpr int NSTAGE = 3;
     static constexpr int DIST = NSTAGE - 1;
-    static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;
+    static constexpr int PATCH = NSTAGE * STAGE_BYTES;      // RAGGED: see ScaleWindows::fill_patch
+    static constexpr int LDS_BYTES = PATCH + (MODE == RAGGED ? 2 * Windows::PATCH : 0);
 };
 
 //
-// REG: the same tiles, LDS layout and compute schedule for operands the direct-to-LDS copies cannot serve: any
-// number of blocks per row (K' a multiple of 16 only) and rows that are only 8-byte aligned.  A thread fetches
+// REGS: the same tiles, LDS layout and compute schedule for operands the direct-to-LDS copies cannot serve.  A thread fetches
 // its pieces of a stage into registers (loads declared with the alignment the interface guarantees, 8 bytes
 // for codes and 1 for scale bytes), all at once right after the barrier that opens
 // stage s+1, and writes them to LDS seven k-steps later, just before the barrier that opens the stage they
 // belong to, with blocks past the end of the row replaced by zeros: every stage is then a whole stage.
-template <int WM, int WN, int GM, int GN, typename OutT, bool REG = false>
+template <int WM, int WN, int GM, int GN, typename OutT, int MODE = COPIES>
 __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N,
     int nbk, float alpha, OutT* __restrict__ y, int64_t ldy, int tiles_m, int tiles_n, int splits,
     int64_t split_stride) {
-    using C = StagedCfg<WM, WN, GM, GN>;
+    using C = StagedCfg<WM, WN, GM, GN, MODE>;
+    constexpr bool REG = MODE == REGS, RAG = MODE == RAGGED;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     // ---- workgroup -> tile.  Workgroups are dealt round-robin to the 8 XCDs (each with its
@@ -218,8 +232,8 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
     // When K' is an odd multiple of 64 the last stage is half a stage (4 blocks): the lanes that
     // would fetch its missing second half re-fetch the first half instead (never used), which
     // keeps every access inside the operand.  `half` selects those adjusted offsets.
-    const bool has_half = !REG && (nbk & 7) != 0;
-    const int nstage = REG ? (nbk + 7) >> 3 : (nbk >> 3) + (has_half ? 1 : 0);   // of the whole reduction dimension
+    const bool has_half = MODE == COPIES && (nbk & 7) != 0;
+    const int nstage = MODE != COPIES ? (nbk + 7) >> 3 : (nbk >> 3) + (has_half ? 1 : 0);   // of the whole reduction dimension
     const int per_split = nstage / splits, extra = nstage % splits;
     const int s_begin = split * per_split + min(split, extra);  // this workgroup's stages [s_begin, s_end)
     const int s_end = s_begin + per_split + (split < extra ? 1 : 0);
@@ -234,11 +248,18 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
     // of all copies are computed on the scalar unit
     const uint32_t wave_slot = __builtin_amdgcn_readfirstlane((uint32_t)(tid & ~63));
     const uint32_t lds0 = lds_address(lds);
-    // DMA instruction d (0 .. NDMA-1) of a stage: A code pieces, W code pieces, A scales, W scales.
+    const typename C::Windows windows = {a_scales, w_scales, M, N, nbk, wg_m0, wg_n0, (uint32_t)tid, wave_slot};    // RAGGED
+    const int patch_from = C::Windows::patch_from(nbk);
+    // DMA instruction d (0 .. NDMA-1) of a stage: (RAGGED: scale windows,) A code pieces, W code pieces, A scales, W scales.
     auto issue_one = [&](int d, int stage, int buf) {
         const uint32_t base = lds0 + buf * C::STAGE_BYTES;
         const bool half = has_half && stage == nstage - 1;
-        const uint32_t oc = (uint32_t)stage * 64u + (half ? adj_c1 : adj_c0);
+        const uint32_t oc = RAG ? 8u * (uint32_t)min(8 * stage + 2 * (int)lp_, nbk - 2) : (uint32_t)stage * 64u + (half ? adj_c1 : adj_c0);
+        if (RAG && d < C::NSW) {
+            windows.issue(d, stage, base + C::WINDOWS);
+            return;
+        }
+        d -= C::NSW;
         const uint32_t os = (uint32_t)stage * 8u + (half ? 0u : adj_s);
         constexpr int NA = C::NA, NW = C::NW, NAS = C::NAS, NT = C::NT;
         // rows past the edge of the operand re-read its last row (never stored)
@@ -263,7 +284,7 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
 #pragma unroll
         for (int d = 0; d < C::NDMA; ++d) issue_one(d, stage, buf);
     };
-    // ---- REG: the same pieces through registers (piece d of a thread lands where DMA instruction d puts it).
+    // ---- REGS: the same pieces through registers (piece d of a thread lands where DMA instruction d puts it).
     // A piece that would reach past the end of its row is fetched from further left, so that it ends with the row
     // (needs nbk >= 4), and shifted into place when it is written to LDS.
     constexpr int NCP = C::NA + C::NW, NSP = C::NAS + C::NWS;
@@ -383,8 +404,15 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
     // keeps reading and decoding a "next" stage whose values are never used.
     int buf = 0;                                // ring slot of the stage being computed
     auto ring_next = [](int b) { return b == C::NSTAGE - 1 ? 0 : b + 1; };
-    auto run_stage = [&](int s, auto nsteps_tag) {
+    // RAGGED: the wanted scale bytes of stage s+1 are picked out of their windows during step FIX (read) and the one after
+    // (write), one copy per step.  tail_tag: the stage before one whose windows or blocks may pass the end (the last two);
+    // all others know that they are whole.
+    constexpr int FIX = 3;
+    auto copies_before = [](int x) { return (x * C::NDMA + 5) / 6; };    // copies of a stage issued before step x <= 6
+    uint3 win[RAG ? 2 : 1];
+    auto run_stage = [&](int s, auto nsteps_tag, auto tail_tag) {
         constexpr int NSTEPS = decltype(nsteps_tag)::value;
+        constexpr bool TAIL = decltype(tail_tag)::value;
         constexpr bool FULL = NSTEPS == 8;      // a half stage is always the last one
         const uint8_t* st = lds + buf * C::STAGE_BYTES;
         // the copies issued during this stage go to the slot of the stage computed before this one
@@ -393,12 +421,23 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
 #pragma unroll
         for (int x = 0; x < NSTEPS; ++x) {
             if (x == 0 && FULL) read_raw(1, st);
+            if constexpr (RAG) {
+                uint8_t* next = lds + buf1 * C::STAGE_BYTES;
+                if (x >= FIX && x < FIX + C::NSW) {
+                    // windows of stage s+1: the code copies of that stage and the copies issued in this one are younger
+                    if (x == FIX) wait_vmcnt<C::NA + C::NW + (FIX * C::NDMA + 5) / 6>();
+                    win[(x - FIX) & 1] = windows.gather(x - FIX, next + C::WINDOWS, TAIL, lds + C::PATCH + 8 * (s + 1 - patch_from));
+                }
+                if (x > FIX && x <= FIX + C::NSW)
+                    windows.template put<true>(x - FIX - 1, win[(x - FIX - 1) & 1], next + C::A_SCALES, TAIL, s + 1);
+            }
             if (x == 6) {
                 // stage s+1 must have landed: the copies of the DIST - 1 later stages are younger, and
                 // everything older has retired once at most that many operations are outstanding
-                // (REG: this wave's LDS writes of stage s+1 must have completed)
+                // (REGS: this wave's LDS writes of stage s+1 must have completed)
                 if constexpr (REG) wait_lgkmcnt0();
                 else wait_vmcnt<(C::DIST - 1) * C::NDMA>();
+                if constexpr (RAG) wait_lgkmcnt0();         // this wave's scale bytes of stage s+1 are written
                 wg_barrier();
                 read_raw(0, lds + buf1 * C::STAGE_BYTES);
                 if constexpr (REG) reg_issue(min(s + 2, s_end - 1));
@@ -422,7 +461,7 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
                 if (!REG && FULL && x < 6) {    // copies of stage s + NSTAGE - 1, spread over steps 0..5
 #pragma unroll
                     for (int d = 0; d < C::NDMA; ++d)
-                        if ((d * 6) / C::NDMA == x && (d - (x * C::NDMA + 5) / 6) == p) issue_one(d, fetch, buf2);
+                        if ((d * 6) / C::NDMA == x && d - copies_before(x) == p) issue_one(d, fetch, buf2);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -443,15 +482,25 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
     } else {
 #pragma unroll
         for (int d = 0; d < C::DIST; ++d) issue_all(min(s_begin + d, s_end - 1), d);
+        if constexpr (RAG) windows.fill_patch(lds + C::PATCH);
         wait_vmcnt<(C::DIST - 1) * C::NDMA>();
+        if constexpr (RAG) {                    // (runs of a split are at least four stages long: the first is whole)
+#pragma unroll
+            for (int d = 0; d < C::NSW; ++d)
+                windows.template put<true>(d, windows.gather(d, lds + C::WINDOWS, false, nullptr), lds + C::A_SCALES, false, 0);
+            wait_lgkmcnt0();
+        }
     }
     wg_barrier();
     read_raw(0, lds);
 #pragma unroll
     for (int gidx = 0; gidx < G; ++gidx) decode_frag(gidx, 0);
-    const int nfull = REG ? nstage : nbk >> 3;
-    for (int s = s_begin; s < min(s_end, nfull); ++s) run_stage(s, std::integral_constant<int, 8>{});
-    if (has_half && s_end == nstage) run_stage(nfull, std::integral_constant<int, 4>{});
+    const int nfull = MODE != COPIES ? nstage : nbk >> 3;
+    int s = s_begin;
+    if constexpr (RAG)
+        for (; s < min(s_end, patch_from - 1); ++s) run_stage(s, std::integral_constant<int, 8>{}, std::false_type{});
+    for (; s < min(s_end, nfull); ++s) run_stage(s, std::integral_constant<int, 8>{}, std::integral_constant<bool, RAG>{});
+    if (has_half && s_end == nstage) run_stage(nfull, std::integral_constant<int, 4>{}, std::false_type{});
     wait_vmcnt<0>();                            // no copy may still be in flight when the LDS is released
 
     const int m0 = wg_m0 + wrow0, n0 = wg_n0 + wcol0;
@@ -475,13 +524,14 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
 // matrix rate of the bigger ones) over one half of every stage: four of its eight k-steps, exactly the
 // 16-byte piece of codes a lane reads per row and stage.  The two waves of a pair (w and w + 4) share a
 // SIMD, so the matrix pipe still draws from two instruction streams; at the end they add their partial
-// tiles through the LDS and each stores one of the two fragment rows.  Needs K' % 128 == 0.
-template <typename OutT>
+// tiles through the LDS and each stores one of the two fragment rows.  MODE: COPIES for K' % 128 == 0, RAGGED otherwise.
+template <typename OutT, int MODE>
 __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N,
     int nbk, float alpha, OutT* __restrict__ y, int64_t ldy, int tiles_m, int tiles_n) {
-    using C = StagedCfg<2, 2, 2, 4>;
+    using C = StagedCfg<2, 2, 2, 4, MODE>;
+    constexpr bool RAG = MODE == RAGGED;
     constexpr int WM = 2, WN = 4;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
@@ -507,7 +557,7 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     const int wg_m0 = tile_m * C::BM, wg_n0 = tile_n * C::BN;
     const int wrow0 = (wq >> 1) * 64;                // first row of this wave inside the A tile
     const int wcol0 = (wq & 1) * 128;                // first row of this wave inside the W tile
-    const int nstage = nbk >> 3;
+    const int nstage = RAG ? (nbk + 7) >> 3 : nbk >> 3;
 
     // ---- copies (see gemm_staged_kernel)
     const uint32_t lp_ = (uint32_t)((tid & 3) ^ ((tid >> 4) & 3));
@@ -516,9 +566,16 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     const uint32_t cpitch32 = (uint32_t)nbk * 8u, spitch32 = (uint32_t)nbk;
     const uint32_t wave_slot = __builtin_amdgcn_readfirstlane((uint32_t)(tid & ~63));
     const uint32_t lds0 = lds_address(lds);
+    const typename C::Windows windows = {a_scales, w_scales, M, N, nbk, wg_m0, wg_n0, (uint32_t)tid, wave_slot};    // RAGGED
+    const int patch_from = C::Windows::patch_from(nbk);
     auto issue_one = [&](int d, int stage, int buf) {
         const uint32_t base = lds0 + buf * C::STAGE_BYTES;
-        const uint32_t oc = (uint32_t)stage * 64u + adj_c0;
+        const uint32_t oc = RAG ? 8u * (uint32_t)min(8 * stage + 2 * (int)lp_, nbk - 2) : (uint32_t)stage * 64u + adj_c0;
+        if (RAG && d < C::NSW) {
+            windows.issue(d, stage, base + C::WINDOWS);
+            return;
+        }
+        d -= C::NSW;
         const uint32_t os = (uint32_t)stage * 8u + adj_s;
         constexpr int NA = C::NA, NW = C::NW, NAS = C::NAS, NT = C::NT;
         if (d < NA) {
@@ -592,13 +649,28 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     // step 3 decodes its first fragments.  The copies of stage s + DIST are issued during steps 0..2.
     int buf = 0;
     auto ring_next = [](int b) { return b == C::NSTAGE - 1 ? 0 : b + 1; };
-    auto run_stage = [&](int s) {
+    uint3 win[RAG ? C::NSW : 1];
+    auto run_stage = [&](int s, auto tail_tag) {    // tail_tag: see gemm_staged_kernel
+        constexpr bool TAIL = decltype(tail_tag)::value;
         const int buf1 = ring_next(buf), buf2 = buf == 0 ? C::NSTAGE - 1 : buf - 1;
         const int fetch = min(s + C::DIST, nstage - 1);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
+            if constexpr (RAG) {                // scale bytes of stage s+1, see gemm_staged_kernel
+                uint8_t* next = lds + buf1 * C::STAGE_BYTES;
+                if (t == 1) {
+                    wait_vmcnt<C::NA + C::NW + (C::NDMA + 2) / 3>();
+#pragma unroll
+                    for (int d = 0; d < C::NSW; ++d)
+                        win[d] = windows.gather(d, next + C::WINDOWS, TAIL, lds + C::PATCH + 8 * (s + 1 - patch_from));
+                }
+                if (t == 2)
+#pragma unroll
+                    for (int d = 0; d < C::NSW; ++d) windows.template put<true>(d, win[d], next + C::A_SCALES, TAIL, s + 1);
+            }
             if (t == 3) {
                 wait_vmcnt<(C::DIST - 1) * C::NDMA>();
+                if constexpr (RAG) wait_lgkmcnt0();
                 wg_barrier();
                 read_raw(lds + buf1 * C::STAGE_BYTES);
             }
@@ -627,12 +699,22 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     for (int d = 0; d < C::DIST; ++d)
 #pragma unroll
         for (int q = 0; q < C::NDMA; ++q) issue_one(q, min(d, nstage - 1), d);
+    if constexpr (RAG) windows.fill_patch(lds + C::PATCH);
     wait_vmcnt<(C::DIST - 1) * C::NDMA>();
+    if constexpr (RAG) {                        // the first stage is whole
+#pragma unroll
+        for (int d = 0; d < C::NSW; ++d)
+            windows.template put<true>(d, windows.gather(d, lds + C::WINDOWS, false, nullptr), lds + C::A_SCALES, false, 0);
+        wait_lgkmcnt0();
+    }
     wg_barrier();
     read_raw(lds);
 #pragma unroll
     for (int gidx = 0; gidx < G; ++gidx) decode_frag(gidx, 0);
-    for (int s = 0; s < nstage; ++s) run_stage(s);
+    int s = 0;
+    for (; s < (RAG ? patch_from - 1 : nstage); ++s) run_stage(s, std::false_type{});
+    if constexpr (RAG)
+        for (; s < nstage; ++s) run_stage(s, std::true_type{});
     wait_vmcnt<0>();                            // no copy may still be in flight when the LDS is released
 
     // ---- the pair adds its partial tiles: in two rounds (columns 0-63, 64-127 of the sub-tile) every wave
@@ -711,15 +793,15 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     }
 }
 
-template <int WM, int WN, int GM, int GN, bool REG = false, typename OutT>
+template <int WM, int WN, int GM, int GN, int MODE = COPIES, typename OutT>
 arcq_status launch_staged(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                           const uint8_t* w_scales, int M, int N, int nbk, float alpha, OutT* y, int64_t ldy,
                           hipStream_t stream, int splits = 1, float* partial = nullptr) {
-    using C = StagedCfg<WM, WN, GM, GN>;
+    using C = StagedCfg<WM, WN, GM, GN, MODE>;
     const int tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
     if (splits > 1) {
         // fp32 partial results [splits, M, N] in the workspace, then one pass that adds them
-        auto kern = gemm_staged_kernel<WM, WN, GM, GN, float, REG>;
+        auto kern = gemm_staged_kernel<WM, WN, GM, GN, float, MODE>;
         static std::atomic<uint64_t> lds_raised{0};
         if (arcq_status st = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_raised)) return st;
         const int64_t stride = (int64_t)M * N;
@@ -729,12 +811,25 @@ arcq_status launch_staged(const uint8_t* a_codes, const uint8_t* a_scales, const
         return launch_splitk_reduce(partial, splits, M, N, alpha, y, std::is_same<OutT, _Float16>::value ? ARCQ_DTYPE_F16 : ARCQ_DTYPE_F32,
                                     ldy, stream);
     }
-    auto kern = gemm_staged_kernel<WM, WN, GM, GN, OutT, REG>;
+    auto kern = gemm_staged_kernel<WM, WN, GM, GN, OutT, MODE>;
     static std::atomic<uint64_t> lds_raised{0};
     if (arcq_status st = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_raised)) return st;
     hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(C::NT), C::LDS_BYTES, stream, a_codes, a_scales, w_codes,
                        w_scales, M, N, nbk, alpha, y, ldy, tiles_m, tiles_n, 1, (int64_t)0);
     return check_launch("gemm_staged_kernel");
+}
+
+template <int MODE, typename OutT>
+arcq_status launch_kpair(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes, const uint8_t* w_scales, int M,
+                         int N, int nbk, float alpha, OutT* y, int64_t ldy, hipStream_t stream) {
+    using C = StagedCfg<2, 2, 2, 4, MODE>;
+    auto kern = gemm_kpair_kernel<OutT, MODE>;
+    static std::atomic<uint64_t> lds_raised{0};
+    if (arcq_status st = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_raised)) return st;
+    const int tiles_m = (M + 127) / 128, tiles_n = (N + 255) / 256;
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(512), C::LDS_BYTES, stream, a_codes, a_scales, w_codes, w_scales, M, N,
+                       nbk, alpha, y, ldy, tiles_m, tiles_n);
+    return check_launch("gemm_kpair_kernel");
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1105,68 +1200,70 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
     if (const int variant = gemm_ksplit_variant(M, N, Kp))
         return launch_gemm_ksplit(variant, a_codes, a_scales, w_codes, w_scales, M, N, Kp, alpha, y,
                                   std::is_same<OutT, _Float16>::value ? ARCQ_DTYPE_F16 : ARCQ_DTYPE_F32, ldy, stream);
+    // Tiles of 256 weight rows by 256, 192 or 128 activation rows when there is work for them.  Workgroups run in
+    // rounds of one per compute unit and a round lasts as long as one tile, so the tile height that minimises
+    // rounds x (time of a stage of that tile) wins: 2.96, 2.59 and 1.96 us measured per 128-k stage (the bigger
+    // tile decodes fewer fragments per matrix instruction: 45, 53 and 60 ps per output element and stage).
+    // E.g. 768 x 14336: 224 tiles of 192 rows in one round 88 us, 336 tiles of 128 rows in two rounds 113 us,
+    // 168 tiles of 256 rows 100 us; 1024 x 14336: 224 tiles of 256 rows 106 us against 120 us.
+    const int64_t tn256 = (N + 255) / 256;
+    const bool wide = ((M + 127) / 128) * tn256 >= 192;
+    auto cost = [&](int bm, double t_stage) { return (double)((((M + bm - 1) / bm) * tn256 + 255) / 256) * t_stage; };
+    const double c256 = cost(256, 2.96), c192 = cost(192, 2.59), c128 = cost(128, 1.96);
+    // More than 256 tiles of 128 x 128 (two workgroups on some compute units, one on the others) but at most 256 of
+    // 192 x 128: one round of the taller tile, which also decodes five fragments per six matrix instructions
+    // instead of four per four (1.52 against 1.3 us per stage and tile): 512 x 10240 over K' = 8448 116 -> 100 us,
+    // 1024 x 5120 over 27904 365 -> 297 us, 1280 x 4096 over 4352 61 -> 49 us.
+    const bool one_round_192 = ((M + 127) / 128) * ((N + 127) / 128) > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256;
     if ((nbk & 3) == 0 && nbk >= 8 && offsets_fit && aligned16) {
-        // Tiles of 256 weight rows by 256, 192 or 128 activation rows when there is work for them.  Workgroups run in
-        // rounds of one per compute unit and a round lasts as long as one tile, so the tile height that minimises
-        // rounds x (time of a stage of that tile) wins: 2.96, 2.59 and 1.96 us measured per 128-k stage (the bigger
-        // tile decodes fewer fragments per matrix instruction: 45, 53 and 60 ps per output element and stage).
-        // E.g. 768 x 14336: 224 tiles of 192 rows in one round 88 us, 336 tiles of 128 rows in two rounds 113 us,
-        // 168 tiles of 256 rows 100 us; 1024 x 14336: 224 tiles of 256 rows 106 us against 120 us.
-        const int64_t tn256 = (N + 255) / 256;
-        const int64_t t128x256 = ((M + 127) / 128) * tn256;
-        if (t128x256 >= 192) {
-            auto cost = [&](int bm, double t_stage) { return (double)((((M + bm - 1) / bm) * tn256 + 255) / 256) * t_stage; };
-            const double c256 = cost(256, 2.96), c192 = cost(192, 2.59), c128 = cost(128, 1.96);
+        if (wide) {
             if (c256 <= c192 && c256 <= c128)
                 return launch_staged<4, 4, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
             if (c192 <= c128)
                 return launch_staged<3, 4, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-        }
-        // 128 x 256 tiles with 8 waves of 64 x 64 (two per SIMD): 5 % faster than 4 waves of 64 x 128 on the
-        // 2048 x 4096 x 4352 problem; on the large shapes 4 and 8 waves measure the same
-        if (t128x256 >= 192) {
-            // whole stages: the variant whose wave pairs split every stage (6 % faster on the 2048 x 4096 x 4352 problem)
-            {
-                if ((nbk & 7) == 0 && nbk >= 16) {
-                    using C = StagedCfg<2, 2, 2, 4>;
-                    auto kern = gemm_kpair_kernel<OutT>;
-                    static std::atomic<uint64_t> lds_raised{0};
-                    if (arcq_status st = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_raised)) return st;
-                    const int tiles_m = (int)((M + 127) / 128), tiles_n = (int)((N + 255) / 256);
-                    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(512), C::LDS_BYTES, stream, a_codes, a_scales, w_codes,
-                                       w_scales, (int)M, (int)N, nbk, alpha, y, ldy, tiles_m, tiles_n);
-                    return check_launch("gemm_kpair_kernel");
-                }
-            }
+            // 128 x 256 tiles: wave pairs that split every stage (6 % faster than 8 waves of 64 x 64 on the 2048 x 4096 x 4352
+            // problem).  A half stage at the end is one of the ragged ends that the RAGGED copies know: 2048 x 4096 over
+            // K' = 4416 69.6 us, 8 waves of 64 x 64 with a shorter last stage 71.8 us; over K' = 8256 123 and 130 us
+            if (nbk >= 16)
+                return (nbk & 7) == 0
+                           ? launch_kpair<COPIES>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream)
+                           : launch_kpair<RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
             return launch_staged<2, 2, 2, 4>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         }
-        // More than 256 tiles of 128 x 128 (two workgroups on some compute units, one on the others) but at most 256 of
-        // 192 x 128: one round of the taller tile, which also decodes five fragments per six matrix instructions
-        // instead of four per four (1.52 against 1.3 us per stage and tile): 512 x 10240 over K' = 8448 116 -> 100 us,
-        // 1024 x 5120 over 27904 365 -> 297 us, 1280 x 4096 over 4352 61 -> 49 us.
-        {
-            const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128), t192 = ((M + 191) / 192) * ((N + 127) / 128);
-            if (t128 > 256 && t192 <= 256)
-                return launch_staged<3, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-        }
+        if (one_round_192)
+            return launch_staged<3, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         return launch_staged<2, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
                                          split_k(M, N, Kp), workspace);
     }
+    if (nbk >= ScaleWindows<128, 128, 256, 8>::MIN_NB && offsets_fit &&
+        ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0) {
+        // Any K' from 256 on, codes that are only 8-byte aligned: the same tiles by the same rule, 1 to 5 % slower than with
+        // whole aligned rows (S = 272 against S = 256, and through registers: 4096 x 8192 over K = 8192 434, 419 and 581 us;
+        // 2048 x 4096 over K = 4096 69.2, 65.2 and 79.4 us; 512 x 10240 over K = 8192 98.1, 93.7 and 112.8 us)
+        if (wide) {
+            if (c256 <= c192 && c256 <= c128)
+                return launch_staged<4, 4, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
+            if (c192 <= c128)
+                return launch_staged<3, 4, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
+            return launch_kpair<RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
+        }
+        if (one_round_192)
+            return launch_staged<3, 2, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
+        return launch_staged<2, 2, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
+                                                 split_k(M, N, Kp), workspace);
+    }
     if (offsets_fit && nbk >= 8) {
-        // any K' that is a multiple of 16, operands that are only 8-byte aligned: stages through registers (no 256 x 256
+        // scale bytes at odd addresses, or K' from 128 to 240 that is no multiple of 64: stages through registers (no 256 x 256
         // tiles: the staging registers do not fit beside 256 accumulators); the same choice by rounds x stage time
         // (3.5 and 2.4 us measured per stage for 192 x 256 and 128 x 256 tiles: 768 x 14336 over K' = 4368 118 us instead of 163)
-        const int64_t tn256 = (N + 255) / 256;
-        if (((M + 127) / 128) * tn256 >= 192) {
-            auto cost = [&](int bm, double t_stage) { return (double)((((M + bm - 1) / bm) * tn256 + 255) / 256) * t_stage; };
+        if (wide) {
             if (cost(192, 3.5) <= cost(128, 2.4))
-                return launch_staged<3, 4, 2, 2, true>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-            return launch_staged<2, 2, 2, 4, true>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
+                return launch_staged<3, 4, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
+            return launch_staged<2, 2, 2, 4, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         }
-        const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128), t192 = ((M + 191) / 192) * ((N + 127) / 128);
-        if (t128 > 256 && t192 <= 256)
-            return launch_staged<3, 2, 2, 2, true>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-        return launch_staged<2, 2, 2, 2, true>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
+        if (one_round_192)
+            return launch_staged<3, 2, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
+        return launch_staged<2, 2, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
                                                split_k(M, N, Kp), workspace);
     }
     dim3 grid((unsigned)((N + 127) / 128), (unsigned)((M + 127) / 128));

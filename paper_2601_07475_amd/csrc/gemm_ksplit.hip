@@ -17,6 +17,7 @@
 #include "gemm_decode.h"
 #include "gemm_epilogue.h"
 #include "lds_dma.h"
+#include "scale_windows.h"
 
 #include <type_traits>
 
@@ -24,7 +25,9 @@ namespace arcq {
 
 namespace {
 
-template <int WM, int WN, int GM, int GN, int KS>
+// How the stages get into LDS, as in gemm.hip: COPIES for K' % 64 == 0, RAGGED for any K' (dword-aligned scale bytes), REGS for
+// scale bytes at odd addresses (see below).
+template <int WM, int WN, int GM, int GN, int KS, int MODE = COPIES>
 struct KsplitCfg {
     static_assert(KS == 2 || KS == 4, "k halves or quarters");
     static constexpr int BM = 32 * WM * GM, BN = 32 * WN * GN;
@@ -36,15 +39,19 @@ struct KsplitCfg {
     // the operand's last rows into padding behind its region, so that every wave issues the same number)
     static constexpr int NA = (BM * PPR + NT - 1) / NT, NW = (BN * PPR + NT - 1) / NT;
     static constexpr int NAS = (BM * KS + NT - 1) / NT, NWS = (BN * KS + NT - 1) / NT;
-    static constexpr int NDMA = NA + NW + NAS + NWS;
+    using Windows = ScaleWindows<BM, BN, NT, 4 * KS>;
+    static constexpr int NSW = MODE == RAGGED ? Windows::NS : 0;           // copies of windows come first
+    static constexpr int NDMA = NA + NW + (MODE == RAGGED ? NSW : NAS + NWS);
     static constexpr int A_CODES = 0;
     static constexpr int W_CODES = NA * NT * 16;
     static constexpr int A_SCALES = W_CODES + NW * NT * 16;
-    static constexpr int W_SCALES = A_SCALES + NAS * NT * 4;
-    static constexpr int STAGE_BYTES = W_SCALES + NWS * NT * 4;
+    static constexpr int W_SCALES = A_SCALES + (MODE == RAGGED ? Windows::DENSE_W : NAS * NT * 4);
+    static constexpr int WINDOWS = A_SCALES + Windows::DENSE_BYTES;
+    static constexpr int STAGE_BYTES = MODE == RAGGED ? WINDOWS + Windows::BYTES : W_SCALES + NWS * NT * 4;
     static constexpr int NSTAGE = 3, DIST = 2;
     static constexpr int OWN = (WM * WN + KS - 1) / KS;  // fragments a wave finishes and stores (at most)
-    static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;
+    static constexpr int PATCH = NSTAGE * STAGE_BYTES;      // RAGGED: see ScaleWindows::fill_patch
+    static constexpr int LDS_BYTES = PATCH + (MODE == RAGGED ? 2 * Windows::PATCH : 0);
     static_assert(NWAVE * OWN * 4096 <= LDS_BYTES, "the exchange regions must fit the operand ring");
     static_assert((NT / PPR) % 16 == 0 && (NT / KS) % 1 == 0, "row swizzle must not depend on the copy index");
     static_assert((DIST - 1) * NDMA < 64, "the vector-memory counter has 6 bits");
@@ -73,17 +80,18 @@ __device__ __forceinline__ void store_fragment(const float16v& a, int m0, int n0
     }
 }
 
-// REG: any K' (a multiple of 16) and operands that are only 8-byte aligned: a thread fetches its pieces of stage s + 2
+// REGS: any K' (a multiple of 16) and operands that are only 8-byte aligned: a thread fetches its pieces of stage s + 2
 // into registers with ordinary loads (declared with the alignment the interface guarantees), right after the barrier
 // that opens stage s + 1, and writes them to LDS before the barrier that opens their stage; blocks past the end of a row
 // become zero codes and zero scale bytes (a piece that would reach past the row's end is fetched from further left and
 // shifted), so the last stage needs no special case.
-template <int WM, int WN, int GM, int GN, int KS, typename OutT, bool REG = false>
+template <int WM, int WN, int GM, int GN, int KS, typename OutT, int MODE = COPIES>
 __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N,
     int nbk, float alpha, OutT* __restrict__ y, int64_t ldy, int tiles_m, int tiles_n) {
-    using C = KsplitCfg<WM, WN, GM, GN, KS>;
+    using C = KsplitCfg<WM, WN, GM, GN, KS, MODE>;
+    constexpr bool REG = MODE == REGS, RAG = MODE == RAGGED;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     // workgroup -> tile: workgroups are dealt round-robin to the 8 XCDs (each with its own L2); every XCD gets a
@@ -113,7 +121,7 @@ __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
     // copies of its missing shares re-fetch the first share (in bounds, never used) and the waves of those shares read
     // their scale bytes as zero, so that their fragments decode to zeros
     const int nstage = (nbk + 4 * KS - 1) / (4 * KS);
-    const int part = REG ? 0 : (nbk % (4 * KS)) / 4; // 0: the last stage is whole (REG: made whole with zeros)
+    const int part = MODE != COPIES ? 0 : (nbk % (4 * KS)) / 4; // 0: the last stage is whole (RAGGED, REGS: made whole with zeros)
 
     // ---- copies
     auto swz = [](int row) -> uint32_t { return KS == 4 ? (uint32_t)(row >> 1) & 7u : (uint32_t)(row >> 2) & 3u; };
@@ -126,10 +134,18 @@ __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
     const uint32_t piece_g = (uint32_t)(tid % C::PPR) ^ swz(crow);      // global piece this lane fetches
     const bool piece_missing = part != 0 && (int)(piece_g >> 1) >= part, scale_missing = part != 0 && tid % KS >= part;
     const uint32_t adj_c_last = piece_missing ? 16u * (piece_g & 1u) : adj_c, adj_s_last = scale_missing ? 0u : adj_s;
+    const typename C::Windows windows = {a_scales, w_scales, M, N, nbk, wg_m0, wg_n0, (uint32_t)tid, wave_slot};    // RAGGED
+    const int patch_from = C::Windows::patch_from(nbk);
     auto issue_one = [&](int d, int stage, int buf) {
         const uint32_t base = lds0 + buf * C::STAGE_BYTES;
         const bool last = stage == nstage - 1;
-        const uint32_t oc = (uint32_t)stage * C::ROWB + (last ? adj_c_last : adj_c);
+        const uint32_t oc = RAG ? 8u * (uint32_t)min(4 * KS * stage + 2 * (int)piece_g, nbk - 2)
+                                : (uint32_t)stage * C::ROWB + (last ? adj_c_last : adj_c);
+        if (RAG && d < C::NSW) {
+            windows.issue(d, stage, base + C::WINDOWS);
+            return;
+        }
+        d -= C::NSW;
         const uint32_t os = (uint32_t)stage * C::SROWB + (last ? adj_s_last : adj_s);
         constexpr int NA = C::NA, NW = C::NW, NAS = C::NAS, NT = C::NT;
         // rows past the edge of the operand re-read its last row (never stored)
@@ -151,7 +167,7 @@ __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
         }
     };
 
-    // ---- REG: the same pieces through registers (piece d of a thread lands where copy d puts it); needs nbk >= 4
+    // ---- REGS: the same pieces through registers (piece d of a thread lands where copy d puts it); needs nbk >= 4
     constexpr int NCP = C::NA + C::NW, NSP = C::NAS + C::NWS;
     uint4 rc[REG ? NCP : 1];
     uint32_t rs[REG ? NSP : 1];
@@ -251,17 +267,34 @@ __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
     // every wave left before the barrier that opened stage s.
     int buf = 0;
     auto ring_next = [](int b) { return b == C::NSTAGE - 1 ? 0 : b + 1; };
-    auto run_stage = [&](int s) {
+    // RAGGED: the scale bytes of stage s+1 are picked out of their windows during step 1 (read) and 2 (write); tail_tag: the stage
+    // before one whose windows or blocks may pass the end (the last two), all others know that they are whole.
+    uint3 win[RAG ? C::NSW : 1];
+    auto run_stage = [&](int s, auto tail_tag) {
+        constexpr bool TAIL = decltype(tail_tag)::value;
         const int buf1 = ring_next(buf), buf2 = buf == 0 ? C::NSTAGE - 1 : buf - 1;
         const int fetch = min(s + C::DIST, nstage - 1);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
+            if constexpr (RAG) {
+                uint8_t* next = lds + buf1 * C::STAGE_BYTES;
+                if (t == 1) {
+                    wait_vmcnt<C::NA + C::NW + (C::NDMA + 2) / 3>();
+#pragma unroll
+                    for (int d = 0; d < C::NSW; ++d)
+                        win[d] = windows.gather(d, next + C::WINDOWS, TAIL, lds + C::PATCH + 4 * KS * (s + 1 - patch_from));
+                }
+                if (t == 2)
+#pragma unroll
+                    for (int d = 0; d < C::NSW; ++d) windows.template put<true>(d, win[d], next + C::A_SCALES, TAIL, s + 1);
+            }
             if (t == 3) {
                 if constexpr (REG) {
                     reg_commit(min(s + 1, nstage - 1), buf1);       // fetched since step 3 of the stage before
                     wait_lgkmcnt0();
                 } else {
                     wait_vmcnt<(C::DIST - 1) * C::NDMA>();
+                    if constexpr (RAG) wait_lgkmcnt0();
                 }
                 wg_barrier();
                 read_raw(lds + buf1 * C::STAGE_BYTES, share_missing && s + 1 >= nstage - 1);
@@ -302,13 +335,23 @@ __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
         for (int d = 0; d < C::DIST; ++d)
 #pragma unroll
             for (int q = 0; q < C::NDMA; ++q) issue_one(q, min(d, nstage - 1), d);
+        if constexpr (RAG) windows.fill_patch(lds + C::PATCH);
         wait_vmcnt<(C::DIST - 1) * C::NDMA>();
+        if constexpr (RAG) {                        // the first stage is whole
+#pragma unroll
+            for (int d = 0; d < C::NSW; ++d)
+                windows.template put<true>(d, windows.gather(d, lds + C::WINDOWS, false, nullptr), lds + C::A_SCALES, false, 0);
+            wait_lgkmcnt0();
+        }
     }
     wg_barrier();
     read_raw(lds, share_missing && nstage == 1);
 #pragma unroll
     for (int gidx = 0; gidx < G; ++gidx) decode_frag(gidx, 0);
-    for (int s = 0; s < nstage; ++s) run_stage(s);
+    int s = 0;
+    for (; s < (RAG ? patch_from - 1 : nstage); ++s) run_stage(s, std::false_type{});
+    if constexpr (RAG)
+        for (; s < nstage; ++s) run_stage(s, std::true_type{});
     wait_vmcnt<0>();                            // no copy may still be in flight when the LDS is released
 
     // ---- the KS partial tiles of a sub-tile are added through the LDS: in round rho every wave hands the fragments
@@ -354,11 +397,11 @@ __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
         if (f % KS == kh) store_fragment(acc[f / WN][f % WN], m0 + 32 * (f / WN), n0 + 32 * (f % WN), r, h, M, N, alpha, y, ldy, vec_ok);
 }
 
-template <int WM, int WN, int GM, int GN, int KS, bool REG, typename OutT>
+template <int WM, int WN, int GM, int GN, int KS, int MODE, typename OutT>
 arcq_status launch_ksplit(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes, const uint8_t* w_scales,
                           int M, int N, int nbk, float alpha, OutT* y, int64_t ldy, hipStream_t stream) {
-    using C = KsplitCfg<WM, WN, GM, GN, KS>;
-    auto kern = gemm_ksplit_kernel<WM, WN, GM, GN, KS, OutT, REG>;
+    using C = KsplitCfg<WM, WN, GM, GN, KS, MODE>;
+    auto kern = gemm_ksplit_kernel<WM, WN, GM, GN, KS, OutT, MODE>;
     static std::atomic<uint64_t> lds_raised{0};
     if (arcq_status st = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_raised)) return st;
     const int tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
@@ -367,16 +410,16 @@ arcq_status launch_ksplit(const uint8_t* a_codes, const uint8_t* a_scales, const
     return check_launch("gemm_ksplit_kernel");
 }
 
-template <bool REG, typename OutT>
+template <int MODE, typename OutT>
 arcq_status launch_ksplit_typed(int variant, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                                 const uint8_t* w_scales, int M, int N, int nbk, float alpha, OutT* y, int64_t ldy,
                                 hipStream_t stream) {
     switch (variant) {
-        case 1: return launch_ksplit<2, 2, 1, 1, 4, REG>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 64 x 64
-        case 2: return launch_ksplit<4, 2, 1, 1, 4, REG>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 128 x 64
-        case 4: return launch_ksplit<3, 2, 1, 1, 4, REG>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 96 x 64
-        case 6: return launch_ksplit<2, 1, 1, 1, 4, REG>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 64 x 32
-        default: return launch_ksplit<2, 4, 2, 1, 4, REG>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);  // 128 x 128
+        case 1: return launch_ksplit<2, 2, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 64 x 64
+        case 2: return launch_ksplit<4, 2, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 128 x 64
+        case 4: return launch_ksplit<3, 2, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 96 x 64
+        case 6: return launch_ksplit<2, 1, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 64 x 32
+        default: return launch_ksplit<2, 4, 2, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);  // 128 x 128
     }
 }
 
@@ -410,19 +453,18 @@ arcq_status launch_gemm_ksplit(int variant, const uint8_t* a_codes, const uint8_
                                const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, float alpha, void* y, int y_dtype,
                                int64_t ldy, hipStream_t stream) {
     const int nbk = (int)(Kp >> 4);
-    // direct-to-LDS copies need rows that start on 16-byte boundaries (K' a multiple of 64 covers the scale bytes too)
+    // whole pieces need rows that start on 16-byte boundaries (K' a multiple of 64 covers the scale bytes too); scale windows need
+    // the base of the scale bytes on a dword (256 x 4096 over K' = 4352 / 4368: 14.6 / 16.3 us; through registers 18.5)
     const bool copies = (nbk & 3) == 0 &&
                         ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 &&
                         ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
-    if (y_dtype == ARCQ_DTYPE_F16)
-        return copies ? launch_ksplit_typed<false>(variant, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha,
-                                                   static_cast<_Float16*>(y), ldy, stream)
-                      : launch_ksplit_typed<true>(variant, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha,
-                                                  static_cast<_Float16*>(y), ldy, stream);
-    return copies ? launch_ksplit_typed<false>(variant, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha,
-                                               static_cast<float*>(y), ldy, stream)
-                  : launch_ksplit_typed<true>(variant, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha,
-                                              static_cast<float*>(y), ldy, stream);
+    const bool windows = ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
+    auto launch = [&](auto* out) {
+        return copies    ? launch_ksplit_typed<COPIES>(variant, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, out, ldy, stream)
+               : windows ? launch_ksplit_typed<RAGGED>(variant, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, out, ldy, stream)
+                         : launch_ksplit_typed<REGS>(variant, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, out, ldy, stream);
+    };
+    return y_dtype == ARCQ_DTYPE_F16 ? launch(static_cast<_Float16*>(y)) : launch(static_cast<float*>(y));
 }
 
 }  // namespace arcq
