@@ -11,6 +11,7 @@
 #include "internal.h"
 #include "gemm_decode.h"
 #include "lds_dma.h"
+#include "scale_windows.h"
 
 #include <type_traits>
 
@@ -44,39 +45,46 @@ __device__ __forceinline__ float16v mfma_mx(const uint4& a, const uint4& b, cons
 // for the missing second half (never used, in bounds).
 // BF16: the same skeleton for plain bf16 operands (the comparison kernel arcq_ref_gemm_bf16): a row of a unit is 128
 // bytes = 64 bf16 values, there are no scale bytes, and a k-step is one v_mfma_f32_32x32x16_bf16.
-template <int WM, int WN, int GM, int GN, bool BF16 = false>
+// How the units get into LDS (MODE): COPIES for K' % 128 == 0, codes 16-byte and scale bytes 4-byte aligned; RAGGED for any K' (a
+// multiple of 32) from 512 on and dword-aligned codes: scale bytes as dword-aligned windows (scale_windows.h), pieces past the
+// end of a row fetched from its last block and their fragments zeroed in the last unit; the base of the scale bytes has
+// to be 4-byte aligned.  REGS: what is left, see below.
+template <int WM, int WN, int GM, int GN, bool BF16 = false, int MODE = COPIES>
 struct MxCfg {
     static constexpr int BM = 32 * WM * GM, BN = 32 * WN * GN;
     static constexpr int NT = 64 * GM * GN;
     static constexpr int NA = (BM * 8 + NT - 1) / NT, NW = (BN * 8 + NT - 1) / NT;       // 16-byte pieces of codes
     static constexpr int NAS = BF16 ? 0 : (BM * 2 + NT - 1) / NT, NWS = BF16 ? 0 : (BN * 2 + NT - 1) / NT;     // 4-byte words of scales
-    static constexpr int NDMA = NA + NW + NAS + NWS;
+    using Windows = ScaleWindows<BM, BN, NT, 8>;
+    static constexpr int NSW = MODE == RAGGED ? Windows::NS : 0;           // copies of windows come first
+    static constexpr int NDMA = NA + NW + (MODE == RAGGED ? NSW : NAS + NWS);
     static constexpr int A_CODES = 0;
     static constexpr int W_CODES = NA * NT * 16;
     static constexpr int A_SCALES = W_CODES + NW * NT * 16;
-    static constexpr int W_SCALES = A_SCALES + NAS * NT * 4;
-    static constexpr int UNIT_BYTES = W_SCALES + NWS * NT * 4;
-    static constexpr int NUNIT = (160 * 1024) / UNIT_BYTES >= 3 ? 3 : 2;
-    static constexpr int LDS_BYTES = NUNIT * UNIT_BYTES;
+    static constexpr int W_SCALES = A_SCALES + (MODE == RAGGED ? Windows::DENSE_W : NAS * NT * 4);
+    static constexpr int WINDOWS = A_SCALES + Windows::DENSE_BYTES;
+    static constexpr int UNIT_BYTES = MODE == RAGGED ? WINDOWS + Windows::BYTES : W_SCALES + NWS * NT * 4;
+    static constexpr int NUNIT = (160 * 1024 - 256) / UNIT_BYTES >= 3 ? 3 : 2;
+    static constexpr int PATCH = NUNIT * UNIT_BYTES;        // RAGGED: see ScaleWindows::fill_patch
+    static constexpr int LDS_BYTES = PATCH + (MODE == RAGGED ? 2 * Windows::PATCH : 0);
     static_assert(NDMA * (NUNIT - 1) < 64, "the counted wait needs the copies of NUNIT - 1 units to fit the counter");
 };
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 //
-// REG: the same tiles, LDS layout and schedule for shapes the direct-to-LDS copies do not serve: any number of
-// blocks per row (K' a multiple of 32 only: rows of scale bytes then start at odd addresses) and operands at the
-// interface's minimum alignment.  A thread fetches its pieces of unit u+2 into registers with ordinary loads
+// REGS: the same tiles, LDS layout and schedule for shapes the direct-to-LDS copies do not serve.  A thread fetches its pieces of unit u+2 into registers with ordinary loads
 // (declared with the alignment the interface guarantees), all at once right after the barrier that opens unit u+1,
 // and writes them to LDS just before the barrier that opens their unit; blocks past the end of a row become zero
 // codes (a scale word that would reach past the end is fetched from further left and shifted), so every unit is a
 // whole unit.
-template <int WM, int WN, int GM, int GN, typename OutT, bool BF16 = false, bool REG = false>
+template <int WM, int WN, int GM, int GN, typename OutT, bool BF16 = false, int MODE = COPIES>
 __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N, int nb,
     OutT* __restrict__ y, int64_t ldy, int tiles_m, int tiles_n, int splits, int64_t split_stride) {
-    using C = MxCfg<WM, WN, GM, GN, BF16>;
+    using C = MxCfg<WM, WN, GM, GN, BF16, MODE>;
+    constexpr bool REG = MODE == REGS, RAG = MODE == RAGGED;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     // workgroup -> tile: a contiguous run of the tile sequence per XCD, column-major groups of 8 tile rows
@@ -101,8 +109,8 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     const int wg_m0 = tile_m * C::BM, wg_n0 = tile_n * C::BN;
     const int wrow0 = (wave / GN) * (32 * WM), wcol0 = (wave % GN) * (32 * WN);
 
-    const bool has_half = !REG && (nb & 7) != 0;            // nb % 8 == 4
-    const int nunit = REG ? (nb + 7) >> 3 : (nb >> 3) + (has_half ? 1 : 0);
+    const bool has_half = MODE == COPIES && (nb & 7) != 0;            // nb % 8 == 4
+    const int nunit = MODE != COPIES ? (nb + 7) >> 3 : (nb >> 3) + (has_half ? 1 : 0);
 
     // ---- copies: thread -> (row, piece) of a workgroup-wide copy; 8 lanes fetch one row's 128 bytes
     const uint32_t cpitch = (uint32_t)nb * 16u, spitch = (uint32_t)nb;
@@ -110,11 +118,18 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     const int crow = tid >> 3, srow = tid >> 1;
     const uint32_t wave_slot = __builtin_amdgcn_readfirstlane((uint32_t)(tid & ~63));
     const uint32_t lds0 = lds_address(lds);
+    const typename C::Windows windows = {a_scales, w_scales, M, N, nb, wg_m0, wg_n0, (uint32_t)tid, wave_slot};    // RAGGED
+    const int patch_from = C::Windows::patch_from(nb);
     auto issue_one = [&](int d, int unit, int buf) {
         const uint32_t base = lds0 + buf * C::UNIT_BYTES;
+        if (RAG && d < C::NSW) {
+            windows.issue(d, unit, base + C::WINDOWS);
+            return;
+        }
+        d -= C::NSW;
         constexpr int NA = C::NA, NW = C::NW, NAS = C::NAS, NT = C::NT;
         const bool half = has_half && unit == nunit - 1;
-        const uint32_t oc = (uint32_t)unit * 128u + (half ? (lp & 3u) : lp) * 16u;
+        const uint32_t oc = RAG ? 16u * (uint32_t)min(8 * unit + (int)lp, nb - 1) : (uint32_t)unit * 128u + (half ? (lp & 3u) : lp) * 16u;
         const uint32_t os = (uint32_t)unit * 8u + (half ? 0u : (uint32_t)(tid & 1) * 4u);
         // rows past the edge of the operand re-read its last row (never stored)
         if (d < NA) {
@@ -135,7 +150,7 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
         }
     };
 
-    // ---- REG: the same pieces through registers (piece d of a thread lands where copy d puts it); needs nb >= 4
+    // ---- REGS: the same pieces through registers (piece d of a thread lands where copy d puts it); needs nb >= 4
     constexpr int NCP = C::NA + C::NW, NSP = C::NAS + C::NWS;
     uint4 rc[REG ? NCP : 1];
     uint32_t rs[REG && NSP > 0 ? NSP : 1];
@@ -194,7 +209,10 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-    uint4 fa[2][WM], fw[2][WN];             // fragments of the k-step being computed and of the next one
+    // EARLY (two ring slots): three sets of fragments, see the pipeline below; otherwise the k-step being computed and the next one
+    constexpr bool EARLY = !REG && C::NUNIT == 2;
+    constexpr int NSET = EARLY ? 3 : 2;
+    uint4 fa[NSET][WM], fw[NSET][WN];
     uint2 sa[WM], sw[WN], sa_n[WM], sw_n[WN];   // scale bytes of the unit (.x: blocks 0-3, .y: 4-7), shifted so
                                                 // that bytes 0 and 2 of each word are this lane's
     auto read_codes = [&](int slot, int t, const uint8_t* st) {
@@ -218,40 +236,92 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     };
 
     // ---- pipeline, scheduled by hand (one wave per SIMD: nothing else hides a stall).  A unit is
-    // NSTEPS WM WN MFMAs.  The copies of unit u + NUNIT - 1 are issued one at a time between the first
+    // NSTEPS WM WN MFMAs.  Three ring slots: the copies of unit u + 2 are issued one at a time between the first
     // MFMAs of unit u (its buffer was last read in unit u-1, which every wave left before the barrier
     // inside unit u-1); the fragments of k-step t+1 are read while k-step t is computed; the barrier
     // that opens unit u+1 and the reads of its first fragments sit before the last half k-step.
+    // Two ring slots (EARLY; the 256- and 192-row tiles): the copies of unit u + 2 go to the slot of unit u itself, as soon
+    // as every wave has its last fragments of the unit in registers: the fragments of k-steps 1 and 2 are read at the
+    // start of the unit, those of k-step 3 at the start of k-step 2 (into the set of k-step 1), and a second barrier at
+    // FREE_Q hands the slot over.  The copies then have 64 + 56 - 38 = 82 of the MFMA slots of a 256 x 256 unit to land;
+    // issued behind the barrier that opens the next unit they had 36 to 56, less than the 68 KB of a unit take at the
+    // rate the L2 delivers, and every unit waited for them.
     constexpr int NM = WM * WN;               // MFMAs per k-step
     constexpr int DIST = C::NUNIT - 1;
     int buf = 0;
-    auto run_unit = [&](int u, auto nsteps_tag) {
+    // RAGGED: the wanted scale bytes of unit u+1 are picked out of their windows at the start of k-step 1 (read) and in the
+    // middle of it (write).  tail_tag: 1: unit u+1 is the last or the one before, whose windows or blocks may pass the end;
+    // 2: unit u is the last and has missing blocks: k-steps past the end are left out, codes past it are zeroed, nothing is
+    // copied or read for a next unit.
+    uint3 win[RAG ? C::NSW : 1];
+    auto run_unit = [&](int u, auto nsteps_tag, auto tail_tag) {
         constexpr int NSTEPS = decltype(nsteps_tag)::value;
+        constexpr int TAIL = decltype(tail_tag)::value;
         constexpr int LAST_Q = NSTEPS * NM - NM / 2;
-        constexpr int COMMIT_Q = LAST_Q - NM / 2;     // REG: the pieces of unit u+1 go to LDS half a k-step before its barrier
+        constexpr int COMMIT_Q = LAST_Q - NM / 2;     // REGS: the pieces of unit u+1 go to LDS half a k-step before its barrier
+        constexpr int FREE_Q = 2 * NM + (3 * NM) / 8; // EARLY: every fragment of the unit is in registers
         const uint8_t* st = lds + buf * C::UNIT_BYTES;
-        const int buf1 = buf + 1 == C::NUNIT ? 0 : buf + 1, bufd = buf == 0 ? C::NUNIT - 1 : buf - 1;
-        const int fetch = min(u + DIST, nunit - 1);
+        const int buf1 = buf + 1 == C::NUNIT ? 0 : buf + 1, bufd = EARLY ? buf : buf == 0 ? C::NUNIT - 1 : buf - 1;
+        const int fetch = min(u + (EARLY ? 2 : DIST), nunit - 1);
 #pragma unroll
         for (int t = 0; t < NSTEPS; ++t) {
-            if (t + 1 < NSTEPS) {
+            if (TAIL == 2 && 8 * u + 2 * t >= nb) break;
+            const int set = !EARLY ? t & 1 : t == 3 ? 1 : t;
+            if constexpr (EARLY) {
+                if (t == 0) {
+                    read_codes(1, 1, st);
+                    if (NSTEPS == 4) read_codes(2, 2, st);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (t == 2) {
+                    read_codes(1, 3, st);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else if (t + 1 < NSTEPS) {
                 read_codes((t + 1) & 1, t + 1, st);
                 __builtin_amdgcn_sched_barrier(0);
+            }
+            if (TAIL == 2 && 8 * u + 2 * t + h >= nb) {
+#pragma unroll
+                for (int i = 0; i < WM; ++i) fa[set][i] = make_uint4(0, 0, 0, 0);
             }
 #pragma unroll
             for (int i = 0; i < WM; ++i)
 #pragma unroll
                 for (int j = 0; j < WN; ++j) {
                     const int q = t * NM + i * WN + j;
+                    if constexpr (RAG && TAIL < 2) {
+                        uint8_t* next = lds + buf1 * C::UNIT_BYTES;
+                        if (q == NM) {
+                            // windows of unit u+1: younger are the code copies of that unit and (three ring slots) the
+                            // copies of unit u+2 issued so far
+                            wait_vmcnt<C::NA + C::NW + (EARLY ? 0 : C::NDMA < NM ? C::NDMA : NM)>();
+#pragma unroll
+                            for (int d = 0; d < C::NSW; ++d)
+                                win[d] = windows.gather(d, next + C::WINDOWS, TAIL == 1, lds + C::PATCH + 8 * (u + 1 - patch_from));
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (q == NM + NM / 2) {
+#pragma unroll
+                            for (int d = 0; d < C::NSW; ++d)
+                                windows.template put<false>(d, win[d], next + C::A_SCALES, TAIL == 1, u + 1);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
                     if (REG && q == COMMIT_Q) {
                         reg_commit(min(u + 1, nunit - 1), buf1);
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    if (q == LAST_Q) {
-                        // unit u+1 must have landed: the copies of the DIST - 1 later units are younger
-                        // (REG: this wave's LDS writes of unit u+1 must have completed)
+                    if (EARLY && NSTEPS == 4 && TAIL < 2 && q == FREE_Q) {
+                        wait_lgkmcnt0();
+                        wg_barrier();
+                    }
+                    if (q == LAST_Q && TAIL < 2 && !(EARLY && NSTEPS < 4)) {
+                        // unit u+1 must have landed: the copies of the DIST - 1 later units (EARLY: of unit u+2) are younger
+                        // (REGS: this wave's LDS writes of unit u+1 must have completed)
                         if constexpr (REG) wait_lgkmcnt0();
-                        else wait_vmcnt<(DIST - 1) * C::NDMA>();
+                        else wait_vmcnt<(EARLY ? 1 : DIST - 1) * C::NDMA>();
+                        if constexpr (RAG) wait_lgkmcnt0();         // this wave's scale bytes of unit u+1 are written
                         wg_barrier();
                         read_codes(0, 0, lds + buf1 * C::UNIT_BYTES);
                         read_scales(lds + buf1 * C::UNIT_BYTES, sa_n, sw_n);
@@ -260,13 +330,21 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
                     }
                     // weights as the row operand: see store_tile_swapped
                     if constexpr (BF16)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fw[t & 1][j]),
-                                                                            __builtin_bit_cast(bf16x8, fa[t & 1][i]), acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fw[set][j]),
+                                                                            __builtin_bit_cast(bf16x8, fa[set][i]), acc[i][j], 0, 0, 0);
                     else
-                        acc[i][j] = mfma_mx(fw[t & 1][j], fa[t & 1][i], acc[i][j], (int)(t < 2 ? sw[j].x : sw[j].y),
+                        acc[i][j] = mfma_mx(fw[set][j], fa[set][i], acc[i][j], (int)(t < 2 ? sw[j].x : sw[j].y),
                                             (int)(t < 2 ? sa[i].x : sa[i].y), t & 1);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (!REG && NSTEPS == 4 && q < C::NDMA) {
+                    if constexpr (EARLY) {
+                        constexpr int E = LAST_Q - FREE_Q;      // the MFMA slots that the copies of unit u + 2 are spread over
+                        if (NSTEPS == 4 && TAIL < 2 && q >= FREE_Q && q < LAST_Q) {
+#pragma unroll
+                            for (int d = 0; d < C::NDMA; ++d)
+                                if (d * E / C::NDMA == q - FREE_Q) issue_one(d, fetch, bufd);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    } else if (!REG && NSTEPS == 4 && TAIL < 2 && q < C::NDMA) {
                         issue_one(q, fetch, bufd);
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -291,17 +369,38 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
         wait_lgkmcnt0();
     } else {
 #pragma unroll
-        for (int u = 0; u < DIST; ++u)
+        for (int u = 0; u < (EARLY ? 2 : DIST); ++u)
 #pragma unroll
             for (int d = 0; d < C::NDMA; ++d) issue_one(d, min(u0 + u, nunit - 1), u);
-        wait_vmcnt<(DIST - 1) * C::NDMA>();
+        if constexpr (RAG) windows.fill_patch(lds + C::PATCH);
+        wait_vmcnt<(EARLY ? 1 : DIST - 1) * C::NDMA>();
+        if constexpr (RAG) {
+            const bool tail = u0 >= patch_from;     // a short run of a split
+            if (tail) {                             // uniform: the patch area is written by the first wave
+                wait_lgkmcnt0();
+                wg_barrier();
+            }
+#pragma unroll
+            for (int d = 0; d < C::NSW; ++d)
+                windows.template put<false>(d, windows.gather(d, lds + C::WINDOWS, tail, lds + C::PATCH + (tail ? 8 * (u0 - patch_from) : 0)),
+                                            lds + C::A_SCALES, tail, u0);
+            wait_lgkmcnt0();
+        }
     }
     wg_barrier();
     read_codes(0, 0, lds);
     read_scales(lds, sa, sw);
-    const int nfull = REG ? nunit : nb >> 3;
-    for (int u = u0; u < min(u1, nfull); ++u) run_unit(u, std::integral_constant<int, 4>{});
-    if (has_half && u1 == nunit) run_unit(nfull, std::integral_constant<int, 2>{});
+    using Steps4 = std::integral_constant<int, 4>;
+    int u = u0;
+    if constexpr (RAG) {
+        for (; u < min(u1, patch_from - 1); ++u) run_unit(u, Steps4{}, std::integral_constant<int, 0>{});
+        for (; u < min(u1, nb >> 3); ++u) run_unit(u, Steps4{}, std::integral_constant<int, 1>{});
+        if (u < u1) run_unit(u, Steps4{}, std::integral_constant<int, 2>{});
+    } else {
+        const int nfull = REG ? nunit : nb >> 3;
+        for (; u < min(u1, nfull); ++u) run_unit(u, Steps4{}, std::integral_constant<int, 0>{});
+        if (has_half && u1 == nunit) run_unit(nfull, std::integral_constant<int, 2>{}, std::integral_constant<int, 0>{});
+    }
     wait_vmcnt<0>();                            // no copy may still be in flight when the LDS is released
 
     const int m0 = wg_m0 + wrow0, n0 = wg_n0 + wcol0;
@@ -533,15 +632,15 @@ arcq_status launch_mx_skinny(const uint8_t* a_codes, const uint8_t* a_scales, co
     return check_launch("mx_gemm_skinny_kernel");
 }
 
-template <int WM, int WN, int GM, int GN, typename OutT, bool BF16 = false, bool REG = false>
+template <int WM, int WN, int GM, int GN, int MODE = COPIES, bool BF16 = false, typename OutT>
 arcq_status launch_mx_staged(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                              const uint8_t* w_scales, int M, int N, int nb, OutT* y, int64_t ldy, hipStream_t stream,
                              int splits = 1, float* partial = nullptr) {
-    using C = MxCfg<WM, WN, GM, GN, BF16>;
+    using C = MxCfg<WM, WN, GM, GN, BF16, MODE>;
     const int tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
     if (splits > 1) {
         // fp32 partial results [splits, M, N] in the workspace, then one pass that adds them
-        auto kern = mx_gemm_staged_kernel<WM, WN, GM, GN, float, BF16, REG>;
+        auto kern = mx_gemm_staged_kernel<WM, WN, GM, GN, float, BF16, MODE>;
         static std::atomic<uint64_t> lds_raised{0};
         if (arcq_status st = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_raised)) return st;
         hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * splits), dim3(C::NT), C::LDS_BYTES, stream, a_codes, a_scales,
@@ -550,7 +649,7 @@ arcq_status launch_mx_staged(const uint8_t* a_codes, const uint8_t* a_scales, co
         return launch_splitk_reduce(partial, splits, M, N, 1.0f, y, std::is_same<OutT, _Float16>::value ? ARCQ_DTYPE_F16 : ARCQ_DTYPE_F32,
                                     ldy, stream);
     }
-    auto kern = mx_gemm_staged_kernel<WM, WN, GM, GN, OutT, BF16, REG>;
+    auto kern = mx_gemm_staged_kernel<WM, WN, GM, GN, OutT, BF16, MODE>;
     static std::atomic<uint64_t> lds_raised{0};
     if (arcq_status st = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_raised)) return st;
     hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(C::NT), C::LDS_BYTES, stream, a_codes, a_scales, w_codes,
@@ -640,34 +739,30 @@ arcq_status launch_mx_typed(const uint8_t* a_codes, const uint8_t* a_scales, con
     const int tile_rows = t128x256 < 192 ? 0
                           : tile_cost(256) <= tile_cost(192) && tile_cost(256) <= tile_cost(128) ? 256
                           : tile_cost(192) <= tile_cost(128) ? 192 : 128;
-    if ((nb & 3) == 0 && offsets_fit && aligned16) {
+    // more than 256 tiles of 128 x 128 but at most 256 of 192 x 128: one round of the taller tile instead of two
+    // workgroups on some compute units (512 x 10240 over K' = 8448: 48 -> 37 us; 1024 x 5120 over 27904: 144 -> 105 us)
+    const bool one_round_192 = ((M + 127) / 128) * ((N + 127) / 128) > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256;
+    auto tiled = [&](auto mode_tag) {
+        constexpr int MODE = decltype(mode_tag)::value;
         if (tile_rows == 256)
-            return launch_mx_staged<4, 4, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
+            return launch_mx_staged<4, 4, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
         if (tile_rows == 192)
-            return launch_mx_staged<3, 4, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
+            return launch_mx_staged<3, 4, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
         if (tile_rows == 128)
-            return launch_mx_staged<2, 4, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
-        // more than 256 tiles of 128 x 128 but at most 256 of 192 x 128: one round of the taller tile instead of two
-        // workgroups on some compute units (512 x 10240 over K' = 8448: 48 -> 37 us; 1024 x 5120 over 27904: 144 -> 105 us)
-        {
-            const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128), t192 = ((M + 191) / 192) * ((N + 127) / 128);
-            if (t128 > 256 && t192 <= 256)
-                return launch_mx_staged<3, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
-        }
-        return launch_mx_staged<2, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream,
-                                            workspace ? mx_split_k(M, N, Kp) : 1, workspace);
-    }
-    if (nb >= 8 && offsets_fit) {
-        // any K' that is a multiple of 32, operands at their minimum alignment: units through registers
-        if (tile_rows == 256)
-            return launch_mx_staged<4, 4, 2, 2, OutT, false, true>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
-        if (tile_rows == 192)
-            return launch_mx_staged<3, 4, 2, 2, OutT, false, true>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
-        if (tile_rows == 128)
-            return launch_mx_staged<2, 4, 2, 2, OutT, false, true>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
-        return launch_mx_staged<2, 2, 2, 2, OutT, false, true>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream,
-                                                               workspace ? mx_split_k(M, N, Kp) : 1, workspace);
-    }
+            return launch_mx_staged<2, 4, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
+        if constexpr (MODE != REGS)
+            if (one_round_192)
+                return launch_mx_staged<3, 2, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
+        return launch_mx_staged<2, 2, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream,
+                                                  workspace ? mx_split_k(M, N, Kp) : 1, workspace);
+    };
+    if ((nb & 3) == 0 && offsets_fit && aligned16) return tiled(std::integral_constant<int, COPIES>{});
+    // any K' (a multiple of 32) from 512 on, codes at their minimum alignment
+    if (nb >= ScaleWindows<128, 128, 256, 8>::MIN_NB && offsets_fit &&
+        ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0)
+        return tiled(std::integral_constant<int, RAGGED>{});
+    // scale bytes at odd addresses, short K': units through registers
+    if (nb >= 8 && offsets_fit) return tiled(std::integral_constant<int, REGS>{});
     dim3 grid((unsigned)((N + 127) / 128), (unsigned)((M + 127) / 128));
     hipLaunchKernelGGL(mx_gemm_direct_kernel<OutT>, grid, dim3(256), 0, stream, a_codes, a_scales, w_codes, w_scales,
                        (int)M, (int)N, nb, y, ldy);
@@ -684,10 +779,10 @@ arcq_status launch_ref_gemm_bf16(const void* x, const void* w, int64_t M, int64_
     const uint8_t* b = static_cast<const uint8_t*>(w);
     const int nb = (int)(K >> 3);
     const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
-    if (t256 >= 256) return launch_mx_staged<4, 4, 2, 2, _Float16, true>(a, nullptr, b, nullptr, (int)M, (int)N, nb, y, ldy, stream);
+    if (t256 >= 256) return launch_mx_staged<4, 4, 2, 2, COPIES, true>(a, nullptr, b, nullptr, (int)M, (int)N, nb, y, ldy, stream);
     const int64_t t128x256 = ((M + 127) / 128) * ((N + 255) / 256);
-    if (t128x256 >= 192) return launch_mx_staged<2, 4, 2, 2, _Float16, true>(a, nullptr, b, nullptr, (int)M, (int)N, nb, y, ldy, stream);
-    return launch_mx_staged<2, 2, 2, 2, _Float16, true>(a, nullptr, b, nullptr, (int)M, (int)N, nb, y, ldy, stream);
+    if (t128x256 >= 192) return launch_mx_staged<2, 4, 2, 2, COPIES, true>(a, nullptr, b, nullptr, (int)M, (int)N, nb, y, ldy, stream);
+    return launch_mx_staged<2, 2, 2, 2, COPIES, true>(a, nullptr, b, nullptr, (int)M, (int)N, nb, y, ldy, stream);
 }
 
 size_t mx_gemm_workspace_bytes(int64_t M, int64_t N, int64_t Kp) {

@@ -67,3 +67,26 @@ def test_nvfp4_any_number_of_blocks(M, N, nb):
     a1 = operand(torch.Generator(device="cuda").manual_seed(M + N + nb), M, nb, 16, lead=1)
     assert torch.equal(a1[0], a[0]) and torch.equal(a1[1], a[1])
     assert worst(B.arcq_gemm(*a1, 1.0, *w, 1.0, out_dtype=torch.float32), ref) <= 2e-5
+
+
+# one shape of each tile: 128 x 128 (the longer ones cut K' into runs of two and more units), 192 x 128, 128 x 256, 192 x 256, 256 x 256
+MX = [(300, 261, b) for b in (16, 17, 22, 31, 67, 130)] + [(1277, 4090, b) for b in (19, 26)] + \
+     [(2047, 4093, b) for b in (17, 20, 23, 30)] + [(767, 14333, b) for b in (18, 21, 25)] + [(1022, 14331, b) for b in (17, 27, 28, 31)]
+
+
+@pytest.mark.parametrize("M,N,nb", MX)
+def test_mxfp4_any_number_of_blocks(M, N, nb):
+    """The scaled matrix instruction keeps fewer bits inside one instruction: 1.5e-4 of the product's 2-norm."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + nb)
+    a, w = operand(g, M, nb, 32), operand(g, N, nb, 32)
+    ref = dequantize(*a, 32) @ dequantize(*w, 32).t()
+    need = B.arcq_mx_gemm_workspace_size(M, N, nb * 32)
+    ws = torch.empty(max(need, 256), dtype=torch.uint8, device="cuda")
+    a1 = operand(torch.Generator(device="cuda").manual_seed(M + N + nb), M, nb, 32, lead=1)   # through registers
+    for case in (a, a1):
+        for workspace in (None, ws):
+            y = B.arcq_mx_gemm(*case, *w, out_dtype=torch.float32, workspace=workspace)
+            assert float((y.double() - ref).norm() / ref.norm()) <= 6e-4 and worst(y, ref) <= 5e-3
+    y = B.arcq_mx_gemm(*a, *w, out_dtype=torch.float32)
+    h = B.arcq_mx_gemm(*a, *w)
+    assert torch.equal(h, y.half())
