@@ -21,14 +21,18 @@ __device__ __forceinline__ uint32_t absmax2(uint32_t acc, uint32_t v) {
 
 // Four waves per workgroup: lane l of every wave owns the 8 channels 8 (64 blockIdx.x + l) .. + 7; wave w
 // scans rows w, w + 4, ... of strip blockIdx.y with 16-byte loads (a wave instruction reads 1 KB of one
-// row), eight rows in flight; the four waves combine through LDS and one of them merges the eight
-// maxima into the running statistic with integer atomic maxima (atomics on one address serialise in
-// the L2, so there are few strips and one atomic per channel and strip).
+// row), eight rows in flight; the four waves combine through LDS and merge the maxima into the running statistic with
+// integer atomic maxima (atomics on one address serialise in the L2, so there are few strips and one atomic per
+// channel and strip).  A lane merges neighbouring channels with its neighbours, so that an atomic instruction covers two
+// cache lines instead of sixteen, and leaves out the channels whose statistic, read when the workgroup
+// started, is no smaller already: from the second batch on that is nearly all of them.
 // HBM-bound: 2 bytes per element read once.
 constexpr int ABSMAX_UNROLL = 8;
 __global__ __launch_bounds__(256) void absmax_kernel(const uint16_t* __restrict__ x, int64_t ldx, int M, int K,
                                                      int rows_per_strip, uint32_t* __restrict__ colmax) {
-    __shared__ uint4 part[3][64];
+    __shared__ uint4 part[4][64];
+    const int tid = threadIdx.y * 64 + threadIdx.x, ch = blockIdx.x * 512 + 2 * tid;    // this thread merges channels ch, ch + 1
+    const uint2 seen = ch < K ? make_uint2(colmax[ch], colmax[ch + 1]) : make_uint2(0, 0);
     const int c8 = min((int)(blockIdx.x * 64 + threadIdx.x), (K >> 3) - 1);     // surplus lanes repeat the last group
     const int m0 = blockIdx.y * rows_per_strip + threadIdx.y, m1 = min(M, (int)(blockIdx.y + 1) * rows_per_strip);
     const uint4* src = reinterpret_cast<const uint4*>(x + 8 * (int64_t)c8);
@@ -63,58 +67,43 @@ __global__ __launch_bounds__(256) void absmax_kernel(const uint16_t* __restrict_
         mx[0].z = absmax2(mx[0].z, mx[u].z);
         mx[0].w = absmax2(mx[0].w, mx[u].w);
     }
-    if (threadIdx.y > 0) part[threadIdx.y - 1][threadIdx.x] = mx[0];
+    part[threadIdx.y][threadIdx.x] = mx[0];
     __syncthreads();
-    if (threadIdx.y > 0) return;
+    const uint32_t* halves = reinterpret_cast<const uint32_t*>(part);   // [wave][pair of channels]
+    uint32_t m2 = halves[tid];
 #pragma unroll
-    for (int w = 0; w < 3; ++w) {
-        const uint4 o = part[w][threadIdx.x];
-        mx[0].x = absmax2(mx[0].x, o.x);
-        mx[0].y = absmax2(mx[0].y, o.y);
-        mx[0].z = absmax2(mx[0].z, o.z);
-        mx[0].w = absmax2(mx[0].w, o.w);
-    }
-    const uint32_t r[4] = {mx[0].x, mx[0].y, mx[0].z, mx[0].w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float lo = __half2float(__ushort_as_half((unsigned short)(r[e] & 0xFFFFu)));
-        const float hi = __half2float(__ushort_as_half((unsigned short)(r[e] >> 16)));
-        atomicMax(colmax + 8 * c8 + 2 * e, __float_as_uint(lo));
-        atomicMax(colmax + 8 * c8 + 2 * e + 1, __float_as_uint(hi));
+    for (int w = 1; w < 4; ++w) m2 = absmax2(m2, halves[256 * w + tid]);
+    const uint32_t lo = __float_as_uint(__half2float(__ushort_as_half((unsigned short)(m2 & 0xFFFFu))));
+    const uint32_t hi = __float_as_uint(__half2float(__ushort_as_half((unsigned short)(m2 >> 16))));
+    if (ch < K) {                                               // K is even
+        if (lo > seen.x) atomicMax(colmax + ch, lo);
+        if (hi > seen.y) atomicMax(colmax + ch + 1, hi);
     }
 }
 
-// One workgroup: layer maximum, tau = 2^-3 max (exact), number of channels above tau, S rounded up to
-// a block of 16.  info = {S, S_raw, bits(max), bits(tau)}.
-__global__ __launch_bounds__(1024) void calib_stats_kernel(const uint32_t* __restrict__ colmax, int K,
-                                                           int32_t* __restrict__ info) {
-    __shared__ uint32_t part[16];
-    __shared__ uint32_t total;
+// Layer maximum, tau = 2^-3 max (exact), number of channels above tau, S rounded up to a block of 16, by one workgroup of
+// 1024 threads.  info = {S, S_raw, bits(max), bits(tau)}.
+__device__ __forceinline__ void calib_stats(const uint32_t* __restrict__ colmax, int K, int32_t* __restrict__ info, int* part) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t mx = 0;
     for (int k = tid; k < K; k += 1024) mx = max(mx, colmax[k]);
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, m, 64));
-    if (lane == 0) part[wave] = mx;
+    if (lane == 0) part[wave] = (int)mx;
     __syncthreads();
-    if (tid == 0) {
-        uint32_t t = 0;
-        for (int w = 0; w < 16; ++w) t = max(t, part[w]);
-        total = t;
-    }
-    __syncthreads();
-    const float layer_max = __uint_as_float(total);
-    const float tau = layer_max * 0.125f;
+    uint32_t total = 0;
+    for (int w = 0; w < 16; ++w) total = max(total, (uint32_t)part[w]);
+    const float tau = __uint_as_float(total) * 0.125f;
     int cnt = 0;
     for (int k = tid; k < K; k += 1024) cnt += __uint_as_float(colmax[k]) > tau ? 1 : 0;
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) cnt += __shfl_xor(cnt, m, 64);
     __syncthreads();
-    if (lane == 0) part[wave] = (uint32_t)cnt;
+    if (lane == 0) part[wave] = cnt;
     __syncthreads();
     if (tid == 0) {
         int s_raw = 0;
-        for (int w = 0; w < 16; ++w) s_raw += (int)part[w];
+        for (int w = 0; w < 16; ++w) s_raw += part[w];
         const int s = min(K, (s_raw + 15) / 16 * 16);
         info[0] = s;
         info[1] = s_raw;
@@ -125,30 +114,41 @@ __global__ __launch_bounds__(1024) void calib_stats_kernel(const uint32_t* __res
 
 // Stable ascending order by counting: the position of channel k is the number of channels that come
 // before it (smaller statistic, or equal statistic and smaller index).  Every position is hit exactly
-// once whatever the values, so the output is always a permutation.  K^2 comparisons, tiles of the
-// keys staged in LDS; K <= 65536 keeps this well under a millisecond, and it runs once per layer.
-constexpr int RANK_TILE = 2048;
-__global__ __launch_bounds__(256) void calib_rank_kernel(const uint32_t* __restrict__ colmax, int K,
-                                                         int32_t* __restrict__ perm) {
-    __shared__ uint32_t keys[RANK_TILE];
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    const uint32_t mine = k < K ? colmax[k] : 0u;
-    int before = 0;
-    for (int j0 = 0; j0 < K; j0 += RANK_TILE) {
-        const int n = min(RANK_TILE, K - j0);
-        __syncthreads();
-        for (int j = threadIdx.x; j < n; j += 256) keys[j] = colmax[j0 + j];
-        __syncthreads();
-        // tiles wholly below / above k need only one of the two comparisons
-        if (j0 + n <= k) {
-            for (int j = 0; j < n; ++j) before += keys[j] <= mine ? 1 : 0;
-        } else if (j0 > k) {
-            for (int j = 0; j < n; ++j) before += keys[j] < mine ? 1 : 0;
-        } else {
-            for (int j = 0; j < n; ++j) before += (keys[j] < mine || (keys[j] == mine && j0 + j < k)) ? 1 : 0;
-        }
+// once whatever the values, so the output is always a permutation.  K^2 comparisons, bound by the vector
+// instructions (a compare and an add with carry each): a workgroup ranks 64 channels, one per lane, and its 16 waves
+// take a sixteenth of the keys each, which are the same for all lanes and come through the scalar unit.  K = 8192: 14.6 us
+// (one lane per channel going over all keys in LDS tiles: 211 us, 32 workgroups on 256 compute units), 65536: 251 (947).  The last
+// workgroup finds the layer's statistics instead, which took a launch of their own (5 us).
+__global__ __launch_bounds__(1024) void calib_select_kernel(const uint32_t* __restrict__ colmax, int K, int32_t* __restrict__ perm,
+                                                            int32_t* __restrict__ info) {
+    __shared__ int part[16][64];
+    if (blockIdx.x == gridDim.x - 1) {
+        calib_stats(colmax, K, info, &part[0][0]);
+        return;
     }
-    if (k < K) perm[before] = k;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int k0 = blockIdx.x * 64, k = k0 + lane;
+    const uint32_t mine = colmax[min(k, K - 1)];
+    const int slice = (K + 1023) / 1024 * 64;                   // a multiple of 64: a workgroup's channels lie in one slice
+    const int j0 = min(wave * slice, K), j1 = min(j0 + slice, K);
+    int before = 0;
+    // keys of lower index come before an equal one, keys of higher index do not
+    int j = j0;
+    for (const int to = min(j1, max(j0, k0)); j < to; j += 16)  // (every bound is a multiple of 16)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) before += colmax[j + e] <= mine ? 1 : 0;
+    for (const int to = min(j1, max(j0, k0 + 64)); j < to; ++j) before += colmax[j] < mine || (colmax[j] == mine && j < k) ? 1 : 0;
+    for (; j < j1; j += 16)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) before += colmax[j + e] < mine ? 1 : 0;
+    part[wave][lane] = before;
+    __syncthreads();
+    if (wave == 0 && k < K) {
+        int position = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) position += part[w][lane];
+        perm[position] = k;
+    }
 }
 
 }  // namespace
@@ -168,9 +168,8 @@ arcq_status launch_calib_absmax(const void* x, int64_t M, int64_t K, int64_t ldx
 arcq_status launch_calib_select(const float* colmax, int64_t K, int32_t* perm, int32_t* info, int* S_host,
                                 hipStream_t stream) {
     const uint32_t* keys = reinterpret_cast<const uint32_t*>(colmax);
-    hipLaunchKernelGGL(calib_stats_kernel, dim3(1), dim3(1024), 0, stream, keys, (int)K, info);
-    hipLaunchKernelGGL(calib_rank_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, stream, keys, (int)K, perm);
-    if (arcq_status st = check_launch("calibration kernels")) return st;
+    hipLaunchKernelGGL(calib_select_kernel, dim3((unsigned)((K + 63) / 64) + 1), dim3(1024), 0, stream, keys, (int)K, perm, info);
+    if (arcq_status st = check_launch("calib_select_kernel")) return st;
     if (S_host) {
         int32_t s = 0;
         hipError_t e = hipMemcpyAsync(&s, info, sizeof(s), hipMemcpyDeviceToHost, stream);
