@@ -878,7 +878,12 @@ __device__ __forceinline__ void transpose_scale_pairs(uint2 s, uint32_t& even_ch
 // path serves in one request like an aligned one.  With an odd number of blocks the last block of a row has no
 // partner: the pairs of the main loops stop before it and the last wave handles it by itself at the end, with
 // 8-byte loads.
-template <int MT, int NT, int WAVES, int U, bool GRP, typename OutT>
+//
+// ROLL: a wave takes several groups, and asks for the next one while it computes: the registers of two chunks are loaded again
+// as soon as both have been used.  Two, because a chunk is half a cache line of every row: asking for the halves one by one,
+// each behind a chunk's decode, was 10 to 20 % slower than asking for whole groups between computing them (16 x 8192 over
+// K' = 29696, weights from HBM: 36.4, 31.0 and, by twos, 30.4 us), although it keeps the most loads in flight.
+template <int MT, int NT, int WAVES, int U, bool GRP, bool ROLL, typename OutT>
 __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N,
@@ -927,26 +932,38 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     // (Left to itself the compiler sinks the loads of the later chunks behind the decode of the earlier ones to
     // save registers, which turns one trip to memory into three; the scheduling barriers behind the calls of
     // these functions keep the loads where they are written.)
-    auto load_group = [&](int g, Group& G) {
-        const int64_t co = 256 * (int64_t)g + 16 * q, so = 32 * (int64_t)g + 8 * q;
+    auto load_scales = [&](int g, Group& G) {
+        const int64_t so = 32 * (int64_t)g + 8 * q;
 #pragma unroll
         for (int r = 0; r < MT; ++r) G.sa2[r] = load8_a1(as[r] + so);
 #pragma unroll
         for (int t = 0; t < NT; ++t) G.sw2[t] = load8_a1(ws[t] + so);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-#pragma unroll
-            for (int r = 0; r < MT; ++r) G.ca[m][r] = load16_a8(ac[r] + co + 64 * m);
-#pragma unroll
-            for (int t = 0; t < NT; ++t) G.cw[m][t] = load16_a8(wc[t] + co + 64 * m);
-        }
     };
-    auto compute_group = [&](const Group& G) {
+    auto load_codes = [&](int g, int m, Group& G) {
+        const int64_t co = 256 * (int64_t)g + 16 * q + 64 * m;
+#pragma unroll
+        for (int r = 0; r < MT; ++r) G.ca[m][r] = load16_a8(ac[r] + co);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) G.cw[m][t] = load16_a8(wc[t] + co);
+    };
+    auto load_group = [&](int g, Group& G) {
+        load_scales(g, G);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) load_codes(g, m, G);
+    };
+    // next: group whose loads go into the registers that have been used (roll_tag), else not looked at
+    auto compute_group = [&](Group& G, int next, auto roll_tag) {
+        constexpr bool roll = decltype(roll_tag)::value;
         uint32_t ea[2][MT], ew[2][NT];     // [chunk parity][tile]: pairs of chunks (0, 2) / (1, 3)
 #pragma unroll
         for (int r = 0; r < MT; ++r) transpose_scale_pairs(G.sa2[r], ea[0][r], ea[1][r]);
 #pragma unroll
         for (int t = 0; t < NT; ++t) transpose_scale_pairs(G.sw2[t], ew[0][t], ew[1][t]);
+        if constexpr (roll) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_scales(next, G);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             const uint32_t sel = (m >> 1) ? 0x0C030C02u : 0x0C010C00u;
@@ -971,6 +988,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
                     for (int r = 0; r < MT; ++r)
                         acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[r], fw, acc[r][t], 0, 0, 0);
                 }
+            }
+            if (roll && (m & 1)) {
+                __builtin_amdgcn_sched_barrier(0);
+                load_codes(next, m - 1, G);
+                load_codes(next, m, G);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
@@ -1034,11 +1057,22 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
         const bool has_tail = tail_c < nchunk;
         Chunks tail;
         if (HOIST && has_tail) load_chunks(tail_c, tail);
-        for (int g = wave; g < ngroup; g += WAVES) {
-            Group ga;
-            load_group(g, ga);
-            __builtin_amdgcn_sched_barrier(0);
-            compute_group(ga);
+        if constexpr (ROLL) {
+            if (wave < ngroup) {
+                Group ga;
+                int g = wave;
+                load_group(g, ga);
+                __builtin_amdgcn_sched_barrier(0);
+                for (; g + WAVES < ngroup; g += WAVES) compute_group(ga, g + WAVES, std::true_type{});
+                compute_group(ga, 0, std::false_type{});
+            }
+        } else {
+            for (int g = wave; g < ngroup; g += WAVES) {
+                Group ga;
+                load_group(g, ga);
+                __builtin_amdgcn_sched_barrier(0);
+                compute_group(ga, 0, std::false_type{});
+            }
         }
         if (!HOIST && has_tail) load_chunks(tail_c, tail);
         if (has_tail) compute_chunks(tail_c, tail);
@@ -1094,11 +1128,11 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     }
 }
 
-template <int MT, int NT, int WAVES, int U, bool GRP, typename OutT>
+template <int MT, int NT, int WAVES, int U, bool GRP, bool ROLL, typename OutT>
 arcq_status launch_skinny(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                                  const uint8_t* w_scales, int M, int N, int nbk, float alpha, OutT* y, int64_t ldy,
                                  hipStream_t stream) {
-    hipLaunchKernelGGL((gemm_skinny_kernel<MT, NT, WAVES, U, GRP, OutT>), dim3((N + 16 * NT - 1) / (16 * NT)),
+    hipLaunchKernelGGL((gemm_skinny_kernel<MT, NT, WAVES, U, GRP, ROLL, OutT>), dim3((N + 16 * NT - 1) / (16 * NT)),
                        dim3(WAVES * 64), 0, stream, a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy);
     return check_launch("gemm_skinny_kernel");
 }
@@ -1169,8 +1203,16 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
         // (257 to 399 tiles used to run one tile per wave, two workgroups sharing a CU: 320 tiles over K' = 27904 33.7 us
         // against 27.3 us with two tiles per wave, over K' = 4352 7.6 against 6.9)
         const int64_t T2 = 257, T3 = 513, T4 = 769;
-#define ARCQ_SKINNY_W(MT_, NT_, W_, U_) \
-    return launch_skinny<MT_, NT_, W_, U_, (MT_ <= 4)>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream)
+#define ARCQ_SKINNY_R(MT_, NT_, W_, U_, R_) \
+    launch_skinny<MT_, NT_, W_, U_, (MT_ <= 4), R_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream)
+        // ROLL where waves take several groups (from HBM, us: 16 x 28672 over K' = 8448 34.9 -> 32.0, 32 x 28672 over 8464 47.5 ->
+        // 45.1, 16 x 10240 over 8448 13.9 -> 13.1); with one group per wave its code without a loop is still 2 to 4 % faster
+        // (32 x 14336 over 4352 12.9 -> 12.4, 16 x 6144 over 4240 7.4 -> 7.3), except for four tiles behind one row tile (16 x 14336
+        // over 4352 10.4 against 10.6); one tile behind one row tile loses with several groups (16 x 4096 over 14592 11.0
+        // against 11.1, over 14544 12.3 against 12.7).  128 rows have no groups.
+#define ARCQ_SKINNY_W(MT_, NT_, W_, U_)                                                                                        \
+    return MT_ <= 4 && (MT_ * NT_ == 1 ? (nbk >> 5) <= W_ : MT_ == 1 && NT_ == 4 ? (nbk >> 5) > W_ : true)                     \
+               ? ARCQ_SKINNY_R(MT_, NT_, W_, U_, (MT_ <= 4)) : ARCQ_SKINNY_R(MT_, NT_, W_, U_, ((MT_ > 1 || NT_ == 2 || NT_ == 3) && MT_ <= 4))
 #define ARCQ_SKINNY(MT_, NT_, U_) ARCQ_SKINNY_W(MT_, NT_, 8, U_)
         if (M <= 16) {
             if (tiles >= T4) ARCQ_SKINNY(1, 4, 1);
@@ -1195,6 +1237,7 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
         ARCQ_SKINNY(8, 1, 1);
 #undef ARCQ_SKINNY
 #undef ARCQ_SKINNY_W
+#undef ARCQ_SKINNY_R
     }
     const bool offsets_fit = (uint64_t)M * (uint64_t)nbk * 8 < 0xFFFF0000ull && (uint64_t)N * (uint64_t)nbk * 8 < 0xFFFF0000ull;
     if (const int variant = gemm_ksplit_variant(M, N, Kp))

@@ -90,3 +90,22 @@ def test_mxfp4_any_number_of_blocks(M, N, nb):
     y = B.arcq_mx_gemm(*a, *w, out_dtype=torch.float32)
     h = B.arcq_mx_gemm(*a, *w)
     assert torch.equal(h, y.half())
+
+
+# weight-streaming kernels: groups of four chunks (512 k) dealt to eight waves: none, one per wave, one or two, two, more; with and
+# without chunks and blocks behind the last group; one to four weight tiles per wave, one to four row tiles
+STREAM = [(M, N, nb) for M, N in ((1, 250), (16, 4100), (13, 8200), (16, 12300), (32, 4090), (29, 8200), (32, 12300), (17, 300), (48, 300), (64, 5000))
+          for nb in (31, 256, 295, 512, 557)]
+
+
+@pytest.mark.parametrize("M,N,nb", STREAM)
+def test_streaming_groups(M, N, nb):
+    g = torch.Generator(device="cuda").manual_seed(M + N + nb)
+    a, w = operand(g, M, nb, 16), operand(g, N, nb, 16)
+    y = B.arcq_gemm(*a, 1.0, *w, 1.0, out_dtype=torch.float32)
+    assert worst(y, dequantize(*a, 16) @ dequantize(*w, 16).t()) <= 2e-5
+    nb = nb // 2 + nb % 2                            # 512 k are 16 blocks of 32
+    a, w = operand(g, M, nb, 32), operand(g, N, nb, 32)
+    ref = dequantize(*a, 32) @ dequantize(*w, 32).t()
+    y = B.arcq_mx_gemm(*a, *w, out_dtype=torch.float32)
+    assert float((y.double() - ref).norm() / ref.norm()) <= 6e-4 and worst(y, ref) <= 5e-3
