@@ -125,7 +125,7 @@ __global__ __launch_bounds__(1024) void mx_quantize_rows_kernel(
         if (DB) {
             __syncthreads();                // row landed for every wave; previous compute finished
             const int next = row + gridDim.x;
-            issue(next < rows ? next : row, base ^ lds_stride);
+            if (next < rows) issue(next, base ^ lds_stride);
         } else {
             issue(row, 0);
             ARCQ_MX_WAIT_VMCNT(0);
@@ -231,6 +231,7 @@ __global__ __launch_bounds__(1024) void mx_quantize_pairs_kernel(
         }
     };
 
+    issue(row, 0);                          // before anything else is asked for or waited for
     // lane pairs past the last block repeat it (same values to the same addresses)
     const int b = min(tid >> 1, nb - 1), half = tid & 1;
     uint32_t chan[8];                       // source channels of the lane's half block, two 16-bit indices per register
@@ -248,12 +249,11 @@ __global__ __launch_bounds__(1024) void mx_quantize_pairs_kernel(
     const int ba = interleaved ? bp + 1 : nb + io;
 
     uint32_t base = 0;
-    issue(row, 0);
     ARCQ_MX_WAIT_VMCNT(0);
     for (; row < rows; row += gridDim.x) {
         __syncthreads();                    // row landed for every wave; previous compute finished
         const int next = row + gridDim.x;
-        issue(next < rows ? next : row, base ^ lds_stride);
+        if (next < rows) issue(next, base ^ lds_stride);
         uint8_t* crow = codes + (int64_t)row * code_pitch;
         uint8_t* srow = scales + (int64_t)row * scale_pitch;
         float v[16];
