@@ -1137,11 +1137,10 @@ arcq_status launch_skinny(const uint8_t* a_codes, const uint8_t* a_scales, const
     return check_launch("gemm_skinny_kernel");
 }
 
-// Shapes the weight-streaming kernel serves (alignment permitting): up to 64 rows always; up to 128 rows
-// unless the problem is big enough for the tiled kernels with split K to be faster (measured over
-// N = 1024 .. 28672, K' = 1088 .. 14592 at M = 80, 96, 128: the eight-row-tile variant of the streaming kernel
-// takes about 1 us per 10^6 weights, the tiled path 20-30 us for everything up to 6 * 10^7 weights, more with
-// a short K' that cannot be split).
+// 65 to 128 rows on the weight-streaming kernel rather than on tiles with K' split across workgroups: unless the problem is
+// big enough for the latter (measured over N = 1024 .. 28672, K' = 1088 .. 14592 at M = 80, 96, 128: the eight-row-tile variant
+// of the streaming kernel takes about 1 us per 10^6 weights, the tiled path 20-30 us for everything up to 6 * 10^7 weights,
+// more with a short K' that cannot be split).
 static bool skinny_shape(int64_t M, int64_t N, int64_t Kp) {
     if (M <= 64) return true;
     if (M > 128) return false;
@@ -1149,33 +1148,73 @@ static bool skinny_shape(int64_t M, int64_t N, int64_t Kp) {
     return !((Kp >= 4096 && weights >= 20000000) || (Kp >= 8192 && weights >= 12000000));
 }
 
-// Number of runs the reduction dimension is cut into (1: no split).  A function of the shape alone,
-// so that the workspace a caller sizes beforehand matches what the launch uses.  Problems off the
-// weight-streaming path with too few 128 x 128 tiles to occupy the chip split K' into runs of at least four
-// stages (256 k).  The number of runs minimises a cost in units of one stage time of a tile (about
-// 1.3 us): rounds of workgroups over the 256 CUs times the stages of a run, plus, when split, the
-// write and read of the fp32 partial results at about 3 TB/s.
-int split_k(int64_t M, int64_t N, int64_t Kp) {
+// Number of runs the reduction dimension is cut into (1: no split) on the 128 x 128 tiles, and the modelled time.  Problems
+// with too few such tiles to occupy the chip split K' into runs of at least four stages (256 k).  The number of runs minimises
+// a cost in units of one stage time of a tile (about 1.3 us): rounds of workgroups over the 256 CUs times the stages of a run,
+// plus, when split, the write and read of the fp32 partial results at about 3 TB/s.
+static int split_runs(int64_t M, int64_t N, int64_t Kp, double* us) {
     const int64_t nbk = Kp >> 4;
-    if (skinny_shape(M, N, Kp) || nbk < 8) return 1;
-    if (gemm_ksplit_variant(M, N, Kp) != 0) return 1;      // the k split happens inside the workgroups
-    if (((M + 255) / 256) * ((N + 255) / 256) >= 256 || ((M + 127) / 128) * ((N + 255) / 256) >= 192) return 1;
     const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
-    if (tiles > 128) return 1;
     const int64_t nstage = (nbk + 7) >> 3;
-    const int64_t max_splits = std::min<int64_t>(8, nstage / 4);
+    const int64_t max_splits = tiles > 128 || nbk < 8 ? 1 : std::min<int64_t>(8, nstage / 4);
     int best = 1;
-    double best_cost = 0.0;
-    for (int64_t sp = 1; sp <= max_splits; ++sp) {
+    double best_cost = (double)((tiles + 255) / 256) * (double)nstage;
+    for (int64_t sp = 2; sp <= max_splits; ++sp) {
         const double rounds = (double)((tiles * sp + 255) / 256);
-        double cost = rounds * (double)((nstage + sp - 1) / sp);
-        if (sp > 1) cost += (double)sp * (double)M * (double)N * 8.0 / 4.0e6;
-        if (sp == 1 || cost < best_cost) {
+        const double cost = rounds * (double)((nstage + sp - 1) / sp) + (double)sp * (double)M * (double)N * 8.0 / 4.0e6;
+        if (cost < best_cost) {
             best = (int)sp;
             best_cost = cost;
         }
     }
+    *us = 1.3 * best_cost + (best > 1 ? 6.0 : 4.0);
     return best;
+}
+
+// Which kernel serves a problem: a function of the shape alone, so that the workspace a caller sizes beforehand matches what the
+// launch uses.  Up to 32 rows the weight-streaming kernel, beyond the smallest modelled time of three:
+//   * the streaming kernel up to 128 rows: start + 512-k groups x time of a round's group (one or two weight tiles per wave);
+//     e.g. 64 rows over K' = 4240: 5120 weight rows 12.5 us against 14.3 on 64 x 32 tiles, 28672 38.9 against 30.4 on 64 x 128;
+//   * the tiles with the k split inside the workgroup (gemm_ksplit_best);
+//   * the tiles of this file, with K' split across workgroups or without, by the stage times that choose among them
+//     (80 x 10240 over K' = 14544: 52.8 us in three runs, 61.2 on 96 x 64 tiles).  Where they would need a larger workspace
+//     than the library's built-in scratch, which problems callers without a workspace can run does not follow the times:
+//     the former take what they occupy the chip with.
+struct GemmPlan {
+    bool stream;
+    int ksplit;         // tile variant of gemm_ksplit.hip, 0: the tiles of this file
+    int splits;         // runs of K' on those
+};
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp) {
+    if (M <= 32) return {true, 0, 1};
+    double tiles_us, split_us;
+    bool ample;
+    const int variant = gemm_ksplit_best(M, N, Kp, &tiles_us, &ample);
+    const double groups = (double)Kp / 512.0;
+    const int64_t tiles16 = (N + 15) / 16;
+    const bool two = tiles16 >= 257;            // weight tiles per wave of the streaming kernel
+    const double rounds = (double)(((two ? (tiles16 + 1) / 2 : tiles16) + 255) / 256);
+    if (skinny_shape(M, N, Kp)) {
+        // a second round costs more than the model says with few groups (48 x 14336 over 1552: 11.9 us against 10.6 on 64 x 64 tiles)
+        const double us = M <= 64 ? 3.0 + groups * rounds * (two ? 1.11 : 0.64) * (rounds > 1.0 ? 1.25 : 1.0)
+                                  : 4.2 + groups * rounds * (two ? 2.27 : 1.135);
+        return variant != 0 && tiles_us < us ? GemmPlan{false, variant, 1} : GemmPlan{true, 0, 1};
+    }
+    const int64_t nstage = ((Kp >> 4) + 7) >> 3, tn256 = (N + 255) / 256, t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    int splits = 1;
+    double us;
+    if (((M + 127) / 128) * tn256 >= 192) {
+        auto cost = [&](int bm, double t_stage) { return (double)((((M + bm - 1) / bm) * tn256 + 255) / 256) * t_stage; };
+        us = 5.0 + (double)nstage * std::min({cost(256, 2.96), cost(192, 2.59), cost(128, 1.96)});
+    } else if (t128 > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256) {
+        us = 5.0 + (double)nstage * 1.52;
+    } else {
+        splits = split_runs(M, N, Kp, &split_us);
+        us = split_us;
+    }
+    const bool too_large = splits > 1 && (uint64_t)splits * (uint64_t)M * (uint64_t)N * sizeof(float) > ARCQ_NOALLOC_SCRATCH_BYTES;
+    if (variant != 0 && (too_large ? ample : tiles_us < us)) return {false, variant, 1};
+    return {false, 0, splits};
 }
 
 template <typename OutT>
@@ -1185,13 +1224,8 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
     const int nbk = (int)(Kp >> 4);
     const bool aligned16 = ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 &&
                            ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
-    // 33 to 64 rows against many weight rows: 64 x 64 tiles with the k split inside the workgroup decode every activation
-    // fragment once per tile, the weight-streaming kernel once per 32 weight rows
-    // (measured with weights from HBM, 64 rows: 14336 x 4352 15.8 us against 21.8, 9216 x 4352 15.3 against 25.3,
-    // 12288 x 8448 25.0 against 44.8; 33 rows gain as long as the tiles are 64 x 64)
-    const int ks_variant = M > 32 ? gemm_ksplit_variant(M, N, Kp) : 0;
-    const bool tiles_instead = ks_variant == 1 || ks_variant == 6 || (ks_variant != 0 && M > 48);
-    if (skinny_shape(M, N, Kp) && !tiles_instead) {
+    const GemmPlan plan = plan_gemm(M, N, Kp);
+    if (plan.stream) {
         // Weight-streaming path.  Enough waves to keep the weight stream in flight, as few as that allows
         // so that each wave has several KB to request at once: with many weight rows several tiles per
         // wave share the activation operand; with few, one tile per wave so that every CU still gets a
@@ -1240,8 +1274,8 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
 #undef ARCQ_SKINNY_R
     }
     const bool offsets_fit = (uint64_t)M * (uint64_t)nbk * 8 < 0xFFFF0000ull && (uint64_t)N * (uint64_t)nbk * 8 < 0xFFFF0000ull;
-    if (const int variant = gemm_ksplit_variant(M, N, Kp))
-        return launch_gemm_ksplit(variant, a_codes, a_scales, w_codes, w_scales, M, N, Kp, alpha, y,
+    if (plan.ksplit != 0)
+        return launch_gemm_ksplit(plan.ksplit, a_codes, a_scales, w_codes, w_scales, M, N, Kp, alpha, y,
                                   std::is_same<OutT, _Float16>::value ? ARCQ_DTYPE_F16 : ARCQ_DTYPE_F32, ldy, stream);
     // Tiles of 256 weight rows by 256, 192 or 128 activation rows when there is work for them.  Workgroups run in
     // rounds of one per compute unit and a round lasts as long as one tile, so the tile height that minimises
@@ -1276,7 +1310,7 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
         if (one_round_192)
             return launch_staged<3, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         return launch_staged<2, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
-                                         split_k(M, N, Kp), workspace);
+                                         plan.splits, workspace);
     }
     if (nbk >= ScaleWindows<128, 128, 256, 8>::MIN_NB && offsets_fit &&
         ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0) {
@@ -1293,7 +1327,7 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
         if (one_round_192)
             return launch_staged<3, 2, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         return launch_staged<2, 2, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
-                                                 split_k(M, N, Kp), workspace);
+                                                 plan.splits, workspace);
     }
     if (offsets_fit && nbk >= 8) {
         // scale bytes at odd addresses, or K' from 128 to 240 that is no multiple of 64: stages through registers (no 256 x 256
@@ -1307,7 +1341,7 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
         if (one_round_192)
             return launch_staged<3, 2, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         return launch_staged<2, 2, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
-                                               split_k(M, N, Kp), workspace);
+                                               plan.splits, workspace);
     }
     dim3 grid((unsigned)((N + 127) / 128), (unsigned)((M + 127) / 128));
     hipLaunchKernelGGL(gemm_direct_kernel<OutT>, grid, dim3(256), 0, stream, a_codes, a_scales, w_codes, w_scales,
@@ -1333,7 +1367,7 @@ arcq_status launch_splitk_reduce(const float* partial, int splits, int M, int N,
 }
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t Kp) {
-    const int splits = split_k(M, N, Kp);
+    const int splits = plan_gemm(M, N, Kp).splits;
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 

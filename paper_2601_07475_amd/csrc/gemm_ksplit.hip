@@ -418,6 +418,8 @@ arcq_status launch_ksplit_typed(int variant, const uint8_t* a_codes, const uint8
         case 1: return launch_ksplit<2, 2, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 64 x 64
         case 2: return launch_ksplit<4, 2, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 128 x 64
         case 4: return launch_ksplit<3, 2, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 96 x 64
+        case 5: return launch_ksplit<3, 2, 1, 2, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);  // 96 x 128
+        case 7: return launch_ksplit<2, 2, 1, 2, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);  // 64 x 128
         case 6: return launch_ksplit<2, 1, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 64 x 32
         default: return launch_ksplit<2, 4, 2, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);  // 128 x 128
     }
@@ -425,28 +427,39 @@ arcq_status launch_ksplit_typed(int variant, const uint8_t* a_codes, const uint8
 
 }  // namespace
 
-// 0: not served here; 6: 64 x 32 tiles; 1: 64 x 64; 4: 96 x 64; 2: 128 x 64; 3: 128 x 128 (k quarters inside the workgroup each)
-int gemm_ksplit_variant(int64_t M, int64_t N, int64_t Kp) {
+// The tile that takes the least time, and that time in us; 0 and a time beyond any other's where none serves the problem.
+// Only tiles that cover it with at most one workgroup per compute unit (256) are looked at: with more, a second round costs
+// as much as the first; and with 32 at least, below which K' is better split across workgroups.  The time of a tile over K' is start + stages (alone + shared x workgroups / 256): a workgroup
+// takes longer the more of the chip is busy (clock, and the weights' way from HBM).  Fitted to 466 problems (M = 20 .. 640,
+// N = 1024 .. 28672, K' = 1552, 4240, 8464, 14544, weights from HBM) to 4 to 9 % rms; the choice among these, the streaming
+// kernel and the tiles of gemm.hip by the modelled times (gemm.hip) is 1.2 % from the best of all on average, where fixed
+// limits of 144 to 256 workgroups on five tile shapes were 5.7 % off.
+// *ample: some tile occupies more than half of the chip, or the smallest one an eighth of it over a short K'.
+int gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp, double* us, bool* ample) {
+    struct Tile {
+        int variant, bm, bn;
+        double start, alone, shared;
+    };
+    static constexpr Tile tiles[] = {{6, 64, 32, 4.1, 0.454, 0.100}, {1, 64, 64, 5.0, 0.552, 0.154}, {4, 96, 64, 5.9, 0.692, 0.249},
+                                     {7, 64, 128, 4.4, 0.955, 0.343}, {2, 128, 64, 7.0, 0.832, 0.236}, {5, 96, 128, 6.5, 1.067, 0.400},
+                                     {3, 128, 128, 7.7, 1.254, 0.497}};
+    *us = 1e30;
+    *ample = false;
     const int64_t nbk = Kp >> 4;
     if (nbk < 32) return 0;                               // at least two stages
     if ((uint64_t)M * (uint64_t)nbk * 8 >= 0xFFFF0000ull || (uint64_t)N * (uint64_t)nbk * 8 >= 0xFFFF0000ull) return 0;
-    // The smallest tile that still covers the problem with at most one workgroup per compute unit (256), as long as
-    // it occupies more than half of them (measured at 4096 x 4352, 14336 x 4352 and 4096 x 14592 weights, M = 128 ..
-    // 1024: against the 128 x 128 tiles with K' split across workgroups these run 64 x 64 tiles 1.2-1.8x, 128 x 64
-    // tiles 1.1-1.5x and 128 x 128 tiles 1.05-1.2x faster; with fewer tiles the split across workgroups wins, with
-    // more the larger tiles of gemm.hip do).
-    const int64_t m64 = (M + 63) / 64, m96 = (M + 95) / 96, m128 = (M + 127) / 128, n64 = (N + 63) / 64, n128 = (N + 127) / 128;
-    auto fits = [](int64_t tiles) { return tiles >= 144 && tiles <= 256; };
-    // the smallest tile also with fewer workgroups, for more than 64 rows and a short reduction (a tile takes 10.7 us
-    // over K' = 4352, 17.3 over 8448, 27 over 14592 whatever their number; the alternatives, the eight-row-tile
-    // streaming kernel and 128 x 128 tiles with K' split across workgroups, take 15-17, 21-29 and 24-26 us there)
-    const int64_t t6 = m64 * ((N + 31) / 32);
-    if (fits(t6) || (M > 64 && nbk <= 544 && t6 >= 32 && t6 <= 256)) return 6;
-    if (fits(m64 * n64)) return 1;
-    if (fits(m96 * n64)) return 4;
-    if (fits(m128 * n64)) return 2;
-    if (fits(m128 * n128)) return 3;
-    return 0;
+    int best = 0;
+    for (const Tile& t : tiles) {
+        const int64_t wgs = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        if (wgs > 256 || wgs < 32) continue;
+        if (t.variant != 7 && t.variant != 5 && (wgs >= 144 || (t.variant == 6 && M > 64 && nbk <= 544))) *ample = true;
+        const double c = t.start + (double)((nbk + 15) / 16) * (t.alone + t.shared * (double)wgs / 256.0);
+        if (c < *us) {
+            *us = c;
+            best = t.variant;
+        }
+    }
+    return best;
 }
 
 arcq_status launch_gemm_ksplit(int variant, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,

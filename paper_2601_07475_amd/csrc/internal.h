@@ -43,8 +43,8 @@ arcq_status launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales,
                         void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 // Tiled kernel whose waves split every stage along k inside the workgroup (gemm_ksplit.hip): which of its tile
-// shapes serves this problem (0: none), and its launch.
-int gemm_ksplit_variant(int64_t M, int64_t N, int64_t Kp);
+// shapes is the fastest for this problem (0: none serves it) and its modelled time, and its launch.
+int gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp, double* us, bool* ample);
 arcq_status launch_gemm_ksplit(int variant, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                                const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, float alpha, void* y, int y_dtype,
                                int64_t ldy, hipStream_t stream);

@@ -49,9 +49,10 @@ def worst(y, ref):
 # 16 blocks (two stages) and more, every residue of the block count modulo 8 with odd and even counts on each tile
 STAGED = [(300, 261, b) for b in (16, 17, 22, 31)] + [(1277, 4090, b) for b in (19, 24, 26)] + \
          [(2047, 4093, b) for b in (17, 20, 23, 30)] + [(767, 14333, b) for b in (18, 21, 25)] + [(1022, 14331, b) for b in (17, 27, 28)]
-# k quarters inside the workgroup: 64 x 32, 64 x 64, 96 x 64, 128 x 64, 128 x 128
+# k quarters inside the workgroup: 64 x 32, 64 x 64, 96 x 64, 128 x 64, 128 x 128, 64 x 128, 96 x 128
 KSPLIT = [(130, 1021, b) for b in (33, 46, 63)] + [(190, 4091, b) for b in (34, 49)] + [(301, 3070, b) for b in (35, 48, 61)] + \
-         [(509, 2555, b) for b in (37, 62)] + [(510, 4090, b) for b in (32, 47, 50)]
+         [(509, 2555, b) for b in (37, 62)] + [(510, 4090, b) for b in (32, 47, 50)] + \
+         [(61, 20475, b) for b in (33, 40, 46)] + [(335, 6140, b) for b in (36, 47, 53)]
 
 
 @pytest.mark.parametrize("M,N,nb", STAGED + KSPLIT)
