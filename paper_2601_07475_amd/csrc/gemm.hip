@@ -1203,11 +1203,11 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp) {
     const int64_t nstage = ((Kp >> 4) + 7) >> 3, tn256 = (N + 255) / 256, t128 = ((M + 127) / 128) * ((N + 127) / 128);
     int splits = 1;
     double us;
-    if (((M + 127) / 128) * tn256 >= 192) {
+    if (t128 > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256) {
+        us = 5.0 + (double)nstage * 1.52;
+    } else if (((M + 127) / 128) * tn256 >= 192) {
         auto cost = [&](int bm, double t_stage) { return (double)((((M + bm - 1) / bm) * tn256 + 255) / 256) * t_stage; };
         us = 5.0 + (double)nstage * std::min({cost(256, 2.96), cost(192, 2.59), cost(128, 1.96)});
-    } else if (t128 > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256) {
-        us = 5.0 + (double)nstage * 1.52;
     } else {
         splits = split_runs(M, N, Kp, &split_us);
         us = split_us;
@@ -1290,9 +1290,12 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
     // More than 256 tiles of 128 x 128 (two workgroups on some compute units, one on the others) but at most 256 of
     // 192 x 128: one round of the taller tile, which also decodes five fragments per six matrix instructions
     // instead of four per four (1.52 against 1.3 us per stage and tile): 512 x 10240 over K' = 8448 116 -> 100 us,
-    // 1024 x 5120 over 27904 365 -> 297 us, 1280 x 4096 over 4352 61 -> 49 us.
+    // 1024 x 5120 over 27904 365 -> 297 us, 1280 x 4096 over 4352 61 -> 49 us.  It goes before the 256-wide tiles, which take
+    // one round as well where both fit, of a larger tile on fewer compute units (160 x 28672 over K' = 4352: 51.2 against 58.9 us).
     const bool one_round_192 = ((M + 127) / 128) * ((N + 127) / 128) > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256;
     if ((nbk & 3) == 0 && nbk >= 8 && offsets_fit && aligned16) {
+        if (one_round_192)
+            return launch_staged<3, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         if (wide) {
             if (c256 <= c192 && c256 <= c128)
                 return launch_staged<4, 4, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
@@ -1307,8 +1310,6 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
                            : launch_kpair<RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
             return launch_staged<2, 2, 2, 4>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         }
-        if (one_round_192)
-            return launch_staged<3, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         return launch_staged<2, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
                                          plan.splits, workspace);
     }
@@ -1317,6 +1318,8 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
         // Any K' from 256 on, codes that are only 8-byte aligned: the same tiles by the same rule, 1 to 5 % slower than with
         // whole aligned rows (S = 272 against S = 256, and through registers: 4096 x 8192 over K = 8192 434, 419 and 581 us;
         // 2048 x 4096 over K = 4096 69.2, 65.2 and 79.4 us; 512 x 10240 over K = 8192 98.1, 93.7 and 112.8 us)
+        if (one_round_192)
+            return launch_staged<3, 2, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         if (wide) {
             if (c256 <= c192 && c256 <= c128)
                 return launch_staged<4, 4, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
@@ -1324,8 +1327,6 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
                 return launch_staged<3, 4, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
             return launch_kpair<RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         }
-        if (one_round_192)
-            return launch_staged<3, 2, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         return launch_staged<2, 2, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
                                                  plan.splits, workspace);
     }
@@ -1333,13 +1334,13 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
         // scale bytes at odd addresses, or K' from 128 to 240 that is no multiple of 64: stages through registers (no 256 x 256
         // tiles: the staging registers do not fit beside 256 accumulators); the same choice by rounds x stage time
         // (3.5 and 2.4 us measured per stage for 192 x 256 and 128 x 256 tiles: 768 x 14336 over K' = 4368 118 us instead of 163)
+        if (one_round_192)
+            return launch_staged<3, 2, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         if (wide) {
             if (cost(192, 3.5) <= cost(128, 2.4))
                 return launch_staged<3, 4, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
             return launch_staged<2, 2, 2, 4, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         }
-        if (one_round_192)
-            return launch_staged<3, 2, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         return launch_staged<2, 2, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
                                                plan.splits, workspace);
     }

@@ -740,19 +740,20 @@ arcq_status launch_mx_typed(const uint8_t* a_codes, const uint8_t* a_scales, con
                           : tile_cost(256) <= tile_cost(192) && tile_cost(256) <= tile_cost(128) ? 256
                           : tile_cost(192) <= tile_cost(128) ? 192 : 128;
     // more than 256 tiles of 128 x 128 but at most 256 of 192 x 128: one round of the taller tile instead of two
-    // workgroups on some compute units (512 x 10240 over K' = 8448: 48 -> 37 us; 1024 x 5120 over 27904: 144 -> 105 us)
+    // workgroups on some compute units (512 x 10240 over K' = 8448: 48 -> 37 us; 1024 x 5120 over 27904: 144 -> 105 us); and
+    // before the 256-wide tiles, which put a round of larger tiles on fewer compute units (160 x 28672 over 4352: 28.6 -> 24.2 us)
     const bool one_round_192 = ((M + 127) / 128) * ((N + 127) / 128) > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256;
     auto tiled = [&](auto mode_tag) {
         constexpr int MODE = decltype(mode_tag)::value;
+        if constexpr (MODE != REGS)
+            if (one_round_192)
+                return launch_mx_staged<3, 2, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
         if (tile_rows == 256)
             return launch_mx_staged<4, 4, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
         if (tile_rows == 192)
             return launch_mx_staged<3, 4, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
         if (tile_rows == 128)
             return launch_mx_staged<2, 4, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
-        if constexpr (MODE != REGS)
-            if (one_round_192)
-                return launch_mx_staged<3, 2, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
         return launch_mx_staged<2, 2, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream,
                                                   workspace ? mx_split_k(M, N, Kp) : 1, workspace);
     };

@@ -52,7 +52,7 @@ STAGED = [(300, 261, b) for b in (16, 17, 22, 31)] + [(1277, 4090, b) for b in (
 # k quarters inside the workgroup: 64 x 32, 64 x 64, 96 x 64, 128 x 64, 128 x 128, 64 x 128, 96 x 128
 KSPLIT = [(130, 1021, b) for b in (33, 46, 63)] + [(190, 4091, b) for b in (34, 49)] + [(301, 3070, b) for b in (35, 48, 61)] + \
          [(509, 2555, b) for b in (37, 62)] + [(510, 4090, b) for b in (32, 47, 50)] + \
-         [(61, 20475, b) for b in (33, 40, 46)] + [(335, 6140, b) for b in (36, 47, 53)]
+         [(150, 28600, b) for b in (33, 40)] + [(61, 20475, b) for b in (33, 40, 46)] + [(335, 6140, b) for b in (36, 47, 53)]
 
 
 @pytest.mark.parametrize("M,N,nb", STAGED + KSPLIT)
@@ -72,7 +72,7 @@ def test_nvfp4_any_number_of_blocks(M, N, nb):
 
 # one shape of each tile: 128 x 128 (the longer ones cut K' into runs of two and more units), 192 x 128, 128 x 256, 192 x 256, 256 x 256
 MX = [(300, 261, b) for b in (16, 17, 22, 31, 67, 130)] + [(1277, 4090, b) for b in (19, 26)] + \
-     [(2047, 4093, b) for b in (17, 20, 23, 30)] + [(767, 14333, b) for b in (18, 21, 25)] + [(1022, 14331, b) for b in (17, 27, 28, 31)]
+     [(2047, 4093, b) for b in (17, 20, 23, 30)] + [(767, 14333, b) for b in (18, 21, 25)] + [(1022, 14331, b) for b in (17, 27, 28, 31)] + [(150, 28600, b) for b in (16, 21)]
 
 
 @pytest.mark.parametrize("M,N,nb", MX)
