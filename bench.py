@@ -350,7 +350,7 @@ def s_sweep(torch, B, case, values):
     for r in rows:
         r["gemm_vs_S0"] = round(r["gemm_ms"] / g0, 4) if g0 else None
         r["Kp_vs_K"] = round((wl.K + r["S"]) / wl.K, 4)
-        r["Kp_mod_64"] = (wl.K + r["S"]) % 64       # non-zero: stages staged through registers instead of copied into LDS
+        r["Kp_mod_64"] = (wl.K + r["S"]) % 64       # non-zero: rows off 64-byte lines, scale bytes as windows
     return rows
 
 

@@ -244,8 +244,8 @@ arcq_status arcq_calib_select(const float* colmax, int64_t K, int32_t* perm, int
  * so arcq_mx_gemm needs no decode:
  *   y[m, n] = sum_b 2^(sa[m,b]-127) 2^(sw[n,b]-127) sum_{i<32} qa[m,32b+i] qw[n,32b+i],  fp32 accumulation
  * (Section 3.2 eq. (2)); Kp % 32 == 0; codes 4-byte aligned.  Every such shape runs on the tiled /
- * weight-streaming kernels; 16-byte aligned codes, 4-byte aligned scales and Kp % 128 == 0 additionally let
- * the tiled kernels copy straight into LDS (about 1.5x faster on large M); y as in arcq_gemm.  No workspace (see arcq_mx_gemm_ws below).
+ * weight-streaming kernels; 16-byte aligned codes and Kp % 128 == 0 are the fastest case on large M (by 1.25 to 1.45x), scale
+ * bytes whose base is not 4-byte aligned the slowest; y as in arcq_gemm.  No workspace (see arcq_mx_gemm_ws below).
  */
 arcq_status arcq_mx_packed_sizes(int64_t rows, int64_t K, int64_t S,
                                  size_t* codes_bytes, size_t* scales_bytes);
