@@ -1176,10 +1176,10 @@ static int split_runs(int64_t M, int64_t N, int64_t Kp, double* us) {
 //   * the streaming kernel up to 128 rows: start + 512-k groups x time of a round's group (one or two weight tiles per wave);
 //     e.g. 64 rows over K' = 4240: 5120 weight rows 12.5 us against 14.3 on 64 x 32 tiles, 28672 38.9 against 30.4 on 64 x 128;
 //   * the tiles with the k split inside the workgroup (gemm_ksplit_best);
-//   * the tiles of this file, with K' split across workgroups or without, by the stage times that choose among them
-//     (80 x 10240 over K' = 14544: 52.8 us in three runs, 61.2 on 96 x 64 tiles).  Where they would need a larger workspace
-//     than the library's built-in scratch, which problems callers without a workspace can run does not follow the times:
-//     the former take what they occupy the chip with.
+//   * the tiles of this file, with K' split across workgroups or without, by the stage times that choose among them.
+// K' is split across workgroups only where the tiles with the split inside leave much of the chip idle, whatever the times
+// say: the others need no workspace, and calls without one and overlapping calls of arcq_gemm_noalloc count on that.  Nor do the
+// times decide where the runs need more than the library's built-in scratch: what arcq_gemm_noalloc takes does not follow them.
 struct GemmPlan {
     bool stream;
     int ksplit;         // tile variant of gemm_ksplit.hip, 0: the tiles of this file
@@ -1213,7 +1213,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp) {
         us = split_us;
     }
     const bool too_large = splits > 1 && (uint64_t)splits * (uint64_t)M * (uint64_t)N * sizeof(float) > ARCQ_NOALLOC_SCRATCH_BYTES;
-    if (variant != 0 && (too_large ? ample : tiles_us < us)) return {false, variant, 1};
+    if (variant != 0 && (splits > 1 && (ample || too_large) ? ample : tiles_us < us)) return {false, variant, 1};
     return {false, 0, splits};
 }
 

@@ -1,7 +1,9 @@
 """No-GPU checks of the C-ABI library: it loads, exports every declared symbol, and rejects
 bad arguments before any HIP call (so these run on a machine without a GPU)."""
 import ctypes
+import math
 import os
+import random
 import re
 
 import pytest
@@ -136,6 +138,31 @@ def test_gemm_noalloc_argument_errors_and_scratch_limit():
     assert n.value > B.NOALLOC_SCRATCH_BYTES == 8 << 20
     assert ga(M=896, N=640, Kp=14592, ldy=640) == B.WORKSPACE_TOO_SMALL
     assert b"built-in" in B.lib().arcq_last_error()
+
+
+def occupied_without_scratch(M, N, Kp):
+    """Some tile with the k split inside the workgroup covers the problem with 144 to 256 workgroups, or the smallest
+    (64 x 32) an eighth of the chip over a short K'; the weight-streaming kernel serves up to 64 rows."""
+    if M <= 64:
+        return True
+    t = lambda bm, bn: -(-M // bm) * -(-N // bn)
+    return Kp >= 512 and (any(144 <= t(*tile) <= 256 for tile in ((64, 32), (64, 64), (96, 64), (128, 64), (128, 128))) or
+                          (Kp <= 8704 and 32 <= t(64, 32) <= 256))
+
+
+def test_gemm_needs_no_workspace_where_a_tile_occupies_the_chip():
+    """Such problems run from a null workspace and leave the built-in scratch of arcq_gemm_noalloc alone, whichever of the
+    paths the modelled times prefer."""
+    shapes = [(68, 5664, 14544), (103, 2336, 20000), (476, 256, 8464), (443, 197, 7104), (893, 67, 7488), (3907, 1, 8560)]
+    rng = random.Random(5)
+    log = lambda a, b: int(math.exp(rng.uniform(math.log(a), math.log(b))))
+    shapes += [(log(1, 9000), log(1, 60000), 16 * log(1, 8192)) for _ in range(40000)]
+    checked = 0
+    for M, N, Kp in shapes:
+        if occupied_without_scratch(M, N, Kp):
+            assert B.arcq_gemm_workspace_size(M, N, Kp) == 0, (M, N, Kp)
+            checked += 1
+    assert checked > 5000
 
 
 def test_check_perm_argument_errors():
