@@ -38,6 +38,24 @@ arcq_status arcq_probe_mfma_fp4(int iters, float* sink, double* flop_host, void*
 arcq_status arcq_ref_gemm_bf16(const void* x, const void* w, int64_t M, int64_t N, int64_t K, void* y, int64_t ldy,
                                void* stream);
 
+/*
+ * Which kernel a GEMM problem runs on: a function of its sizes alone (host only, nothing is launched).  Tests ask it, so that
+ * a shape written for a tile cannot leave that tile unnoticed when the rule changes; not needed to call the library.
+ * ahead: the weight-streaming kernel's waves ask for their next weights while they compute.
+ * arcq_gemm_route: operands whose scale bytes lie at odd addresses, or K' < 256 off the grid of 64, have no 256 x 256 tiles and
+ * may run 192 x 256 or 128 x 256 ones instead.  arcq_mx_gemm_route: such operands (or K' < 512 off the grid of 128) run 256-wide
+ * or 128 x 128 tiles instead of 192 x 128 ones; with_workspace: as arcq_mx_gemm_ws (non-zero) or arcq_mx_gemm (0).
+ */
+#define ARCQ_ROUTE_STREAM 0     /* weight-streaming kernel: tile_cols / 16 weight tiles per wave */
+#define ARCQ_ROUTE_KSPLIT 1     /* tiles whose waves split every stage along k */
+#define ARCQ_ROUTE_TILES 2      /* tiles, K' in `runs` runs across workgroups */
+#define ARCQ_ROUTE_DIRECT 3     /* plain kernel (K' < 128 off the streaming kernel, operands of 4 GiB and more) */
+typedef struct {
+    int32_t kernel, tile_rows, tile_cols, runs, ahead;
+} arcq_route;
+arcq_status arcq_gemm_route(int64_t M, int64_t N, int64_t Kp, arcq_route* route);
+arcq_status arcq_mx_gemm_route(int64_t M, int64_t N, int64_t Kp, int with_workspace, arcq_route* route);
+
 #ifdef __cplusplus
 }
 #endif

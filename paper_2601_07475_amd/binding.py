@@ -16,6 +16,13 @@ OK, INVALID_ARG, BAD_SHAPE, BAD_ALIGN, HIP_ERROR, WORKSPACE_TOO_SMALL = range(6)
 DTYPE_F16, DTYPE_F32 = 0, 1
 LAYOUT_INTERLEAVED, SCALE_ROUND_UP, RMSNORM_EXACT_SUM = 1, 2, 4
 MAX_K = 65536
+ROUTE_STREAM, ROUTE_KSPLIT, ROUTE_TILES, ROUTE_DIRECT = range(4)
+
+
+class Route(ctypes.Structure):
+    """arcq_route of arcq_bench.h."""
+    _fields_ = [(n, ctypes.c_int32) for n in ("kernel", "tile_rows", "tile_cols", "runs", "ahead")]
+
 
 # every symbol include/arcq.h and include/arcq_bench.h declare: name -> (restype, argtypes)
 _i64, _f32, _vp, _sz, _u32 = ctypes.c_int64, ctypes.c_float, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_uint32
@@ -46,6 +53,8 @@ SIGNATURES = {
     "arcq_probe_mfma_f16": (ctypes.c_int, [ctypes.c_int, _vp, ctypes.POINTER(ctypes.c_double), _vp]),
     "arcq_probe_mfma_fp4": (ctypes.c_int, [ctypes.c_int, _vp, ctypes.POINTER(ctypes.c_double), _vp]),
     "arcq_ref_gemm_bf16": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _vp, _i64, _vp]),
+    "arcq_gemm_route": (ctypes.c_int, [_i64, _i64, _i64, ctypes.POINTER(Route)]),
+    "arcq_mx_gemm_route": (ctypes.c_int, [_i64, _i64, _i64, ctypes.c_int, ctypes.POINTER(Route)]),
     "arcq_check_perm": (ctypes.c_int, [_vp, _i64, _vp, ctypes.POINTER(ctypes.c_int), _vp]),
 }
 
@@ -394,6 +403,20 @@ def arcq_probe_mfma_f16(iters, sink=None):
 def arcq_probe_mfma_fp4(iters, sink=None):
     """Enqueues the scaled-FP4 matrix-rate probe; returns the floating-point operations of the launch."""
     return _probe("arcq_probe_mfma_fp4", iters, sink)
+
+
+def arcq_gemm_route(M, N, Kp):
+    """(kernel, tile rows, tile columns, runs of K', ahead) arcq_gemm takes for these sizes; no GPU needed."""
+    r = Route()
+    _check(lib().arcq_gemm_route(M, N, Kp, ctypes.byref(r)))
+    return r.kernel, r.tile_rows, r.tile_cols, r.runs, r.ahead
+
+
+def arcq_mx_gemm_route(M, N, Kp, with_workspace=False):
+    """The same for arcq_mx_gemm, with or without a workspace."""
+    r = Route()
+    _check(lib().arcq_mx_gemm_route(M, N, Kp, int(with_workspace), ctypes.byref(r)))
+    return r.kernel, r.tile_rows, r.tile_cols, r.runs, r.ahead
 
 
 def arcq_check_perm(perm):

@@ -193,6 +193,18 @@ arcq_status arcq_gemm_workspace_size(int64_t M, int64_t N, int64_t Kp, size_t* b
     return ARCQ_OK;
 }
 
+static arcq_status fill_route(const GemmPlan& p, arcq_route* route) {
+    *route = {p.kernel, p.rows, p.cols, p.runs, p.ahead ? 1 : 0};
+    return ARCQ_OK;
+}
+
+arcq_status arcq_gemm_route(int64_t M, int64_t N, int64_t Kp, arcq_route* route) {
+    clear_error();
+    if (arcq_status st = check_gemm_shape(M, N, Kp)) return st;
+    if (!route) return fail(ARCQ_INVALID_ARG, "null output pointer");
+    return fill_route(plan_gemm(M, N, Kp), route);
+}
+
 // Validation shared by arcq_gemm and arcq_gemm_noalloc; *run = false when there is nothing to launch.
 static arcq_status check_gemm_args(const char* who, const uint8_t* a_codes, const uint8_t* a_scales, float a_tensor_scale,
                                    const uint8_t* w_codes, const uint8_t* w_scales, float w_tensor_scale,
@@ -342,14 +354,19 @@ arcq_status arcq_mx_pack_weight_ex(const void* w, int64_t N, int64_t K, int64_t 
     return mx_quantize_entry(1, "arcq_mx_pack_weight_ex", w, N, K, ldw, perm, S, codes, scales, stream, flags);
 }
 
-static arcq_status mx_gemm_entry(const char* name, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
-                                 const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, void* y, int y_dtype, int64_t ldy,
-                                 bool with_workspace, void* workspace, size_t workspace_bytes, void* stream) {
-    clear_error();
+static arcq_status check_mx_gemm_shape(int64_t M, int64_t N, int64_t Kp) {
     if (M < 0 || N < 0 || M > 0x7FFFFFFF || N > 0x7FFFFFFF)
         return fail(ARCQ_BAD_SHAPE, "M = %lld, N = %lld out of range", (long long)M, (long long)N);
     if (Kp <= 0 || (Kp % 32) != 0 || Kp > 2 * (int64_t)ARCQ_MAX_K)
         return fail(ARCQ_BAD_SHAPE, "K' = %lld: must be a positive multiple of 32, at most %d", (long long)Kp, 2 * ARCQ_MAX_K);
+    return ARCQ_OK;
+}
+
+static arcq_status mx_gemm_entry(const char* name, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
+                                 const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, void* y, int y_dtype, int64_t ldy,
+                                 bool with_workspace, void* workspace, size_t workspace_bytes, void* stream) {
+    clear_error();
+    if (arcq_status st = check_mx_gemm_shape(M, N, Kp)) return st;
     if (y_dtype != ARCQ_DTYPE_F16 && y_dtype != ARCQ_DTYPE_F32) return fail(ARCQ_INVALID_ARG, "y_dtype = %d", y_dtype);
     if (ldy < N) return fail(ARCQ_BAD_SHAPE, "ldy = %lld < N = %lld", (long long)ldy, (long long)N);
     if (M == 0 || N == 0) return ARCQ_OK;
@@ -376,13 +393,17 @@ arcq_status arcq_mx_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const 
 
 arcq_status arcq_mx_gemm_workspace_size(int64_t M, int64_t N, int64_t Kp, size_t* bytes) {
     clear_error();
-    if (M < 0 || N < 0 || M > 0x7FFFFFFF || N > 0x7FFFFFFF)
-        return fail(ARCQ_BAD_SHAPE, "M = %lld, N = %lld out of range", (long long)M, (long long)N);
-    if (Kp <= 0 || (Kp % 32) != 0 || Kp > 2 * (int64_t)ARCQ_MAX_K)
-        return fail(ARCQ_BAD_SHAPE, "K' = %lld: must be a positive multiple of 32, at most %d", (long long)Kp, 2 * ARCQ_MAX_K);
+    if (arcq_status st = check_mx_gemm_shape(M, N, Kp)) return st;
     if (!bytes) return fail(ARCQ_INVALID_ARG, "null output pointer");
     *bytes = (M == 0 || N == 0) ? 0 : mx_gemm_workspace_bytes(M, N, Kp);
     return ARCQ_OK;
+}
+
+arcq_status arcq_mx_gemm_route(int64_t M, int64_t N, int64_t Kp, int with_workspace, arcq_route* route) {
+    clear_error();
+    if (arcq_status st = check_mx_gemm_shape(M, N, Kp)) return st;
+    if (!route) return fail(ARCQ_INVALID_ARG, "null output pointer");
+    return fill_route(plan_mx_gemm(M, N, Kp, with_workspace != 0), route);
 }
 
 arcq_status arcq_mx_gemm_ws(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes, const uint8_t* w_scales,

@@ -1137,6 +1137,8 @@ arcq_status launch_skinny(const uint8_t* a_codes, const uint8_t* a_scales, const
     return check_launch("gemm_skinny_kernel");
 }
 
+}  // namespace
+
 // 65 to 128 rows on the weight-streaming kernel rather than on tiles with K' split across workgroups: unless the problem is
 // big enough for the latter (measured over N = 1024 .. 28672, K' = 1088 .. 14592 at M = 80, 96, 128: the eight-row-tile variant
 // of the streaming kernel takes about 1 us per 10^6 weights, the tiled path 20-30 us for everything up to 6 * 10^7 weights,
@@ -1171,6 +1173,40 @@ static int split_runs(int64_t M, int64_t N, int64_t Kp, double* us) {
     return best;
 }
 
+// Rounds of tiles of `rows` x 256, one per compute unit, times the time of a stage of such a tile.
+static double wide_cost(int64_t M, int64_t N, int rows, double t_stage) {
+    return (double)((((M + rows - 1) / rows) * ((N + 255) / 256) + 255) / 256) * t_stage;
+}
+
+constexpr int STREAM_WAVES = 8;     // of a workgroup of the weight-streaming kernel (8 x 2 tiles: 4)
+
+// The weight-streaming kernel's share of the rule: row tiles, weight tiles per wave, and whether the waves load ahead.
+static GemmPlan plan_stream(int64_t M, int64_t N, int64_t Kp) {
+    // Enough waves to keep the weight stream in flight, as few as that allows so that each wave has several KB to request at
+    // once: with many weight rows several tiles per wave share the activation operand; with few, one tile per wave so that
+    // every CU still gets a workgroup (measured at the decode shapes).
+    // Tiles per wave: as few as give the chip at most one workgroup per compute unit (256), up to four, two with more than 32
+    // activation rows; measured with weights from HBM at 16 rows: 640 tiles (N = 10240, K' = 8448) 13.7 us with three tiles per
+    // wave against 18.1 us with two (320 workgroups: two rounds), 576 tiles 8.7 against 10.6 (257 to 399 tiles used to run one
+    // tile per wave, two workgroups sharing a CU: 320 tiles over K' = 27904 33.7 us against 27.3 us with two tiles per wave,
+    // over K' = 4352 7.6 against 6.9); 32 rows: 640 tiles 17.2 us with three against 24.0 with one, 512 tiles 14.7 with two
+    // against 17.9, 896 tiles 12.4 with four against 15.7 with two; 64 rows: 512 tiles over K' = 8464 23.2 us with two against
+    // 34.6 with one; 128 rows: 512 tiles over K' = 2064 16.2 us with two against 20.0.
+    const int64_t tiles = (N + 15) / 16;
+    const int mt = M <= 16 ? 1 : M <= 32 ? 2 : M <= 64 ? 4 : 8;
+    const int nt = tiles <= 256 ? 1 : tiles <= 512 || mt > 2 ? 2 : tiles <= 768 ? 3 : 4;
+    // Ahead where waves take several groups (from HBM, us: 16 x 28672 over K' = 8448 34.9 -> 32.0, 32 x 28672 over 8464 47.5 ->
+    // 45.1, 16 x 10240 over 8448 13.9 -> 13.1); with one group per wave its code without a loop is still 2 to 4 % faster
+    // (32 x 14336 over 4352 12.9 -> 12.4, 16 x 6144 over 4240 7.4 -> 7.3), except for four tiles behind one row tile (16 x 14336
+    // over 4352 10.4 against 10.6); one tile behind one row tile loses with several groups (16 x 4096 over 14592 11.0
+    // against 11.1, over 14544 12.3 against 12.7).  128 rows have no groups.
+    const int64_t ngroup = Kp >> 9;
+    bool ahead = mt <= 4;
+    if (mt == 1 && nt == 1) ahead = ngroup <= STREAM_WAVES;
+    if (mt == 1 && nt == 4) ahead = ngroup > STREAM_WAVES;
+    return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, ahead};
+}
+
 // Which kernel serves a problem: a function of the shape alone, so that the workspace a caller sizes beforehand matches what the
 // launch uses.  Up to 32 rows the weight-streaming kernel, beyond the smallest modelled time of three:
 //   * the streaming kernel up to 128 rows: start + 512-k groups x time of a round's group (one or two weight tiles per wave);
@@ -1178,172 +1214,132 @@ static int split_runs(int64_t M, int64_t N, int64_t Kp, double* us) {
 //   * the tiles with the k split inside the workgroup (gemm_ksplit_best);
 //   * the tiles of this file, with K' split across workgroups or without, by the stage times that choose among them.
 // K' is split across workgroups only where the tiles with the split inside leave much of the chip idle, whatever the times
-// say: the others need no workspace, and calls without one and overlapping calls of arcq_gemm_noalloc count on that.  Nor do the
-// times decide where the runs need more than the library's built-in scratch: what arcq_gemm_noalloc takes does not follow them.
-struct GemmPlan {
-    bool stream;
-    int ksplit;         // tile variant of gemm_ksplit.hip, 0: the tiles of this file
-    int splits;         // runs of K' on those
-};
+// say: the others need no workspace, and calls without one and overlapping calls of arcq_gemm_noalloc count on that (the 64 x 128
+// and 96 x 128 tiles, which came later, do not enter: what they alone could take still splits).  Nor do the times decide where
+// the runs need more than the library's built-in scratch: what arcq_gemm_noalloc takes does not follow them.
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp) {
-    if (M <= 32) return {true, 0, 1};
-    double tiles_us, split_us;
-    bool ample;
-    const int variant = gemm_ksplit_best(M, N, Kp, &tiles_us, &ample);
-    const double groups = (double)Kp / 512.0;
-    const int64_t tiles16 = (N + 15) / 16;
-    const bool two = tiles16 >= 257;            // weight tiles per wave of the streaming kernel
-    const double rounds = (double)(((two ? (tiles16 + 1) / 2 : tiles16) + 255) / 256);
+    const GemmPlan stream = plan_stream(M, N, Kp);
+    if (M <= 32) return stream;
+    const KsplitTile ks = gemm_ksplit_best(M, N, Kp);
+    const GemmPlan ksplit = {ARCQ_ROUTE_KSPLIT, ks.rows, ks.cols, 1, false};
     if (skinny_shape(M, N, Kp)) {
+        const double groups = (double)Kp / 512.0;
+        const int64_t wgs = (N + stream.cols - 1) / stream.cols;
+        const double rounds = (double)((wgs + 255) / 256);
+        const bool two = stream.cols == 32;         // weight tiles per wave
         // a second round costs more than the model says with few groups (48 x 14336 over 1552: 11.9 us against 10.6 on 64 x 64 tiles)
         const double us = M <= 64 ? 3.0 + groups * rounds * (two ? 1.11 : 0.64) * (rounds > 1.0 ? 1.25 : 1.0)
                                   : 4.2 + groups * rounds * (two ? 2.27 : 1.135);
-        return variant != 0 && tiles_us < us ? GemmPlan{false, variant, 1} : GemmPlan{true, 0, 1};
+        return ks.rows != 0 && ks.us < us ? ksplit : stream;
     }
-    const int64_t nstage = ((Kp >> 4) + 7) >> 3, tn256 = (N + 255) / 256, t128 = ((M + 127) / 128) * ((N + 127) / 128);
-    int splits = 1;
+    const int64_t nbk = Kp >> 4, nstage = (nbk + 7) >> 3, tn256 = (N + 255) / 256;
+    const bool offsets_fit = (uint64_t)M * (uint64_t)nbk * 8 < 0xFFFF0000ull && (uint64_t)N * (uint64_t)nbk * 8 < 0xFFFF0000ull;
+    if (nbk < 8 || !offsets_fit) return {ARCQ_ROUTE_DIRECT, 128, 128, 1, false};
+    GemmPlan tiles = {ARCQ_ROUTE_TILES, 128, 128, 1, false};
     double us;
-    if (t128 > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256) {
+    if (((M + 127) / 128) * ((N + 127) / 128) > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256) {
+        // More than 256 tiles of 128 x 128 (two workgroups on some compute units, one on the others) but at most 256 of
+        // 192 x 128: one round of the taller tile, which also decodes five fragments per six matrix instructions
+        // instead of four per four (1.52 against 1.3 us per stage and tile): 512 x 10240 over K' = 8448 116 -> 100 us,
+        // 1024 x 5120 over 27904 365 -> 297 us, 1280 x 4096 over 4352 61 -> 49 us.  It goes before the 256-wide tiles, which
+        // take one round as well where both fit, of a larger tile on fewer compute units (160 x 28672 over K' = 4352: 51.2
+        // against 58.9 us).
+        tiles.rows = 192;
         us = 5.0 + (double)nstage * 1.52;
     } else if (((M + 127) / 128) * tn256 >= 192) {
-        auto cost = [&](int bm, double t_stage) { return (double)((((M + bm - 1) / bm) * tn256 + 255) / 256) * t_stage; };
-        us = 5.0 + (double)nstage * std::min({cost(256, 2.96), cost(192, 2.59), cost(128, 1.96)});
+        // Tiles of 256 weight rows by 256, 192 or 128 activation rows when there is work for them.  Workgroups run in
+        // rounds of one per compute unit and a round lasts as long as one tile, so the tile height that minimises
+        // rounds x (time of a stage of that tile) wins: 2.96, 2.59 and 1.96 us measured per 128-k stage (the bigger
+        // tile decodes fewer fragments per matrix instruction: 45, 53 and 60 ps per output element and stage).
+        // E.g. 768 x 14336: 224 tiles of 192 rows in one round 88 us, 336 tiles of 128 rows in two rounds 113 us,
+        // 168 tiles of 256 rows 100 us; 1024 x 14336: 224 tiles of 256 rows 106 us against 120 us.
+        const double c256 = wide_cost(M, N, 256, 2.96), c192 = wide_cost(M, N, 192, 2.59), c128 = wide_cost(M, N, 128, 1.96);
+        tiles.rows = c256 <= c192 && c256 <= c128 ? 256 : c192 <= c128 ? 192 : 128;
+        tiles.cols = 256;
+        us = 5.0 + (double)nstage * std::min({c256, c192, c128});
     } else {
-        splits = split_runs(M, N, Kp, &split_us);
-        us = split_us;
+        tiles.runs = split_runs(M, N, Kp, &us);
     }
-    const bool too_large = splits > 1 && (uint64_t)splits * (uint64_t)M * (uint64_t)N * sizeof(float) > ARCQ_NOALLOC_SCRATCH_BYTES;
-    if (variant != 0 && (splits > 1 && (ample || too_large) ? ample : tiles_us < us)) return {false, variant, 1};
-    return {false, 0, splits};
+    const bool too_large = tiles.runs > 1 && (uint64_t)tiles.runs * (uint64_t)M * (uint64_t)N * sizeof(float) > ARCQ_NOALLOC_SCRATCH_BYTES;
+    if (ks.rows != 0 && (tiles.runs > 1 && (ks.ample || too_large) ? ks.ample : ks.us < us)) return ksplit;
+    return tiles;
 }
+
+namespace {
 
 template <typename OutT>
 arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                          const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, float alpha, OutT* y,
                          int64_t ldy, float* workspace, hipStream_t stream) {
     const int nbk = (int)(Kp >> 4);
-    const bool aligned16 = ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 &&
-                           ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
+    const bool dword_scales = ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
+    const bool aligned16 = ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 && dword_scales;
     const GemmPlan plan = plan_gemm(M, N, Kp);
-    if (plan.stream) {
-        // Weight-streaming path.  Enough waves to keep the weight stream in flight, as few as that allows
-        // so that each wave has several KB to request at once: with many weight rows several tiles per
-        // wave share the activation operand; with few, one tile per wave so that every CU still gets a
-        // workgroup (measured at the decode shapes).
-        const int64_t tiles = (N + 15) / 16;
-        // tiles per wave: as few as give the chip at most one workgroup per compute unit (256), up to four (three with
-        // 17 to 32 activation rows); measured with weights from HBM at 16 rows: 640 tiles (N = 10240, K' = 8448) 13.7 us
-        // with three tiles per wave against 18.1 us with two (320 workgroups: two rounds), 576 tiles 8.7 against 10.6
-        // (257 to 399 tiles used to run one tile per wave, two workgroups sharing a CU: 320 tiles over K' = 27904 33.7 us
-        // against 27.3 us with two tiles per wave, over K' = 4352 7.6 against 6.9)
-        const int64_t T2 = 257, T3 = 513, T4 = 769;
-#define ARCQ_SKINNY_R(MT_, NT_, W_, U_, R_) \
-    launch_skinny<MT_, NT_, W_, U_, (MT_ <= 4), R_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream)
-        // ROLL where waves take several groups (from HBM, us: 16 x 28672 over K' = 8448 34.9 -> 32.0, 32 x 28672 over 8464 47.5 ->
-        // 45.1, 16 x 10240 over 8448 13.9 -> 13.1); with one group per wave its code without a loop is still 2 to 4 % faster
-        // (32 x 14336 over 4352 12.9 -> 12.4, 16 x 6144 over 4240 7.4 -> 7.3), except for four tiles behind one row tile (16 x 14336
-        // over 4352 10.4 against 10.6); one tile behind one row tile loses with several groups (16 x 4096 over 14592 11.0
-        // against 11.1, over 14544 12.3 against 12.7).  128 rows have no groups.
-#define ARCQ_SKINNY_W(MT_, NT_, W_, U_)                                                                                        \
-    return MT_ <= 4 && (MT_ * NT_ == 1 ? (nbk >> 5) <= W_ : MT_ == 1 && NT_ == 4 ? (nbk >> 5) > W_ : true)                     \
-               ? ARCQ_SKINNY_R(MT_, NT_, W_, U_, (MT_ <= 4)) : ARCQ_SKINNY_R(MT_, NT_, W_, U_, ((MT_ > 1 || NT_ == 2 || NT_ == 3) && MT_ <= 4))
-#define ARCQ_SKINNY(MT_, NT_, U_) ARCQ_SKINNY_W(MT_, NT_, 8, U_)
-        if (M <= 16) {
-            if (tiles >= T4) ARCQ_SKINNY(1, 4, 1);
-            if (tiles >= T3) ARCQ_SKINNY(1, 3, 1);
-            if (tiles >= T2) ARCQ_SKINNY(1, 2, 2);
-            ARCQ_SKINNY(1, 1, 2);
-        }
-        if (M <= 32) {
-            // (32 rows, weights from HBM: 640 tiles 17.2 us with three tiles per wave against 24.0 with one, 512 tiles
-            // 14.7 with two against 17.9, 896 tiles 12.4 with four against 15.7 with two)
-            if (tiles >= T4) ARCQ_SKINNY(2, 4, 1);
-            if (tiles >= T3) ARCQ_SKINNY(2, 3, 1);
-            if (tiles >= T2) ARCQ_SKINNY(2, 2, 1);
-            ARCQ_SKINNY(2, 1, 2);
-        }
-        if (M <= 64) {
-            // (64 rows, weights from HBM: 512 tiles over K' = 8464 23.2 us with two tiles per wave against 34.6 with one)
-            if (tiles >= T2) ARCQ_SKINNY(4, 2, 1);
-            ARCQ_SKINNY(4, 1, 1);
-        }
-        if (tiles >= T2) ARCQ_SKINNY_W(8, 2, 4, 1);    // 128 rows, 512 tiles over K' = 2064: 16.2 us against 20.0
-        ARCQ_SKINNY(8, 1, 1);
-#undef ARCQ_SKINNY
-#undef ARCQ_SKINNY_W
-#undef ARCQ_SKINNY_R
+    if (plan.kernel == ARCQ_ROUTE_STREAM) {
+        // (the variants that exist: plan_stream)
+#define ARCQ_STREAM(MT_, NT_, W_, U_, AHEAD_)                                                                                   \
+    if (plan.rows == 16 * MT_ && plan.cols == 16 * NT_ && plan.ahead == AHEAD_)                                                 \
+    return launch_skinny<MT_, NT_, W_, U_, (MT_ <= 4), AHEAD_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, \
+                                                               y, ldy, stream)
+        ARCQ_STREAM(1, 1, STREAM_WAVES, 2, false);
+        ARCQ_STREAM(1, 1, STREAM_WAVES, 2, true);
+        ARCQ_STREAM(1, 2, STREAM_WAVES, 2, true);
+        ARCQ_STREAM(1, 3, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(1, 4, STREAM_WAVES, 1, false);
+        ARCQ_STREAM(1, 4, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(2, 1, STREAM_WAVES, 2, true);
+        ARCQ_STREAM(2, 2, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(2, 3, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(2, 4, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(4, 1, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(4, 2, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(8, 1, STREAM_WAVES, 1, false);
+        ARCQ_STREAM(8, 2, 4, 1, false);
+#undef ARCQ_STREAM
+        return fail(ARCQ_HIP_ERROR, "no weight-streaming kernel of %d x %d rows, ahead %d", plan.rows, plan.cols, (int)plan.ahead);
     }
-    const bool offsets_fit = (uint64_t)M * (uint64_t)nbk * 8 < 0xFFFF0000ull && (uint64_t)N * (uint64_t)nbk * 8 < 0xFFFF0000ull;
-    if (plan.ksplit != 0)
-        return launch_gemm_ksplit(plan.ksplit, a_codes, a_scales, w_codes, w_scales, M, N, Kp, alpha, y,
+    if (plan.kernel == ARCQ_ROUTE_KSPLIT)
+        return launch_gemm_ksplit(plan.rows, plan.cols, a_codes, a_scales, w_codes, w_scales, M, N, Kp, alpha, y,
                                   std::is_same<OutT, _Float16>::value ? ARCQ_DTYPE_F16 : ARCQ_DTYPE_F32, ldy, stream);
-    // Tiles of 256 weight rows by 256, 192 or 128 activation rows when there is work for them.  Workgroups run in
-    // rounds of one per compute unit and a round lasts as long as one tile, so the tile height that minimises
-    // rounds x (time of a stage of that tile) wins: 2.96, 2.59 and 1.96 us measured per 128-k stage (the bigger
-    // tile decodes fewer fragments per matrix instruction: 45, 53 and 60 ps per output element and stage).
-    // E.g. 768 x 14336: 224 tiles of 192 rows in one round 88 us, 336 tiles of 128 rows in two rounds 113 us,
-    // 168 tiles of 256 rows 100 us; 1024 x 14336: 224 tiles of 256 rows 106 us against 120 us.
-    const int64_t tn256 = (N + 255) / 256;
-    const bool wide = ((M + 127) / 128) * tn256 >= 192;
-    auto cost = [&](int bm, double t_stage) { return (double)((((M + bm - 1) / bm) * tn256 + 255) / 256) * t_stage; };
-    const double c256 = cost(256, 2.96), c192 = cost(192, 2.59), c128 = cost(128, 1.96);
-    // More than 256 tiles of 128 x 128 (two workgroups on some compute units, one on the others) but at most 256 of
-    // 192 x 128: one round of the taller tile, which also decodes five fragments per six matrix instructions
-    // instead of four per four (1.52 against 1.3 us per stage and tile): 512 x 10240 over K' = 8448 116 -> 100 us,
-    // 1024 x 5120 over 27904 365 -> 297 us, 1280 x 4096 over 4352 61 -> 49 us.  It goes before the 256-wide tiles, which take
-    // one round as well where both fit, of a larger tile on fewer compute units (160 x 28672 over K' = 4352: 51.2 against 58.9 us).
-    const bool one_round_192 = ((M + 127) / 128) * ((N + 127) / 128) > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256;
-    if ((nbk & 3) == 0 && nbk >= 8 && offsets_fit && aligned16) {
-        if (one_round_192)
-            return launch_staged<3, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-        if (wide) {
-            if (c256 <= c192 && c256 <= c128)
-                return launch_staged<4, 4, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-            if (c192 <= c128)
-                return launch_staged<3, 4, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-            // 128 x 256 tiles: wave pairs that split every stage (6 % faster than 8 waves of 64 x 64 on the 2048 x 4096 x 4352
-            // problem).  A half stage at the end is one of the ragged ends that the RAGGED copies know: 2048 x 4096 over
-            // K' = 4416 69.6 us, 8 waves of 64 x 64 with a shorter last stage 71.8 us; over K' = 8256 123 and 130 us
-            if (nbk >= 16)
-                return (nbk & 7) == 0
-                           ? launch_kpair<COPIES>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream)
-                           : launch_kpair<RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-            return launch_staged<2, 2, 2, 4>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-        }
-        return launch_staged<2, 2, 2, 2>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
-                                         plan.splits, workspace);
+#define ARCQ_TILES(WM_, WN_, MODE_)                                                                                      \
+    if (plan.rows == 64 * WM_ && plan.cols == 64 * WN_)                                                                  \
+    return launch_staged<WM_, WN_, 2, 2, MODE_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, \
+                                                stream, plan.runs, workspace)
+    if (plan.kernel == ARCQ_ROUTE_TILES && (nbk & 3) == 0 && aligned16) {
+        ARCQ_TILES(3, 2, COPIES);
+        ARCQ_TILES(4, 4, COPIES);
+        ARCQ_TILES(3, 4, COPIES);
+        ARCQ_TILES(2, 2, COPIES);
+        // 128 x 256 tiles: wave pairs that split every stage (6 % faster than 8 waves of 64 x 64 on the 2048 x 4096 x 4352
+        // problem).  A half stage at the end is one of the ragged ends that the RAGGED copies know: 2048 x 4096 over
+        // K' = 4416 69.6 us, 8 waves of 64 x 64 with a shorter last stage 71.8 us; over K' = 8256 123 and 130 us
+        if (nbk >= 16)
+            return (nbk & 7) == 0
+                       ? launch_kpair<COPIES>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream)
+                       : launch_kpair<RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
+        return launch_staged<2, 2, 2, 4>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
     }
-    if (nbk >= ScaleWindows<128, 128, 256, 8>::MIN_NB && offsets_fit &&
-        ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0) {
+    if (plan.kernel == ARCQ_ROUTE_TILES && nbk >= ScaleWindows<128, 128, 256, 8>::MIN_NB && dword_scales) {
         // Any K' from 256 on, codes that are only 8-byte aligned: the same tiles by the same rule, 1 to 5 % slower than with
         // whole aligned rows (S = 272 against S = 256, and through registers: 4096 x 8192 over K = 8192 434, 419 and 581 us;
         // 2048 x 4096 over K = 4096 69.2, 65.2 and 79.4 us; 512 x 10240 over K = 8192 98.1, 93.7 and 112.8 us)
-        if (one_round_192)
-            return launch_staged<3, 2, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-        if (wide) {
-            if (c256 <= c192 && c256 <= c128)
-                return launch_staged<4, 4, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-            if (c192 <= c128)
-                return launch_staged<3, 4, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-            return launch_kpair<RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-        }
-        return launch_staged<2, 2, 2, 2, RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
-                                                 plan.splits, workspace);
+        ARCQ_TILES(3, 2, RAGGED);
+        ARCQ_TILES(4, 4, RAGGED);
+        ARCQ_TILES(3, 4, RAGGED);
+        ARCQ_TILES(2, 2, RAGGED);
+        return launch_kpair<RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
     }
-    if (offsets_fit && nbk >= 8) {
+    if (plan.kernel == ARCQ_ROUTE_TILES) {
         // scale bytes at odd addresses, or K' from 128 to 240 that is no multiple of 64: stages through registers (no 256 x 256
-        // tiles: the staging registers do not fit beside 256 accumulators); the same choice by rounds x stage time
-        // (3.5 and 2.4 us measured per stage for 192 x 256 and 128 x 256 tiles: 768 x 14336 over K' = 4368 118 us instead of 163)
-        if (one_round_192)
-            return launch_staged<3, 2, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-        if (wide) {
-            if (cost(192, 3.5) <= cost(128, 2.4))
-                return launch_staged<3, 4, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-            return launch_staged<2, 2, 2, 4, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
-        }
-        return launch_staged<2, 2, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream,
-                                               plan.splits, workspace);
+        // tiles: the staging registers do not fit beside 256 accumulators); 192 or 128 rows by rounds x stage time, 3.5 and 2.4 us
+        // here (768 x 14336 over K' = 4368 118 us instead of 163)
+        ARCQ_TILES(3, 2, REGS);
+        ARCQ_TILES(2, 2, REGS);
+        if (wide_cost(M, N, 192, 3.5) <= wide_cost(M, N, 128, 2.4))
+            return launch_staged<3, 4, 2, 2, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
+        return launch_staged<2, 2, 2, 4, REGS>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
     }
+#undef ARCQ_TILES
     dim3 grid((unsigned)((N + 127) / 128), (unsigned)((M + 127) / 128));
     hipLaunchKernelGGL(gemm_direct_kernel<OutT>, grid, dim3(256), 0, stream, a_codes, a_scales, w_codes, w_scales,
                        (int)M, (int)N, nbk, alpha, y, ldy);
@@ -1368,8 +1364,8 @@ arcq_status launch_splitk_reduce(const float* partial, int splits, int M, int N,
 }
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t Kp) {
-    const int splits = plan_gemm(M, N, Kp).splits;
-    return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
+    const int runs = plan_gemm(M, N, Kp).runs;
+    return runs > 1 ? (size_t)runs * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -411,18 +411,20 @@ arcq_status launch_ksplit(const uint8_t* a_codes, const uint8_t* a_scales, const
 }
 
 template <int MODE, typename OutT>
-arcq_status launch_ksplit_typed(int variant, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
+arcq_status launch_ksplit_typed(int rows, int cols, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                                 const uint8_t* w_scales, int M, int N, int nbk, float alpha, OutT* y, int64_t ldy,
                                 hipStream_t stream) {
-    switch (variant) {
-        case 1: return launch_ksplit<2, 2, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 64 x 64
-        case 2: return launch_ksplit<4, 2, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 128 x 64
-        case 4: return launch_ksplit<3, 2, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 96 x 64
-        case 5: return launch_ksplit<3, 2, 1, 2, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);  // 96 x 128
-        case 7: return launch_ksplit<2, 2, 1, 2, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);  // 64 x 128
-        case 6: return launch_ksplit<2, 1, 1, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);   // 64 x 32
-        default: return launch_ksplit<2, 4, 2, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);  // 128 x 128
-    }
+#define ARCQ_KSPLIT(WM_, WN_, GN_)                  \
+    if (rows == 32 * WM_ && cols == 32 * WN_ * GN_) \
+    return launch_ksplit<WM_, WN_, 1, GN_, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream)
+    ARCQ_KSPLIT(2, 1, 1);
+    ARCQ_KSPLIT(2, 2, 1);
+    ARCQ_KSPLIT(3, 2, 1);
+    ARCQ_KSPLIT(4, 2, 1);
+    ARCQ_KSPLIT(2, 2, 2);
+    ARCQ_KSPLIT(3, 2, 2);
+#undef ARCQ_KSPLIT
+    return launch_ksplit<2, 4, 2, 1, 4, MODE>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, stream);     // 128 x 128
 }
 
 }  // namespace
@@ -434,35 +436,34 @@ arcq_status launch_ksplit_typed(int variant, const uint8_t* a_codes, const uint8
 // N = 1024 .. 28672, K' = 1552, 4240, 8464, 14544, weights from HBM) to 4 to 9 % rms; the choice among these, the streaming
 // kernel and the tiles of gemm.hip by the modelled times (gemm.hip) is 1.2 % from the best of all on average, where fixed
 // limits of 144 to 256 workgroups on five tile shapes were 5.7 % off.
-// *ample: some tile occupies more than half of the chip, or the smallest one an eighth of it over a short K'.
-int gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp, double* us, bool* ample) {
+KsplitTile gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp) {
     struct Tile {
-        int variant, bm, bn;
+        int rows, cols;
         double start, alone, shared;
     };
-    static constexpr Tile tiles[] = {{6, 64, 32, 4.1, 0.454, 0.100}, {1, 64, 64, 5.0, 0.552, 0.154}, {4, 96, 64, 5.9, 0.692, 0.249},
-                                     {7, 64, 128, 4.4, 0.955, 0.343}, {2, 128, 64, 7.0, 0.832, 0.236}, {5, 96, 128, 6.5, 1.067, 0.400},
-                                     {3, 128, 128, 7.7, 1.254, 0.497}};
-    *us = 1e30;
-    *ample = false;
+    static constexpr Tile tiles[] = {{64, 32, 4.1, 0.454, 0.100}, {64, 64, 5.0, 0.552, 0.154}, {96, 64, 5.9, 0.692, 0.249},
+                                     {64, 128, 4.4, 0.955, 0.343}, {128, 64, 7.0, 0.832, 0.236}, {96, 128, 6.5, 1.067, 0.400},
+                                     {128, 128, 7.7, 1.254, 0.497}};
+    KsplitTile best = {0, 0, 1e30, false};
     const int64_t nbk = Kp >> 4;
-    if (nbk < 32) return 0;                               // at least two stages
-    if ((uint64_t)M * (uint64_t)nbk * 8 >= 0xFFFF0000ull || (uint64_t)N * (uint64_t)nbk * 8 >= 0xFFFF0000ull) return 0;
-    int best = 0;
+    if (nbk < 32) return best;                            // at least two stages
+    if ((uint64_t)M * (uint64_t)nbk * 8 >= 0xFFFF0000ull || (uint64_t)N * (uint64_t)nbk * 8 >= 0xFFFF0000ull) return best;
     for (const Tile& t : tiles) {
-        const int64_t wgs = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        const int64_t wgs = ((M + t.rows - 1) / t.rows) * ((N + t.cols - 1) / t.cols);
         if (wgs > 256 || wgs < 32) continue;
-        if (t.variant != 7 && t.variant != 5 && (wgs >= 144 || (t.variant == 6 && M > 64 && nbk <= 544))) *ample = true;
+        const bool added = t.cols == 128 && t.rows < 128;   // 64 x 128 and 96 x 128: see `ample` in plan_gemm
+        if (!added && (wgs >= 144 || (t.cols == 32 && M > 64 && nbk <= 544))) best.ample = true;
         const double c = t.start + (double)((nbk + 15) / 16) * (t.alone + t.shared * (double)wgs / 256.0);
-        if (c < *us) {
-            *us = c;
-            best = t.variant;
+        if (c < best.us) {
+            best.rows = t.rows;
+            best.cols = t.cols;
+            best.us = c;
         }
     }
     return best;
 }
 
-arcq_status launch_gemm_ksplit(int variant, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
+arcq_status launch_gemm_ksplit(int rows, int cols, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                                const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, float alpha, void* y, int y_dtype,
                                int64_t ldy, hipStream_t stream) {
     const int nbk = (int)(Kp >> 4);
@@ -473,9 +474,9 @@ arcq_status launch_gemm_ksplit(int variant, const uint8_t* a_codes, const uint8_
                         ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
     const bool windows = ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
     auto launch = [&](auto* out) {
-        return copies    ? launch_ksplit_typed<COPIES>(variant, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, out, ldy, stream)
-               : windows ? launch_ksplit_typed<RAGGED>(variant, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, out, ldy, stream)
-                         : launch_ksplit_typed<REGS>(variant, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, out, ldy, stream);
+        return copies    ? launch_ksplit_typed<COPIES>(rows, cols, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, out, ldy, stream)
+               : windows ? launch_ksplit_typed<RAGGED>(rows, cols, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, out, ldy, stream)
+                         : launch_ksplit_typed<REGS>(rows, cols, a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, out, ldy, stream);
     };
     return y_dtype == ARCQ_DTYPE_F16 ? launch(static_cast<_Float16*>(y)) : launch(static_cast<float*>(y));
 }

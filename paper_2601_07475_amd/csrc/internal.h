@@ -42,10 +42,26 @@ arcq_status launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales,
                         void* y, int y_dtype, int64_t ldy,
                         void* workspace, size_t workspace_bytes, hipStream_t stream);
 
-// Tiled kernel whose waves split every stage along k inside the workgroup (gemm_ksplit.hip): which of its tile
-// shapes is the fastest for this problem (0: none serves it) and its modelled time, and its launch.
-int gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp, double* us, bool* ample);
-arcq_status launch_gemm_ksplit(int variant, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
+// Which kernel serves a GEMM problem (a function of its sizes alone): the weight-streaming kernel, the tiles whose waves split
+// every stage along k (NVFP4 only), the tiles whose waves do not, or the plain kernel for what those cannot address.
+struct GemmPlan {
+    int kernel;         // ARCQ_ROUTE_*
+    int rows, cols;     // activation and weight rows of a workgroup's tile
+    int runs;           // runs of K' across workgroups (ARCQ_ROUTE_TILES)
+    bool ahead;         // ARCQ_ROUTE_STREAM: a wave asks for its next group of chunks while it computes one
+};
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp);
+GemmPlan plan_mx_gemm(int64_t M, int64_t N, int64_t Kp, bool workspace);
+
+// Tiled kernel whose waves split every stage along k inside the workgroup (gemm_ksplit.hip): the fastest of its tiles for this
+// problem (rows = 0: none serves it), and its launch.
+struct KsplitTile {
+    int rows, cols;
+    double us;          // modelled time
+    bool ample;         // some tile occupies more than half of the chip, or the smallest one an eighth of it over a short K'
+};
+KsplitTile gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp);
+arcq_status launch_gemm_ksplit(int rows, int cols, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                                const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, float alpha, void* y, int y_dtype,
                                int64_t ldy, hipStream_t stream);
 

@@ -657,11 +657,8 @@ arcq_status launch_mx_staged(const uint8_t* a_codes, const uint8_t* a_scales, co
     return check_launch("mx_gemm_staged_kernel");
 }
 
-// Number of runs the units of the reduction dimension are cut into when the caller provides a workspace (1: no
-// split): a function of the shape alone.  Only the 128 x 128 tiles of few-tile problems split; the cost, in
-// microseconds, is rounds of workgroups over the 256 CUs times the units of a run at about 0.65 us a unit, plus,
-// when split, the write and read of the fp32 partial results at about 3 TB/s and 5.5 us for the shorter runs'
-// pipeline fill and the second launch (fitted to measurements over N = 2048 .. 8192, K' = 4352 .. 29696).
+}  // namespace
+
 // Shapes the weight-streaming kernel serves: up to 64 rows while the tiled kernels (with K' split across workgroups
 // where tiles are few) are not faster already.  Measured over N = 1024 .. 28672, K' = 4352 .. 28928: up to 16 rows
 // below 2 * 10^8 weights (10^8 when K' >= 16384: 5120 x 27904 27.5 us streamed, 19 us tiled); 17 to 32 rows below
@@ -674,7 +671,12 @@ static bool mx_streaming_shape(int64_t M, int64_t N, int64_t Kp) {
     return M <= 32 ? weights < 120000000 : M <= 64 && N < 8192 && weights < 22000000;
 }
 
-int mx_split_k(int64_t M, int64_t N, int64_t Kp) {
+// Number of runs the units of the reduction dimension are cut into when the caller provides a workspace (1: no
+// split): a function of the shape alone.  Only the 128 x 128 tiles of few-tile problems split; the cost, in
+// microseconds, is rounds of workgroups over the 256 CUs times the units of a run at about 0.65 us a unit, plus,
+// when split, the write and read of the fp32 partial results at about 3 TB/s and 5.5 us for the shorter runs'
+// pipeline fill and the second launch (fitted to measurements over N = 2048 .. 8192, K' = 4352 .. 29696).
+static int mx_split_k(int64_t M, int64_t N, int64_t Kp) {
     const int64_t nb = Kp >> 5;
     const bool streaming = mx_streaming_shape(M, N, Kp);
     if (streaming || nb < 8) return 1;
@@ -697,73 +699,91 @@ int mx_split_k(int64_t M, int64_t N, int64_t Kp) {
     return best;
 }
 
+// Tiles of 256 weight rows by 256, 192 or 128 activation rows when there is work for them (0: there is not): workgroups run in
+// rounds of one per compute unit, a round lasts as long as one tile, and a tile's time follows the bytes it copies per
+// unit, 136 (rows of A + rows of W): the height that minimises rounds x (height + 256) wins (e.g. 1024 x 10240:
+// 240 tiles of 192 rows in one round instead of 320 of 128 rows in two).
+static int mx_wide_rows(int64_t M, int64_t N) {
+    const int64_t tn256 = (N + 255) / 256;
+    if (((M + 127) / 128) * tn256 < 192) return 0;
+    auto cost = [&](int64_t bm) { return ((((M + bm - 1) / bm) * tn256 + 255) / 256) * (bm + 256); };
+    return cost(256) <= cost(192) && cost(256) <= cost(128) ? 256 : cost(192) <= cost(128) ? 192 : 128;
+}
+
+GemmPlan plan_mx_gemm(int64_t M, int64_t N, int64_t Kp, bool workspace) {
+    const int64_t nb = Kp >> 5;
+    // up to 64 rows the tiled kernels only win where they can split K' across workgroups, which needs the workspace
+    if (mx_streaming_shape(M, N, Kp) || (M <= 64 && !workspace && mx_split_k(M, N, Kp) > 1)) {
+        // weight tiles per wave: as few as keep the launch at one workgroup per compute unit, up to four, two with more than 32
+        // rows (measured with weights from HBM, 32 rows: 640 tiles 14.8 us with three per wave against 21.7 with one, 896 tiles
+        // 10.4 us with four against 13.0 with two, 320 tiles over K' = 8448 11.2 us with two against 15.2 with one)
+        const int64_t tiles = (N + 15) / 16;
+        const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+        const int nt = tiles <= 256 ? 1 : tiles <= 512 || mt > 2 ? 2 : tiles <= 768 ? 3 : 4;
+        return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, false};
+    }
+    const bool offsets_fit = (uint64_t)M * (uint64_t)nb * 16 < 0xFFFF0000ull && (uint64_t)N * (uint64_t)nb * 16 < 0xFFFF0000ull;
+    if (!offsets_fit || (nb < 8 && nb != 4)) return {ARCQ_ROUTE_DIRECT, 128, 128, 1, false};
+    // more than 256 tiles of 128 x 128 but at most 256 of 192 x 128: one round of the taller tile instead of two
+    // workgroups on some compute units (512 x 10240 over K' = 8448: 48 -> 37 us; 1024 x 5120 over 27904: 144 -> 105 us); and
+    // before the 256-wide tiles, which put a round of larger tiles on fewer compute units (160 x 28672 over 4352: 28.6 -> 24.2 us)
+    if (((M + 127) / 128) * ((N + 127) / 128) > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256)
+        return {ARCQ_ROUTE_TILES, 192, 128, 1, false};
+    if (const int rows = mx_wide_rows(M, N)) return {ARCQ_ROUTE_TILES, rows, 256, 1, false};
+    return {ARCQ_ROUTE_TILES, 128, 128, workspace ? mx_split_k(M, N, Kp) : 1, false};
+}
+
+namespace {
+
 template <typename OutT>
 arcq_status launch_mx_typed(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                             const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, OutT* y, int64_t ldy,
                             float* workspace, hipStream_t stream) {
     const int nb = (int)(Kp >> 5);
-    const bool offsets_fit = (uint64_t)M * (uint64_t)nb * 16 < 0xFFFF0000ull && (uint64_t)N * (uint64_t)nb * 16 < 0xFFFF0000ull;
-    const bool aligned16 = ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 &&
-                           ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
-    // up to 64 rows the tiled kernels only win where they can split K' across workgroups, which needs the workspace
-    const bool streaming = mx_streaming_shape(M, N, Kp) || (M <= 64 && workspace == nullptr && mx_split_k(M, N, Kp) > 1);
-    if (streaming) {
-        const int64_t tiles = (N + 15) / 16;
-#define ARCQ_MX_SKINNY(MT_, NT_, W_, U_) \
-    return launch_mx_skinny<MT_, NT_, W_, U_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream)
-        // weight tiles per wave: as few as keep the launch at one workgroup per compute unit, up to four (measured with
-        // weights from HBM, 32 rows: 640 tiles 14.8 us with three per wave against 21.7 with one, 896 tiles 10.4 us
-        // with four against 13.0 with two, 320 tiles over K' = 8448 11.2 us with two against 15.2 with one)
-        if (M <= 16) {
-            if (tiles >= 769) ARCQ_MX_SKINNY(1, 4, 8, 1);
-            if (tiles >= 513) ARCQ_MX_SKINNY(1, 3, 8, 1);
-            if (tiles >= 257) ARCQ_MX_SKINNY(1, 2, 8, 2);
-            ARCQ_MX_SKINNY(1, 1, 8, 2);
-        }
-        if (M <= 32) {
-            if (tiles >= 769) ARCQ_MX_SKINNY(2, 4, 8, 1);
-            if (tiles >= 513) ARCQ_MX_SKINNY(2, 3, 8, 1);
-            if (tiles >= 257) ARCQ_MX_SKINNY(2, 2, 8, 1);
-            ARCQ_MX_SKINNY(2, 1, 8, 2);
-        }
-        if (tiles >= 257) ARCQ_MX_SKINNY(4, 2, 8, 1);
-        ARCQ_MX_SKINNY(4, 1, 8, 1);
-#undef ARCQ_MX_SKINNY
+    const bool dword_scales = ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
+    const bool aligned16 = ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 && dword_scales;
+    const GemmPlan plan = plan_mx_gemm(M, N, Kp, workspace != nullptr);
+    if (plan.kernel == ARCQ_ROUTE_STREAM) {
+#define ARCQ_MX_STREAM(MT_, NT_, U_)                    \
+    if (plan.rows == 16 * MT_ && plan.cols == 16 * NT_) \
+    return launch_mx_skinny<MT_, NT_, 8, U_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream)
+        ARCQ_MX_STREAM(1, 1, 2);
+        ARCQ_MX_STREAM(1, 2, 2);
+        ARCQ_MX_STREAM(1, 3, 1);
+        ARCQ_MX_STREAM(1, 4, 1);
+        ARCQ_MX_STREAM(2, 1, 2);
+        ARCQ_MX_STREAM(2, 2, 1);
+        ARCQ_MX_STREAM(2, 3, 1);
+        ARCQ_MX_STREAM(2, 4, 1);
+        ARCQ_MX_STREAM(4, 1, 1);
+        ARCQ_MX_STREAM(4, 2, 1);
+#undef ARCQ_MX_STREAM
+        return fail(ARCQ_HIP_ERROR, "no weight-streaming kernel of %d x %d rows", plan.rows, plan.cols);
     }
-    // Tiles of 256 weight rows by 256, 192 or 128 activation rows when there is work for them: workgroups run in rounds
-    // of one per compute unit, a round lasts as long as one tile, and a tile's time follows the bytes it copies per
-    // unit, 136 (rows of A + rows of W): the height that minimises rounds x (height + 256) wins (e.g. 1024 x 10240:
-    // 240 tiles of 192 rows in one round instead of 320 of 128 rows in two).
-    const int64_t tn256 = (N + 255) / 256, t128x256 = ((M + 127) / 128) * tn256;
-    auto tile_cost = [&](int64_t bm) { return ((((M + bm - 1) / bm) * tn256 + 255) / 256) * (bm + 256); };
-    const int tile_rows = t128x256 < 192 ? 0
-                          : tile_cost(256) <= tile_cost(192) && tile_cost(256) <= tile_cost(128) ? 256
-                          : tile_cost(192) <= tile_cost(128) ? 192 : 128;
-    // more than 256 tiles of 128 x 128 but at most 256 of 192 x 128: one round of the taller tile instead of two
-    // workgroups on some compute units (512 x 10240 over K' = 8448: 48 -> 37 us; 1024 x 5120 over 27904: 144 -> 105 us); and
-    // before the 256-wide tiles, which put a round of larger tiles on fewer compute units (160 x 28672 over 4352: 28.6 -> 24.2 us)
-    const bool one_round_192 = ((M + 127) / 128) * ((N + 127) / 128) > 256 && ((M + 191) / 192) * ((N + 127) / 128) <= 256;
+    // How the units get into LDS: whole aligned pieces; any K' (a multiple of 32) from 512 on, codes at their minimum alignment;
+    // through registers, for scale bytes at odd addresses and short K' (no 192 x 128 tiles there)
+    const int mode = (nb & 3) == 0 && aligned16 ? COPIES
+                     : nb >= ScaleWindows<128, 128, 256, 8>::MIN_NB && dword_scales ? RAGGED : REGS;
     auto tiled = [&](auto mode_tag) {
         constexpr int MODE = decltype(mode_tag)::value;
+        const bool tall = plan.rows == 192 && plan.cols == 128;
+        const int wide = plan.cols == 256 ? plan.rows : MODE == REGS && tall ? mx_wide_rows(M, N) : 0;
         if constexpr (MODE != REGS)
-            if (one_round_192)
+            if (tall)
                 return launch_mx_staged<3, 2, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
-        if (tile_rows == 256)
+        if (wide == 256)
             return launch_mx_staged<4, 4, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
-        if (tile_rows == 192)
+        if (wide == 192)
             return launch_mx_staged<3, 4, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
-        if (tile_rows == 128)
+        if (wide == 128)
             return launch_mx_staged<2, 4, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream);
         return launch_mx_staged<2, 2, 2, 2, MODE>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream,
-                                                  workspace ? mx_split_k(M, N, Kp) : 1, workspace);
+                                                  plan.runs, workspace);
     };
-    if ((nb & 3) == 0 && offsets_fit && aligned16) return tiled(std::integral_constant<int, COPIES>{});
-    // any K' (a multiple of 32) from 512 on, codes at their minimum alignment
-    if (nb >= ScaleWindows<128, 128, 256, 8>::MIN_NB && offsets_fit &&
-        ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0)
-        return tiled(std::integral_constant<int, RAGGED>{});
-    // scale bytes at odd addresses, short K': units through registers
-    if (nb >= 8 && offsets_fit) return tiled(std::integral_constant<int, REGS>{});
+    if (plan.kernel == ARCQ_ROUTE_TILES && (mode != REGS || nb >= 8))
+        return mode == COPIES   ? tiled(std::integral_constant<int, COPIES>{})
+               : mode == RAGGED ? tiled(std::integral_constant<int, RAGGED>{})
+                                : tiled(std::integral_constant<int, REGS>{});
     dim3 grid((unsigned)((N + 127) / 128), (unsigned)((M + 127) / 128));
     hipLaunchKernelGGL(mx_gemm_direct_kernel<OutT>, grid, dim3(256), 0, stream, a_codes, a_scales, w_codes, w_scales,
                        (int)M, (int)N, nb, y, ldy);

@@ -140,6 +140,12 @@ def test_gemm_noalloc_argument_errors_and_scratch_limit():
     assert b"built-in" in B.lib().arcq_last_error()
 
 
+def random_sizes(seed, count, block):
+    rng = random.Random(seed)
+    log = lambda a, b: int(math.exp(rng.uniform(math.log(a), math.log(b))))
+    return [(log(1, 9000), log(1, 60000), block * log(1, 65536 // block)) for _ in range(count)]
+
+
 def occupied_without_scratch(M, N, Kp):
     """Some tile with the k split inside the workgroup covers the problem with 144 to 256 workgroups, or the smallest
     (64 x 32) an eighth of the chip over a short K'; the weight-streaming kernel serves up to 64 rows."""
@@ -154,15 +160,42 @@ def test_gemm_needs_no_workspace_where_a_tile_occupies_the_chip():
     """Such problems run from a null workspace and leave the built-in scratch of arcq_gemm_noalloc alone, whichever of the
     paths the modelled times prefer."""
     shapes = [(68, 5664, 14544), (103, 2336, 20000), (476, 256, 8464), (443, 197, 7104), (893, 67, 7488), (3907, 1, 8560)]
-    rng = random.Random(5)
-    log = lambda a, b: int(math.exp(rng.uniform(math.log(a), math.log(b))))
-    shapes += [(log(1, 9000), log(1, 60000), 16 * log(1, 8192)) for _ in range(40000)]
+    shapes += random_sizes(5, 40000, 16)
     checked = 0
     for M, N, Kp in shapes:
         if occupied_without_scratch(M, N, Kp):
             assert B.arcq_gemm_workspace_size(M, N, Kp) == 0, (M, N, Kp)
             checked += 1
     assert checked > 5000
+
+
+def test_routes():
+    """The kernel, the tile and the number of runs come from one rule: the workspace is what the runs need, the runs are at
+    least four stages (NVFP4) or two units (MXFP4) long, and only tiles that exist are named."""
+    r = B.Route()
+    assert B.lib().arcq_gemm_route(4, 8, 40, ctypes.byref(r)) == B.BAD_SHAPE
+    assert B.lib().arcq_gemm_route(4, 8, 64, None) == B.INVALID_ARG
+    assert B.lib().arcq_mx_gemm_route(4, 8, 48, 0, ctypes.byref(r)) == B.BAD_SHAPE
+    assert B.lib().arcq_mx_gemm_route(4, 8, 64, 0, None) == B.INVALID_ARG
+    wide = [(256, 256), (192, 256), (128, 256), (192, 128), (128, 128)]
+    narrow = [(64, 32), (64, 64), (96, 64), (128, 64), (64, 128), (96, 128), (128, 128)]
+    stream = [(16 * m, 16 * n) for m, n in ((1, 1), (1, 2), (1, 3), (1, 4), (2, 1), (2, 2), (2, 3), (2, 4), (4, 1), (4, 2), (8, 1), (8, 2))]
+    seen = set()
+    for M, N, Kp in random_sizes(6, 40000, 16):
+        kernel, rows, cols, runs, ahead = B.arcq_gemm_route(M, N, Kp)
+        seen.add((kernel, rows, cols))
+        assert (rows, cols) in {B.ROUTE_STREAM: stream, B.ROUTE_KSPLIT: narrow, B.ROUTE_TILES: wide, B.ROUTE_DIRECT: [(128, 128)]}[kernel]
+        assert B.arcq_gemm_workspace_size(M, N, Kp) == (runs * M * N * 4 if runs > 1 else 0)
+        assert runs == 1 or (kernel == B.ROUTE_TILES and (rows, cols) == (128, 128) and 2 <= runs <= 8 and 512 * runs <= Kp + 127)
+        if kernel == B.ROUTE_STREAM:
+            assert M <= rows and (rows == 16 or M > rows // 2)
+    assert len(seen) == len(wide) + len(narrow) + len(stream) + 1        # every tile is some shape's
+    for M, N, Kp in random_sizes(7, 10000, 32):
+        kernel, rows, cols, runs, _ = B.arcq_mx_gemm_route(M, N, Kp, True)
+        assert (rows, cols) in {B.ROUTE_STREAM: stream, B.ROUTE_TILES: wide, B.ROUTE_DIRECT: [(128, 128)]}[kernel]
+        assert B.arcq_mx_gemm_workspace_size(M, N, Kp) == (runs * M * N * 4 if runs > 1 else 0)
+        assert runs == 1 or (kernel == B.ROUTE_TILES and (rows, cols) == (128, 128) and 2 <= runs <= 8)
+        assert B.arcq_mx_gemm_route(M, N, Kp)[3] == 1                   # no workspace: never split
 
 
 def test_check_perm_argument_errors():
