@@ -879,7 +879,7 @@ __device__ __forceinline__ void transpose_scale_pairs(uint2 s, uint32_t& even_ch
 // partner: the pairs of the main loops stop before it and the last wave handles it by itself at the end, with
 // 8-byte loads.
 //
-// ROLL: a wave takes several groups, and asks for the next one while it computes: the registers of two chunks are loaded again
+// ROLL (see plan_stream): a wave takes several groups, and asks for the next one while it computes: the registers of two chunks are loaded again
 // as soon as both have been used.  Two, because a chunk is half a cache line of every row: asking for the halves one by one,
 // each behind a chunk's decode, was 10 to 20 % slower than asking for whole groups between computing them (16 x 8192 over
 // K' = 29696, weights from HBM: 36.4, 31.0 and, by twos, 30.4 us), although it keeps the most loads in flight.
@@ -1196,14 +1196,20 @@ static GemmPlan plan_stream(int64_t M, int64_t N, int64_t Kp) {
     const int mt = M <= 16 ? 1 : M <= 32 ? 2 : M <= 64 ? 4 : 8;
     const int nt = tiles <= 256 ? 1 : tiles <= 512 || mt > 2 ? 2 : tiles <= 768 ? 3 : 4;
     // Ahead where waves take several groups (from HBM, us: 16 x 28672 over K' = 8448 34.9 -> 32.0, 32 x 28672 over 8464 47.5 ->
-    // 45.1, 16 x 10240 over 8448 13.9 -> 13.1); with one group per wave its code without a loop is still 2 to 4 % faster
-    // (32 x 14336 over 4352 12.9 -> 12.4, 16 x 6144 over 4240 7.4 -> 7.3), except for four tiles behind one row tile (16 x 14336
-    // over 4352 10.4 against 10.6); one tile behind one row tile loses with several groups (16 x 4096 over 14592 11.0
+    // 45.1, 16 x 10240 over 8448 13.9 -> 13.1), and with one group per wave, where its code without a loop is still 2 to 4 %
+    // faster (32 x 14336 over 4352 12.9 -> 12.4, 16 x 6144 over 4240 7.4 -> 7.3) except for four tiles behind one row tile (16 x
+    // 14336 over 4352 10.4 against 10.6).  Not where one wave or a few take a group more than the others (they alone go
+    // through the loop's copy of the code, which presumably is not in the instruction cache then).  Nine groups cost 1 us more that way
+    // (33 x 213 over 5008 9.7 against 8.5, 24 x 28672 over 5008 5 % more, 16 x 9216 over 4608 4 %), ten and eleven 2 to 7 % with
+    // three weight tiles or more than 32 rows, 17 and 25 up to 3 %; 33 to 48 rows lose up to 7 % with any but a whole number of
+    // rounds (33 x 1103 over 15616).  One tile behind one row tile loses with several groups (16 x 4096 over 14592 11.0
     // against 11.1, over 14544 12.3 against 12.7).  128 rows have no groups.
     const int64_t ngroup = Kp >> 9;
-    bool ahead = mt <= 4;
-    if (mt == 1 && nt == 1) ahead = ngroup <= STREAM_WAVES;
-    if (mt == 1 && nt == 4) ahead = ngroup > STREAM_WAVES;
+    bool ahead;
+    if (ngroup <= STREAM_WAVES) ahead = mt <= 4 && !(mt == 1 && nt == 4);
+    else if (mt == 4) ahead = M > 48 ? ngroup >= 12 : ngroup % STREAM_WAVES == 0;
+    else if (nt >= 3) ahead = ngroup >= 11 && ngroup % STREAM_WAVES != 1;
+    else ahead = mt < 4 && mt * nt != 1 && (mt * nt == 2 || ngroup >= 10);
     return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, ahead};
 }
 
@@ -1284,14 +1290,20 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
         ARCQ_STREAM(1, 1, STREAM_WAVES, 2, false);
         ARCQ_STREAM(1, 1, STREAM_WAVES, 2, true);
         ARCQ_STREAM(1, 2, STREAM_WAVES, 2, true);
+        ARCQ_STREAM(1, 3, STREAM_WAVES, 1, false);
         ARCQ_STREAM(1, 3, STREAM_WAVES, 1, true);
         ARCQ_STREAM(1, 4, STREAM_WAVES, 1, false);
         ARCQ_STREAM(1, 4, STREAM_WAVES, 1, true);
         ARCQ_STREAM(2, 1, STREAM_WAVES, 2, true);
+        ARCQ_STREAM(2, 2, STREAM_WAVES, 1, false);
         ARCQ_STREAM(2, 2, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(2, 3, STREAM_WAVES, 1, false);
         ARCQ_STREAM(2, 3, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(2, 4, STREAM_WAVES, 1, false);
         ARCQ_STREAM(2, 4, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(4, 1, STREAM_WAVES, 1, false);
         ARCQ_STREAM(4, 1, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(4, 2, STREAM_WAVES, 1, false);
         ARCQ_STREAM(4, 2, STREAM_WAVES, 1, true);
         ARCQ_STREAM(8, 1, STREAM_WAVES, 1, false);
         ARCQ_STREAM(8, 2, 4, 1, false);

@@ -198,6 +198,19 @@ def test_routes():
         assert B.arcq_mx_gemm_route(M, N, Kp)[3] == 1                   # no workspace: never split
 
 
+# 512-k groups of a row over eight waves: one each, a few waves with one more, all with more; chunks behind the last group do not count
+@pytest.mark.parametrize("M,N,Kp,ahead", [
+    (16, 14336, 4352, 0), (16, 4096, 4352, 1), (16, 4096, 14592, 0), (32, 28672, 4096, 1), (48, 500, 4352, 1),     # at most eight
+    (16, 7168, 4608, 1), (16, 9216, 4608, 0), (16, 28672, 4672, 0), (24, 28672, 5008, 0), (32, 4096, 4608, 1), (32, 5120, 4608, 0),
+    (32, 5120, 5120, 1), (32, 9216, 5264, 0), (33, 213, 5008, 0), (38, 282, 10560, 0), (35, 4383, 5072, 0), (64, 500, 5632, 0),
+    (16, 28672, 13008, 0), (32, 28672, 8720, 0), (33, 1103, 15616, 0),
+    (16, 10240, 8448, 1), (16, 28672, 8448, 1), (32, 28672, 8464, 1), (48, 4096, 8208, 1), (64, 2048, 14592, 1), (32, 16384, 5632, 1),
+])
+def test_streaming_waves_load_ahead_where_most_of_them_take_another_group(M, N, Kp, ahead):
+    route = B.arcq_gemm_route(M, N, Kp)
+    assert route[0] == B.ROUTE_STREAM and route[4] == ahead
+
+
 def test_check_perm_argument_errors():
     r = ctypes.c_int(0)
     assert B.lib().arcq_check_perm(None, 16, FAKE, ctypes.byref(r), None) == B.INVALID_ARG
