@@ -524,7 +524,7 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
 // matrix rate of the bigger ones) over one half of every stage: four of its eight k-steps, exactly the
 // 16-byte piece of codes a lane reads per row and stage.  The two waves of a pair (w and w + 4) share a
 // SIMD, so the matrix pipe still draws from two instruction streams; at the end they add their partial
-// tiles through the LDS and each stores one of the two fragment rows.  MODE: COPIES for K' % 128 == 0, RAGGED otherwise.
+// tiles through the LDS and each stores one of the two fragment rows.  MODE: COPIES for K' % 128 == 0, RAGGED for rows off the grid of 64.
 template <typename OutT, int MODE>
 __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
@@ -1323,12 +1323,11 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
         ARCQ_TILES(3, 4, COPIES);
         ARCQ_TILES(2, 2, COPIES);
         // 128 x 256 tiles: wave pairs that split every stage (6 % faster than 8 waves of 64 x 64 on the 2048 x 4096 x 4352
-        // problem).  A half stage at the end is one of the ragged ends that the RAGGED copies know: 2048 x 4096 over
-        // K' = 4416 69.6 us, 8 waves of 64 x 64 with a shorter last stage 71.8 us; over K' = 8256 123 and 130 us
-        if (nbk >= 16)
-            return (nbk & 7) == 0
-                       ? launch_kpair<COPIES>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream)
-                       : launch_kpair<RAGGED>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
+        // problem); a half stage at the end has its own code in the other kernel.  (The pairs' RAGGED copies know half stages
+        // too, and are 3 % faster on 2048 x 4096 over K' = 4416, but 5 to 20 % slower up to K' = 2000 and on most others: 754 x
+        // 10432 over 960 29.1 against 33.1 us, 374 x 20167 over 12224 211 against 238.)
+        if ((nbk & 7) == 0 && nbk >= 16)
+            return launch_kpair<COPIES>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
         return launch_staged<2, 2, 2, 4>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
     }
     if (plan.kernel == ARCQ_ROUTE_TILES && nbk >= ScaleWindows<128, 128, 256, 8>::MIN_NB && dword_scales) {
