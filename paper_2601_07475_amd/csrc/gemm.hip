@@ -1150,11 +1150,11 @@ static bool skinny_shape(int64_t M, int64_t N, int64_t Kp) {
     return !((Kp >= 4096 && weights >= 20000000) || (Kp >= 8192 && weights >= 12000000));
 }
 
-// Number of runs the reduction dimension is cut into (1: no split) on the 128 x 128 tiles, and the modelled time.  Problems
+// Number of runs the reduction dimension is cut into (1: no split) on the 128 x 128 tiles.  Problems
 // with too few such tiles to occupy the chip split K' into runs of at least four stages (256 k).  The number of runs minimises
 // a cost in units of one stage time of a tile (about 1.3 us): rounds of workgroups over the 256 CUs times the stages of a run,
 // plus, when split, the write and read of the fp32 partial results at about 3 TB/s.
-static int split_runs(int64_t M, int64_t N, int64_t Kp, double* us) {
+static int split_runs(int64_t M, int64_t N, int64_t Kp) {
     const int64_t nbk = Kp >> 4;
     const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
     const int64_t nstage = (nbk + 7) >> 3;
@@ -1169,8 +1169,30 @@ static int split_runs(int64_t M, int64_t N, int64_t Kp, double* us) {
             best_cost = cost;
         }
     }
-    *us = 1.3 * best_cost + (best > 1 ? 6.0 : 4.0);
     return best;
+}
+
+// Modelled times in us of the 128 x 128 tiles in that number of runs and of the streaming kernel with 33 to 128 rows, to compare
+// with gemm_ksplit_best's and fitted to the same problems (8 and 6 to 10 % rms).
+static double tiles_time(int64_t M, int64_t N, int64_t Kp, int runs) {
+    const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128) * runs, nstage = ((Kp >> 4) + 7) >> 3;
+    const double rounds = (double)((wgs + 255) / 256), stages = (double)((nstage + runs - 1) / runs), ragged = (Kp & 63) ? 0.5 : 0.0;
+    const double fill = (double)wgs / 256.0;
+    if (runs > 1) return 7.4 + ((N & 3) ? 5.3 * (0.2 + 0.8 * fill) : 0.0) + ragged + stages * 0.95 * rounds +
+                         0.366e-6 * 8.0 * (double)runs * (double)M * (double)N;
+    // (values stored one by one or in pairs; the fill by itself is for fp32 results, which take these tiles 1 to 3 us longer)
+    return 4.5 + fill + ((N & 7) ? 5.0 * (0.15 * rounds + 0.85 * fill) : 0.0) + ragged + stages * (0.84 * rounds + 0.195 * fill);
+}
+static double stream_time(const GemmPlan& plan, int64_t N, int64_t Kp) {
+    const int64_t wgs = (N + plan.cols - 1) / plan.cols;
+    const double rounds = (double)((wgs + 255) / 256), fill = (double)wgs / 256.0;
+    // 512-k groups; a round over a short K' takes as long as one over a few of them
+    const double groups = (double)Kp / 512.0;
+    if (plan.rows == 64) return plan.cols == 32 ? 1.0 + 2.5 * rounds + std::max(groups, 1.6) * (0.674 * rounds + 0.303 * fill)
+                                                : 2.9 + std::max(groups, 3.1) * (0.543 + 0.132 * fill);
+    // (one tile: 0.7 us more than the fit, which is that much short over K' = 1024 .. 1900)
+    return plan.cols == 32 ? 4.8 + std::max(groups, 1.2) * (1.547 * rounds + 0.531 * fill)
+                           : 3.2 + std::max(groups, 1.7) * (1.341 + 0.268 * fill);
 }
 
 // Rounds of tiles of `rows` x 256, one per compute unit, times the time of a stage of such a tile.
@@ -1215,8 +1237,8 @@ static GemmPlan plan_stream(int64_t M, int64_t N, int64_t Kp) {
 
 // Which kernel serves a problem: a function of the shape alone, so that the workspace a caller sizes beforehand matches what the
 // launch uses.  Up to 32 rows the weight-streaming kernel, beyond the smallest modelled time of three:
-//   * the streaming kernel up to 128 rows: start + 512-k groups x time of a round's group (one or two weight tiles per wave);
-//     e.g. 64 rows over K' = 4240: 5120 weight rows 12.5 us against 14.3 on 64 x 32 tiles, 28672 38.9 against 30.4 on 64 x 128;
+//   * the streaming kernel up to 128 rows, e.g. 64 rows over K' = 4240: 5120 weight rows 12.5 us against 14.3 on 64 x 32 tiles,
+//     28672 38.9 against 30.4 on 64 x 128; 46 x 9600 over K' = 512 8.5 against 6.1 on 64 x 64;
 //   * the tiles with the k split inside the workgroup (gemm_ksplit_best);
 //   * the tiles of this file, with K' split across workgroups or without, by the stage times that choose among them.
 // K' is split across workgroups only where the tiles with the split inside leave much of the chip idle, whatever the times
@@ -1228,16 +1250,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp) {
     if (M <= 32) return stream;
     const KsplitTile ks = gemm_ksplit_best(M, N, Kp);
     const GemmPlan ksplit = {ARCQ_ROUTE_KSPLIT, ks.rows, ks.cols, 1, false};
-    if (skinny_shape(M, N, Kp)) {
-        const double groups = (double)Kp / 512.0;
-        const int64_t wgs = (N + stream.cols - 1) / stream.cols;
-        const double rounds = (double)((wgs + 255) / 256);
-        const bool two = stream.cols == 32;         // weight tiles per wave
-        // a second round costs more than the model says with few groups (48 x 14336 over 1552: 11.9 us against 10.6 on 64 x 64 tiles)
-        const double us = M <= 64 ? 3.0 + groups * rounds * (two ? 1.11 : 0.64) * (rounds > 1.0 ? 1.25 : 1.0)
-                                  : 4.2 + groups * rounds * (two ? 2.27 : 1.135);
-        return ks.rows != 0 && ks.us < us ? ksplit : stream;
-    }
+    if (skinny_shape(M, N, Kp)) return ks.rows != 0 && ks.us < stream_time(stream, N, Kp) ? ksplit : stream;
     const int64_t nbk = Kp >> 4, nstage = (nbk + 7) >> 3, tn256 = (N + 255) / 256;
     const bool offsets_fit = (uint64_t)M * (uint64_t)nbk * 8 < 0xFFFF0000ull && (uint64_t)N * (uint64_t)nbk * 8 < 0xFFFF0000ull;
     if (nbk < 8 || !offsets_fit) return {ARCQ_ROUTE_DIRECT, 128, 128, 1, false};
@@ -1264,7 +1277,8 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp) {
         tiles.cols = 256;
         us = 5.0 + (double)nstage * std::min({c256, c192, c128});
     } else {
-        tiles.runs = split_runs(M, N, Kp, &us);
+        tiles.runs = split_runs(M, N, Kp);
+        us = tiles_time(M, N, Kp, tiles.runs);
     }
     const bool too_large = tiles.runs > 1 && (uint64_t)tiles.runs * (uint64_t)M * (uint64_t)N * sizeof(float) > ARCQ_NOALLOC_SCRATCH_BYTES;
     if (ks.rows != 0 && (tiles.runs > 1 && (ks.ample || too_large) ? ks.ample : ks.us < us)) return ksplit;

@@ -429,31 +429,38 @@ arcq_status launch_ksplit_typed(int rows, int cols, const uint8_t* a_codes, cons
 
 }  // namespace
 
-// The tile that takes the least time, and that time in us; 0 and a time beyond any other's where none serves the problem.
+// The tile that takes the least time, and that time in us; rows = 0 and a time beyond any other's where none serves the problem.
 // Only tiles that cover it with at most one workgroup per compute unit (256) are looked at: with more, a second round costs
-// as much as the first; and with 32 at least, below which K' is better split across workgroups.  The time of a tile over K' is start + stages (alone + shared x workgroups / 256): a workgroup
-// takes longer the more of the chip is busy (clock, and the weights' way from HBM).  Fitted to 466 problems (M = 20 .. 640,
-// N = 1024 .. 28672, K' = 1552, 4240, 8464, 14544, weights from HBM) to 4 to 9 % rms; the choice among these, the streaming
-// kernel and the tiles of gemm.hip by the modelled times (gemm.hip) is 1.2 % from the best of all on average, where fixed
-// limits of 144 to 256 workgroups on five tile shapes were 5.7 % off.
+// as much as the first; and with 32 at least, below which K' is better split across workgroups.  The time of a tile over K' is
+// start + stages (alone + shared x workgroups / 256): a workgroup takes longer the more of the chip is busy (clock, and the
+// weights' way from HBM).  Where weight rows are no multiple of four, every value is stored by itself (single, on a full
+// chip); rows off the grid of 64 have their windows of scale bytes, 0.5 us.  Fitted to 6700 problems (M = 33 .. 8000, N = 16 .. 30000, K' = 512 ..
+// 30000, weights from HBM), each path of each timed: 4 to 8 % rms.  The choice among these, the streaming kernel and the tiles
+// of gemm.hip by the modelled times is 2 % from the best of all on average, where fixed limits of 144 to 256 workgroups on five
+// tile shapes were 5 %; eleven of the 6700 are more than 4 % slower than with those limits, 1000 more than 4 % faster.
+// 96 x 128 tiles are left out where they pad more rows than 128 x 128: what is multiplied in vain costs clock that the model does
+// not know of (195 x 10832 over K' = 12096: 90.6 us against 81.8).
 KsplitTile gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp) {
     struct Tile {
         int rows, cols;
-        double start, alone, shared;
+        double start, alone, shared, single;
     };
-    static constexpr Tile tiles[] = {{64, 32, 4.1, 0.454, 0.100}, {64, 64, 5.0, 0.552, 0.154}, {96, 64, 5.9, 0.692, 0.249},
-                                     {64, 128, 4.4, 0.955, 0.343}, {128, 64, 7.0, 0.832, 0.236}, {96, 128, 6.5, 1.067, 0.400},
-                                     {128, 128, 7.7, 1.254, 0.497}};
+    static constexpr Tile tiles[] = {{64, 32, 4.1, 0.421, 0.089, 1.1}, {64, 64, 4.95, 0.484, 0.200, 1.95}, {96, 64, 6.1, 0.641, 0.250, 2.65},
+                                     {64, 128, 5.4, 0.759, 0.461, 3.7}, {128, 64, 7.0, 0.818, 0.209, 3.4}, {96, 128, 6.9, 0.966, 0.533, 5.1},
+                                     {128, 128, 7.9, 1.206, 0.598, 6.8}};
     KsplitTile best = {0, 0, 1e30, false};
     const int64_t nbk = Kp >> 4;
     if (nbk < 32) return best;                            // at least two stages
     if ((uint64_t)M * (uint64_t)nbk * 8 >= 0xFFFF0000ull || (uint64_t)N * (uint64_t)nbk * 8 >= 0xFFFF0000ull) return best;
     for (const Tile& t : tiles) {
-        const int64_t wgs = ((M + t.rows - 1) / t.rows) * ((N + t.cols - 1) / t.cols);
+        const int64_t tiles_m = (M + t.rows - 1) / t.rows, wgs = tiles_m * ((N + t.cols - 1) / t.cols);
         if (wgs > 256 || wgs < 32) continue;
-        const bool added = t.cols == 128 && t.rows < 128;   // 64 x 128 and 96 x 128: see `ample` in plan_gemm
+        const bool added = t.cols == 128 && t.rows < 128;   // 64 x 128 and 96 x 128: see plan_gemm
         if (!added && (wgs >= 144 || (t.cols == 32 && M > 64 && nbk <= 544))) best.ample = true;
-        const double c = t.start + (double)((nbk + 15) / 16) * (t.alone + t.shared * (double)wgs / 256.0);
+        if (t.rows == 96 && t.cols == 128 && tiles_m * 96 > (M + 127) / 128 * 128) continue;
+        const double fill = (double)wgs / 256.0;
+        const double c = t.start + ((N & 3) ? t.single * (0.2 + 0.8 * fill) : 0.0) + ((Kp & 63) ? 0.5 : 0.0) +
+                         (double)((nbk + 15) / 16) * (t.alone + t.shared * fill);
         if (c < best.us) {
             best.rows = t.rows;
             best.cols = t.cols;
