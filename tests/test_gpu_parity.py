@@ -264,7 +264,9 @@ def test_empty_inputs_and_check_perm():
 
 
 # --------------------------------------------------------------------------------------
-GEMM_SHAPES = [  # M, N, K, S : ragged tiles, K' with every residue mod 64, tiny and skinny cases
+# M, N, K, S.  The comments say what a line is for; which kernel and tile a shape runs on follows the dispatch rule.  Shapes for every
+# tile in every copy mode, asserted to reach it, are in test_gpu_ragged.py.
+GEMM_SHAPES = [  # ragged tiles, K' with every residue mod 64, tiny and skinny cases
     (1, 1, 16, 0), (16, 512, 512, 32), (77, 200, 48, 16), (130, 129, 96, 16), (128, 256, 256, 0),
     (257, 131, 1040, 48), (16, 1000, 4096, 256), (300, 77, 2048, 2048),
     (7, 45, 160, 32), (16, 4097, 1008, 16), (3, 16, 14336, 256), (17, 40, 512, 0), (128, 384, 192, 0), (500, 260, 4160, 64),
@@ -281,19 +283,19 @@ GEMM_SHAPES = [  # M, N, K, S : ragged tiles, K' with every residue mod 64, tiny
     # the same 128 x 256 tiles with K' a multiple of 128: the kernel whose wave pairs split every stage
     # (ragged edges, the shortest and a longer reduction, both output types)
     (1990, 4070, 192, 64), (2048, 3000, 1024, 128),
-    # 65 to 128 rows with enough weights for the tiled kernels with split K instead of the weight-streaming kernel
+    # 65 to 128 rows with enough weights for tiles instead of the weight-streaming kernel
     # (K' >= 4096 with 2 * 10^7 weights, K' >= 8192 with 1.2 * 10^7)
     (100, 4800, 4096, 256), (128, 1500, 8192, 512),
-    # between 144 and 256 tiles of 64 x 64, 128 x 64 or 128 x 128 and K' a multiple of 256: the kernel whose waves split
-    # every stage into k quarters inside the workgroup (ragged edges in both directions; two, five and 17 stages)
+    # the kernel whose waves split every stage into k quarters inside the workgroup, K' a multiple of 256 (ragged edges in both
+    # directions; two, five and 17 stages)
     (130, 3100, 512, 0), (192, 4096, 4096, 256), (300, 3500, 1024, 256), (700, 3900, 448, 64), (1024, 4096, 1024, 256),
-    # ... K' a multiple of 64 but not of 256: the last stage holds one, two or three of the four k shares (every tile shape)
+    # ... K' a multiple of 64 but not of 256: the last stage holds one, two or three of the four k shares
     (130, 3100, 512, 64), (192, 4096, 1024, 128), (300, 3500, 1024, 192), (1024, 4096, 512, 64), (512, 4000, 512, 192),
     (64, 6100, 512, 64), (700, 3900, 448, 128),
-    # ... K' with an odd number of blocks, or K' % 64 = 32: the same tiles with stages through registers (every tile shape)
+    # ... K' with an odd number of blocks, or K' % 64 = 32: the same shapes with windows of scale bytes
     (130, 3100, 512, 16), (192, 4096, 1024, 48), (300, 3500, 1024, 208), (1024, 4096, 512, 16), (512, 4000, 512, 176),
     (64, 6100, 512, 16),
-    # ... 96 x 64 tiles (six fragments over four waves: two waves finish two, two finish one), exact and ragged; 128 x 64
+    # ... exact and ragged edges over whole stages
     (384, 4096, 1024, 0), (290, 3500, 512, 256), (512, 4000, 512, 0),
     # four weight tiles per wave at up to 16 rows, left-over chunks behind the last group of four: 2 chunks (the last one
     # block), 1 chunk of two blocks, 4 chunks (the last six blocks), none
@@ -301,9 +303,9 @@ GEMM_SHAPES = [  # M, N, K, S : ragged tiles, K' with every residue mod 64, tiny
     # three weight tiles per wave on the weight-streaming kernel (513 to 768 tiles of 16 weight rows), 16 and 32 rows
     (16, 10240, 512, 32), (9, 8300, 1040, 16), (32, 9000, 256, 64), (20, 12288, 4096, 256), (32, 7000, 512, 0),
     (32, 12400, 528, 0),
-    # 33 to 64 rows against many weight rows: the 64 x 64 k-split tiles instead of the weight-streaming kernel
+    # 33 to 64 rows against many weight rows
     (50, 9300, 512, 0), (64, 14336, 256, 256), (33, 9216, 1024, 0),
-    # 64 x 32 tiles (two fragments over four k-quarter waves: two of the waves finish none)
+    # few hundred rows against few weight rows (64 x 32 tiles: two fragments over four k-quarter waves, two of the waves finish none)
     (64, 6100, 512, 0), (100, 4000, 768, 256), (40, 5000, 4096, 256), (128, 500, 512, 0), (200, 1000, 4096, 256),
     # 192 x 128 tiles (more than 256 tiles of 128 x 128, too few for the 256-wide ones): ragged edges, a half stage at the end
     (500, 10200, 192, 64), (640, 8100, 256, 64),
@@ -314,11 +316,11 @@ GEMM_SHAPES = [  # M, N, K, S : ragged tiles, K' with every residue mod 64, tiny
     # boundary.  Weight-streaming kernel with 1, 2, 4 and 8 row tiles, one block per row, last chunk of 1, 3, 5, 7 blocks
     (8, 40, 16, 0), (1, 300, 1008, 0), (16, 1000, 4096, 272), (16, 4097, 1008, 48), (33, 77, 2048, 2000), (20, 300, 512, 48),
     (64, 4097, 240, 64), (100, 260, 4160, 80), (128, 45, 160, 16), (17, 14336, 512, 496),
-    # the same on the tiled kernels, stages through registers: 128 x 128 tiles without and with split K' (the last stage
+    # the same on the tiled kernels: 128 x 128 tiles without and with split K' (the last stage
     # holds 2, 7, 1 and 4 blocks), 128 x 256 tiles, and a large output
     (257, 131, 1040, 16), (200, 140, 560, 64), (300, 260, 4160, 80), (256, 512, 4096, 320), (1990, 4070, 240, 64),
     (2048, 3000, 1024, 144), (4000, 4100, 112, 64), (128, 1500, 8192, 528),
-    # ... 192 x 256 and 192 x 128 tiles with stages through registers
+    # ... 192 x 256 tiles, and 192 x 128 ones through registers (a row too short for windows)
     (570, 14000, 192, 80), (500, 10200, 192, 48),
 ]
 
@@ -790,7 +792,7 @@ def test_ref_gemm_bf16_against_fp64(M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K,S", [(200, 260, 8192, 512), (130, 129, 4192, 32), (384, 1000, 6144, 0), (100, 300, 14336, 256),
-                                     (200, 260, 8192, 544)])      # the last: an odd number of blocks, units through registers
+                                     (200, 260, 8192, 544)])      # the last: an odd number of blocks
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 def test_mx_gemm_with_workspace_splits_the_reduction(M, N, K, S, dtype):
     """Few-tile problems with a long K' on arcq_mx_gemm_ws: 2 to 8 runs (the second ends with a half unit), against the

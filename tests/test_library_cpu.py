@@ -224,6 +224,25 @@ def test_the_route_is_the_path_that_measured_faster(M, N, Kp, tile):
     assert runs == 1 and (kernel == B.ROUTE_STREAM if tile is None else (rows, cols) == tile)
 
 
+def test_gpu_shape_lists_reach_every_kernel():
+    """The lists of test_gpu_ragged.py against the rule as it is: every tile, with the copies of whole rows and with windows; every
+    tile of the streaming kernel, loading ahead and not, with several groups per wave and something behind the last."""
+    import test_gpu_ragged as R
+    for kernel, lists in ((B.ROUTE_TILES, R.STAGED), (B.ROUTE_KSPLIT, R.KSPLIT)):
+        for tile, shapes in lists.items():
+            assert all(B.arcq_gemm_route(M, N, 16 * nb)[:4] == (kernel, *tile, 1) for M, N, nb in shapes), tile
+            assert {nb % 4 == 0 for _, _, nb in shapes} == {True, False}, tile
+    for runs, shapes in R.RUNS.items():
+        assert all(B.arcq_gemm_route(M, N, 16 * nb)[:4] == (B.ROUTE_TILES, 128, 128, runs) for M, N, nb in shapes), runs
+    for (rows, cols, runs), shapes in R.MX.items():
+        assert all(B.arcq_mx_gemm_route(M, N, 32 * nb, True)[:4] == (B.ROUTE_TILES, rows, cols, runs) for M, N, nb in shapes)
+    routes = {(nb // 32 > 8, nb % 32 > 0) + B.arcq_gemm_route(M, N, 16 * nb)[1:] for M, N, nb in R.STREAM
+              if B.arcq_gemm_route(M, N, 16 * nb)[0] == B.ROUTE_STREAM}
+    for rows, cols in ((16, 48), (16, 64), (32, 32), (32, 48), (32, 64), (64, 16), (64, 32)):
+        assert (True, True, rows, cols, 1, 0) in routes and (True, True, rows, cols, 1, 1) in routes, (rows, cols)
+    assert (True, True, 16, 16, 1, 0) in routes and (True, True, 16, 32, 1, 1) in routes and (True, True, 32, 16, 1, 1) in routes
+
+
 def test_check_perm_argument_errors():
     r = ctypes.c_int(0)
     assert B.lib().arcq_check_perm(None, 16, FAKE, ctypes.byref(r), None) == B.INVALID_ARG
