@@ -161,8 +161,8 @@ arcq_status arcq_gemm_workspace_size(int64_t M, int64_t N, int64_t Kp, size_t* b
  * product fits fp16) and multiplied on the fp16 MFMA path.
  * a_*  packed activations [M, Kp] from arcq_quantize_act;  w_*  packed weights [N, Kp]
  *      from arcq_pack_weight; codes 8-byte aligned.  Kp % 16 == 0, Kp > 0.  Every such Kp and alignment runs
- *      on the tiled / weight-streaming kernels.  Kp % 64 == 0 with 16-byte aligned codes is the fastest case on large M (by 1 to
- *      5 %); scale bytes whose base is not 4-byte aligned cost the tiled kernels up to 1.35x.
+ *      on the tiled / weight-streaming kernels.  Kp % 64 == 0 with 16-byte aligned codes is the fastest case (by 3 to
+ *      10 % on large M, 9 to 20 % on a few hundred rows, up to 18 % on decode); scale bytes whose base is not 4-byte aligned cost the tiled kernels up to 1.35x.
  * y    out [M, N] row-major, pitch ldy elements (ldy >= N), y_dtype ARCQ_DTYPE_F16 / _F32,
  *      4-byte aligned (16-byte aligned with ldy % 8 == 0 lets the tiled kernels store whole lines).
  * workspace  device scratch of at least arcq_gemm_workspace_size bytes, 256-byte
@@ -244,7 +244,7 @@ arcq_status arcq_calib_select(const float* colmax, int64_t K, int32_t* perm, int
  * so arcq_mx_gemm needs no decode:
  *   y[m, n] = sum_b 2^(sa[m,b]-127) 2^(sw[n,b]-127) sum_{i<32} qa[m,32b+i] qw[n,32b+i],  fp32 accumulation
  * (Section 3.2 eq. (2)); Kp % 32 == 0; codes 4-byte aligned.  Every such shape runs on the tiled /
- * weight-streaming kernels; 16-byte aligned codes and Kp % 128 == 0 are the fastest case on large M (by 1.25 to 1.45x), scale
+ * weight-streaming kernels; 16-byte aligned codes and Kp % 128 == 0 are the fastest case on large M (by 1.2 to 1.35x), scale
  * bytes whose base is not 4-byte aligned the slowest; y as in arcq_gemm.  No workspace (see arcq_mx_gemm_ws below).
  */
 arcq_status arcq_mx_packed_sizes(int64_t rows, int64_t K, int64_t S,

@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256) void gemm_direct_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Staged kernel for K' % 64 == 0.  Workgroup = GM x GN waves; each wave owns WM x WN MFMA tiles
+// Staged kernel.  Workgroup = GM x GN waves; each wave owns WM x WN MFMA tiles
 // of 32 x 32, so the workgroup tile is BM x BN = 32 WM GM x 32 WN GN.  With 4 waves (one per
 // SIMD, up to 256 accumulator registers) the hand-made schedule has to hide every stall.  8 waves
 // (two per SIMD, 128 accumulator registers each, <2,4,4,2> / <4,2,2,4>) let the hardware interleave
@@ -843,10 +843,9 @@ arcq_status launch_kpair(const uint8_t* a_codes, const uint8_t* a_scales, const 
 // load 16 x 64 contiguous bytes.  Rows of the activation operand past M repeat row M-1 and are
 // not stored.
 //
-// Everything is loaded straight into registers, U chunks at a time, and latency is hidden by
-// occupancy (about 64 registers per lane, so more than twenty waves per CU) rather than by
-// prefetching: variants that staged the activations and scale bytes in LDS or double-buffered
-// the weight stream in registers measured 1.4-1.6x slower at the decode shapes.  Every wave
+// Everything is loaded straight into registers, U chunks or a group of four at a time: variants that staged the
+// activations and scale bytes in LDS, or kept a second set of registers for the next group of the weight stream, measured
+// 1.4-1.6x slower at the decode shapes (what loads ahead below reuses the registers of chunks that have been decoded).  Every wave
 // handles NT tiles of 16 weight rows for the same chunks, which shares the loads and the decode
 // of the activation operand; the WAVES waves of a workgroup split K' (wave w takes chunks
 // w*U .. w*U+U-1, then strides on) and add their partial tiles through LDS at the end.
@@ -1345,9 +1344,10 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
         return launch_staged<2, 2, 2, 4>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, y, ldy, stream);
     }
     if (plan.kernel == ARCQ_ROUTE_TILES && nbk >= ScaleWindows<128, 128, 256, 8>::MIN_NB && dword_scales) {
-        // Any K' from 256 on, codes that are only 8-byte aligned: the same tiles by the same rule, 1 to 5 % slower than with
-        // whole aligned rows (S = 272 against S = 256, and through registers: 4096 x 8192 over K = 8192 434, 419 and 581 us;
-        // 2048 x 4096 over K = 4096 69.2, 65.2 and 79.4 us; 512 x 10240 over K = 8192 98.1, 93.7 and 112.8 us)
+        // Any K' from 256 on, codes that are only 8-byte aligned: the same tiles by the same rule, 3 to 10 % slower than with
+        // whole aligned rows (S = 272 against S = 256, weights from HBM, one card: 8192 x 8192 over K = 28928 3037 and 2954 us, 4096 x
+        // 8192 over 8192 461 and 444, 2048 x 4096 over 4096 74.1 and 69.4, 512 x 10240 over 8192 110 and 99;
+        // through registers 1.15 to 1.35 times as long as with whole rows)
         ARCQ_TILES(3, 2, RAGGED);
         ARCQ_TILES(4, 4, RAGGED);
         ARCQ_TILES(3, 4, RAGGED);

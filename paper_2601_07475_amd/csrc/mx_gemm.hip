@@ -29,7 +29,7 @@ __device__ __forceinline__ float16v mfma_mx(const uint4& a, const uint4& b, cons
                   : __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va, vb, c, 4, 4, 2, sa, 2, sb);
 }
 
-// Staged kernel for K' % 128 == 0.  A unit is 256 k: per row 128 bytes of codes (eight 16-byte pieces =
+// Staged kernel.  A unit is 256 k: per row 128 bytes of codes (eight 16-byte pieces =
 // eight MX blocks) and 8 scale bytes, so that a copy instruction asks for whole 128-byte cache lines
 // (8 lanes per row): the texture-address unit of a CU spends about 34 cycles on a copy that touches
 // sixteen 64-byte segments and 17.5 on one that touches eight full lines (measured), and with FP4
@@ -41,7 +41,7 @@ __device__ __forceinline__ float16v mfma_mx(const uint4& a, const uint4& b, cons
 // 64 banks, rows are 128 bytes apart, so 16 consecutive rows must land on 16 different 16-byte bank groups
 // (measured: a swizzle with a period of 8 rows spent 44 % of its LDS cycles on bank conflicts); applied by
 // choosing which global piece a lane fetches (a wave-wide copy writes lane l to base + 16 l).
-// When K' is an odd multiple of 128 the last unit is half a unit: its copies re-fetch the first half
+// With the copies of whole rows (COPIES, below) and K' an odd multiple of 128 the last unit is half a unit: its copies re-fetch the first half
 // for the missing second half (never used, in bounds).
 // BF16: the same skeleton for plain bf16 operands (the comparison kernel arcq_ref_gemm_bf16): a row of a unit is 128
 // bytes = 64 bf16 values, there are no scale bytes, and a k-step is one v_mfma_f32_32x32x16_bf16.
@@ -244,8 +244,8 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     // as every wave has its last fragments of the unit in registers: the fragments of k-steps 1 and 2 are read at the
     // start of the unit, those of k-step 3 at the start of k-step 2 (into the set of k-step 1), and a second barrier at
     // FREE_Q hands the slot over.  The copies then have 64 + 56 - 38 = 82 of the MFMA slots of a 256 x 256 unit to land;
-    // issued behind the barrier that opens the next unit they had 36 to 56, less than the 68 KB of a unit take at the
-    // rate the L2 delivers, and every unit waited for them.
+    // issued behind the barrier that opens the next unit they had 36 to 56 (8192 x 8192 over K' = 29696 972 -> 944 us, 1777 x
+    // 10240 over 8576 129 -> 118, 4096 x 27648 over 5632 1.00 to 1.02 times as fast: the wait for copies is not all that bounds it).
     constexpr int NM = WM * WN;               // MFMAs per k-step
     constexpr int DIST = C::NUNIT - 1;
     int buf = 0;
