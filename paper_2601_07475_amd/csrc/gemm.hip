@@ -17,6 +17,7 @@
 #include "gemm_epilogue.h"
 #include "lds_dma.h"
 #include "scale_windows.h"
+#include "tile_order.h"
 
 #include <hip/hip_fp16.h>
 
@@ -201,24 +202,14 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
     constexpr bool REG = MODE == REGS, RAG = MODE == RAGGED;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
-    // ---- workgroup -> tile.  Workgroups are dealt round-robin to the 8 XCDs (each with its
-    // own L2); give every XCD a contiguous run of the tile sequence, and walk the sequence in
-    // column-major groups of 8 tile rows so that concurrently running tiles share A and W rows.
+    // ---- workgroup -> tile: tile_order.h
     // With splits > 1 the reduction dimension is cut into `splits` runs of whole stages: workgroup
     // blockIdx.x = split * num_tiles + tile accumulates its run and stores an fp32 partial tile at
     // y + split * split_stride (a reduction kernel adds the partial results).
     const int num_tiles = tiles_m * tiles_n;
     const int split = (int)blockIdx.x / num_tiles;
-    int pid = (int)blockIdx.x - split * num_tiles;
-    if ((num_tiles & 7) == 0) pid = (pid & 7) * (num_tiles >> 3) + (pid >> 3);
-    constexpr int GROUP = 8;
-    const int group_size = GROUP * tiles_n;
-    const int g = pid / group_size;
-    const int first_m = g * GROUP;
-    const int gm = min(GROUP, tiles_m - first_m);
-    const int in_g = pid - g * group_size;
-    const int tile_m = first_m + in_g % gm;
-    const int tile_n = in_g / gm;
+    const TileOrder tile((int)blockIdx.x - split * num_tiles, tiles_m, tiles_n);
+    const int tile_m = tile.m, tile_n = tile.n;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -535,18 +526,9 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     constexpr int WM = 2, WN = 4;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
-    // workgroup -> tile as in gemm_staged_kernel
-    const int num_tiles = tiles_m * tiles_n;
-    int pid = (int)blockIdx.x;
-    if ((num_tiles & 7) == 0) pid = (pid & 7) * (num_tiles >> 3) + (pid >> 3);
-    constexpr int GROUP = 8;
-    const int group_size = GROUP * tiles_n;
-    const int g = pid / group_size;
-    const int first_m = g * GROUP;
-    const int gm = min(GROUP, tiles_m - first_m);
-    const int in_g = pid - g * group_size;
-    const int tile_m = first_m + in_g % gm;
-    const int tile_n = in_g / gm;
+    // workgroup -> tile: tile_order.h
+    const TileOrder tile((int)blockIdx.x, tiles_m, tiles_n);
+    const int tile_m = tile.m, tile_n = tile.n;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;

@@ -18,6 +18,7 @@
 #include "gemm_epilogue.h"
 #include "lds_dma.h"
 #include "scale_windows.h"
+#include "tile_order.h"
 
 #include <type_traits>
 
@@ -94,19 +95,9 @@ __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
     constexpr bool REG = MODE == REGS, RAG = MODE == RAGGED;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
-    // workgroup -> tile: workgroups are dealt round-robin to the 8 XCDs (each with its own L2); every XCD gets a
-    // contiguous run of the tile sequence, walked in column-major groups of 8 tile rows
-    const int num_tiles = tiles_m * tiles_n;
-    int pid = (int)blockIdx.x;
-    if ((num_tiles & 7) == 0) pid = (pid & 7) * (num_tiles >> 3) + (pid >> 3);
-    constexpr int GROUP = 8;
-    const int group_size = GROUP * tiles_n;
-    const int g = pid / group_size;
-    const int first_m = g * GROUP;
-    const int gm = min(GROUP, tiles_m - first_m);
-    const int in_g = pid - g * group_size;
-    const int tile_m = first_m + in_g % gm;
-    const int tile_n = in_g / gm;
+    // workgroup -> tile: tile_order.h
+    const TileOrder tile((int)blockIdx.x, tiles_m, tiles_n);
+    const int tile_m = tile.m, tile_n = tile.n;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;

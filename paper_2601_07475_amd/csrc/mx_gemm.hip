@@ -12,6 +12,7 @@
 #include "gemm_decode.h"
 #include "lds_dma.h"
 #include "scale_windows.h"
+#include "tile_order.h"
 
 #include <type_traits>
 
@@ -87,22 +88,14 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     constexpr bool REG = MODE == REGS, RAG = MODE == RAGGED;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
-    // workgroup -> tile: a contiguous run of the tile sequence per XCD, column-major groups of 8 tile rows
+    // workgroup -> tile: tile_order.h
     // With splits > 1 the units of the reduction dimension are cut into `splits` runs: workgroup
     // blockIdx.x = split * num_tiles + tile accumulates its run and stores an fp32 partial tile at
     // y + split * split_stride (a reduction kernel adds the partial results in index order).
     const int num_tiles = tiles_m * tiles_n;
     const int split = (int)blockIdx.x / num_tiles;
-    int pid = (int)blockIdx.x - split * num_tiles;
-    if ((num_tiles & 7) == 0) pid = (pid & 7) * (num_tiles >> 3) + (pid >> 3);
-    constexpr int GROUP = 8;
-    const int group_size = GROUP * tiles_n;
-    const int g = pid / group_size;
-    const int first_m = g * GROUP;
-    const int gm = min(GROUP, tiles_m - first_m);
-    const int in_g = pid - g * group_size;
-    const int tile_m = first_m + in_g % gm;
-    const int tile_n = in_g / gm;
+    const TileOrder tile((int)blockIdx.x - split * num_tiles, tiles_m, tiles_n);
+    const int tile_m = tile.m, tile_n = tile.n;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = lane & 31, h = lane >> 5;
