@@ -390,9 +390,10 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
         }
     };
 
-    // The steady-state stage is free of branches (they would split the hand-made schedule):
-    // past the end of K' it keeps issuing copies (of the last stage, into a free ring slot) and
-    // keeps reading and decoding a "next" stage whose values are never used.
+    // A stage is free of branches (they would split the hand-made schedule): the last two stages of a workgroup's run have code of
+    // their own (left_tag: stages behind this one, up to DIST = 2), which issues no copies and, in the last one, reads and decodes
+    // nothing for a next stage.  (Both used to go on with the last stage, whose copies the end of the kernel then waited for: 1 % of
+    // the time on average over 200 problems of 513 to 8192 rows, 0.2 us a round; 2048 x 4096 over K' = 4352 with norm 72.6 -> 71.5 us.)
     int buf = 0;                                // ring slot of the stage being computed
     auto ring_next = [](int b) { return b == C::NSTAGE - 1 ? 0 : b + 1; };
     // RAGGED: the wanted scale bytes of stage s+1 are picked out of their windows during step FIX (read) and the one after
@@ -401,45 +402,47 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
     constexpr int FIX = 3;
     auto copies_before = [](int x) { return (x * C::NDMA + 5) / 6; };    // copies of a stage issued before step x <= 6
     uint3 win[RAG ? 2 : 1];
-    auto run_stage = [&](int s, auto nsteps_tag, auto tail_tag) {
-        constexpr int NSTEPS = decltype(nsteps_tag)::value;
+    auto run_stage = [&](int s, auto tail_tag, auto left_tag) {
         constexpr bool TAIL = decltype(tail_tag)::value;
-        constexpr bool FULL = NSTEPS == 8;      // a half stage is always the last one
+        constexpr int LEFT = decltype(left_tag)::value;
         const uint8_t* st = lds + buf * C::STAGE_BYTES;
         // the copies issued during this stage go to the slot of the stage computed before this one
         const int buf1 = ring_next(buf), buf2 = buf == 0 ? C::NSTAGE - 1 : buf - 1;
-        const int fetch = min(s + C::DIST, s_end - 1);
+        int fetch = s + C::DIST;        // opaque: followed as an induction variable it costs the copies 14 more additions a stage
+        asm("" : "+s"(fetch));
 #pragma unroll
-        for (int x = 0; x < NSTEPS; ++x) {
-            if (x == 0 && FULL) read_raw(1, st);
-            if constexpr (RAG) {
+        for (int x = 0; x < 8; ++x) {
+            // (a half stage leaves here; with code of its own, beside that of a whole last stage, the accumulators spill)
+            if (LEFT == 0 && x == 4 && has_half && s == nstage - 1) break;
+            if (x == 0) read_raw(1, st);
+            if constexpr (RAG && LEFT > 0) {
                 uint8_t* next = lds + buf1 * C::STAGE_BYTES;
                 if (x >= FIX && x < FIX + C::NSW) {
                     // windows of stage s+1: the code copies of that stage and the copies issued in this one are younger
-                    if (x == FIX) wait_vmcnt<C::NA + C::NW + (FIX * C::NDMA + 5) / 6>();
-                    win[(x - FIX) & 1] = windows.gather(x - FIX, next + C::WINDOWS, TAIL, lds + C::PATCH + 8 * (s + 1 - patch_from));
+                    if (x == FIX) wait_vmcnt<C::NA + C::NW + (LEFT == 2 ? (FIX * C::NDMA + 5) / 6 : 0)>();
+                    win[(x - FIX) & 1] = windows.gather(x - FIX, next + C::WINDOWS, TAIL && s + 1 >= patch_from, lds + C::PATCH + 8 * (s + 1 - patch_from));
                 }
                 if (x > FIX && x <= FIX + C::NSW)
                     windows.template put<true>(x - FIX - 1, win[(x - FIX - 1) & 1], next + C::A_SCALES, TAIL, s + 1);
             }
-            if (x == 6) {
+            if (x == 6 && LEFT > 0) {
                 // stage s+1 must have landed: the copies of the DIST - 1 later stages are younger, and
                 // everything older has retired once at most that many operations are outstanding
                 // (REGS: this wave's LDS writes of stage s+1 must have completed)
                 if constexpr (REG) wait_lgkmcnt0();
-                else wait_vmcnt<(C::DIST - 1) * C::NDMA>();
+                else wait_vmcnt<LEFT == 2 ? (C::DIST - 1) * C::NDMA : 0>();
                 if constexpr (RAG) wait_lgkmcnt0();         // this wave's scale bytes of stage s+1 are written
                 wg_barrier();
                 read_raw(0, lds + buf1 * C::STAGE_BYTES);
-                if constexpr (REG) reg_issue(min(s + 2, s_end - 1));
+                if constexpr (REG && LEFT == 2) reg_issue(s + 2);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int p = 0; p < P; ++p) {
 #pragma unroll
                 for (int gidx = (p * G) / P; gidx < ((p + 1) * G) / P; ++gidx) {
-                    if (x + 1 < NSTEPS) decode_frag(gidx, x + 1);
-                    else if (FULL) decode_frag(gidx, 0);          // first step of stage s+1
+                    if (x + 1 < 8) decode_frag(gidx, x + 1);
+                    else if (LEFT > 0) decode_frag(gidx, 0);      // first step of stage s+1
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -449,16 +452,16 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[x & 1][j], fa[x & 1][i], acc[i][j], 0, 0, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                if (!REG && FULL && x < 6) {    // copies of stage s + NSTAGE - 1, spread over steps 0..5
+                if (!REG && LEFT == 2 && x < 6) {    // copies of stage s + NSTAGE - 1, spread over steps 0..5
 #pragma unroll
                     for (int d = 0; d < C::NDMA; ++d)
                         if ((d * 6) / C::NDMA == x && d - copies_before(x) == p) issue_one(d, fetch, buf2);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            if constexpr (REG)
+            if constexpr (REG && LEFT > 0)
                 if (x == 5) {                   // stage s+1, fetched since step 6 of the stage before
-                    reg_commit(min(s + 1, s_end - 1), buf1);
+                    reg_commit(s + 1, buf1);
                     __builtin_amdgcn_sched_barrier(0);
                 }
         }
@@ -486,12 +489,13 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
     read_raw(0, lds);
 #pragma unroll
     for (int gidx = 0; gidx < G; ++gidx) decode_frag(gidx, 0);
-    const int nfull = MODE != COPIES ? nstage : nbk >> 3;
+    using Rag = std::integral_constant<bool, RAG>;
     int s = s_begin;
+    for (; s < (RAG ? min(patch_from - 1, s_end - 2) : s_end - 2); ++s) run_stage(s, std::false_type{}, std::integral_constant<int, 2>{});
     if constexpr (RAG)
-        for (; s < min(s_end, patch_from - 1); ++s) run_stage(s, std::integral_constant<int, 8>{}, std::false_type{});
-    for (; s < min(s_end, nfull); ++s) run_stage(s, std::integral_constant<int, 8>{}, std::integral_constant<bool, RAG>{});
-    if (has_half && s_end == nstage) run_stage(nfull, std::integral_constant<int, 4>{}, std::false_type{});
+        for (; s < s_end - 2; ++s) run_stage(s, std::true_type{}, std::integral_constant<int, 2>{});
+    if (s_end - s_begin > 1) run_stage(s_end - 2, Rag{}, std::integral_constant<int, 1>{});
+    run_stage(s_end - 1, std::false_type{}, std::integral_constant<int, 0>{});
     wait_vmcnt<0>();                            // no copy may still be in flight when the LDS is released
 
     const int m0 = wg_m0 + wrow0, n0 = wg_n0 + wcol0;
@@ -632,16 +636,18 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     int buf = 0;
     auto ring_next = [](int b) { return b == C::NSTAGE - 1 ? 0 : b + 1; };
     uint3 win[RAG ? C::NSW : 1];
-    auto run_stage = [&](int s, auto tail_tag) {    // tail_tag: see gemm_staged_kernel
+    auto run_stage = [&](int s, auto tail_tag, auto left_tag) {     // tags: see gemm_staged_kernel
         constexpr bool TAIL = decltype(tail_tag)::value;
+        constexpr int LEFT = decltype(left_tag)::value;
         const int buf1 = ring_next(buf), buf2 = buf == 0 ? C::NSTAGE - 1 : buf - 1;
-        const int fetch = min(s + C::DIST, nstage - 1);
+        int fetch = s + C::DIST;        // opaque: followed as an induction variable it costs the copies 14 more additions a stage
+        asm("" : "+s"(fetch));
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            if constexpr (RAG) {                // scale bytes of stage s+1, see gemm_staged_kernel
+            if constexpr (RAG && LEFT > 0) {    // scale bytes of stage s+1, see gemm_staged_kernel
                 uint8_t* next = lds + buf1 * C::STAGE_BYTES;
                 if (t == 1) {
-                    wait_vmcnt<C::NA + C::NW + (C::NDMA + 2) / 3>();
+                    wait_vmcnt<C::NA + C::NW + (LEFT == 2 ? (C::NDMA + 2) / 3 : 0)>();
 #pragma unroll
                     for (int d = 0; d < C::NSW; ++d)
                         win[d] = windows.gather(d, next + C::WINDOWS, TAIL, lds + C::PATCH + 8 * (s + 1 - patch_from));
@@ -650,8 +656,8 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
 #pragma unroll
                     for (int d = 0; d < C::NSW; ++d) windows.template put<true>(d, win[d], next + C::A_SCALES, TAIL, s + 1);
             }
-            if (t == 3) {
-                wait_vmcnt<(C::DIST - 1) * C::NDMA>();
+            if (t == 3 && LEFT > 0) {
+                wait_vmcnt<LEFT == 2 ? (C::DIST - 1) * C::NDMA : 0>();
                 if constexpr (RAG) wait_lgkmcnt0();
                 wg_barrier();
                 read_raw(lds + buf1 * C::STAGE_BYTES);
@@ -660,13 +666,14 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
 #pragma unroll
             for (int p = 0; p < P; ++p) {
 #pragma unroll
-                for (int gidx = (p * G) / P; gidx < ((p + 1) * G) / P; ++gidx) decode_frag(gidx, (t + 1) & 3);
+                for (int gidx = (p * G) / P; gidx < ((p + 1) * G) / P; ++gidx)
+                    if (t < 3 || LEFT > 0) decode_frag(gidx, (t + 1) & 3);
                 __builtin_amdgcn_sched_barrier(0);
                 const int i = p / WN, j = p % WN;
                 // weights as the row operand: see store_tile_swapped
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[t & 1][j], fa[t & 1][i], acc[i][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                if (t < 3) {
+                if (t < 3 && LEFT == 2) {
 #pragma unroll
                     for (int d = 0; d < C::NDMA; ++d)
                         if ((d * 3) / C::NDMA == t && (d - (t * C::NDMA + 2) / 3) == p) issue_one(d, fetch, buf2);
@@ -693,10 +700,13 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     read_raw(lds);
 #pragma unroll
     for (int gidx = 0; gidx < G; ++gidx) decode_frag(gidx, 0);
+    using Rag = std::integral_constant<bool, RAG>;
     int s = 0;
-    for (; s < (RAG ? patch_from - 1 : nstage); ++s) run_stage(s, std::false_type{});
+    for (; s < (RAG ? min(patch_from - 1, nstage - 2) : nstage - 2); ++s) run_stage(s, std::false_type{}, std::integral_constant<int, 2>{});
     if constexpr (RAG)
-        for (; s < nstage; ++s) run_stage(s, std::true_type{});
+        for (; s < nstage - 2; ++s) run_stage(s, std::true_type{}, std::integral_constant<int, 2>{});
+    if (nstage > 1) run_stage(nstage - 2, Rag{}, std::integral_constant<int, 1>{});
+    run_stage(nstage - 1, std::false_type{}, std::integral_constant<int, 0>{});
     wait_vmcnt<0>();                            // no copy may still be in flight when the LDS is released
 
     // ---- the pair adds its partial tiles: in two rounds (columns 0-63, 64-127 of the sub-tile) every wave

@@ -244,26 +244,32 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     int buf = 0;
     // RAGGED: the wanted scale bytes of unit u+1 are picked out of their windows at the start of k-step 1 (read) and in the
     // middle of it (write).  tail_tag: 1: unit u+1 is the last or the one before, whose windows or blocks may pass the end;
-    // 2: unit u is the last and has missing blocks: k-steps past the end are left out, codes past it are zeroed, nothing is
-    // copied or read for a next unit.
+    // 2: unit u is the last and may have missing blocks: k-steps past the end are left out, codes past it are zeroed.
+    // left_tag: units behind this one, up to 2: the last two units of a workgroup's run have code of their own, which copies
+    // nothing and, in the last one, reads nothing for a next unit.  (Both used to copy the last unit once more, and the end of the
+    // kernel waited for that: 1.0 % of the time on average over 200 problems of 513 to 8192 rows, 1500 x 14336 over K' = 4320 with the
+    // quantizer 85.6 -> 84.2 us.)
     uint3 win[RAG ? C::NSW : 1];
-    auto run_unit = [&](int u, auto nsteps_tag, auto tail_tag) {
-        constexpr int NSTEPS = decltype(nsteps_tag)::value;
+    auto run_unit = [&](int u, auto tail_tag, auto left_tag) {
+        constexpr int NSTEPS = 4;
         constexpr int TAIL = decltype(tail_tag)::value;
+        constexpr int LEFT = decltype(left_tag)::value;
         constexpr int LAST_Q = NSTEPS * NM - NM / 2;
         constexpr int COMMIT_Q = LAST_Q - NM / 2;     // REGS: the pieces of unit u+1 go to LDS half a k-step before its barrier
         constexpr int FREE_Q = 2 * NM + (3 * NM) / 8; // EARLY: every fragment of the unit is in registers
         const uint8_t* st = lds + buf * C::UNIT_BYTES;
         const int buf1 = buf + 1 == C::NUNIT ? 0 : buf + 1, bufd = EARLY ? buf : buf == 0 ? C::NUNIT - 1 : buf - 1;
-        const int fetch = min(u + (EARLY ? 2 : DIST), nunit - 1);
+        int fetch = u + 2;              // opaque: followed as an induction variable it costs the copies 17 more additions a unit
+        asm("" : "+s"(fetch));
 #pragma unroll
         for (int t = 0; t < NSTEPS; ++t) {
             if (TAIL == 2 && 8 * u + 2 * t >= nb) break;
+            if (LEFT == 0 && t == 2 && has_half && u == nunit - 1) break;       // half a unit
             const int set = !EARLY ? t & 1 : t == 3 ? 1 : t;
             if constexpr (EARLY) {
                 if (t == 0) {
                     read_codes(1, 1, st);
-                    if (NSTEPS == 4) read_codes(2, 2, st);
+                    read_codes(2, 2, st);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (t == 2) {
@@ -283,15 +289,15 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
 #pragma unroll
                 for (int j = 0; j < WN; ++j) {
                     const int q = t * NM + i * WN + j;
-                    if constexpr (RAG && TAIL < 2) {
+                    if constexpr (RAG && LEFT > 0) {
                         uint8_t* next = lds + buf1 * C::UNIT_BYTES;
                         if (q == NM) {
                             // windows of unit u+1: younger are the code copies of that unit and (three ring slots) the
                             // copies of unit u+2 issued so far
-                            wait_vmcnt<C::NA + C::NW + (EARLY ? 0 : C::NDMA < NM ? C::NDMA : NM)>();
+                            wait_vmcnt<C::NA + C::NW + (EARLY || LEFT < 2 ? 0 : C::NDMA < NM ? C::NDMA : NM)>();
 #pragma unroll
                             for (int d = 0; d < C::NSW; ++d)
-                                win[d] = windows.gather(d, next + C::WINDOWS, TAIL == 1, lds + C::PATCH + 8 * (u + 1 - patch_from));
+                                win[d] = windows.gather(d, next + C::WINDOWS, TAIL == 1 && u + 1 >= patch_from, lds + C::PATCH + 8 * (u + 1 - patch_from));
                             __builtin_amdgcn_sched_barrier(0);
                         }
                         if (q == NM + NM / 2) {
@@ -301,24 +307,24 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
                             __builtin_amdgcn_sched_barrier(0);
                         }
                     }
-                    if (REG && q == COMMIT_Q) {
-                        reg_commit(min(u + 1, nunit - 1), buf1);
+                    if (REG && LEFT > 0 && q == COMMIT_Q) {
+                        reg_commit(u + 1, buf1);
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    if (EARLY && NSTEPS == 4 && TAIL < 2 && q == FREE_Q) {
+                    if (EARLY && LEFT == 2 && q == FREE_Q) {
                         wait_lgkmcnt0();
                         wg_barrier();
                     }
-                    if (q == LAST_Q && TAIL < 2 && !(EARLY && NSTEPS < 4)) {
+                    if (q == LAST_Q && LEFT > 0) {
                         // unit u+1 must have landed: the copies of the DIST - 1 later units (EARLY: of unit u+2) are younger
                         // (REGS: this wave's LDS writes of unit u+1 must have completed)
                         if constexpr (REG) wait_lgkmcnt0();
-                        else wait_vmcnt<(EARLY ? 1 : DIST - 1) * C::NDMA>();
+                        else wait_vmcnt<LEFT == 2 ? C::NDMA : 0>();
                         if constexpr (RAG) wait_lgkmcnt0();         // this wave's scale bytes of unit u+1 are written
                         wg_barrier();
                         read_codes(0, 0, lds + buf1 * C::UNIT_BYTES);
                         read_scales(lds + buf1 * C::UNIT_BYTES, sa_n, sw_n);
-                        if constexpr (REG) reg_issue(min(u + 2, nunit - 1));
+                        if constexpr (REG && LEFT == 2) reg_issue(u + 2);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     // weights as the row operand: see store_tile_swapped
@@ -331,19 +337,19 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
                     __builtin_amdgcn_sched_barrier(0);
                     if constexpr (EARLY) {
                         constexpr int E = LAST_Q - FREE_Q;      // the MFMA slots that the copies of unit u + 2 are spread over
-                        if (NSTEPS == 4 && TAIL < 2 && q >= FREE_Q && q < LAST_Q) {
+                        if (LEFT == 2 && q >= FREE_Q && q < LAST_Q) {
 #pragma unroll
                             for (int d = 0; d < C::NDMA; ++d)
                                 if (d * E / C::NDMA == q - FREE_Q) issue_one(d, fetch, bufd);
                             __builtin_amdgcn_sched_barrier(0);
                         }
-                    } else if (!REG && NSTEPS == 4 && TAIL < 2 && q < C::NDMA) {
+                    } else if (!REG && LEFT == 2 && q < C::NDMA) {
                         issue_one(q, fetch, bufd);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
         }
-        if constexpr (!BF16) {
+        if constexpr (!BF16 && LEFT > 0) {
 #pragma unroll
             for (int i = 0; i < WM; ++i) sa[i] = sa_n[i];
 #pragma unroll
@@ -353,7 +359,7 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     };
     static_assert(C::NDMA <= 3 * NM, "copies are issued during the first three k-steps of a unit");
 
-    // this workgroup's run of units [u0, u1); copies past the run fetch units the run never uses (in bounds)
+    // this workgroup's run of units [u0, u1)
     const int u0 = (int)((int64_t)split * nunit / splits), u1 = (int)((int64_t)(split + 1) * nunit / splits);
     if constexpr (REG) {
         reg_issue(u0);
@@ -383,16 +389,18 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     wg_barrier();
     read_codes(0, 0, lds);
     read_scales(lds, sa, sw);
-    using Steps4 = std::integral_constant<int, 4>;
+    using Tag0 = std::integral_constant<int, 0>;
+    using Tag1 = std::integral_constant<int, 1>;
+    using Tag2 = std::integral_constant<int, 2>;
     int u = u0;
+    for (; u < (RAG ? min(patch_from - 1, u1 - 2) : u1 - 2); ++u) run_unit(u, Tag0{}, Tag2{});
     if constexpr (RAG) {
-        for (; u < min(u1, patch_from - 1); ++u) run_unit(u, Steps4{}, std::integral_constant<int, 0>{});
-        for (; u < min(u1, nb >> 3); ++u) run_unit(u, Steps4{}, std::integral_constant<int, 1>{});
-        if (u < u1) run_unit(u, Steps4{}, std::integral_constant<int, 2>{});
+        for (; u < u1 - 2; ++u) run_unit(u, Tag1{}, Tag2{});
+        if (u1 - u0 > 1) run_unit(u1 - 2, Tag1{}, Tag1{});
+        run_unit(u1 - 1, Tag2{}, Tag0{});
     } else {
-        const int nfull = REG ? nunit : nb >> 3;
-        for (; u < min(u1, nfull); ++u) run_unit(u, Steps4{}, std::integral_constant<int, 0>{});
-        if (has_half && u1 == nunit) run_unit(nfull, std::integral_constant<int, 2>{}, std::integral_constant<int, 0>{});
+        if (u1 - u0 > 1) run_unit(u1 - 2, Tag0{}, Tag1{});
+        run_unit(u1 - 1, Tag0{}, Tag0{});
     }
     wait_vmcnt<0>();                            // no copy may still be in flight when the LDS is released
 
