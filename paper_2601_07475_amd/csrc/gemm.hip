@@ -502,12 +502,10 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
     if constexpr (std::is_same<OutT, _Float16>::value) {
         static_assert(epilogue_lds_bytes(WN) * GM * GN <= C::LDS_BYTES, "one epilogue region per wave must fit the operand ring");
         wg_barrier();                           // every wave has read its last operands: the ring is free
-        const bool vec_ok = (ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
         store_tile_f16_via_lds<WM, WN>(acc, lds + wave * epilogue_lds_bytes(WN), m0, n0, lane, M, N, alpha,
-                                       y + (int64_t)split * split_stride, ldy, vec_ok);
+                                       y + (int64_t)split * split_stride, ldy);
     } else {
-        const bool vec_ok = (ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
-        store_tile_swapped<WM, WN>(acc, m0, n0, r, h, M, N, alpha, y + (int64_t)split * split_stride, ldy, vec_ok);
+        store_tile_swapped<WM, WN>(acc, m0, n0, r, h, M, N, alpha, y + (int64_t)split * split_stride, ldy);
     }
 }
 
@@ -746,18 +744,16 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     wg_barrier();                               // every wave has read its partner's last round
     const int m0 = wg_m0 + wrow0, n0 = wg_n0 + wcol0;
     if constexpr (std::is_same<OutT, _Float16>::value) {
-        const bool vec_ok = (ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
         uint8_t* region = lds + wave * (epilogue_lds_bytes(WN) / 2);
         if (mine == 0)
-            store_fragment_rows_f16_via_lds<WM, WN, 0, 1>(acc, region, m0, n0, lane, M, N, alpha, y, ldy, vec_ok);
+            store_fragment_rows_f16_via_lds<WM, WN, 0, 1>(acc, region, m0, n0, lane, M, N, alpha, y, ldy);
         else
-            store_fragment_rows_f16_via_lds<WM, WN, 1, 1>(acc, region, m0, n0, lane, M, N, alpha, y, ldy, vec_ok);
+            store_fragment_rows_f16_via_lds<WM, WN, 1, 1>(acc, region, m0, n0, lane, M, N, alpha, y, ldy);
     } else {
-        const bool vec_ok = (ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
         if (mine == 0)
-            store_fragment_row_swapped<WM, WN, 0>(acc, m0, n0, r, h, M, N, alpha, y, ldy, vec_ok);
+            store_fragment_row_swapped<WM, WN, 0>(acc, m0, n0, r, h, M, N, alpha, y, ldy);
         else
-            store_fragment_row_swapped<WM, WN, 1>(acc, m0, n0, r, h, M, N, alpha, y, ldy, vec_ok);
+            store_fragment_row_swapped<WM, WN, 1>(acc, m0, n0, r, h, M, N, alpha, y, ldy);
     }
 }
 

@@ -62,7 +62,7 @@ struct KsplitCfg {
 // e holds column n0 + 8 (e / 4) + 4 (lane / 32) + e % 4.
 template <typename OutT>
 __device__ __forceinline__ void store_fragment(const float16v& a, int m0, int n0, int r, int h, int M, int N, float alpha,
-                                               OutT* __restrict__ y, int64_t ldy, bool vec_ok) {
+                                               OutT* __restrict__ y, int64_t ldy) {
     const int m = m0 + r;
     if (m >= M) return;
     OutT* yrow = y + (int64_t)m * ldy;
@@ -70,7 +70,7 @@ __device__ __forceinline__ void store_fragment(const float16v& a, int m0, int n0
     for (int g = 0; g < 4; ++g) {
         const int n = n0 + 8 * g + 4 * h;
         const float v0 = a[4 * g] * alpha, v1 = a[4 * g + 1] * alpha, v2 = a[4 * g + 2] * alpha, v3 = a[4 * g + 3] * alpha;
-        if (vec_ok && n + 3 < N) {
+        if (n + 3 < N) {
             store4(yrow + n, v0, v1, v2, v3);
         } else {
             if (n < N) store_out(yrow + n, v0);
@@ -391,11 +391,9 @@ __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
             }
     }
     const int m0 = wg_m0 + wrow0, n0 = wg_n0 + wcol0;
-    const bool vec_ok = (ldy & (std::is_same<OutT, _Float16>::value ? 3 : 3)) == 0 &&
-                        (reinterpret_cast<uintptr_t>(y) & (std::is_same<OutT, _Float16>::value ? 7 : 15)) == 0;
 #pragma unroll
     for (int f = 0; f < WM * WN; ++f)
-        if (f % KS == kh) store_fragment(acc[f / WN][f % WN], m0 + 32 * (f / WN), n0 + 32 * (f % WN), r, h, M, N, alpha, y, ldy, vec_ok);
+        if (f % KS == kh) store_fragment(acc[f / WN][f % WN], m0 + 32 * (f / WN), n0 + 32 * (f % WN), r, h, M, N, alpha, y, ldy);
 }
 
 template <int WM, int WN, int GM, int GN, int KS, int MODE, typename OutT>

@@ -408,11 +408,9 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     if constexpr (std::is_same<OutT, _Float16>::value) {
         static_assert(epilogue_lds_bytes(WN) * GM * GN <= C::LDS_BYTES, "one epilogue region per wave must fit the operand ring");
         wg_barrier();                           // every wave has read its last operands: the ring is free
-        const bool vec_ok = (ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
-        store_tile_f16_via_lds<WM, WN>(acc, lds + wave * epilogue_lds_bytes(WN), m0, n0, lane, M, N, 1.0f, y, ldy, vec_ok);
+        store_tile_f16_via_lds<WM, WN>(acc, lds + wave * epilogue_lds_bytes(WN), m0, n0, lane, M, N, 1.0f, y, ldy);
     } else {
-        const bool vec_ok = (ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
-        store_tile_swapped<WM, WN>(acc, m0, n0, r, h, M, N, 1.0f, y + (int64_t)split * split_stride, ldy, vec_ok);
+        store_tile_swapped<WM, WN>(acc, m0, n0, r, h, M, N, 1.0f, y + (int64_t)split * split_stride, ldy);
     }
 }
 
@@ -465,7 +463,7 @@ __global__ __launch_bounds__(256) void mx_gemm_direct_kernel(
 #pragma unroll
             for (int j = 0; j < 2; ++j) acc[i][j] = mfma_mx(fw[j], fa[i], acc[i][j], sw[j], sa[i], 0);
     }
-    store_tile_swapped<2, 2>(acc, m0, n0, r, h, M, N, 1.0f, y, ldy, false);
+    store_tile_swapped<2, 2>(acc, m0, n0, r, h, M, N, 1.0f, y, ldy);
 }
 
 // Weight-streaming kernel for M <= 64 (decode, batched decode), any K' (a multiple of 32): bound by
