@@ -55,6 +55,15 @@ typedef struct {
 } arcq_route;
 arcq_status arcq_gemm_route(int64_t M, int64_t N, int64_t Kp, arcq_route* route);
 arcq_status arcq_mx_gemm_route(int64_t M, int64_t N, int64_t Kp, int with_workspace, arcq_route* route);
+/*
+ * Problems whose last round of tiles would leave much of the chip idle run in two launches: the route above for whole rounds, and
+ * this one for the last `rows` x `cols` of the output (0 x 0: there is no second launch; else one of the two is M or N).
+ */
+typedef struct {
+    int64_t rows, cols;
+    arcq_route route;
+} arcq_rest;
+arcq_status arcq_gemm_rest(int64_t M, int64_t N, int64_t Kp, arcq_rest* rest);
 
 #ifdef __cplusplus
 }

@@ -24,6 +24,11 @@ class Route(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int32) for n in ("kernel", "tile_rows", "tile_cols", "runs", "ahead")]
 
 
+class Rest(ctypes.Structure):
+    """arcq_rest of arcq_bench.h."""
+    _fields_ = [("rows", ctypes.c_int64), ("cols", ctypes.c_int64), ("route", Route)]
+
+
 # every symbol include/arcq.h and include/arcq_bench.h declare: name -> (restype, argtypes)
 _i64, _f32, _vp, _sz, _u32 = ctypes.c_int64, ctypes.c_float, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_uint32
 SIGNATURES = {
@@ -55,6 +60,7 @@ SIGNATURES = {
     "arcq_ref_gemm_bf16": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _vp, _i64, _vp]),
     "arcq_gemm_route": (ctypes.c_int, [_i64, _i64, _i64, ctypes.POINTER(Route)]),
     "arcq_mx_gemm_route": (ctypes.c_int, [_i64, _i64, _i64, ctypes.c_int, ctypes.POINTER(Route)]),
+    "arcq_gemm_rest": (ctypes.c_int, [_i64, _i64, _i64, ctypes.POINTER(Rest)]),
     "arcq_check_perm": (ctypes.c_int, [_vp, _i64, _vp, ctypes.POINTER(ctypes.c_int), _vp]),
 }
 
@@ -410,6 +416,13 @@ def arcq_gemm_route(M, N, Kp):
     r = Route()
     _check(lib().arcq_gemm_route(M, N, Kp, ctypes.byref(r)))
     return r.kernel, r.tile_rows, r.tile_cols, r.runs, r.ahead
+
+
+def arcq_gemm_rest(M, N, Kp):
+    """(rows, columns, (kernel, tile rows, tile columns)) of arcq_gemm's second launch, the last of the output; None: there is none."""
+    r = Rest()
+    _check(lib().arcq_gemm_rest(M, N, Kp, ctypes.byref(r)))
+    return (r.rows, r.cols, (r.route.kernel, r.route.tile_rows, r.route.tile_cols)) if r.rows else None
 
 
 def arcq_mx_gemm_route(M, N, Kp, with_workspace=False):

@@ -205,6 +205,17 @@ arcq_status arcq_gemm_route(int64_t M, int64_t N, int64_t Kp, arcq_route* route)
     return fill_route(plan_gemm(M, N, Kp), route);
 }
 
+arcq_status arcq_gemm_rest(int64_t M, int64_t N, int64_t Kp, arcq_rest* rest) {
+    clear_error();
+    if (arcq_status st = check_gemm_shape(M, N, Kp)) return st;
+    if (!rest) return fail(ARCQ_INVALID_ARG, "null output pointer");
+    const GemmParts parts = plan_gemm_parts(M, N, Kp);
+    const bool two = parts.rows < M || parts.cols < N;
+    rest->rows = !two ? 0 : parts.rows < M ? M - parts.rows : M;
+    rest->cols = !two ? 0 : parts.cols < N ? N - parts.cols : N;
+    return fill_route(parts.rest, &rest->route);
+}
+
 // Validation shared by arcq_gemm and arcq_gemm_noalloc; *run = false when there is nothing to launch.
 static arcq_status check_gemm_args(const char* who, const uint8_t* a_codes, const uint8_t* a_scales, float a_tensor_scale,
                                    const uint8_t* w_codes, const uint8_t* w_scales, float w_tensor_scale,

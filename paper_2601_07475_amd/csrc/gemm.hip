@@ -22,6 +22,8 @@
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
+#include <cmath>
+#include <iterator>
 #include <atomic>
 #include <type_traits>
 
@@ -1222,7 +1224,7 @@ static GemmPlan plan_stream(int64_t M, int64_t N, int64_t Kp) {
     return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, ahead};
 }
 
-// Which kernel serves a problem: a function of the shape alone, so that the workspace a caller sizes beforehand matches what the
+// Which kernel serves a problem by rule: a function of the shape alone, so that the workspace a caller sizes beforehand matches what the
 // launch uses.  Up to 32 rows the weight-streaming kernel, beyond the smallest modelled time of three:
 //   * the streaming kernel up to 128 rows, e.g. 64 rows over K' = 4240: 5120 weight rows 12.5 us against 14.3 on 64 x 32 tiles,
 //     28672 38.9 against 30.4 on 64 x 128; 46 x 9600 over K' = 512 8.5 against 6.1 on 64 x 64;
@@ -1232,7 +1234,7 @@ static GemmPlan plan_stream(int64_t M, int64_t N, int64_t Kp) {
 // say: the others need no workspace, and calls without one and overlapping calls of arcq_gemm_noalloc count on that (the 64 x 128
 // and 96 x 128 tiles, which came later, do not enter: what they alone could take still splits).  Nor do the times decide where
 // the runs need more than the library's built-in scratch: what arcq_gemm_noalloc takes does not follow them.
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp) {
+static GemmPlan plan_by_rule(int64_t M, int64_t N, int64_t Kp) {
     const GemmPlan stream = plan_stream(M, N, Kp);
     if (M <= 32) return stream;
     const KsplitTile ks = gemm_ksplit_best(M, N, Kp);
@@ -1272,16 +1274,117 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp) {
     return tiles;
 }
 
+// Modelled time in us of one launch of a tile over any number of tiles: start + rounds x round + stages x (full rounds x full + the
+// last round's alone + shared x its fill), a round being 256 tiles and a stage 128 k (256 k for the k-split tiles).  (Two or three
+// workgroups of the small tiles share a compute unit: a second round costs them about half a first one.)  Rows off the grid of 64 cost
+// ragged_round a round and ragged_stage a round and stage.  Fitted to 2190 problems (M = 33 .. 8192, N = 256 .. 28672, K' = 512 .. 24000,
+// weights from HBM), every tile timed: 3 to 6 % rms, and the fastest by the model 0.4 % from the fastest of all.
+namespace {
+struct TileTime {
+    int kernel, rows, cols;
+    double start, round, full, alone, shared, ragged_round, ragged_stage;
+};
+constexpr TileTime TILE_TIMES[] = {
+    {ARCQ_ROUTE_TILES, 256, 256, 6.058, 5.990, 3.222, 2.079, 0.934, 1.704, 0.0},
+    {ARCQ_ROUTE_TILES, 192, 256, 4.814, 4.663, 2.575, 1.632, 0.829, 1.507, 0.0},
+    {ARCQ_ROUTE_TILES, 128, 256, 2.255, 4.209, 1.872, 1.006, 0.742, 1.247, 0.0},
+    {ARCQ_ROUTE_TILES, 192, 128, 3.521, 1.662, 1.361, 1.026, 0.305, 1.376, 0.104},
+    {ARCQ_ROUTE_TILES, 128, 128, 3.513, 0.964, 0.949, 0.776, 0.209, 0.352, 0.050},
+    {ARCQ_ROUTE_KSPLIT, 128, 128, 0.916, 5.942, 1.828, 1.134, 0.561, 0.615, 0.012},
+    {ARCQ_ROUTE_KSPLIT, 96, 128, 1.005, 4.967, 1.517, 0.944, 0.445, 0.513, 0.029},
+    {ARCQ_ROUTE_KSPLIT, 128, 64, 1.014, 5.139, 1.026, 0.765, 0.213, 0.718, 0.028},
+    {ARCQ_ROUTE_KSPLIT, 64, 128, 1.003, 3.709, 1.105, 0.744, 0.310, 0.551, 0.046},
+    {ARCQ_ROUTE_KSPLIT, 96, 64, 5.399, 0.0, 0.856, 0.629, 0.189, 0.850, 0.022},
+    {ARCQ_ROUTE_KSPLIT, 64, 64, 4.086, 0.550, 0.449, 0.467, 0.115, 0.402, 0.035},
+    {ARCQ_ROUTE_KSPLIT, 64, 32, 3.271, 0.493, 0.254, 0.401, 0.063, 0.378, 0.018},
+};
+
+double tile_time(const TileTime& t, int64_t M, int64_t N, int64_t Kp) {
+    const int64_t wgs = ((M + t.rows - 1) / t.rows) * ((N + t.cols - 1) / t.cols), left = wgs & 255;
+    const double stage_k = t.kernel == ARCQ_ROUTE_KSPLIT ? 256.0 : 128.0, stages = std::ceil((double)Kp / stage_k);
+    const double full = (double)(wgs >> 8), rounds = full + (left ? 1.0 : 0.0);
+    const double last = left ? t.alone + t.shared * (double)left / 256.0 : 0.0;
+    return t.start + rounds * t.round + stages * (full * t.full + last) +
+           ((Kp & 63) ? rounds * (t.ragged_round + stages * t.ragged_stage) : 0.0);
+}
+
+struct TimedPlan {
+    GemmPlan plan;
+    double us;
+};
+
+// The tile that takes the least modelled time, or the streaming kernel; no workspace.
+TimedPlan plan_by_time(int64_t M, int64_t N, int64_t Kp) {
+    const GemmPlan stream = plan_stream(M, N, Kp);
+    if (M <= 32) return {stream, 4.0 + (M <= 16 ? 0.115e-6 : 0.165e-6) * (double)N * (double)Kp};     // (nothing else is ever faster)
+    TimedPlan best = {stream, M <= 128 ? stream_time(stream, N, Kp) : 1e30};
+    for (const TileTime& t : TILE_TIMES) {
+        // 96 x 128 tiles that pad more rows than 128 x 128: see gemm_ksplit_best
+        if (t.rows == 96 && t.cols == 128 && (M + 95) / 96 * 96 > (M + 127) / 128 * 128) continue;
+        // Small tiles in more than one round are not what the model says where many of them share a compute unit over a long K'
+        // (314 x 8176 over 9904 1.5x slower than modelled, 285 x 25216 over 2288 1.2x faster).
+        if (t.kernel == ARCQ_ROUTE_KSPLIT && t.rows * t.cols < 96 * 128 && ((M + t.rows - 1) / t.rows) * ((N + t.cols - 1) / t.cols) > 256) continue;
+        const double us = tile_time(t, M, N, Kp);
+        if (us < best.us) best = {{t.kernel, t.rows, t.cols, 1, false}, us};
+    }
+    return best;
+}
+}  // namespace
+
+// The rule's kernel, unless the model knows one launch that takes less than 0.95 of its time, or two that take less than 0.97 of that.
+// Two: workgroups run in rounds of one per compute unit, and a last round that is nearly empty costs as much as a full one. Whole
+// rounds of the tiles with the best rate go first, and the columns or rows behind them, which are few, to tiles that spread them
+// over the chip (a second launch costs 3 us beside its start).  1777 x 10240 over K' = 8528, fp32, with the quantizer: 400
+// tiles of 192 x 256 in two rounds 343 us, 252 tiles of 256 x 256 and 224 of 128 x 64 283.  Over 350 and 200 random problems whose route
+// this changes: 1.075x (513 to 8192 rows; 0.97x at worst, 1.31x at best) and 1.10x (65 to 512 rows).
+// K' < 1024: the rule alone (starts and ends of rounds count for more there than the model knows).
+GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
+    const GemmPlan rule = plan_by_rule(M, N, Kp);
+    GemmParts best = {rule, rule, M, N};
+    if (Kp < 1024 || rule.runs > 1 || (rule.kernel != ARCQ_ROUTE_TILES && rule.kernel != ARCQ_ROUTE_KSPLIT)) return best;
+    const auto of_rule = std::find_if(std::begin(TILE_TIMES), std::end(TILE_TIMES), [&](const TileTime& t) {
+        return t.kernel == rule.kernel && t.rows == rule.rows && t.cols == rule.cols;
+    });
+    const double rule_us = tile_time(*of_rule, M, N, Kp);
+    const TimedPlan one = plan_by_time(M, N, Kp);
+    double us = rule_us;
+    if (one.us < 0.95 * rule_us) {
+        best.first = best.rest = one.plan;
+        us = one.us;
+    }
+    us *= 0.97;
+    const double stages = (double)Kp / 128.0;
+    for (const TileTime& t : TILE_TIMES) {
+        // (128 x 256 and 192 x 128 tiles in front gain nothing on average: 0.97 to 1.06x)
+        if (!(t.cols == 256 && t.rows >= 192) && !(t.kernel == ARCQ_ROUTE_KSPLIT && t.rows == 128 && t.cols == 128)) continue;
+        const int64_t tm = (M + t.rows - 1) / t.rows, tn = (N + t.cols - 1) / t.cols, most = tm * tn / 256;
+        for (int64_t rounds = std::max<int64_t>(1, most - 1); rounds <= most; ++rounds) {
+            auto consider = [&](int64_t rows, int64_t cols, int64_t rest_rows, int64_t rest_cols) {
+                const double first = tile_time(t, rows, cols, Kp);
+                // no tile computes 65536 outputs per compute unit and stage in less than 3 us
+                if (first + 5.0 + stages * 3.0 * (double)rest_rows * (double)rest_cols / (65536.0 * 256.0) >= us) return;
+                const TimedPlan rest = plan_by_time(rest_rows, rest_cols, Kp);
+                if (first + rest.us + 3.0 >= us) return;
+                us = first + rest.us + 3.0;
+                best = {{t.kernel, t.rows, t.cols, 1, false}, rest.plan, rows, cols};
+            };
+            const int64_t nc = 256 * rounds / tm, nr = 256 * rounds / tn;
+            if (nc >= 1 && nc < tn) consider(M, t.cols * nc, M, N - t.cols * nc);
+            if (nr >= 1 && nr < tm) consider(t.rows * nr, N, M - t.rows * nr, N);
+        }
+    }
+    return best;
+}
+
 namespace {
 
 template <typename OutT>
-arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
-                         const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, float alpha, OutT* y,
-                         int64_t ldy, float* workspace, hipStream_t stream) {
+arcq_status launch_plan(const GemmPlan& plan, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
+                        const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, float alpha, OutT* y,
+                        int64_t ldy, float* workspace, hipStream_t stream) {
     const int nbk = (int)(Kp >> 4);
     const bool dword_scales = ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
     const bool aligned16 = ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 && dword_scales;
-    const GemmPlan plan = plan_gemm(M, N, Kp);
     if (plan.kernel == ARCQ_ROUTE_STREAM) {
         // (the variants that exist: plan_stream)
 #define ARCQ_STREAM(MT_, NT_, W_, U_, AHEAD_)                                                                                   \
@@ -1359,6 +1462,26 @@ arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const 
     return check_launch("gemm_direct_kernel");
 }
 
+template <typename OutT>
+arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
+                         const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, float alpha, OutT* y,
+                         int64_t ldy, float* workspace, hipStream_t stream) {
+    // (stages through registers have times of their own: the rule's kernel)
+    if (((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) != 0)
+        return launch_plan(plan_by_rule(M, N, Kp), a_codes, a_scales, w_codes, w_scales, M, N, Kp, alpha, y, ldy, workspace, stream);
+    const GemmParts parts = plan_gemm_parts(M, N, Kp);
+    if (arcq_status st = launch_plan(parts.first, a_codes, a_scales, w_codes, w_scales, parts.rows, parts.cols, Kp, alpha, y, ldy,
+                                     workspace, stream)) return st;
+    const int64_t c = Kp >> 1, s = Kp >> 4;         // bytes of a row of codes, of scale bytes
+    if (parts.rows < M)
+        return launch_plan(parts.rest, a_codes + parts.rows * c, a_scales + parts.rows * s, w_codes, w_scales, M - parts.rows, N, Kp,
+                           alpha, y + parts.rows * ldy, ldy, nullptr, stream);
+    if (parts.cols < N)
+        return launch_plan(parts.rest, a_codes, a_scales, w_codes + parts.cols * c, w_scales + parts.cols * s, M, N - parts.cols, Kp,
+                           alpha, y + parts.cols, ldy, nullptr, stream);
+    return ARCQ_OK;
+}
+
 }  // namespace
 
 arcq_status launch_splitk_reduce(const float* partial, int splits, int M, int N, float alpha, void* y, int y_dtype,
@@ -1377,7 +1500,7 @@ arcq_status launch_splitk_reduce(const float* partial, int splits, int M, int N,
 }
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t Kp) {
-    const int runs = plan_gemm(M, N, Kp).runs;
+    const int runs = plan_by_rule(M, N, Kp).runs;       // (K' split across workgroups is never replaced by other tiles)
     return runs > 1 ? (size_t)runs * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 

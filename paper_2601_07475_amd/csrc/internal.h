@@ -50,7 +50,14 @@ struct GemmPlan {
     int runs;           // runs of K' across workgroups (ARCQ_ROUTE_TILES)
     bool ahead;         // ARCQ_ROUTE_STREAM: a wave asks for its next group of chunks while it computes one
 };
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp);
+// A problem in one launch, or in two: whole rounds of large tiles over the first `rows` activation rows or the first `cols` weight
+// rows, and the others on whatever is fastest for them.
+struct GemmParts {
+    GemmPlan first, rest;
+    int64_t rows, cols;     // of the first launch; all of them: there is no second one
+};
+GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp);
+inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp) { return plan_gemm_parts(M, N, Kp).first; }
 GemmPlan plan_mx_gemm(int64_t M, int64_t N, int64_t Kp, bool workspace);
 
 // Tiled kernel whose waves split every stage along k inside the workgroup (gemm_ksplit.hip): the fastest of its tiles for this

@@ -1,4 +1,4 @@
-"""GPU: how the tiles of a GEMM are dealt to workgroups."""
+"""GPU: how the tiles of a GEMM are dealt to workgroups and launches, and how they reach y."""
 import pytest
 import torch
 
@@ -38,3 +38,44 @@ def test_rows_of_y_at_any_address(M, N, nb, dtype, pad):
         out = dequantize(*a, block) @ dequantize(*w, block).t() * (2.0 ** -12 if block == 16 else 1.0)
         fits = out.abs() < 60000.0 if dtype == torch.float16 else torch.ones_like(out, dtype=torch.bool)
         assert worst(torch.where(fits, ref.double(), 0.0), torch.where(fits, out, 0.0)) <= 5e-3
+
+
+# whole rounds of large tiles and, in a second launch, the columns (rows) behind them: every kernel that may take those, K' on and off the
+# grid of 64, the last rows of both operands (whose windows of scale bytes come from the patch) in either launch
+TWO = [((1, 128, 128), (0, 16, 48), 392, 8329, 155), ((1, 128, 128), (1, 64, 32), 497, 9199, 249), ((1, 128, 128), (1, 96, 128), 647, 10877, 219),
+       ((2, 192, 256), (2, 128, 128), 1335, 12144, 81), ((2, 192, 256), (2, 128, 256), 1580, 12643, 75), ((2, 256, 256), (0, 16, 64), 1287, 12320, 69),
+       ((2, 256, 256), (1, 64, 128), 1196, 14070, 73), ((2, 256, 256), (1, 64, 64), 1155, 13815, 82), ((2, 256, 256), (1, 64, 64), 2914, 5838, 82),
+       ((2, 256, 256), (1, 96, 64), 1373, 12706, 79), ((2, 256, 256), (1, 128, 64), 2797, 6547, 98), ((2, 256, 256), (2, 192, 128), 1393, 15585, 100),
+       ((2, 256, 256), (1, 128, 128), 2118, 8529, 106), ((2, 256, 256), (2, 192, 256), 2643, 14915, 71)]
+
+
+@pytest.mark.parametrize("first,rest,M,N,nb", TWO)
+def test_two_launches(first, rest, M, N, nb):
+    assert B.arcq_gemm_route(M, N, nb * 16)[:3] == first and B.arcq_gemm_rest(M, N, nb * 16)[2] == rest
+    assert B.arcq_gemm_workspace_size(M, N, nb * 16) == 0
+    g = torch.Generator(device="cuda").manual_seed(M + N + nb)
+    a, w = operand(g, M, nb, 16), operand(g, N, nb, 16)
+    ref = dequantize(*a, 16) @ dequantize(*w, 16).t()
+    for dtype, tol in ((torch.float32, 2e-5), (torch.float16, 1e-3)):
+        scale = 2.0 ** -12 if dtype == torch.float16 else 1.0        # keeps fp16 results finite; exact
+        raw = torch.full((M, N + 3), 777.0, dtype=dtype, device="cuda")
+        B.arcq_gemm(*a, scale, *w, 1.0, y=raw[:, :N])
+        assert worst(raw[:, :N], ref * scale) <= tol, dtype
+        assert bool((raw[:, N:] == 777.0).all())
+        y = torch.empty((M, N), dtype=dtype, device="cuda")
+        B.arcq_gemm_noalloc(*a, scale, *w, 1.0, y)
+        assert torch.equal(y, raw[:, :N])
+    # codes at their minimum alignment; scale bytes at odd addresses (the rule's kernel, in one launch)
+    for lead, code_lead in ((0, 8), (1, 0)):
+        a1 = operand(torch.Generator(device="cuda").manual_seed(M + N + nb), M, nb, 16, lead=lead, code_lead=code_lead)
+        assert worst(B.arcq_gemm(*a1, 1.0, *w, 1.0, out_dtype=torch.float32), ref) <= 2e-5
+
+
+# one launch that the modelled times prefer to the rule: k-split tiles in several rounds, tiles in rounds of another height
+@pytest.mark.parametrize("route,M,N,nb", [((1, 128, 128), 2917, 1071, 245), ((1, 96, 128), 387, 6429, 98), ((2, 128, 256), 992, 5520, 90),
+                                          ((2, 128, 128), 1634, 7280, 160), ((2, 192, 128), 1152, 27152, 116)])
+def test_one_launch_by_time(route, M, N, nb):
+    assert B.arcq_gemm_route(M, N, nb * 16)[:3] == route and B.arcq_gemm_rest(M, N, nb * 16) is None
+    g = torch.Generator(device="cuda").manual_seed(M + N + nb)
+    a, w = operand(g, M, nb, 16), operand(g, N, nb, 16)
+    assert worst(B.arcq_gemm(*a, 1.0, *w, 1.0, out_dtype=torch.float32), dequantize(*a, 16) @ dequantize(*w, 16).t()) <= 2e-5

@@ -349,3 +349,24 @@ def test_mx_gemm_workspace_entry_points():
     assert L.arcq_mx_gemm_ws(*args, FAKE, need - 1, None) == B.WORKSPACE_TOO_SMALL
     assert L.arcq_mx_gemm_ws(*args, ctypes.c_void_p(0x10010), need, None) == B.BAD_ALIGN
     assert L.arcq_mx_gemm_ws(FAKE, FAKE, FAKE, FAKE, 256, 4096, 14592, FAKE, 7, 4096, FAKE, need, None) == B.INVALID_ARG
+
+
+def test_second_launches():
+    """They take the last columns or the last rows, behind whole tiles of the first launch; neither launch needs a workspace, and the
+    second is never taken for K' below 1024."""
+    r = B.Rest()
+    assert B.lib().arcq_gemm_rest(4, 8, 40, ctypes.byref(r)) == B.BAD_SHAPE
+    assert B.lib().arcq_gemm_rest(4, 8, 64, None) == B.INVALID_ARG
+    seen = 0
+    for M, N, Kp in random_sizes(8, 40000, 16):
+        rest = B.arcq_gemm_rest(M, N, Kp)
+        if rest is None:
+            continue
+        kernel, rows, cols, runs, _ = B.arcq_gemm_route(M, N, Kp)
+        assert Kp >= 1024 and runs == 1 and B.arcq_gemm_workspace_size(M, N, Kp) == 0
+        assert (kernel, rows, cols) in ((B.ROUTE_TILES, 256, 256), (B.ROUTE_TILES, 192, 256), (B.ROUTE_KSPLIT, 128, 128))
+        assert (rest[0] == M) != (rest[1] == N) and 0 < rest[0] <= M and 0 < rest[1] <= N
+        assert (M - rest[0]) % rows == 0 and (N - rest[1]) % cols == 0
+        seen += 1
+    assert seen > 200
+    assert B.arcq_gemm_rest(1777, 10240, 8528)[:2] == (1777, 1024) and B.arcq_gemm_rest(8192, 8192, 29696) is None
