@@ -219,8 +219,8 @@ arcq_status arcq_check_perm(const int32_t* perm, int64_t K, uint8_t* flags,
  *         bit pattern of tau = 2^-3 * maximum}.  S_raw = number of channels with colmax > tau
  *         (a channel AT the threshold needs no compensation); S = S_raw rounded up to a multiple
  *         of 16, at most K (this library works on blocks of 16; the paper does not say).
- *   S_host  if not NULL the call synchronises the stream and stores S there; if NULL nothing is
- *         synchronised and the caller reads info in stream order.
+ *   S_host  if not NULL the call synchronises the stream and stores S there (10 us sooner in page-locked memory, which the
+ *         kernel writes itself); if NULL nothing is synchronised and the caller reads info in stream order.
  * colmax must hold finite values >= 0 (what arcq_calib_absmax produces); K as everywhere else.
  */
 arcq_status arcq_calib_absmax(const void* x, int64_t M, int64_t K, int64_t ldx,

@@ -50,7 +50,7 @@ SIGNATURES = {
     "arcq_mx_gemm_workspace_size": (ctypes.c_int, [_i64, _i64, _i64, ctypes.POINTER(_sz)]),
     "arcq_mx_gemm_ws": (ctypes.c_int, [_vp, _vp, _vp, _vp, _i64, _i64, _i64, _vp, ctypes.c_int, _i64, _vp, _sz, _vp]),
     "arcq_calib_absmax": (ctypes.c_int, [_vp, _i64, _i64, _i64, _vp, _vp]),
-    "arcq_calib_select": (ctypes.c_int, [_vp, _i64, _vp, _vp, ctypes.POINTER(ctypes.c_int), _vp]),
+    "arcq_calib_select": (ctypes.c_int, [_vp, _i64, _vp, _vp, _vp, _vp]),
     "arcq_gemm_workspace_size": (ctypes.c_int, [_i64, _i64, _i64, ctypes.POINTER(_sz)]),
     "arcq_gemm": (ctypes.c_int, [_vp, _vp, _f32, _vp, _vp, _f32, _i64, _i64, _i64, _vp, ctypes.c_int, _i64,
                                  _vp, _sz, _vp]),
@@ -257,9 +257,9 @@ def arcq_calib_select(colmax, perm=None, info=None):
         perm = torch.empty(K, dtype=torch.int32, device=colmax.device)
     if info is None:
         info = torch.empty(4, dtype=torch.int32, device=colmax.device)
-    S = ctypes.c_int(-1)
-    _check(lib().arcq_calib_select(_ptr(colmax), K, _ptr(perm), _ptr(info), ctypes.byref(S), _stream()))
-    return perm, S.value, info
+    S = torch.empty(1, dtype=torch.int32, pin_memory=True)      # page-locked: the kernel writes S itself
+    _check(lib().arcq_calib_select(_ptr(colmax), K, _ptr(perm), _ptr(info), _ptr(S), _stream()))
+    return perm, S.item(), info
 
 
 def _mx_quantize(fn, x, perm, S, codes=None, scales=None):

@@ -12,6 +12,7 @@ namespace arcq {
 namespace {
 
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // |a|, |b| as fp16 bit patterns, element-wise maximum (patterns of non-negative halves order like integers)
 __device__ __forceinline__ uint32_t absmax2(uint32_t acc, uint32_t v) {
@@ -83,7 +84,9 @@ __global__ __launch_bounds__(256) void absmax_kernel(const uint16_t* __restrict_
 
 // Layer maximum, tau = 2^-3 max (exact), number of channels above tau, S rounded up to a block of 16, by one workgroup of
 // 1024 threads.  info = {S, S_raw, bits(max), bits(tau)}.
-__device__ __forceinline__ void calib_stats(const uint32_t* __restrict__ colmax, int K, int32_t* __restrict__ info, int* part) {
+// s_host (or null): S once more, for the host.
+__device__ __forceinline__ void calib_stats(const uint32_t* __restrict__ colmax, int K, int32_t* __restrict__ info, int* part,
+                                            int32_t* s_host) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t mx = 0;
     for (int k = tid; k < K; k += 1024) mx = max(mx, colmax[k]);
@@ -109,44 +112,74 @@ __device__ __forceinline__ void calib_stats(const uint32_t* __restrict__ colmax,
         info[1] = s_raw;
         info[2] = (int32_t)total;
         info[3] = (int32_t)__float_as_uint(tau);
+        if (s_host) __hip_atomic_store(s_host, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
 // Stable ascending order by counting: the position of channel k is the number of channels that come
 // before it (smaller statistic, or equal statistic and smaller index).  Every position is hit exactly
 // once whatever the values, so the output is always a permutation.  K^2 comparisons, bound by the vector
-// instructions (a compare and an add with carry each): a workgroup ranks 64 channels, one per lane, and its 16 waves
-// take a sixteenth of the keys each, which are the same for all lanes and come through the scalar unit.  K = 8192: 14.6 us
-// (one lane per channel going over all keys in LDS tiles: 211 us, 32 workgroups on 256 compute units), 65536: 251 (947).  The last
-// workgroup finds the layer's statistics instead, which took a launch of their own (5 us).
+// instructions (a compare and an add with carry each).  The first workgroup finds the layer's statistics instead, which took a
+// launch of their own (5 us).
+// HALVES: a workgroup ranks 32 channels, and its 16 waves take a sixteenth of the keys each, of which either half of a wave compares its
+// own half with the 32 channels: 256 workgroups for K = 8192.  Keys of lower index come before an equal one, keys of higher index do
+// not: patterns order like integers, so the former are compared with the channel's key + 1.
+// Otherwise it ranks 64 channels, one per lane, against keys that are the same for all lanes and come through the scalar unit:
+// 1.6 times fewer cycles a comparison, but 128 workgroups for K = 8192.  Both, us (HALVES first): K = 4096 6.3 and 9.2, 8192 10.8 and 14.5,
+// 14336 27 and 22, 28672 101 and 63, 65536 449 and 250; so the line lies between 8192 and 14336.
+constexpr int HALVES_UP_TO = 8192;      // channels
+template <bool HALVES>
 __global__ __launch_bounds__(1024) void calib_select_kernel(const uint32_t* __restrict__ colmax, int K, int32_t* __restrict__ perm,
-                                                            int32_t* __restrict__ info) {
+                                                            int32_t* __restrict__ info, int32_t* __restrict__ s_host) {
     __shared__ int part[16][64];
-    if (blockIdx.x == gridDim.x - 1) {
-        calib_stats(colmax, K, info, &part[0][0]);
+    if (blockIdx.x == 0) {
+        calib_stats(colmax, K, info, &part[0][0], s_host);
         return;
     }
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int k0 = blockIdx.x * 64, k = k0 + lane;
+    constexpr int RANKED = HALVES ? 32 : 64;
+    const int lane = threadIdx.x & 63, wave = HALVES ? (int)(threadIdx.x >> 6) : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int k0 = (blockIdx.x - 1) * RANKED, k = k0 + (lane & (RANKED - 1));
     const uint32_t mine = colmax[min(k, K - 1)];
-    const int slice = (K + 1023) / 1024 * 64;                   // a multiple of 64: a workgroup's channels lie in one slice
-    const int j0 = min(wave * slice, K), j1 = min(j0 + slice, K);
     int before = 0;
-    // keys of lower index come before an equal one, keys of higher index do not
-    int j = j0;
-    for (const int to = min(j1, max(j0, k0)); j < to; j += 16)  // (every bound is a multiple of 16)
+    if constexpr (HALVES) {
+        // slices of a multiple of 32 keys, so that a workgroup's channels lie in one; every bound is a multiple of 16
+        const int slice = (K + 1023) / 1024 * 32;
+        const int j0 = min((2 * wave + (lane >> 5)) * slice, K), j1 = min(j0 + slice, K);
+        for (int j = j0; j < j1; j += 16) {
+            // (the channels' own 32 keys, which need their indices as well, are left to the first wave)
+            const uint32_t bound = j + 16 <= k0 ? mine + 1 : j >= k0 + RANKED ? mine : 0u;
+            u32x4_a4 key[4];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) before += colmax[j + e] <= mine ? 1 : 0;
-    for (const int to = min(j1, max(j0, k0 + 64)); j < to; ++j) before += colmax[j] < mine || (colmax[j] == mine && j < k) ? 1 : 0;
-    for (; j < j1; j += 16)
+            for (int e = 0; e < 4; ++e) key[e] = *reinterpret_cast<const u32x4_a4*>(colmax + j + 4 * e);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) before += colmax[j + e] < mine ? 1 : 0;
+            for (int e = 0; e < 16; ++e) before += key[e >> 2][e & 3] < bound ? 1 : 0;
+        }
+        if (wave == 0) {
+            const int first = k0 + 16 * (lane >> 5);                // 16 keys for either half
+            if (first < K)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) before += colmax[first + e] < (first + e < k ? mine + 1 : mine) ? 1 : 0;
+        }
+        // (no pattern is greater than the greatest: every key of lower index comes before it)
+        if (mine + 1 == 0) before += max(min(j1, k0) - j0, 0) + (wave == 0 ? min(max(k - k0 - 16 * (lane >> 5), 0), 16) : 0);
+    } else {
+        const int slice = (K + 1023) / 1024 * 64;               // a multiple of 64: a workgroup's channels lie in one slice
+        const int j0 = min(wave * slice, K), j1 = min(j0 + slice, K);
+        int j = j0;
+        for (const int to = min(j1, max(j0, k0)); j < to; j += 16)      // (every bound is a multiple of 16)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) before += colmax[j + e] <= mine ? 1 : 0;
+        for (const int to = min(j1, max(j0, k0 + 64)); j < to; ++j) before += colmax[j] < mine || (colmax[j] == mine && j < k) ? 1 : 0;
+        for (; j < j1; j += 16)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) before += colmax[j + e] < mine ? 1 : 0;
+    }
     part[wave][lane] = before;
     __syncthreads();
-    if (wave == 0 && k < K) {
+    if (threadIdx.x < RANKED && k < K) {
         int position = 0;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) position += part[w][lane];
+        for (int w = 0; w < 16; ++w) position += part[w][lane] + (HALVES ? part[w][lane + 32] : 0);
         perm[position] = k;
     }
 }
@@ -168,14 +201,25 @@ arcq_status launch_calib_absmax(const void* x, int64_t M, int64_t K, int64_t ldx
 arcq_status launch_calib_select(const float* colmax, int64_t K, int32_t* perm, int32_t* info, int* S_host,
                                 hipStream_t stream) {
     const uint32_t* keys = reinterpret_cast<const uint32_t*>(colmax);
-    hipLaunchKernelGGL(calib_select_kernel, dim3((unsigned)((K + 63) / 64) + 1), dim3(1024), 0, stream, keys, (int)K, perm, info);
+    // Page-locked memory takes S from the kernel itself; any other needs a copy, which the host waits for 10 us longer (K = 8192: 31 against 22 us a call).
+    int32_t* direct = nullptr;
+    if (S_host) {
+        hipPointerAttribute_t at;
+        if (hipPointerGetAttributes(&at, S_host) == hipSuccess && at.type == hipMemoryTypeHost)
+            direct = static_cast<int32_t*>(at.devicePointer);
+        else (void)hipGetLastError();           // memory the runtime does not know is no error of this call
+    }
+    const bool halves = K <= HALVES_UP_TO;
+    const unsigned workgroups = (unsigned)(halves ? (K + 31) / 32 : (K + 63) / 64) + 1;
+    hipLaunchKernelGGL(halves ? calib_select_kernel<true> : calib_select_kernel<false>, dim3(workgroups), dim3(1024), 0, stream, keys,
+                       (int)K, perm, info, direct);
     if (arcq_status st = check_launch("calib_select_kernel")) return st;
     if (S_host) {
         int32_t s = 0;
-        hipError_t e = hipMemcpyAsync(&s, info, sizeof(s), hipMemcpyDeviceToHost, stream);
+        hipError_t e = direct ? hipSuccess : hipMemcpyAsync(&s, info, sizeof(s), hipMemcpyDeviceToHost, stream);
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
         if (e != hipSuccess) return fail(ARCQ_HIP_ERROR, "arcq_calib_select: %s", hipGetErrorString(e));
-        *S_host = s;
+        if (!direct) *S_host = s;
     }
     return ARCQ_OK;
 }

@@ -19,6 +19,28 @@ def test_order_is_the_stable_ascending_one(K, values):
     assert info[1].item() == raw and S == min(K, -(-raw // 16) * 16)
 
 
+# either side of the size from which a lane ranks a channel against every key; patterns that are no finite value >= 0 still give a permutation
+@pytest.mark.parametrize("K", [48, 4112, 8176, 8192, 8208, 14336])
+def test_order_of_any_patterns(K):
+    rng = np.random.default_rng(K)
+    c = rng.choice(np.array([0, 1, 0x3F800000, 0x7F800000, 0x80000000, 0xFFFFFFFE, 0xFFFFFFFF], dtype=np.uint32), K)
+    perm, _, _ = B.arcq_calib_select(torch.from_numpy(c.view(np.float32)).cuda())
+    assert np.array_equal(perm.cpu().numpy(), np.argsort(c, kind="stable"))
+
+
+def test_S_reaches_any_host_memory():
+    """Page-locked memory takes it from the kernel, other memory from a copy."""
+    c = torch.rand(4096, device="cuda")
+    perm, info = torch.empty(4096, dtype=torch.int32, device="cuda"), torch.empty(4, dtype=torch.int32, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    plain, pinned = torch.full((3,), -1, dtype=torch.int32), torch.full((3,), -1, dtype=torch.int32).pin_memory()
+    for host in (plain, pinned, plain[1:], pinned[1:]):
+        host.fill_(-1)
+        assert B.lib().arcq_calib_select(c.data_ptr(), 4096, perm.data_ptr(), info.data_ptr(), host.data_ptr(), stream) == B.OK
+        assert host[0].item() == info[0].item() > 0 and (host[1:] == -1).all()
+    assert torch.cuda.current_stream().query()
+
+
 @pytest.mark.parametrize("M,K", [(1, 16), (3, 528), (33, 1008), (257, 2064)])
 def test_maxima_over_batches_that_rise_and_fall(M, K):
     g = torch.Generator(device="cuda").manual_seed(M)
