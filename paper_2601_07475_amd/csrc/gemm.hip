@@ -1190,6 +1190,7 @@ static double wide_cost(int64_t M, int64_t N, int rows, double t_stage) {
 }
 
 constexpr int STREAM_WAVES = 8;     // of a workgroup of the weight-streaming kernel (8 x 2 tiles: 4)
+constexpr int STREAM_ROUND = 256 * 64;      // weight rows of a round of that kernel: a workgroup of four tiles on every compute unit
 
 // The weight-streaming kernel's share of the rule: row tiles, weight tiles per wave, and whether the waves load ahead.
 static GemmPlan plan_stream(int64_t M, int64_t N, int64_t Kp) {
@@ -1341,6 +1342,15 @@ TimedPlan plan_by_time(int64_t M, int64_t N, int64_t Kp) {
 GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
     const GemmPlan rule = plan_by_rule(M, N, Kp);
     GemmParts best = {rule, rule, M, N};
+    // The streaming kernel with more weight rows than one round of four tiles a wave takes: that round, and the rest with as few tiles a
+    // wave as give it a round of its own.  (Four tiles a wave throughout: a second round that most of the chip has no part in.)
+    // From HBM, us: 16 x 20480 over K' = 4352 18.6 -> 16.0, over 14592 48.6 -> 39.9; 1 x 18000 over 8464 31.9 -> 25.5; 32 x 24576 over 8464
+    // 43.6 -> 39.1, 32 x 28672 45.0 -> 43.5.  Over a short K' a second launch costs what the round did: 1 x 24576 over 2176 11.5 and 11.9 (two
+    // tiles a wave), 16 x 28672 over 4352 20.2 and 20.2 (three), 16 x 16400 over 2176 10.3 and 10.8 (a few rows behind).
+    const int64_t behind = N - STREAM_ROUND;
+    if (rule.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind > 0 && behind <= STREAM_ROUND / 4 * 3 &&
+        Kp >= (behind > STREAM_ROUND / 2 ? 6144 : behind > STREAM_ROUND / 4 || behind < 1024 ? 4096 : 2048))
+        return {plan_stream(M, STREAM_ROUND, Kp), plan_stream(M, behind, Kp), M, STREAM_ROUND};
     if (Kp < 1024 || rule.runs > 1 || (rule.kernel != ARCQ_ROUTE_TILES && rule.kernel != ARCQ_ROUTE_KSPLIT)) return best;
     const auto of_rule = std::find_if(std::begin(TILE_TIMES), std::end(TILE_TIMES), [&](const TileTime& t) {
         return t.kernel == rule.kernel && t.rows == rule.rows && t.cols == rule.cols;
@@ -1466,10 +1476,10 @@ template <typename OutT>
 arcq_status launch_typed(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                          const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, float alpha, OutT* y,
                          int64_t ldy, float* workspace, hipStream_t stream) {
-    // (stages through registers have times of their own: the rule's kernel)
-    if (((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) != 0)
-        return launch_plan(plan_by_rule(M, N, Kp), a_codes, a_scales, w_codes, w_scales, M, N, Kp, alpha, y, ldy, workspace, stream);
     const GemmParts parts = plan_gemm_parts(M, N, Kp);
+    // (stages through registers have times of their own: the rule's kernel; the streaming kernel has none)
+    if (((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) != 0 && parts.first.kernel != ARCQ_ROUTE_STREAM)
+        return launch_plan(plan_by_rule(M, N, Kp), a_codes, a_scales, w_codes, w_scales, M, N, Kp, alpha, y, ldy, workspace, stream);
     if (arcq_status st = launch_plan(parts.first, a_codes, a_scales, w_codes, w_scales, parts.rows, parts.cols, Kp, alpha, y, ldy,
                                      workspace, stream)) return st;
     const int64_t c = Kp >> 1, s = Kp >> 4;         // bytes of a row of codes, of scale bytes

@@ -79,3 +79,21 @@ def test_one_launch_by_time(route, M, N, nb):
     g = torch.Generator(device="cuda").manual_seed(M + N + nb)
     a, w = operand(g, M, nb, 16), operand(g, N, nb, 16)
     assert worst(B.arcq_gemm(*a, 1.0, *w, 1.0, out_dtype=torch.float32), dequantize(*a, 16) @ dequantize(*w, 16).t()) <= 2e-5
+
+
+# the streaming kernels with more weight rows than a round takes: one, two and three tiles a wave behind it, ragged rows and edges
+@pytest.mark.parametrize("M,N,nb", [(1, 17500, 128), (16, 20479, 130), (13, 16390, 257), (32, 24571, 259), (7, 28670, 384), (31, 24577, 385)])
+def test_streaming_in_two_launches(M, N, nb):
+    rows, cols, rest = B.arcq_gemm_rest(M, N, nb * 16)
+    assert (rows, cols, rest[0]) == (M, N - 16384, B.ROUTE_STREAM)
+    for block, gemm in ((16, lambda a, w, y: B.arcq_gemm(*a, 1.0, *w, 1.0, y=y)), (32, lambda a, w, y: B.arcq_mx_gemm(*a, *w, y=y))):
+        g = torch.Generator(device="cuda").manual_seed(M + N + nb)
+        a, w = operand(g, M, nb, block), operand(g, N, nb, block)
+        ref = dequantize(*a, block) @ dequantize(*w, block).t()
+        raw = torch.full((M, N + 3), 777.0, dtype=torch.float32, device="cuda")
+        gemm(a, w, raw[:, :N])
+        assert worst(raw[:, :N], ref) <= (2e-5 if block == 16 else 5e-3) and bool((raw[:, N:] == 777.0).all())
+        a1 = operand(torch.Generator(device="cuda").manual_seed(M + N + nb), M, nb, block, lead=1)
+        y = torch.empty((M, N), dtype=torch.float32, device="cuda")
+        gemm(a1, w, y)
+        assert worst(y, ref) <= (2e-5 if block == 16 else 5e-3)

@@ -357,16 +357,19 @@ def test_second_launches():
     r = B.Rest()
     assert B.lib().arcq_gemm_rest(4, 8, 40, ctypes.byref(r)) == B.BAD_SHAPE
     assert B.lib().arcq_gemm_rest(4, 8, 64, None) == B.INVALID_ARG
-    seen = 0
+    seen = [0] * 4
     for M, N, Kp in random_sizes(8, 40000, 16):
         rest = B.arcq_gemm_rest(M, N, Kp)
         if rest is None:
             continue
         kernel, rows, cols, runs, _ = B.arcq_gemm_route(M, N, Kp)
         assert Kp >= 1024 and runs == 1 and B.arcq_gemm_workspace_size(M, N, Kp) == 0
-        assert (kernel, rows, cols) in ((B.ROUTE_TILES, 256, 256), (B.ROUTE_TILES, 192, 256), (B.ROUTE_KSPLIT, 128, 128))
+        if kernel == B.ROUTE_STREAM:
+            assert M <= 32 and rest[0] == M and N - rest[1] == 16384 and cols == 64 and rest[2][0] == B.ROUTE_STREAM
+        else:
+            assert (kernel, rows, cols) in ((B.ROUTE_TILES, 256, 256), (B.ROUTE_TILES, 192, 256), (B.ROUTE_KSPLIT, 128, 128))
         assert (rest[0] == M) != (rest[1] == N) and 0 < rest[0] <= M and 0 < rest[1] <= N
         assert (M - rest[0]) % rows == 0 and (N - rest[1]) % cols == 0
-        seen += 1
-    assert seen > 200
+        seen[kernel] += 1
+    assert seen[B.ROUTE_STREAM] > 20 and seen[B.ROUTE_KSPLIT] > 50 and seen[B.ROUTE_TILES] > 100
     assert B.arcq_gemm_rest(1777, 10240, 8528)[:2] == (1777, 1024) and B.arcq_gemm_rest(8192, 8192, 29696) is None
