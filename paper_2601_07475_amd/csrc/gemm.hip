@@ -1342,14 +1342,15 @@ TimedPlan plan_by_time(int64_t M, int64_t N, int64_t Kp) {
 GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
     const GemmPlan rule = plan_by_rule(M, N, Kp);
     GemmParts best = {rule, rule, M, N};
-    // The streaming kernel with more weight rows than one round of four tiles a wave takes: that round, and the rest with as few tiles a
-    // wave as give it a round of its own.  (Four tiles a wave throughout: a second round that most of the chip has no part in.)
-    // From HBM, us: 16 x 20480 over K' = 4352 18.6 -> 16.0, over 14592 48.6 -> 39.9; 1 x 18000 over 8464 31.9 -> 25.5; 32 x 24576 over 8464
-    // 43.6 -> 39.1, 32 x 28672 45.0 -> 43.5.  Over a short K' a second launch costs what the round did: 1 x 24576 over 2176 11.5 and 11.9 (two
-    // tiles a wave), 16 x 28672 over 4352 20.2 and 20.2 (three), 16 x 16400 over 2176 10.3 and 10.8 (a few rows behind).
+    // The streaming kernel with more weight rows than one round of four tiles a wave takes: that round, and the rest with one or two
+    // tiles a wave, which gives it a round of its own.  (Four tiles a wave throughout: a second round that most of the chip has no part
+    // in.)  From HBM, us: 16 x 20480 over K' = 4352 18.6 -> 16.0, over 14592 48.6 -> 39.9; 1 x 18000 over 8464 31.9 -> 25.5; 32 x 24576 over
+    // 8464 43.6 -> 39.1.  A pass that runs the second kernel for the first time takes 5 us more, so the line lies where about that
+    // much is gained: not with three tiles a wave (32 x 28672 over 8464 45.0 -> 43.5), few rows behind the round (16 x 16400 over 4352
+    // 15.7 -> 15.5) or a shorter K' (16 x 20480 over 2176 12.0 -> 11.5, 16 x 24576 over 4352 19.1 -> 18.0).
     const int64_t behind = N - STREAM_ROUND;
-    if (rule.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind > 0 && behind <= STREAM_ROUND / 4 * 3 &&
-        Kp >= (behind > STREAM_ROUND / 2 ? 6144 : behind > STREAM_ROUND / 4 || behind < 1024 ? 4096 : 2048))
+    if (rule.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= STREAM_ROUND / 2 &&
+        Kp >= (behind > STREAM_ROUND / 4 ? 6144 : 4096))
         return {plan_stream(M, STREAM_ROUND, Kp), plan_stream(M, behind, Kp), M, STREAM_ROUND};
     if (Kp < 1024 || rule.runs > 1 || (rule.kernel != ARCQ_ROUTE_TILES && rule.kernel != ARCQ_ROUTE_KSPLIT)) return best;
     const auto of_rule = std::find_if(std::begin(TILE_TIMES), std::end(TILE_TIMES), [&](const TileTime& t) {

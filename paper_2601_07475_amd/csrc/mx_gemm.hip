@@ -747,9 +747,10 @@ arcq_status launch_mx_typed(const uint8_t* a_codes, const uint8_t* a_scales, con
     // The streaming kernel with more weight rows than one round of four tiles a wave takes: that round, and the rest with one or two tiles a
     // wave in a launch of its own (see plan_gemm_parts in gemm.hip).  From HBM, us: 16 x 20480 over K' = 4352 15.8 -> 14.1, over 8448 27.7 ->
     // 22.9, 16 x 24576 over 6400 23.2 -> 21.3.  Not worth a launch: few rows behind the round (1 x 16400 over 4352 11.0, 12.0 in two),
-    // three tiles a wave (1 x 28672 over 6400 21.6 and 22.3), a short K' (16 x 24576 over 2176 9.9 and 10.4).
+    // three tiles a wave (1 x 28672 over 6400 21.6 and 22.3), a shorter K' (16 x 24576 over 2176 9.9 and 10.4).
     const int64_t behind = N - MX_STREAM_ROUND;
-    if (plan.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= MX_STREAM_ROUND / 2 && Kp >= 4096) {
+    if (plan.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= MX_STREAM_ROUND / 2 &&
+        Kp >= (behind > MX_STREAM_ROUND / 4 ? 6144 : 4096)) {
         if (arcq_status st = launch_mx_typed(a_codes, a_scales, w_codes, w_scales, M, MX_STREAM_ROUND, Kp, y, ldy, workspace, stream)) return st;
         return launch_mx_typed(a_codes, a_scales, w_codes + MX_STREAM_ROUND * (Kp >> 1), w_scales + MX_STREAM_ROUND * (Kp >> 5), M, behind,
                                Kp, y + MX_STREAM_ROUND, ldy, workspace, stream);
