@@ -1169,7 +1169,8 @@ static double tiles_time(int64_t M, int64_t N, int64_t Kp, int runs) {
     const double fill = (double)wgs / 256.0;
     if (runs > 1) return 7.4 + ((N & 3) ? 5.3 * (0.2 + 0.8 * fill) : 0.0) + ragged + stages * 0.95 * rounds +
                          0.366e-6 * 8.0 * (double)runs * (double)M * (double)N;
-    // (values stored one by one or in pairs; the fill by itself is for fp32 results, which take these tiles 1 to 3 us longer)
+    // (N & 7: values stored one by one or in pairs, see gemm_ksplit_best; the fill by itself is for fp32 results, which take these tiles 1 to
+    // 3 us longer)
     return 4.5 + fill + ((N & 7) ? 5.0 * (0.15 * rounds + 0.85 * fill) : 0.0) + ragged + stages * (0.84 * rounds + 0.195 * fill);
 }
 static double stream_time(const GemmPlan& plan, int64_t N, int64_t Kp) {

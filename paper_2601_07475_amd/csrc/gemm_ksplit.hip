@@ -432,8 +432,8 @@ arcq_status launch_ksplit_typed(int rows, int cols, const uint8_t* a_codes, cons
 // Only tiles that cover it with at most one workgroup per compute unit (256) are looked at: with more, a second round costs
 // as much as the first; and with 32 at least, below which K' is better split across workgroups.  The time of a tile over K' is
 // start + stages (alone + shared x workgroups / 256): a workgroup takes longer the more of the chip is busy (clock, and the
-// weights' way from HBM).  Where weight rows are no multiple of four, every value is stored by itself (single, on a full
-// chip); rows off the grid of 64 have their windows of scale bytes, 0.5 us.  Fitted to 6700 problems (M = 33 .. 8000, N = 16 .. 30000, K' = 512 ..
+// weights' way from HBM).  single: what values stored one by one cost where weight rows are no multiple of four; they are stored by
+// fours now, but the rule keeps the term, whose choice from K' = 1024 on stands only where plan_gemm_parts knows nothing 5 % faster; rows off the grid of 64 have their windows of scale bytes, 0.5 us.  Fitted to 6700 problems (M = 33 .. 8000, N = 16 .. 30000, K' = 512 ..
 // 30000, weights from HBM), each path of each timed: 4 to 8 % rms.  The choice among these, the streaming kernel and the tiles
 // of gemm.hip by the modelled times is 2 % from the best of all on average, where fixed limits of 144 to 256 workgroups on five
 // tile shapes were 5 %; eleven of the 6700 are more than 4 % slower than with those limits, 1000 more than 4 % faster.
