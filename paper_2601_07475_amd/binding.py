@@ -257,7 +257,8 @@ def arcq_calib_select(colmax, perm=None, info=None):
         perm = torch.empty(K, dtype=torch.int32, device=colmax.device)
     if info is None:
         info = torch.empty(4, dtype=torch.int32, device=colmax.device)
-    S = torch.empty(1, dtype=torch.int32, pin_memory=True)      # page-locked: the kernel writes S itself
+    # page-locked: the kernel writes S itself (device named: torch's default one may be another)
+    S = torch.empty(1, dtype=torch.int32, device="cpu", pin_memory=True)
     _check(lib().arcq_calib_select(_ptr(colmax), K, _ptr(perm), _ptr(info), _ptr(S), _stream()))
     return perm, S.item(), info
 

@@ -41,6 +41,14 @@ def test_S_reaches_any_host_memory():
     assert torch.cuda.current_stream().query()
 
 
+def test_select_under_a_default_device():
+    c = torch.rand(528, device="cuda")
+    perm, S, info = B.arcq_calib_select(c)
+    with torch.device("cuda"):
+        again, S_again, info_again = B.arcq_calib_select(c)
+    assert torch.equal(perm, again) and S == S_again == info[0].item() and torch.equal(info, info_again)
+
+
 @pytest.mark.parametrize("M,K", [(1, 16), (3, 528), (33, 1008), (257, 2064)])
 def test_maxima_over_batches_that_rise_and_fall(M, K):
     g = torch.Generator(device="cuda").manual_seed(M)
