@@ -94,9 +94,12 @@ def _check(status):
 
 
 def _stream():
-    """Handle of the current device's current stream (torch.cuda.current_stream().cuda_stream, which builds a Stream object to
-    tell it: 2.7 us of the 11 that a call took on the host)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    """Handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object to tell it, 2.7 us of the 11
+    that a call took on the host; the functions below it are private to torch, so another torch may not have them."""
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):

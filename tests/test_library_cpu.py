@@ -5,8 +5,10 @@ import math
 import os
 import random
 import re
+import types
 
 import pytest
+import torch
 
 from paper_2601_07475_amd import binding as B
 
@@ -373,3 +375,14 @@ def test_second_launches():
         seen[kernel] += 1
     assert seen[B.ROUTE_STREAM] > 20 and seen[B.ROUTE_KSPLIT] > 50 and seen[B.ROUTE_TILES] > 100
     assert B.arcq_gemm_rest(1777, 10240, 8528)[:2] == (1777, 1024) and B.arcq_gemm_rest(8192, 8192, 29696) is None
+
+
+def test_stream_handle_without_torch_private_names(monkeypatch):
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1234))
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        with monkeypatch.context() as m:
+            m.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+            m.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x5678, raising=False)
+            assert B._stream() == 0x5678
+            m.delattr(torch._C, name)
+            assert B._stream() == 0x1234
