@@ -41,6 +41,20 @@ def test_S_reaches_any_host_memory():
     assert torch.cuda.current_stream().query()
 
 
+@pytest.mark.parametrize("pinned", [False, True])
+@pytest.mark.parametrize("at", [1, 2, 4])
+def test_S_at_any_address(pinned, at):
+    c = torch.rand(4096, device="cuda")
+    perm, info = torch.empty(4096, dtype=torch.int32, device="cuda"), torch.empty(4, dtype=torch.int32, device="cuda")
+    host = torch.full((16,), 0x55, dtype=torch.uint8)
+    host = host.pin_memory() if pinned else host
+    stream = torch.cuda.current_stream().cuda_stream
+    assert B.lib().arcq_calib_select(c.data_ptr(), 4096, perm.data_ptr(), info.data_ptr(), host.data_ptr() + at, stream) == B.OK
+    value = host[at:at + 4].numpy().tobytes()
+    assert int.from_bytes(value, "little") == info[0].item() > 0
+    assert bool((host[:at] == 0x55).all()) and bool((host[at + 4:] == 0x55).all())
+
+
 def test_select_under_a_default_device():
     c = torch.rand(528, device="cuda")
     perm, S, info = B.arcq_calib_select(c)
