@@ -66,6 +66,7 @@ typedef struct {
     arcq_route route;
 } arcq_rest;
 arcq_status arcq_gemm_rest(int64_t M, int64_t N, int64_t Kp, arcq_rest* rest);
+arcq_status arcq_mx_gemm_rest(int64_t M, int64_t N, int64_t Kp, int with_workspace, arcq_rest* rest);
 
 #ifdef __cplusplus
 }

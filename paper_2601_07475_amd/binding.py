@@ -61,6 +61,7 @@ SIGNATURES = {
     "arcq_gemm_route": (ctypes.c_int, [_i64, _i64, _i64, ctypes.POINTER(Route)]),
     "arcq_mx_gemm_route": (ctypes.c_int, [_i64, _i64, _i64, ctypes.c_int, ctypes.POINTER(Route)]),
     "arcq_gemm_rest": (ctypes.c_int, [_i64, _i64, _i64, ctypes.POINTER(Rest)]),
+    "arcq_mx_gemm_rest": (ctypes.c_int, [_i64, _i64, _i64, ctypes.c_int, ctypes.POINTER(Rest)]),
     "arcq_check_perm": (ctypes.c_int, [_vp, _i64, _vp, ctypes.POINTER(ctypes.c_int), _vp]),
 }
 
@@ -424,6 +425,13 @@ def arcq_gemm_rest(M, N, Kp):
     """(rows, columns, (kernel, tile rows, tile columns)) of arcq_gemm's second launch, the last of the output; None: there is none."""
     r = Rest()
     _check(lib().arcq_gemm_rest(M, N, Kp, ctypes.byref(r)))
+    return (r.rows, r.cols, (r.route.kernel, r.route.tile_rows, r.route.tile_cols)) if r.rows else None
+
+
+def arcq_mx_gemm_rest(M, N, Kp, with_workspace=False):
+    """The same for arcq_mx_gemm, with or without a workspace."""
+    r = Rest()
+    _check(lib().arcq_mx_gemm_rest(M, N, Kp, int(with_workspace), ctypes.byref(r)))
     return (r.rows, r.cols, (r.route.kernel, r.route.tile_rows, r.route.tile_cols)) if r.rows else None
 
 

@@ -205,15 +205,18 @@ arcq_status arcq_gemm_route(int64_t M, int64_t N, int64_t Kp, arcq_route* route)
     return fill_route(plan_gemm(M, N, Kp), route);
 }
 
-arcq_status arcq_gemm_rest(int64_t M, int64_t N, int64_t Kp, arcq_rest* rest) {
-    clear_error();
-    if (arcq_status st = check_gemm_shape(M, N, Kp)) return st;
-    if (!rest) return fail(ARCQ_INVALID_ARG, "null output pointer");
-    const GemmParts parts = plan_gemm_parts(M, N, Kp);
+static arcq_status fill_rest(const GemmParts& parts, int64_t M, int64_t N, arcq_rest* rest) {
     const bool two = parts.rows < M || parts.cols < N;
     rest->rows = !two ? 0 : parts.rows < M ? M - parts.rows : M;
     rest->cols = !two ? 0 : parts.cols < N ? N - parts.cols : N;
     return fill_route(parts.rest, &rest->route);
+}
+
+arcq_status arcq_gemm_rest(int64_t M, int64_t N, int64_t Kp, arcq_rest* rest) {
+    clear_error();
+    if (arcq_status st = check_gemm_shape(M, N, Kp)) return st;
+    if (!rest) return fail(ARCQ_INVALID_ARG, "null output pointer");
+    return fill_rest(plan_gemm_parts(M, N, Kp), M, N, rest);
 }
 
 // Validation shared by arcq_gemm and arcq_gemm_noalloc; *run = false when there is nothing to launch.
@@ -415,6 +418,13 @@ arcq_status arcq_mx_gemm_route(int64_t M, int64_t N, int64_t Kp, int with_worksp
     if (arcq_status st = check_mx_gemm_shape(M, N, Kp)) return st;
     if (!route) return fail(ARCQ_INVALID_ARG, "null output pointer");
     return fill_route(plan_mx_gemm(M, N, Kp, with_workspace != 0), route);
+}
+
+arcq_status arcq_mx_gemm_rest(int64_t M, int64_t N, int64_t Kp, int with_workspace, arcq_rest* rest) {
+    clear_error();
+    if (arcq_status st = check_mx_gemm_shape(M, N, Kp)) return st;
+    if (!rest) return fail(ARCQ_INVALID_ARG, "null output pointer");
+    return fill_rest(plan_mx_gemm_parts(M, N, Kp, with_workspace != 0), M, N, rest);
 }
 
 arcq_status arcq_mx_gemm_ws(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes, const uint8_t* w_scales,

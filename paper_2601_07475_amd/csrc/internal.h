@@ -58,7 +58,8 @@ struct GemmParts {
 };
 GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp);
 inline GemmPlan plan_gemm(int64_t M, int64_t N, int64_t Kp) { return plan_gemm_parts(M, N, Kp).first; }
-GemmPlan plan_mx_gemm(int64_t M, int64_t N, int64_t Kp, bool workspace);
+GemmParts plan_mx_gemm_parts(int64_t M, int64_t N, int64_t Kp, bool workspace);
+inline GemmPlan plan_mx_gemm(int64_t M, int64_t N, int64_t Kp, bool workspace) { return plan_mx_gemm_parts(M, N, Kp, workspace).first; }
 
 // Tiled kernel whose waves split every stage along k inside the workgroup (gemm_ksplit.hip): the fastest of its tiles for this
 // problem (rows = 0: none serves it), and its launch.

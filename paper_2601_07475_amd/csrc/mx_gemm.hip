@@ -709,18 +709,20 @@ static int mx_wide_rows(int64_t M, int64_t N) {
     return cost(256) <= cost(192) && cost(256) <= cost(128) ? 256 : cost(192) <= cost(128) ? 192 : 128;
 }
 
-GemmPlan plan_mx_gemm(int64_t M, int64_t N, int64_t Kp, bool workspace) {
+static GemmPlan plan_mx_stream(int64_t M, int64_t N) {
+    // weight tiles per wave: as few as keep the launch at one workgroup per compute unit, up to four, two with more than 32
+    // rows (measured with weights from HBM, 32 rows: 640 tiles 14.8 us with three per wave against 21.7 with one, 896 tiles
+    // 10.4 us with four against 13.0 with two, 320 tiles over K' = 8448 11.2 us with two against 15.2 with one)
+    const int64_t tiles = (N + 15) / 16;
+    const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+    const int nt = tiles <= 256 ? 1 : tiles <= 512 || mt > 2 ? 2 : tiles <= 768 ? 3 : 4;
+    return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, false};
+}
+
+static GemmPlan plan_mx_one(int64_t M, int64_t N, int64_t Kp, bool workspace) {
     const int64_t nb = Kp >> 5;
     // up to 64 rows the tiled kernels only win where they can split K' across workgroups, which needs the workspace
-    if (mx_streaming_shape(M, N, Kp) || (M <= 64 && !workspace && mx_split_k(M, N, Kp) > 1)) {
-        // weight tiles per wave: as few as keep the launch at one workgroup per compute unit, up to four, two with more than 32
-        // rows (measured with weights from HBM, 32 rows: 640 tiles 14.8 us with three per wave against 21.7 with one, 896 tiles
-        // 10.4 us with four against 13.0 with two, 320 tiles over K' = 8448 11.2 us with two against 15.2 with one)
-        const int64_t tiles = (N + 15) / 16;
-        const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
-        const int nt = tiles <= 256 ? 1 : tiles <= 512 || mt > 2 ? 2 : tiles <= 768 ? 3 : 4;
-        return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, false};
-    }
+    if (mx_streaming_shape(M, N, Kp) || (M <= 64 && !workspace && mx_split_k(M, N, Kp) > 1)) return plan_mx_stream(M, N);
     const bool offsets_fit = (uint64_t)M * (uint64_t)nb * 16 < 0xFFFF0000ull && (uint64_t)N * (uint64_t)nb * 16 < 0xFFFF0000ull;
     if (!offsets_fit || (nb < 8 && nb != 4)) return {ARCQ_ROUTE_DIRECT, 128, 128, 1, false};
     // more than 256 tiles of 128 x 128 but at most 256 of 192 x 128: one round of the taller tile instead of two
@@ -732,29 +734,30 @@ GemmPlan plan_mx_gemm(int64_t M, int64_t N, int64_t Kp, bool workspace) {
     return {ARCQ_ROUTE_TILES, 128, 128, workspace ? mx_split_k(M, N, Kp) : 1, false};
 }
 
-namespace {
-
 constexpr int64_t MX_STREAM_ROUND = 256 * 64;       // weight rows: a workgroup of eight waves x four tiles on every compute unit
 
-template <typename OutT>
-arcq_status launch_mx_typed(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
-                            const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, OutT* y, int64_t ldy,
-                            float* workspace, hipStream_t stream) {
-    const int nb = (int)(Kp >> 5);
-    const bool dword_scales = ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
-    const bool aligned16 = ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 && dword_scales;
-    const GemmPlan plan = plan_mx_gemm(M, N, Kp, workspace != nullptr);
+GemmParts plan_mx_gemm_parts(int64_t M, int64_t N, int64_t Kp, bool workspace) {
+    const GemmPlan one = plan_mx_one(M, N, Kp, workspace);
     // The streaming kernel with more weight rows than one round of four tiles a wave takes: that round, and the rest with one or two tiles a
     // wave in a launch of its own (see plan_gemm_parts in gemm.hip).  From HBM, us: 16 x 20480 over K' = 4352 15.8 -> 14.1, over 8448 27.7 ->
     // 22.9, 16 x 24576 over 6400 23.2 -> 21.3.  Not worth a launch: few rows behind the round (1 x 16400 over 4352 11.0, 12.0 in two),
     // three tiles a wave (1 x 28672 over 6400 21.6 and 22.3), a shorter K' (16 x 24576 over 2176 9.9 and 10.4).
     const int64_t behind = N - MX_STREAM_ROUND;
-    if (plan.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= MX_STREAM_ROUND / 2 &&
-        Kp >= (behind > MX_STREAM_ROUND / 4 ? 6144 : 4096)) {
-        if (arcq_status st = launch_mx_typed(a_codes, a_scales, w_codes, w_scales, M, MX_STREAM_ROUND, Kp, y, ldy, workspace, stream)) return st;
-        return launch_mx_typed(a_codes, a_scales, w_codes + MX_STREAM_ROUND * (Kp >> 1), w_scales + MX_STREAM_ROUND * (Kp >> 5), M, behind,
-                               Kp, y + MX_STREAM_ROUND, ldy, workspace, stream);
-    }
+    if (one.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= MX_STREAM_ROUND / 2 &&
+        Kp >= (behind > MX_STREAM_ROUND / 4 ? 6144 : 4096))
+        return {plan_mx_stream(M, MX_STREAM_ROUND), plan_mx_stream(M, behind), M, MX_STREAM_ROUND};
+    return {one, one, M, N};
+}
+
+namespace {
+
+template <typename OutT>
+arcq_status launch_mx_plan(const GemmPlan& plan, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
+                           const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, OutT* y, int64_t ldy,
+                           float* workspace, hipStream_t stream) {
+    const int nb = (int)(Kp >> 5);
+    const bool dword_scales = ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
+    const bool aligned16 = ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 && dword_scales;
     if (plan.kernel == ARCQ_ROUTE_STREAM) {
 #define ARCQ_MX_STREAM(MT_, NT_, U_)                    \
     if (plan.rows == 16 * MT_ && plan.cols == 16 * NT_) \
@@ -800,6 +803,17 @@ arcq_status launch_mx_typed(const uint8_t* a_codes, const uint8_t* a_scales, con
     hipLaunchKernelGGL(mx_gemm_direct_kernel<OutT>, grid, dim3(256), 0, stream, a_codes, a_scales, w_codes, w_scales,
                        (int)M, (int)N, nb, y, ldy);
     return check_launch("mx_gemm_direct_kernel");
+}
+
+template <typename OutT>
+arcq_status launch_mx_typed(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
+                            const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, OutT* y, int64_t ldy,
+                            float* workspace, hipStream_t stream) {
+    const GemmParts parts = plan_mx_gemm_parts(M, N, Kp, workspace != nullptr);
+    if (arcq_status st = launch_mx_plan(parts.first, a_codes, a_scales, w_codes, w_scales, M, parts.cols, Kp, y, ldy, workspace, stream)) return st;
+    if (parts.cols == N) return ARCQ_OK;
+    return launch_mx_plan(parts.rest, a_codes, a_scales, w_codes + parts.cols * (Kp >> 1), w_scales + parts.cols * (Kp >> 5), M,
+                          N - parts.cols, Kp, y + parts.cols, ldy, nullptr, stream);
 }
 
 }  // namespace

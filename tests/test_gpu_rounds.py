@@ -82,18 +82,30 @@ def test_one_launch_by_time(route, M, N, nb):
 
 
 # the streaming kernels with more weight rows than a round takes: one and two tiles a wave behind it, ragged rows and edges
+def streamed(M, N, nb, block, gemm):
+    g = torch.Generator(device="cuda").manual_seed(M + N + nb)
+    a, w = operand(g, M, nb, block), operand(g, N, nb, block)
+    ref = dequantize(*a, block) @ dequantize(*w, block).t()
+    raw = torch.full((M, N + 3), 777.0, dtype=torch.float32, device="cuda")
+    gemm(a, w, raw[:, :N])
+    assert worst(raw[:, :N], ref) <= (2e-5 if block == 16 else 5e-3) and bool((raw[:, N:] == 777.0).all())
+    a1 = operand(torch.Generator(device="cuda").manual_seed(M + N + nb), M, nb, block, lead=1)
+    y = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    gemm(a1, w, y)
+    assert worst(y, ref) <= (2e-5 if block == 16 else 5e-3)
+
+
 @pytest.mark.parametrize("M,N,nb", [(1, 17408, 256), (16, 20479, 258), (13, 17500, 257), (32, 20481, 385), (7, 24576, 384), (31, 24571, 386)])
 def test_streaming_in_two_launches(M, N, nb):
-    rows, cols, rest = B.arcq_gemm_rest(M, N, nb * 16)
-    assert (rows, cols, rest[0]) == (M, N - 16384, B.ROUTE_STREAM)
-    for block, gemm in ((16, lambda a, w, y: B.arcq_gemm(*a, 1.0, *w, 1.0, y=y)), (32, lambda a, w, y: B.arcq_mx_gemm(*a, *w, y=y))):
-        g = torch.Generator(device="cuda").manual_seed(M + N + nb)
-        a, w = operand(g, M, nb, block), operand(g, N, nb, block)
-        ref = dequantize(*a, block) @ dequantize(*w, block).t()
-        raw = torch.full((M, N + 3), 777.0, dtype=torch.float32, device="cuda")
-        gemm(a, w, raw[:, :N])
-        assert worst(raw[:, :N], ref) <= (2e-5 if block == 16 else 5e-3) and bool((raw[:, N:] == 777.0).all())
-        a1 = operand(torch.Generator(device="cuda").manual_seed(M + N + nb), M, nb, block, lead=1)
-        y = torch.empty((M, N), dtype=torch.float32, device="cuda")
-        gemm(a1, w, y)
-        assert worst(y, ref) <= (2e-5 if block == 16 else 5e-3)
+    cols = 16 if N - 16384 <= 4096 else 32
+    assert B.arcq_gemm_rest(M, N, nb * 16) == (M, N - 16384, (B.ROUTE_STREAM, 16 if M <= 16 else 32, cols))
+    streamed(M, N, nb, 16, lambda a, w, y: B.arcq_gemm(*a, 1.0, *w, 1.0, y=y))
+
+
+# (32 x 20481 over 12832 streams only where no workspace lets tiles split K')
+@pytest.mark.parametrize("M,N,nb", [(1, 17408, 128), (16, 20479, 129), (13, 17500, 257), (7, 24576, 192), (16, 24571, 193), (17, 17500, 128),
+                                    (20, 20480, 175), (32, 20479, 129), (32, 20481, 401)])
+def test_mx_streaming_in_two_launches(M, N, nb):
+    cols = 16 if N - 16384 <= 4096 else 32
+    assert B.arcq_mx_gemm_rest(M, N, nb * 32) == (M, N - 16384, (B.ROUTE_STREAM, 16 if M <= 16 else 32, cols))
+    streamed(M, N, nb, 32, lambda a, w, y: B.arcq_mx_gemm(*a, *w, y=y))

@@ -377,6 +377,29 @@ def test_second_launches():
     assert B.arcq_gemm_rest(1777, 10240, 8528)[:2] == (1777, 1024) and B.arcq_gemm_rest(8192, 8192, 29696) is None
 
 
+def test_mx_second_launches():
+    r = B.Rest()
+    assert B.lib().arcq_mx_gemm_rest(4, 8, 48, 0, ctypes.byref(r)) == B.BAD_SHAPE
+    assert B.lib().arcq_mx_gemm_rest(4, 8, 64, 0, None) == B.INVALID_ARG
+    # the smallest and largest number of weight rows behind the round, and the shortest K' for one and for two tiles a wave
+    for M in (1, 16, 17, 32):
+        for N, Kp, two in ((17408, 4096, True), (17407, 4096, False), (17408, 4064, False), (20480, 4096, True), (20481, 4096, False),
+                           (24577, 4096, False)):
+            rest = B.arcq_mx_gemm_rest(M, N, Kp)
+            assert B.arcq_mx_gemm_route(M, N, Kp)[0] == B.ROUTE_STREAM
+            assert rest == ((M, N - 16384, (B.ROUTE_STREAM, 16 if M <= 16 else 32, 16)) if two else None), (M, N, Kp)
+    for M in (1, 16):
+        assert B.arcq_mx_gemm_route(M, 20481, 6112)[0] == B.ROUTE_STREAM and B.arcq_mx_gemm_rest(M, 20481, 6112) is None
+        assert B.arcq_mx_gemm_rest(M, 20481, 6144) == (M, 4097, (B.ROUTE_STREAM, 16, 32))
+        assert B.arcq_mx_gemm_rest(M, 24576, 6144) == (M, 8192, (B.ROUTE_STREAM, 16, 32))
+        assert B.arcq_mx_gemm_rest(M, 24577, 6144) is None
+    assert B.arcq_mx_gemm_rest(32, 20481, 12832) == (32, 4097, (B.ROUTE_STREAM, 32, 32))        # without a workspace only
+    assert B.arcq_mx_gemm_rest(32, 20481, 12832, True) is None
+    # never off the streaming kernel
+    assert all(B.arcq_mx_gemm_rest(M, N, Kp, ws) is None or B.arcq_mx_gemm_route(M, N, Kp, ws)[0] == B.ROUTE_STREAM
+               for M, N, Kp in random_sizes(9, 20000, 32) for ws in (False, True))
+
+
 def test_stream_handle_without_torch_private_names(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1234))
     for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
