@@ -1310,17 +1310,27 @@ double tile_time(const TileTime& t, int64_t M, int64_t N, int64_t Kp) {
            ((Kp & 63) ? rounds * (t.ragged_round + stages * t.ragged_stage) : 0.0);
 }
 
+// Chains that an output's products over K' are added up in, before those are added to each other: one for each wave of a workgroup that
+// takes a share of K'.  Fewer and longer ones round more (fp32 against 64 bits, 3573 x 6744 over K' = 7472: 1.17e-7 with pairs of waves on 128 x 256
+// tiles, 1.80e-7 on 256 x 256).  at_least: of 128 x 256 tiles, which have pairs or not by the operands' alignment where K' is 64 mod 128.
+int sum_chains(int kernel, int rows, int cols, int64_t Kp, bool at_least) {
+    if (kernel == ARCQ_ROUTE_STREAM) return rows == 128 && cols == 32 ? 4 : 8;
+    if (kernel == ARCQ_ROUTE_KSPLIT) return 4;
+    return rows == 128 && cols == 256 && !(at_least && (Kp & 127) == 64) ? 2 : 1;
+}
+
 struct TimedPlan {
     GemmPlan plan;
     double us;
 };
 
-// The tile that takes the least modelled time, or the streaming kernel; no workspace.
-TimedPlan plan_by_time(int64_t M, int64_t N, int64_t Kp) {
+// The tile that takes the least modelled time among those with that many chains, or the streaming kernel; no workspace.
+TimedPlan plan_by_time(int64_t M, int64_t N, int64_t Kp, int chains) {
     const GemmPlan stream = plan_stream(M, N, Kp);
     if (M <= 32) return {stream, 4.0 + (M <= 16 ? 0.115e-6 : 0.165e-6) * (double)N * (double)Kp};     // (nothing else is ever faster)
     TimedPlan best = {stream, M <= 128 ? stream_time(stream, N, Kp) : 1e30};
     for (const TileTime& t : TILE_TIMES) {
+        if (sum_chains(t.kernel, t.rows, t.cols, Kp, true) < chains) continue;
         // 96 x 128 tiles that pad more rows than 128 x 128: see gemm_ksplit_best
         if (t.rows == 96 && t.cols == 128 && (M + 95) / 96 * 96 > (M + 127) / 128 * 128) continue;
         // Small tiles in more than one round are not what the model says where many of them share a compute unit over a long K'
@@ -1358,7 +1368,9 @@ GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
         return t.kernel == rule.kernel && t.rows == rule.rows && t.cols == rule.cols;
     });
     const double rule_us = tile_time(*of_rule, M, N, Kp);
-    const TimedPlan one = plan_by_time(M, N, Kp);
+    // (not for the price of precision: neither launch adds up K' in fewer chains than the rule's kernel)
+    const int chains = sum_chains(rule.kernel, rule.rows, rule.cols, Kp, false);
+    const TimedPlan one = plan_by_time(M, N, Kp, chains);
     double us = rule_us;
     if (one.us < 0.95 * rule_us) {
         best.first = best.rest = one.plan;
@@ -1367,6 +1379,7 @@ GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
     us *= 0.97;
     const double stages = (double)Kp / 128.0;
     for (const TileTime& t : TILE_TIMES) {
+        if (sum_chains(t.kernel, t.rows, t.cols, Kp, true) < chains) continue;
         // (128 x 256 and 192 x 128 tiles in front gain nothing on average: 0.97 to 1.06x)
         if (!(t.cols == 256 && t.rows >= 192) && !(t.kernel == ARCQ_ROUTE_KSPLIT && t.rows == 128 && t.cols == 128)) continue;
         const int64_t tm = (M + t.rows - 1) / t.rows, tn = (N + t.cols - 1) / t.cols, most = tm * tn / 256;
@@ -1375,7 +1388,7 @@ GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
                 const double first = tile_time(t, rows, cols, Kp);
                 // no tile computes 65536 outputs per compute unit and stage in less than 3 us
                 if (first + 5.0 + stages * 3.0 * (double)rest_rows * (double)rest_cols / (65536.0 * 256.0) >= us) return;
-                const TimedPlan rest = plan_by_time(rest_rows, rest_cols, Kp);
+                const TimedPlan rest = plan_by_time(rest_rows, rest_cols, Kp, chains);
                 if (first + rest.us + 3.0 >= us) return;
                 us = first + rest.us + 3.0;
                 best = {{t.kernel, t.rows, t.cols, 1, false}, rest.plan, rows, cols};

@@ -377,6 +377,19 @@ def test_second_launches():
     assert B.arcq_gemm_rest(1777, 10240, 8528)[:2] == (1777, 1024) and B.arcq_gemm_rest(8192, 8192, 29696) is None
 
 
+# sizes whose tiles by rule share K' out to the waves of a workgroup (128 x 256 tiles to pairs, k-split tiles to four) and whose modelled
+# times are in favour of tiles that do not
+@pytest.mark.parametrize("M,N,Kp,chains", [(3573, 6744, 7472, 2), (2627, 5990, 6128, 2), (541, 25166, 11760, 2), (519, 24363, 9936, 2), (566, 23804, 15120, 2),
+                                           (967, 22693, 13920, 2), (2079, 7428, 7552, 2), (2837, 5561, 4560, 2), (521, 6084, 1328, 4),
+                                           (2168, 1468, 1392, 4), (249, 12300, 1120, 4)])
+def test_no_precision_for_speed(M, N, Kp, chains):
+    """Neither launch adds K' up in fewer chains than the tiles of the rule."""
+    rest = B.arcq_gemm_rest(M, N, Kp)
+    for kernel, rows, cols in [B.arcq_gemm_route(M, N, Kp)[:3]] + ([rest[2]] if rest else []):
+        has = {B.ROUTE_STREAM: 4 if rows == 128 else 8, B.ROUTE_KSPLIT: 4, B.ROUTE_TILES: 2 if (rows, cols) == (128, 256) else 1}[kernel]
+        assert has >= chains, (kernel, rows, cols)
+
+
 def test_mx_second_launches():
     r = B.Rest()
     assert B.lib().arcq_mx_gemm_rest(4, 8, 48, 0, ctypes.byref(r)) == B.BAD_SHAPE
