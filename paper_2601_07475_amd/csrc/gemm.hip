@@ -1223,7 +1223,7 @@ static GemmPlan plan_stream(int64_t M, int64_t N, int64_t Kp) {
     else if (mt == 4) ahead = M > 48 ? ngroup >= 12 : ngroup % STREAM_WAVES == 0;
     else if (nt >= 3) ahead = ngroup >= 11 && ngroup % STREAM_WAVES != 1;
     else ahead = mt < 4 && mt * nt != 1 && (mt * nt == 2 || ngroup >= 10);
-    return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, ahead};
+    return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, ahead, mt * nt <= 2 ? 2 : 1};
 }
 
 // Which kernel serves a problem by rule: a function of the shape alone, so that the workspace a caller sizes beforehand matches what the
@@ -1361,8 +1361,11 @@ GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
     // 15.7 -> 15.5) or a shorter K' (16 x 20480 over 2176 12.0 -> 11.5, 16 x 24576 over 4352 19.1 -> 18.0).
     const int64_t behind = N - STREAM_ROUND;
     if (rule.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= STREAM_ROUND / 2 &&
-        Kp >= (behind > STREAM_ROUND / 4 ? 6144 : 4096))
-        return {plan_stream(M, STREAM_ROUND, Kp), plan_stream(M, behind, Kp), M, STREAM_ROUND};
+        Kp >= (behind > STREAM_ROUND / 4 ? 6144 : 4096)) {
+        GemmParts parts = {plan_stream(M, STREAM_ROUND, Kp), plan_stream(M, behind, Kp), M, STREAM_ROUND};
+        parts.rest.chunks = 1;      // K' in the order of four tiles a wave: the same bits as in one launch
+        return parts;
+    }
     if (Kp < 1024 || rule.runs > 1 || (rule.kernel != ARCQ_ROUTE_TILES && rule.kernel != ARCQ_ROUTE_KSPLIT)) return best;
     const auto of_rule = std::find_if(std::begin(TILE_TIMES), std::end(TILE_TIMES), [&](const TileTime& t) {
         return t.kernel == rule.kernel && t.rows == rule.rows && t.cols == rule.cols;
@@ -1413,7 +1416,7 @@ arcq_status launch_plan(const GemmPlan& plan, const uint8_t* a_codes, const uint
     if (plan.kernel == ARCQ_ROUTE_STREAM) {
         // (the variants that exist: plan_stream)
 #define ARCQ_STREAM(MT_, NT_, W_, U_, AHEAD_)                                                                                   \
-    if (plan.rows == 16 * MT_ && plan.cols == 16 * NT_ && plan.ahead == AHEAD_)                                                 \
+    if (plan.rows == 16 * MT_ && plan.cols == 16 * NT_ && plan.chunks == U_ && plan.ahead == AHEAD_)                            \
     return launch_skinny<MT_, NT_, W_, U_, (MT_ <= 4), AHEAD_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, \
                                                                y, ldy, stream)
         ARCQ_STREAM(1, 1, STREAM_WAVES, 2, false);
@@ -1436,8 +1439,13 @@ arcq_status launch_plan(const GemmPlan& plan, const uint8_t* a_codes, const uint
         ARCQ_STREAM(4, 2, STREAM_WAVES, 1, true);
         ARCQ_STREAM(8, 1, STREAM_WAVES, 1, false);
         ARCQ_STREAM(8, 2, 4, 1, false);
+        // the second launch of two
+        ARCQ_STREAM(1, 1, STREAM_WAVES, 1, false);
+        ARCQ_STREAM(1, 1, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(1, 2, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(2, 1, STREAM_WAVES, 1, true);
 #undef ARCQ_STREAM
-        return fail(ARCQ_HIP_ERROR, "no weight-streaming kernel of %d x %d rows, ahead %d", plan.rows, plan.cols, (int)plan.ahead);
+        return fail(ARCQ_HIP_ERROR, "no weight-streaming kernel of %d x %d rows, %d chunks, ahead %d", plan.rows, plan.cols, plan.chunks, (int)plan.ahead);
     }
     if (plan.kernel == ARCQ_ROUTE_KSPLIT)
         return launch_gemm_ksplit(plan.rows, plan.cols, a_codes, a_scales, w_codes, w_scales, M, N, Kp, alpha, y,

@@ -49,6 +49,7 @@ struct GemmPlan {
     int rows, cols;     // activation and weight rows of a workgroup's tile
     int runs;           // runs of K' across workgroups (ARCQ_ROUTE_TILES)
     bool ahead;         // ARCQ_ROUTE_STREAM: a wave asks for its next group of chunks while it computes one
+    int chunks = 1;     // ARCQ_ROUTE_STREAM: left-over chunks (behind the last group) that a wave takes at a time
 };
 // A problem in one launch, or in two: whole rounds of large tiles over the first `rows` activation rows or the first `cols` weight
 // rows, and the others on whatever is fastest for them.

@@ -716,7 +716,7 @@ static GemmPlan plan_mx_stream(int64_t M, int64_t N) {
     const int64_t tiles = (N + 15) / 16;
     const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
     const int nt = tiles <= 256 ? 1 : tiles <= 512 || mt > 2 ? 2 : tiles <= 768 ? 3 : 4;
-    return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, false};
+    return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, false, mt * nt <= 2 ? 2 : 1};
 }
 
 static GemmPlan plan_mx_one(int64_t M, int64_t N, int64_t Kp, bool workspace) {
@@ -744,8 +744,11 @@ GemmParts plan_mx_gemm_parts(int64_t M, int64_t N, int64_t Kp, bool workspace) {
     // three tiles a wave (1 x 28672 over 6400 21.6 and 22.3), a shorter K' (16 x 24576 over 2176 9.9 and 10.4).
     const int64_t behind = N - MX_STREAM_ROUND;
     if (one.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= MX_STREAM_ROUND / 2 &&
-        Kp >= (behind > MX_STREAM_ROUND / 4 ? 6144 : 4096))
-        return {plan_mx_stream(M, MX_STREAM_ROUND), plan_mx_stream(M, behind), M, MX_STREAM_ROUND};
+        Kp >= (behind > MX_STREAM_ROUND / 4 ? 6144 : 4096)) {
+        GemmParts parts = {plan_mx_stream(M, MX_STREAM_ROUND), plan_mx_stream(M, behind), M, MX_STREAM_ROUND};
+        parts.rest.chunks = 1;      // K' in the order of four tiles a wave: the same bits as in one launch
+        return parts;
+    }
     return {one, one, M, N};
 }
 
@@ -759,8 +762,8 @@ arcq_status launch_mx_plan(const GemmPlan& plan, const uint8_t* a_codes, const u
     const bool dword_scales = ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
     const bool aligned16 = ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 && dword_scales;
     if (plan.kernel == ARCQ_ROUTE_STREAM) {
-#define ARCQ_MX_STREAM(MT_, NT_, U_)                    \
-    if (plan.rows == 16 * MT_ && plan.cols == 16 * NT_) \
+#define ARCQ_MX_STREAM(MT_, NT_, U_)                                           \
+    if (plan.rows == 16 * MT_ && plan.cols == 16 * NT_ && plan.chunks == U_) \
     return launch_mx_skinny<MT_, NT_, 8, U_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream)
         ARCQ_MX_STREAM(1, 1, 2);
         ARCQ_MX_STREAM(1, 2, 2);
@@ -772,8 +775,12 @@ arcq_status launch_mx_plan(const GemmPlan& plan, const uint8_t* a_codes, const u
         ARCQ_MX_STREAM(2, 4, 1);
         ARCQ_MX_STREAM(4, 1, 1);
         ARCQ_MX_STREAM(4, 2, 1);
+        // the second launch of two
+        ARCQ_MX_STREAM(1, 1, 1);
+        ARCQ_MX_STREAM(1, 2, 1);
+        ARCQ_MX_STREAM(2, 1, 1);
 #undef ARCQ_MX_STREAM
-        return fail(ARCQ_HIP_ERROR, "no weight-streaming kernel of %d x %d rows", plan.rows, plan.cols);
+        return fail(ARCQ_HIP_ERROR, "no weight-streaming kernel of %d x %d rows, %d chunks", plan.rows, plan.cols, plan.chunks);
     }
     // How the units get into LDS: whole aligned pieces; any K' (a multiple of 32) from 512 on, codes at their minimum alignment;
     // through registers, for scale bytes at odd addresses and short K' (no 192 x 128 tiles there)

@@ -109,3 +109,18 @@ def test_mx_streaming_in_two_launches(M, N, nb):
     cols = 16 if N - 16384 <= 4096 else 32
     assert B.arcq_mx_gemm_rest(M, N, nb * 32) == (M, N - 16384, (B.ROUTE_STREAM, 16 if M <= 16 else 32, cols))
     streamed(M, N, nb, 32, lambda a, w, y: B.arcq_mx_gemm(*a, *w, y=y))
+
+
+# two left-over chunks of K' and more: an output's sum has the order, and so the bits, that it has in one launch of four tiles a wave
+@pytest.mark.parametrize("M,N,Kp", [(1, 18432, 4352), (16, 20480, 4480), (16, 20480, 8448), (16, 22000, 6400), (17, 17500, 4352), (32, 20480, 4480), (32, 24576, 6400)])
+@pytest.mark.parametrize("block", [16, 32])
+def test_streaming_in_two_launches_is_the_same_sum(M, N, Kp, block):
+    gemm, rest = ((lambda a, w: B.arcq_gemm(*a, 1.0, *w, 1.0, out_dtype=torch.float32), B.arcq_gemm_rest) if block == 16 else
+                  (lambda a, w: B.arcq_mx_gemm(*a, *w, out_dtype=torch.float32), B.arcq_mx_gemm_rest))
+    whole = 24640
+    if block == 32:                     # longer ones run tiles
+        Kp, N = (min(Kp, 6400), N) if M <= 16 else (min(Kp, 4480), min(N, 20480))
+    assert rest(M, N, Kp)[2][0] == B.ROUTE_STREAM and rest(M, whole, Kp) is None
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    a, w = operand(g, M, Kp // block, block), operand(g, whole, Kp // block, block)
+    assert torch.equal(gemm(a, (w[0][:N], w[1][:N])), gemm(a, w)[:, :N])
