@@ -68,6 +68,12 @@ typedef struct {
 arcq_status arcq_gemm_rest(int64_t M, int64_t N, int64_t Kp, arcq_rest* rest);
 arcq_status arcq_mx_gemm_rest(int64_t M, int64_t N, int64_t Kp, int with_workspace, arcq_rest* rest);
 
+/*
+ * The order in which the tiled kernels deal tiles to workgroups, as the kernels compute it: workgroup i of a launch over
+ * tiles_m x tiles_n tiles (both at least 1, at most 2^20 together) takes tile (rows[i], cols[i]).  Host only, for tests.
+ */
+arcq_status arcq_tile_order(int64_t tiles_m, int64_t tiles_n, int32_t* rows, int32_t* cols);
+
 #ifdef __cplusplus
 }
 #endif

@@ -62,6 +62,7 @@ SIGNATURES = {
     "arcq_mx_gemm_route": (ctypes.c_int, [_i64, _i64, _i64, ctypes.c_int, ctypes.POINTER(Route)]),
     "arcq_gemm_rest": (ctypes.c_int, [_i64, _i64, _i64, ctypes.POINTER(Rest)]),
     "arcq_mx_gemm_rest": (ctypes.c_int, [_i64, _i64, _i64, ctypes.c_int, ctypes.POINTER(Rest)]),
+    "arcq_tile_order": (ctypes.c_int, [_i64, _i64, _vp, _vp]),
     "arcq_check_perm": (ctypes.c_int, [_vp, _i64, _vp, ctypes.POINTER(ctypes.c_int), _vp]),
 }
 
@@ -426,6 +427,13 @@ def arcq_gemm_rest(M, N, Kp):
     r = Rest()
     _check(lib().arcq_gemm_rest(M, N, Kp, ctypes.byref(r)))
     return (r.rows, r.cols, (r.route.kernel, r.route.tile_rows, r.route.tile_cols)) if r.rows else None
+
+
+def arcq_tile_order(tiles_m, tiles_n):
+    """(tile row, tile column) of every workgroup of a tiled GEMM; no GPU needed."""
+    rows, cols = (torch.empty(tiles_m * tiles_n, dtype=torch.int32, device="cpu") for _ in range(2))
+    _check(lib().arcq_tile_order(tiles_m, tiles_n, _ptr(rows), _ptr(cols)))
+    return list(zip(rows.tolist(), cols.tolist()))
 
 
 def arcq_mx_gemm_rest(M, N, Kp, with_workspace=False):

@@ -1,5 +1,6 @@
 // C entry points of libarcq: argument validation (before any HIP call), then launch.
 #include "internal.h"
+#include "tile_order.h"
 
 #include <cmath>
 #include <cstdarg>
@@ -217,6 +218,20 @@ arcq_status arcq_gemm_rest(int64_t M, int64_t N, int64_t Kp, arcq_rest* rest) {
     if (arcq_status st = check_gemm_shape(M, N, Kp)) return st;
     if (!rest) return fail(ARCQ_INVALID_ARG, "null output pointer");
     return fill_rest(plan_gemm_parts(M, N, Kp), M, N, rest);
+}
+
+arcq_status arcq_tile_order(int64_t tiles_m, int64_t tiles_n, int32_t* rows, int32_t* cols) {
+    clear_error();
+    if (tiles_m < 1 || tiles_n < 1 || tiles_m > (1 << 20) || tiles_n > (1 << 20) / tiles_m)
+        return fail(ARCQ_BAD_SHAPE, "arcq_tile_order: %lld x %lld tiles", (long long)tiles_m, (long long)tiles_n);
+    if (!rows || !cols) return fail(ARCQ_INVALID_ARG, "null output pointer");
+    const int group_rows = tile_group_rows((int)tiles_m, (int)tiles_n);
+    for (int wg = 0; wg < (int)(tiles_m * tiles_n); ++wg) {
+        const TileOrder tile(wg, (int)tiles_m, (int)tiles_n, group_rows);
+        rows[wg] = tile.m;
+        cols[wg] = tile.n;
+    }
+    return ARCQ_OK;
 }
 
 // Validation shared by arcq_gemm and arcq_gemm_noalloc; *run = false when there is nothing to launch.

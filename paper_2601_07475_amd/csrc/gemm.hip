@@ -198,7 +198,7 @@ template <int WM, int WN, int GM, int GN, typename OutT, int MODE = COPIES>
 __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N,
-    int nbk, float alpha, OutT* __restrict__ y, int64_t ldy, int tiles_m, int tiles_n, int splits,
+    int nbk, float alpha, OutT* __restrict__ y, int64_t ldy, int tiles_m, int tiles_n, int group_rows, int splits,
     int64_t split_stride) {
     using C = StagedCfg<WM, WN, GM, GN, MODE>;
     constexpr bool REG = MODE == REGS, RAG = MODE == RAGGED;
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
     // y + split * split_stride (a reduction kernel adds the partial results).
     const int num_tiles = tiles_m * tiles_n;
     const int split = (int)blockIdx.x / num_tiles;
-    const TileOrder tile((int)blockIdx.x - split * num_tiles, tiles_m, tiles_n);
+    const TileOrder tile((int)blockIdx.x - split * num_tiles, tiles_m, tiles_n, group_rows);
     const int tile_m = tile.m, tile_n = tile.n;
 
     const int tid = threadIdx.x;
@@ -524,14 +524,14 @@ template <typename OutT, int MODE>
 __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N,
-    int nbk, float alpha, OutT* __restrict__ y, int64_t ldy, int tiles_m, int tiles_n) {
+    int nbk, float alpha, OutT* __restrict__ y, int64_t ldy, int tiles_m, int tiles_n, int group_rows) {
     using C = StagedCfg<2, 2, 2, 4, MODE>;
     constexpr bool RAG = MODE == RAGGED;
     constexpr int WM = 2, WN = 4;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     // workgroup -> tile: tile_order.h
-    const TileOrder tile((int)blockIdx.x, tiles_m, tiles_n);
+    const TileOrder tile((int)blockIdx.x, tiles_m, tiles_n, group_rows);
     const int tile_m = tile.m, tile_n = tile.n;
 
     const int tid = threadIdx.x;
@@ -796,7 +796,7 @@ arcq_status launch_staged(const uint8_t* a_codes, const uint8_t* a_scales, const
         if (arcq_status st = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_raised)) return st;
         const int64_t stride = (int64_t)M * N;
         hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * splits), dim3(C::NT), C::LDS_BYTES, stream, a_codes, a_scales,
-                           w_codes, w_scales, M, N, nbk, 1.0f, partial, (int64_t)N, tiles_m, tiles_n, splits, stride);
+                           w_codes, w_scales, M, N, nbk, 1.0f, partial, (int64_t)N, tiles_m, tiles_n, tile_group_rows(tiles_m, tiles_n), splits, stride);
         if (arcq_status st = check_launch("gemm_staged_kernel (split K)")) return st;
         return launch_splitk_reduce(partial, splits, M, N, alpha, y, std::is_same<OutT, _Float16>::value ? ARCQ_DTYPE_F16 : ARCQ_DTYPE_F32,
                                     ldy, stream);
@@ -805,7 +805,7 @@ arcq_status launch_staged(const uint8_t* a_codes, const uint8_t* a_scales, const
     static std::atomic<uint64_t> lds_raised{0};
     if (arcq_status st = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_raised)) return st;
     hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(C::NT), C::LDS_BYTES, stream, a_codes, a_scales, w_codes,
-                       w_scales, M, N, nbk, alpha, y, ldy, tiles_m, tiles_n, 1, (int64_t)0);
+                       w_scales, M, N, nbk, alpha, y, ldy, tiles_m, tiles_n, tile_group_rows(tiles_m, tiles_n), 1, (int64_t)0);
     return check_launch("gemm_staged_kernel");
 }
 
@@ -818,7 +818,7 @@ arcq_status launch_kpair(const uint8_t* a_codes, const uint8_t* a_scales, const 
     if (arcq_status st = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_raised)) return st;
     const int tiles_m = (M + 127) / 128, tiles_n = (N + 255) / 256;
     hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(512), C::LDS_BYTES, stream, a_codes, a_scales, w_codes, w_scales, M, N,
-                       nbk, alpha, y, ldy, tiles_m, tiles_n);
+                       nbk, alpha, y, ldy, tiles_m, tiles_n, tile_group_rows(tiles_m, tiles_n));
     return check_launch("gemm_kpair_kernel");
 }
 

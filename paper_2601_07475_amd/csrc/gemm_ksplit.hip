@@ -90,13 +90,13 @@ template <int WM, int WN, int GM, int GN, int KS, typename OutT, int MODE = COPI
 __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N,
-    int nbk, float alpha, OutT* __restrict__ y, int64_t ldy, int tiles_m, int tiles_n) {
+    int nbk, float alpha, OutT* __restrict__ y, int64_t ldy, int tiles_m, int tiles_n, int group_rows) {
     using C = KsplitCfg<WM, WN, GM, GN, KS, MODE>;
     constexpr bool REG = MODE == REGS, RAG = MODE == RAGGED;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     // workgroup -> tile: tile_order.h
-    const TileOrder tile((int)blockIdx.x, tiles_m, tiles_n);
+    const TileOrder tile((int)blockIdx.x, tiles_m, tiles_n, group_rows);
     const int tile_m = tile.m, tile_n = tile.n;
 
     const int tid = threadIdx.x;
@@ -405,7 +405,7 @@ arcq_status launch_ksplit(const uint8_t* a_codes, const uint8_t* a_scales, const
     if (arcq_status st = raise_lds_limit(reinterpret_cast<const void*>(kern), lds_raised)) return st;
     const int tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
     hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(C::NT), C::LDS_BYTES, stream, a_codes, a_scales, w_codes, w_scales,
-                       M, N, nbk, alpha, y, ldy, tiles_m, tiles_n);
+                       M, N, nbk, alpha, y, ldy, tiles_m, tiles_n, tile_group_rows(tiles_m, tiles_n));
     return check_launch("gemm_ksplit_kernel");
 }
 

@@ -377,6 +377,22 @@ def test_second_launches():
     assert B.arcq_gemm_rest(1777, 10240, 8528)[:2] == (1777, 1024) and B.arcq_gemm_rest(8192, 8192, 29696) is None
 
 
+def test_tile_order():
+    """Every tile once, whatever the numbers of tile rows and columns; an XCD (every eighth workgroup) has a contiguous run of the
+    sequence: of a tall problem with few tile columns whole tile rows, but for its first and last."""
+    for m, n in ((0, 4), (4, 0), (1 << 11, 1 << 10)):
+        assert B.lib().arcq_tile_order(m, n, FAKE, FAKE) == B.BAD_SHAPE
+    assert B.lib().arcq_tile_order(4, 4, None, FAKE) == B.INVALID_ARG
+    sizes = [(m, n) for m in range(1, 34) for n in range(1, 34)] + [(57, 3), (65, 8), (49, 30), (113, 7), (20, 7), (19, 7), (5, 97), (1, 500), (500, 1)]
+    for m, n in sizes:
+        order = B.arcq_tile_order(m, n)
+        assert sorted(order) == [(r, c) for r in range(m) for c in range(n)], (m, n)
+        if n < 8 and m >= 20:
+            for xcd in range(8):
+                rows = [r for r, _ in order[xcd::8]]
+                assert rows == sorted(rows) and len(set(rows)) <= -(-len(rows) // n) + 1, (m, n, xcd)
+
+
 # sizes whose tiles by rule share K' out to the waves of a workgroup (128 x 256 tiles to pairs, k-split tiles to four) and whose modelled
 # times are in favour of tiles that do not
 @pytest.mark.parametrize("M,N,Kp,chains", [(3573, 6744, 7472, 2), (2627, 5990, 6128, 2), (541, 25166, 11760, 2), (519, 24363, 9936, 2), (566, 23804, 15120, 2),
