@@ -1169,8 +1169,8 @@ static double tiles_time(int64_t M, int64_t N, int64_t Kp, int runs) {
     const double fill = (double)wgs / 256.0;
     if (runs > 1) return 7.4 + ((N & 3) ? 5.3 * (0.2 + 0.8 * fill) : 0.0) + ragged + stages * 0.95 * rounds +
                          0.366e-6 * 8.0 * (double)runs * (double)M * (double)N;
-    // (N & 7: values stored one by one or in pairs, see gemm_ksplit_best; the fill by itself is for fp32 results, which take these tiles 1 to
-    // 3 us longer)
+    // (N & 7: what values stored one by one or in pairs cost; no tile stores them so any more, see gemm_ksplit_best.  The fill by itself is for
+    // fp32 results, which take these tiles 1 to 3 us longer)
     return 4.5 + fill + ((N & 7) ? 5.0 * (0.15 * rounds + 0.85 * fill) : 0.0) + ragged + stages * (0.84 * rounds + 0.195 * fill);
 }
 static double stream_time(const GemmPlan& plan, int64_t N, int64_t Kp) {
@@ -1239,7 +1239,7 @@ static GemmPlan plan_stream(int64_t M, int64_t N, int64_t Kp) {
 static GemmPlan plan_by_rule(int64_t M, int64_t N, int64_t Kp) {
     const GemmPlan stream = plan_stream(M, N, Kp);
     if (M <= 32) return stream;
-    const KsplitTile ks = gemm_ksplit_best(M, N, Kp);
+    const KsplitTile ks = gemm_ksplit_best(M, N, Kp, true);
     const GemmPlan ksplit = {ARCQ_ROUTE_KSPLIT, ks.rows, ks.cols, 1, false};
     if (skinny_shape(M, N, Kp)) return ks.rows != 0 && ks.us < stream_time(stream, N, Kp) ? ksplit : stream;
     const int64_t nbk = Kp >> 4, nstage = (nbk + 7) >> 3, tn256 = (N + 255) / 256;
@@ -1351,7 +1351,16 @@ TimedPlan plan_by_time(int64_t M, int64_t N, int64_t Kp, int chains) {
 // this changes: 1.075x (513 to 8192 rows; 0.97x at worst, 1.31x at best) and 1.10x (65 to 512 rows).
 // K' < 1024: the rule alone (starts and ends of rounds count for more there than the model knows).
 GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
-    const GemmPlan rule = plan_by_rule(M, N, Kp);
+    GemmPlan rule = plan_by_rule(M, N, Kp);
+    const int chains = sum_chains(rule.kernel, rule.rows, rule.cols, Kp, false);
+    // Where the price of stores value by value, which no tile has any more, makes the rule stream 65 to 128 rows, it is asked once more
+    // without: 267 random problems with N odd or 2 mod 4 1.22x (1.07 to 1.42; 122 x 28115 over K' = 1088 25.2 -> 17.3 us, 121 x 24097 over 1264
+    // 23.5 -> 18.9, 89 x 7319 over 1520 11.4 -> 9.1).  Below K' = 1024, where starts count for more than the model knows, only for a tenth: 1.2x
+    // (0.98 to 1.5; without the tenth down to 0.95).  33 to 64 rows and up to 4096 weight rows are streamed in eight chains, the tiles have four.
+    if (rule.kernel == ARCQ_ROUTE_STREAM && M > 32 && (N & 3) != 0 && chains <= sum_chains(ARCQ_ROUTE_KSPLIT, 0, 0, Kp, true)) {
+        const KsplitTile ks = gemm_ksplit_best(M, N, Kp, false);
+        if (ks.rows != 0 && ks.us < (Kp < 1024 ? 0.9 : 1.0) * stream_time(rule, N, Kp)) rule = {ARCQ_ROUTE_KSPLIT, ks.rows, ks.cols, 1, false};
+    }
     GemmParts best = {rule, rule, M, N};
     // The streaming kernel with more weight rows than one round of four tiles a wave takes: that round, and the rest with one or two
     // tiles a wave, which gives it a round of its own.  (Four tiles a wave throughout: a second round that most of the chip has no part
@@ -1372,7 +1381,6 @@ GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
     });
     const double rule_us = tile_time(*of_rule, M, N, Kp);
     // (not for the price of precision: neither launch adds up K' in fewer chains than the rule's kernel)
-    const int chains = sum_chains(rule.kernel, rule.rows, rule.cols, Kp, false);
     const TimedPlan one = plan_by_time(M, N, Kp, chains);
     double us = rule_us;
     if (one.us < 0.95 * rule_us) {

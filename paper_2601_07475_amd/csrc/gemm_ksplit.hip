@@ -432,14 +432,16 @@ arcq_status launch_ksplit_typed(int rows, int cols, const uint8_t* a_codes, cons
 // Only tiles that cover it with at most one workgroup per compute unit (256) are looked at: with more, a second round costs
 // as much as the first; and with 32 at least, below which K' is better split across workgroups.  The time of a tile over K' is
 // start + stages (alone + shared x workgroups / 256): a workgroup takes longer the more of the chip is busy (clock, and the
-// weights' way from HBM).  single: what values stored one by one cost where weight rows are no multiple of four; they are stored by
-// fours now, but the rule keeps the term, whose choice from K' = 1024 on stands only where plan_gemm_parts knows nothing 5 % faster; rows off the grid of 64 have their windows of scale bytes, 0.5 us.  Fitted to 6700 problems (M = 33 .. 8000, N = 16 .. 30000, K' = 512 ..
-// 30000, weights from HBM), each path of each timed: 4 to 8 % rms.  The choice among these, the streaming kernel and the tiles
-// of gemm.hip by the modelled times is 2 % from the best of all on average, where fixed limits of 144 to 256 workgroups on five
+// weights' way from HBM); rows off the grid of 64 have their windows of scale bytes, 0.5 us.  Fitted to 6700 problems (M = 33 .. 8000, N = 16 ..
+// 30000, K' = 512 .. 30000, weights from HBM), each path of each timed: 4 to 8 % rms.  The choice among these, the streaming kernel and
+// the tiles of gemm.hip by the modelled times is 2 % from the best of all on average, where fixed limits of 144 to 256 workgroups on five
 // tile shapes were 5 %; eleven of the 6700 are more than 4 % slower than with those limits, 1000 more than 4 % faster.
+// by_value: with what it cost then (single, on a full chip) that values were stored one by one where weight rows are no multiple of four.
+// They are stored by fours at any address now.  The rule keeps the price because it decides about splitting K' across workgroups, and with it
+// about workspaces; plan_gemm_parts asks without it where it matters otherwise: for what is streamed, and from K' = 1024 on by the times.
 // 96 x 128 tiles are left out where they pad more rows than 128 x 128: what is multiplied in vain costs clock that the model does
 // not know of (195 x 10832 over K' = 12096: 90.6 us against 81.8).
-KsplitTile gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp) {
+KsplitTile gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp, bool by_value) {
     struct Tile {
         int rows, cols;
         double start, alone, shared, single;
@@ -458,7 +460,7 @@ KsplitTile gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp) {
         if (!added && (wgs >= 144 || (t.cols == 32 && M > 64 && nbk <= 544))) best.ample = true;
         if (t.rows == 96 && t.cols == 128 && tiles_m * 96 > (M + 127) / 128 * 128) continue;
         const double fill = (double)wgs / 256.0;
-        const double c = t.start + ((N & 3) ? t.single * (0.2 + 0.8 * fill) : 0.0) + ((Kp & 63) ? 0.5 : 0.0) +
+        const double c = t.start + (by_value && (N & 3) ? t.single * (0.2 + 0.8 * fill) : 0.0) + ((Kp & 63) ? 0.5 : 0.0) +
                          (double)((nbk + 15) / 16) * (t.alone + t.shared * fill);
         if (c < best.us) {
             best.rows = t.rows;

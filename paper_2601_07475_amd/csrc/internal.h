@@ -69,7 +69,7 @@ struct KsplitTile {
     double us;          // modelled time
     bool ample;         // some tile occupies more than half of the chip, or the smallest one an eighth of it over a short K'
 };
-KsplitTile gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp);
+KsplitTile gemm_ksplit_best(int64_t M, int64_t N, int64_t Kp, bool by_value);
 arcq_status launch_gemm_ksplit(int rows, int cols, const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                                const uint8_t* w_scales, int64_t M, int64_t N, int64_t Kp, float alpha, void* y, int y_dtype,
                                int64_t ldy, hipStream_t stream);

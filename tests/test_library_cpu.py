@@ -406,6 +406,15 @@ def test_no_precision_for_speed(M, N, Kp, chains):
         assert has >= chains, (kernel, rows, cols)
 
 
+# 65 to 128 rows, weight rows off the vectors of y: the k-split tiles that weight rows in whole vectors run, no more the streaming kernel
+@pytest.mark.parametrize("M,N,Kp", [(121, 24097, 1264), (122, 28115, 1088), (89, 7319, 1520), (112, 23375, 1232), (75, 7103, 1776), (100, 8125, 1152),
+                                    (66, 4990, 1040), (80, 24001, 768), (110, 26002, 800)])
+def test_stores_of_odd_weight_rows_cost_nothing(M, N, Kp):
+    whole = -(-N // 8) * 8
+    assert B.arcq_gemm_route(M, N, Kp)[:3] == B.arcq_gemm_route(M, whole, Kp)[:3] and B.arcq_gemm_route(M, N, Kp)[0] == B.ROUTE_KSPLIT
+    assert B.arcq_gemm_workspace_size(M, N, Kp) == 0
+
+
 def test_mx_second_launches():
     r = B.Rest()
     assert B.lib().arcq_mx_gemm_rest(4, 8, 48, 0, ctypes.byref(r)) == B.BAD_SHAPE
