@@ -1364,10 +1364,11 @@ GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
     GemmParts best = {rule, rule, M, N};
     // The streaming kernel with more weight rows than one round of four tiles a wave takes: that round, and the rest with one or two
     // tiles a wave, which gives it a round of its own.  (Four tiles a wave throughout: a second round that most of the chip has no part
-    // in.)  From HBM, us: 16 x 20480 over K' = 4352 18.6 -> 16.0, over 14592 48.6 -> 39.9; 1 x 18000 over 8464 31.9 -> 25.5; 32 x 24576 over
-    // 8464 43.6 -> 39.1.  A pass that runs the second kernel for the first time takes 5 us more, so the line lies where about that
-    // much is gained: not with three tiles a wave (32 x 28672 over 8464 45.0 -> 43.5), few rows behind the round (16 x 16400 over 4352
-    // 15.7 -> 15.5) or a shorter K' (16 x 20480 over 2176 12.0 -> 11.5, 16 x 24576 over 4352 19.1 -> 18.0).
+    // in.)  From HBM, us, 1 and 32 rows: 17408 weight rows over K' = 4096 16.2 -> 13.6 and 20.9 -> 18.1, over 14592 44.5 -> 35.8 and 58.0 -> 47.4;
+    // 20480 over 4352 17.1 -> 14.9 and 23.0 -> 20.0; 24576 over 6144 22.9 -> 20.7 and 29.7 -> 28.0, over 14592 47.2 -> 42.9 and 60.3 -> 55.0.  Within
+    // the limits 84 sizes gain 1.5 us and more, 1.05 to 1.26x.  A pass that runs the second kernel for the first time takes 5 us more, which the
+    // fifth at the latest has made up for.  Less is gained, and one launch kept, with three tiles a wave (32 x 28672 over 8464
+    // 45.0 -> 43.5), few rows behind the round (16 x 16400 over 4352 15.7 -> 15.5) or a shorter K' (16 x 20480 over 2176 12.0 -> 11.5, 16 x 24576 over 4352 19.1 -> 18.0).
     const int64_t behind = N - STREAM_ROUND;
     if (rule.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= STREAM_ROUND / 2 &&
         Kp >= (behind > STREAM_ROUND / 4 ? 6144 : 4096)) {
