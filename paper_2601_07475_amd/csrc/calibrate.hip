@@ -128,7 +128,8 @@ __device__ __forceinline__ void calib_stats(const uint32_t* __restrict__ colmax,
 // not: patterns order like integers, so the former are compared with the channel's key + 1.
 // Otherwise it ranks 64 channels, one per lane, against keys that are the same for all lanes and come through the scalar unit:
 // 1.6 times fewer cycles a comparison, but 128 workgroups for K = 8192.  Both, us (HALVES first): K = 4096 6.3 and 9.2, 8192 10.8 and 14.5,
-// 14336 27 and 22, 28672 101 and 63, 65536 449 and 250; so the line lies between 8192 and 14336.
+// 9216 18.4 and 15.6, 12288 23.9 and 19.4, 14336 27 and 22, 28672 101 and 63, 65536 449 and 250: beyond 8192 HALVES' workgroups are more than one a
+// compute unit.
 constexpr int HALVES_UP_TO = 8192;      // channels
 template <bool HALVES>
 __global__ __launch_bounds__(1024) void calib_select_kernel(const uint32_t* __restrict__ colmax, int K, int32_t* __restrict__ perm,

@@ -15,9 +15,10 @@ namespace arcq {
 // At most 8, about 8 x 4 tiles an XCD, in as few groups as that allows and about equal ones (17 rows 6, 6 and 5; 57 seven times 8 and
 // one).  8 and what is left: 0.3 % slower; 6 or 4, or across columns first: 0.2 to 2 % slower.
 // Tall problems go row by row: in groups, the run of an XCD ends in the middle of one, and with few columns it then reads the rows of two groups, while
-// every XCD reads all of W anyway.  In MXFP4, 85 problems with 2 to 7 tile columns and 20 to 60 tile rows, us in groups and by rows: 1.03x on
-// average, 1.05x from K' = 3000 on, 0.96 to 1.22x (6121 x 273 over K' = 8864 33.7 and 27.6, 5675 x 140 over 7072 27.2 and 22.4, 7533 x 395
-// over 2208 13.3 and 13.8); NVFP4 1.01x.  With 8 to 12 columns it is 0.97x, with fewer than 20 rows, two and a half an XCD, 0.94 to 1.0x.
+// every XCD reads all of W anyway.  In MXFP4, 129 problems with 2 to 7 tile columns and 20 to 60 tile rows, us in groups and by rows: 1.04x on
+// average, 1.06x from K' = 3000 on, 0.94 to 1.22x (6121 x 273 over K' = 8864 33.7 and 27.2, 5675 x 140 over 7072 26.6 and 21.7, 7533 x 395
+// over 2208 11.2 and 11.4); NVFP4 1.015x over 45.  No clear gain any more with 8 to 11 columns, 1.01x (0.96 to 1.07), and with fewer than 20 rows,
+// two and a half an XCD, 0.98 to 1.0x.
 __host__ __device__ inline int tile_group_rows(int tiles_m, int tiles_n) {
     if (tiles_n < 8 && tiles_m >= 20) return 1;
     const int groups = (tiles_m + 7) / 8;

@@ -100,6 +100,18 @@ def test_one_launch_by_time(route, M, N, nb):
     assert worst(B.arcq_gemm(*a, 1.0, *w, 1.0, out_dtype=torch.float32), dequantize(*a, 16) @ dequantize(*w, 16).t()) <= 2e-5
 
 
+# 65 to 128 rows with odd weight rows: k-split tiles, and the streaming kernel where scale bytes lie at odd addresses
+@pytest.mark.parametrize("M,N,nb", [(75, 7103, 111), (112, 23375, 77), (128, 9998, 66), (80, 24001, 48)])
+def test_odd_weight_rows_on_tiles(M, N, nb):
+    assert B.arcq_gemm_route(M, N, nb * 16)[0] == B.ROUTE_KSPLIT
+    g = torch.Generator(device="cuda").manual_seed(M + N + nb)
+    a, w = operand(g, M, nb, 16), operand(g, N, nb, 16)
+    ref = dequantize(*a, 16) @ dequantize(*w, 16).t()
+    for lead, code_lead in ((0, 0), (0, 8), (1, 0)):
+        a1 = operand(torch.Generator(device="cuda").manual_seed(M + N + nb), M, nb, 16, lead=lead, code_lead=code_lead)
+        assert worst(B.arcq_gemm(*a1, 1.0, *w, 1.0, out_dtype=torch.float32), ref) <= 2e-5
+
+
 # the streaming kernels with more weight rows than a round takes: one and two tiles a wave behind it, ragged rows and edges
 def streamed(M, N, nb, block, gemm):
     g = torch.Generator(device="cuda").manual_seed(M + N + nb)
