@@ -42,10 +42,10 @@ arcq_status arcq_ref_gemm_bf16(const void* x, const void* w, int64_t M, int64_t 
  * Which kernel a GEMM problem runs on: a function of its sizes alone (host only, nothing is launched).  Tests ask it, so that
  * a shape written for a tile cannot leave that tile unnoticed when the rule changes; not needed to call the library.
  * ahead: the weight-streaming kernel's waves ask for their next weights while they compute.
- * arcq_gemm_route: operands whose scale bytes lie at odd addresses, or K' < 256 off the grid of 64, have no 256 x 256 tiles and
- * may run 192 x 256 or 128 x 256 ones instead.  arcq_mx_gemm_route: such operands (or K' < 512 off the grid of 128) run 256-wide
- * or 128 x 128 tiles instead of 192 x 128 ones; with_workspace: as arcq_mx_gemm_ws (non-zero) or arcq_mx_gemm (0).  On the streaming
- * kernel, more weight rows than 16384 may run in two launches of it.
+ * arcq_gemm_route: operands whose scale bytes lie at odd addresses run another tile where the one named was taken for its modelled time (with
+ * 65 to 128 rows the streaming kernel), and they, or K' < 256 off the grid of 64, have no 256 x 256 tiles and may run 192 x 256 or
+ * 128 x 256 ones instead.  arcq_mx_gemm_route: such operands (or K' < 512 off the grid of 128) run 256-wide
+ * or 128 x 128 tiles instead of 192 x 128 ones; with_workspace: as arcq_mx_gemm_ws (non-zero) or arcq_mx_gemm (0).
  */
 #define ARCQ_ROUTE_STREAM 0     /* weight-streaming kernel: tile_cols / 16 weight tiles per wave */
 #define ARCQ_ROUTE_KSPLIT 1     /* tiles whose waves split every stage along k */
@@ -59,7 +59,7 @@ arcq_status arcq_mx_gemm_route(int64_t M, int64_t N, int64_t Kp, int with_worksp
 /*
  * Problems whose last round of tiles would leave much of the chip idle run in two launches: the route above for whole rounds, and
  * this one for the last `rows` x `cols` of the output (0 x 0: there is no second launch; else one of the two is M or N).  Operands
- * whose scale bytes lie at odd addresses run in one launch, of the streaming kernel in two.
+ * whose scale bytes lie at odd addresses run in one launch, except on the streaming kernels, where more than 16384 weight rows may run in two.
  */
 typedef struct {
     int64_t rows, cols;
