@@ -38,6 +38,31 @@ __device__ __forceinline__ void dma4(const void* gbase, uint32_t voffset, uint32
                  : "memory", "m0");
 }
 
+// The same through a buffer descriptor: address = base + voffset (a lane's) + soffset0 + soffset1 (scalars), and words at or past `bytes` from the
+// base arrive as zeros and are not read.  A copy then needs no vector instruction: rows a fixed distance apart are a scalar apart, and rows
+// past the edge of an operand need no clamp.  (With addresses of their own a copy costs up to six vector instructions, a 32-bit multiplication
+// among them, where registers are short.)  The addition keeps the distance that M0 needs from its use.
+typedef uint32_t buffer_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ buffer_t buffer_of(const uint8_t* base, uint32_t bytes) {
+    const uint64_t at = reinterpret_cast<uint64_t>(base);
+    return buffer_t{(uint32_t)at, (uint32_t)(at >> 32) & 0xFFFFu, bytes, 0x00020000u};      // raw, no stride
+}
+__device__ __forceinline__ void copy16(const buffer_t& b, uint32_t voffset, uint32_t soffset0, uint32_t soffset1, uint32_t lds_wave_base) {
+    uint32_t sum;
+    asm volatile("s_mov_b32 m0, %2\n\ts_add_u32 %0, %4, %5\n\tbuffer_load_dwordx4 %1, %3, %0 offen lds"
+                 : "=&s"(sum)
+                 : "v"(voffset), "s"(lds_wave_base), "s"(b), "s"(soffset0), "s"(soffset1)
+                 : "memory", "m0", "scc");
+}
+
+__device__ __forceinline__ void copy4(const buffer_t& b, uint32_t voffset, uint32_t soffset0, uint32_t soffset1, uint32_t lds_wave_base) {
+    uint32_t sum;
+    asm volatile("s_mov_b32 m0, %2\n\ts_add_u32 %0, %4, %5\n\tbuffer_load_dword %1, %3, %0 offen lds"
+                 : "=&s"(sum)
+                 : "v"(voffset), "s"(lds_wave_base), "s"(b), "s"(soffset0), "s"(soffset1)
+                 : "memory", "m0", "scc");
+}
+
 // s_waitcnt on the vector-memory counter only (gfx9 encoding: vmcnt in bits 3:0 and 15:14;
 // expcnt 6:4 and lgkmcnt 11:8 left at "no wait").
 template <int N>

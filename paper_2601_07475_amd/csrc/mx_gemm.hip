@@ -11,6 +11,7 @@
 #include "internal.h"
 #include "gemm_decode.h"
 #include "lds_dma.h"
+#include "scale_chunks.h"
 #include "scale_windows.h"
 #include "tile_order.h"
 
@@ -31,13 +32,13 @@ __device__ __forceinline__ float16v mfma_mx(const uint4& a, const uint4& b, cons
 }
 
 // Staged kernel.  A unit is 256 k: per row 128 bytes of codes (eight 16-byte pieces =
-// eight MX blocks) and 8 scale bytes, so that a copy instruction asks for whole 128-byte cache lines
+// eight MX blocks) and 8 scale bytes, which come for several units at a time (scale_chunks.h), so that a copy instruction asks for whole 128-byte cache lines
 // (8 lanes per row): the texture-address unit of a CU spends about 34 cycles on a copy that touches
 // sixteen 64-byte segments and 17.5 on one that touches eight full lines (measured), and with FP4
 // MFMAs the copies of a 256 x 256 tile would otherwise take as long as its arithmetic.  Units travel
 // global -> LDS with global_load_lds through a ring of NUNIT buffers (2 for the 256 x 256 tile: 2 x 68 KB),
-// one barrier per unit.  LDS layout of one unit: A codes [BM][128] | W codes [BN][128] | A scales [BM][8] |
-// W scales [BN][8] (regions padded to whole workgroup-wide copies).  The eight pieces of a row are stored
+// one barrier per unit.  LDS layout of one unit: A codes [BM][128] | W codes [BN][128] (RAGGED and REGS: | A scales [BM][8] |
+// W scales [BN][8]), in front of the units the scale bytes' chunks or windows.  The eight pieces of a row are stored
 // XOR-swizzled with (row >> 1) & 7: the LDS serves a 16-byte read of 16 consecutive lanes per clock from
 // 64 banks, rows are 128 bytes apart, so 16 consecutive rows must land on 16 different 16-byte bank groups
 // (measured: a swizzle with a period of 8 rows spent 44 % of its LDS cycles on bank conflicts); applied by
@@ -46,8 +47,13 @@ __device__ __forceinline__ float16v mfma_mx(const uint4& a, const uint4& b, cons
 // for the missing second half (never used, in bounds).
 // BF16: the same skeleton for plain bf16 operands (the comparison kernel arcq_ref_gemm_bf16): a row of a unit is 128
 // bytes = 64 bf16 values, there are no scale bytes, and a k-step is one v_mfma_f32_32x32x16_bf16.
+// What the loop spends beside the matrix instructions is the copies: a vector multiplication and four to five other vector instructions each, with
+// addresses per lane, and the copies of scale bytes, two words a row and unit.  With buffer copies (no vector instruction) and scale bytes for several units
+// at once, and without 64-bit divisions in front of the first copy (480 instructions before it, 205 now): 300 random problems of 65 to 8192 rows 1.08x on
+// average (0.978 to 1.40; by tiles 1.05 to 1.16, the same bits), 8192 x 8192 over K' = 29696 1011 -> 950 us, 4096 x 27648 over 5632 377 -> 359 with the
+// quantizer, over 5664 458 -> 418, 1500 x 14336 over 4320 83.0 -> 75.6, 1592 x 2461 over 24000 117 -> 84.
 // How the units get into LDS (MODE): COPIES for K' % 128 == 0, codes 16-byte and scale bytes 4-byte aligned; RAGGED for any K' (a
-// multiple of 32) from 512 on and dword-aligned codes: scale bytes as dword-aligned windows (scale_windows.h), pieces past the
+// multiple of 32) from 512 on and dword-aligned codes: scale bytes as dword-aligned windows (scale_chunks.h), pieces past the
 // end of a row fetched from its last block and their fragments zeroed in the last unit; the base of the scale bytes has
 // to be 4-byte aligned.  REGS: what is left, see below.
 template <int WM, int WN, int GM, int GN, bool BF16 = false, int MODE = COPIES>
@@ -55,20 +61,32 @@ struct MxCfg {
     static constexpr int BM = 32 * WM * GM, BN = 32 * WN * GN;
     static constexpr int NT = 64 * GM * GN;
     static constexpr int NA = (BM * 8 + NT - 1) / NT, NW = (BN * 8 + NT - 1) / NT;       // 16-byte pieces of codes
-    static constexpr int NAS = BF16 ? 0 : (BM * 2 + NT - 1) / NT, NWS = BF16 ? 0 : (BN * 2 + NT - 1) / NT;     // 4-byte words of scales
-    using Windows = ScaleWindows<BM, BN, NT, 8>;
-    static constexpr int NSW = MODE == RAGGED ? Windows::NS : 0;           // copies of windows come first
-    static constexpr int NDMA = NA + NW + (MODE == RAGGED ? NSW : NAS + NWS);
+    static constexpr int NDMA = NA + NW;
     static constexpr int A_CODES = 0;
     static constexpr int W_CODES = NA * NT * 16;
-    static constexpr int A_SCALES = W_CODES + NW * NT * 16;
-    static constexpr int W_SCALES = A_SCALES + (MODE == RAGGED ? Windows::DENSE_W : NAS * NT * 4);
-    static constexpr int WINDOWS = A_SCALES + Windows::DENSE_BYTES;
-    static constexpr int UNIT_BYTES = MODE == RAGGED ? WINDOWS + Windows::BYTES : W_SCALES + NWS * NT * 4;
-    static constexpr int NUNIT = (160 * 1024 - 256) / UNIT_BYTES >= 3 ? 3 : 2;
-    static constexpr int PATCH = NUNIT * UNIT_BYTES;        // RAGGED: see ScaleWindows::fill_patch
-    static constexpr int LDS_BYTES = PATCH + (MODE == RAGGED ? 2 * Windows::PATCH : 0);
-    static_assert(NDMA * (NUNIT - 1) < 64, "the counted wait needs the copies of NUNIT - 1 units to fit the counter");
+    static constexpr int A_SCALES = W_CODES + NW * NT * 16;             // (COPIES: none in a unit)
+    static constexpr int LDS_MOST = 160 * 1024;
+    // Scale bytes: chunks or windows of several units (scale_chunks.h); REGS: words of a unit
+    static constexpr bool SCALES = !BF16 && MODE != REGS;               // come with copies
+    using Narrow = ScaleChunkWindows<BM, BN, NT, 1>;
+    using Wide = ScaleChunkWindows<BM, BN, NT, 3>;
+    static constexpr int NAS = BF16 ? 0 : (BM * 2 + NT - 1) / NT, NWS = BF16 ? 0 : (BN * 2 + NT - 1) / NT;     // 4-byte words of scales
+    static constexpr int UNIT_BYTES = A_SCALES + (MODE == RAGGED ? Wide::DENSE_BYTES : MODE == REGS ? (NAS + NWS) * NT * 4 : 0);
+    static constexpr int NUNIT = 3 * UNIT_BYTES + (!SCALES ? 0 : MODE == COPIES ? 2 * ScaleChunks<BM, BN, NT, 16>::BYTES : 2 * Wide::BYTES + Wide::PATCH) <= LDS_MOST ? 3 : 2;
+    // chunks of two units where those of four do not fit beside three ring slots (128 x 256 tiles, 2048 x 4096 over K' = 4352: 31 us on two slots, 24.4 on three)
+    using Chunks = ScaleChunks<BM, BN, NT, NUNIT * UNIT_BYTES + 2 * ScaleChunks<BM, BN, NT, 32>::BYTES <= LDS_MOST ? 32 : 16>;
+    // windows of one unit where those of three do not fit (256 x 256 tiles)
+    using Windows = ScaleChunkWindows<BM, BN, NT, NUNIT * UNIT_BYTES + 2 * Wide::BYTES + Wide::PATCH <= LDS_MOST ? 3 : 1>;
+    static constexpr int NG = MODE == COPIES && SCALES ? Chunks::NG : 0;        // copies of scale bytes a unit
+    static constexpr int NWG = MODE == RAGGED ? Windows::NG : 0;
+    static constexpr int SROW = MODE == COPIES ? 8 * Chunks::Q : 8;     // from a row's scale bytes to the next row's
+    static constexpr int W_SCALES = MODE == RAGGED ? Windows::DENSE_W : MODE == REGS ? NAS * NT * 4 : Chunks::W_ROWS * SROW;    // behind those of A
+    // chunks or windows, patch (RAGGED: see ScaleWindows::fill_patch), units
+    static constexpr int PATCH = !SCALES ? 0 : MODE == COPIES ? 2 * Chunks::BYTES : 2 * Windows::BYTES;
+    static constexpr int UNITS = PATCH + (MODE == RAGGED ? Windows::PATCH : 0);
+    static constexpr int LDS_BYTES = UNITS + NUNIT * UNIT_BYTES;
+    static_assert(LDS_BYTES <= LDS_MOST, "LDS of a compute unit");
+    static_assert(NDMA + (MODE == RAGGED ? Windows::NS : NG) < 64, "the counted wait needs the copies of NUNIT - 1 units to fit the counter");
 };
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -98,7 +116,7 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     // blockIdx.x = split * num_tiles + tile accumulates its run and stores an fp32 partial tile at
     // y + split * split_stride (a reduction kernel adds the partial results in index order).
     const int num_tiles = tiles_m * tiles_n;
-    const int split = (int)blockIdx.x / num_tiles;
+    const int split = splits > 1 ? (int)blockIdx.x / num_tiles : 0;
     const TileOrder tile((int)blockIdx.x - split * num_tiles, tiles_m, tiles_n, group_rows);
     const int tile_m = tile.m, tile_n = tile.n;
 
@@ -116,36 +134,30 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     const int crow = tid >> 3, srow = tid >> 1;
     const uint32_t wave_slot = __builtin_amdgcn_readfirstlane((uint32_t)(tid & ~63));
     const uint32_t lds0 = lds_address(lds);
-    const typename C::Windows windows = {a_scales, w_scales, M, N, nb, wg_m0, wg_n0, (uint32_t)tid, wave_slot};    // RAGGED
+    // this workgroup's run of units [u0, u1); a division is 30 instructions in front of the first copy
+    int u0 = 0, u1 = nunit;
+    if (splits > 1) {
+        u0 = (int)((uint32_t)(split * nunit) / (uint32_t)splits);
+        u1 = (int)((uint32_t)((split + 1) * nunit) / (uint32_t)splits);
+    }
+    const typename C::Chunks chunks(a_scales, w_scales, M, N, nb, wg_m0, wg_n0, (uint32_t)lane, wave_slot >> 6, 8 * u0);      // COPIES
+    const typename C::Windows windows(a_scales, w_scales, M, N, nb, wg_m0, wg_n0, (uint32_t)tid, wave_slot, 8 * u0);    // RAGGED
     const int patch_from = C::Windows::patch_from(nb);
-    auto issue_one = [&](int d, int unit, int buf) {
-        const uint32_t base = lds0 + buf * C::UNIT_BYTES;
-        if (RAG && d < C::NSW) {
-            windows.issue(d, unit, base + C::WINDOWS);
-            return;
-        }
-        d -= C::NSW;
-        constexpr int NA = C::NA, NW = C::NW, NAS = C::NAS, NT = C::NT;
-        const bool half = has_half && unit == nunit - 1;
-        const uint32_t oc = RAG ? 16u * (uint32_t)min(8 * unit + (int)lp, nb - 1) : (uint32_t)unit * 128u + (half ? (lp & 3u) : lp) * 16u;
-        const uint32_t os = (uint32_t)unit * 8u + (half ? 0u : (uint32_t)(tid & 1) * 4u);
-        // rows past the edge of the operand re-read its last row (never stored)
-        if (d < NA) {
-            const uint32_t row = (uint32_t)min(wg_m0 + d * (NT / 8) + crow, M - 1);
-            dma16(a_codes, row * cpitch + oc, base + C::A_CODES + 16u * (d * NT + wave_slot));
-        } else if (d < NA + NW) {
-            const int p = d - NA;
-            const uint32_t row = (uint32_t)min(wg_n0 + p * (NT / 8) + crow, N - 1);
-            dma16(w_codes, row * cpitch + oc, base + C::W_CODES + 16u * (p * NT + wave_slot));
-        } else if (d < NA + NW + NAS) {
-            const int p = d - NA - NW;
-            const uint32_t row = (uint32_t)min(wg_m0 + p * (NT / 2) + srow, M - 1);
-            dma4(a_scales, row * spitch + os, base + C::A_SCALES + 4u * (p * NT + wave_slot));
-        } else {
-            const int p = d - NA - NW - NAS;
-            const uint32_t row = (uint32_t)min(wg_n0 + p * (NT / 2) + srow, N - 1);
-            dma4(w_scales, row * spitch + os, base + C::W_SCALES + 4u * (p * NT + wave_slot));
-        }
+    // The offset of this lane's piece of a unit: the same for every copy, whose rows are a scalar apart; rows past the edge of an operand
+    // arrive as zeros (never stored).
+    const buffer_t buf_a = buffer_of(a_codes + (int64_t)wg_m0 * cpitch, (uint32_t)(M - wg_m0) * cpitch);
+    const buffer_t buf_w = buffer_of(w_codes + (int64_t)wg_n0 * cpitch, (uint32_t)(N - wg_n0) * cpitch);
+    const uint32_t row_off = (uint32_t)crow * cpitch;
+    auto lane_offset = [&](int unit) -> uint32_t {
+        if (RAG) return row_off + 16u * (uint32_t)min(8 * unit + (int)lp, nb - 1);
+        return row_off + 16u * (has_half && unit == nunit - 1 ? lp & 3u : lp);
+    };
+    // copy d of a unit: A code pieces, W code pieces
+    auto issue_one = [&](int d, int unit, int buf, uint32_t voffset) {
+        const uint32_t base = lds0 + C::UNITS + buf * C::UNIT_BYTES + 16u * wave_slot, soffset = RAG ? 0u : (uint32_t)unit * 128u;
+        constexpr int NA = C::NA, NT = C::NT;
+        if (d < NA) copy16(buf_a, voffset, soffset, d * (NT / 8) * cpitch, base + C::A_CODES + 16 * d * NT);
+        else copy16(buf_w, voffset, soffset, (d - NA) * (NT / 8) * cpitch, base + C::W_CODES + 16 * (d - NA) * NT);
     };
 
     // ---- REGS: the same pieces through registers (piece d of a thread lands where copy d puts it); needs nb >= 4
@@ -171,7 +183,7 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
         }
     };
     auto reg_commit = [&](int unit, int buf) {
-        uint8_t* st = lds + buf * C::UNIT_BYTES;
+        uint8_t* st = lds + C::UNITS + buf * C::UNIT_BYTES;
         const bool ok = 8 * unit + (int)lp < nb;       // this piece's block exists
 #pragma unroll
         for (int d = 0; d < NCP; ++d) {
@@ -184,8 +196,7 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
 #pragma unroll
         for (int d = 0; d < NSP; ++d) {
             const uint32_t word = skip >= 4 ? 0u : rs[d] >> (8 * skip);
-            const int at = d < C::NAS ? C::A_SCALES + 4 * (d * C::NT + tid) : C::W_SCALES + 4 * ((d - C::NAS) * C::NT + tid);
-            *reinterpret_cast<uint32_t*>(st + at) = word;
+            *reinterpret_cast<uint32_t*>(st + C::A_SCALES + 4 * (d * C::NT + tid)) = word;        // (W_SCALES follow at 4 NAS NT)
         }
     };
 
@@ -194,7 +205,8 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     // row are multiples of 32
     const uint32_t swz = (uint32_t)(r >> 1) & 7u;
     const uint32_t rd_a = C::A_CODES + (wrow0 + r) * 128, rd_w = C::W_CODES + (wcol0 + r) * 128;
-    const uint32_t rd_as = C::A_SCALES + (wrow0 + r) * 8, rd_ws = C::W_SCALES + (wcol0 + r) * 8;
+    const uint32_t rd_as = MODE == COPIES ? C::Chunks::row_at(wrow0 + r) : (wrow0 + r) * C::SROW;
+    const uint32_t rd_ws = C::W_SCALES + (MODE == COPIES ? C::Chunks::row_at(wcol0 + r) : (wcol0 + r) * C::SROW);
     uint32_t pc[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) pc[t] = 16u * ((uint32_t)(2 * t + h) ^ swz);
@@ -219,17 +231,21 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
 #pragma unroll
         for (int j = 0; j < WN; ++j) fw[slot][j] = *reinterpret_cast<const uint4*>(st + rd_w + j * 4096 + pc[t]);
     };
-    auto read_scales = [&](const uint8_t* st, uint2 (&da)[WM], uint2 (&dw)[WN]) {
-        if (BF16) return;
+    // (in the unit's slot, or in the ring of chunks)
+    auto read_scales = [&](int unit, int slot, uint2 (&da)[WM], uint2 (&dw)[WN]) {
+        if constexpr (!BF16) {
+            const uint32_t flip = MODE == COPIES ? C::Chunks::at(unit - u0) : 0u;
+            const uint8_t* at = lds + (MODE == COPIES ? C::Chunks::base(unit - u0) : (uint32_t)(C::UNITS + slot * C::UNIT_BYTES + C::A_SCALES));
 #pragma unroll
-        for (int i = 0; i < WM; ++i) {
-            const uint2 v = *reinterpret_cast<const uint2*>(st + rd_as + i * 256);
-            da[i] = make_uint2(v.x >> (8 * h), v.y >> (8 * h));
-        }
+            for (int i = 0; i < WM; ++i) {
+                const uint2 v = *reinterpret_cast<const uint2*>(at + (rd_as ^ flip) + i * 32 * C::SROW);
+                da[i] = make_uint2(v.x >> (8 * h), v.y >> (8 * h));
+            }
 #pragma unroll
-        for (int j = 0; j < WN; ++j) {
-            const uint2 v = *reinterpret_cast<const uint2*>(st + rd_ws + j * 256);
-            dw[j] = make_uint2(v.x >> (8 * h), v.y >> (8 * h));
+            for (int j = 0; j < WN; ++j) {
+                const uint2 v = *reinterpret_cast<const uint2*>(at + (rd_ws ^ flip) + j * 32 * C::SROW);
+                dw[j] = make_uint2(v.x >> (8 * h), v.y >> (8 * h));
+            }
         }
     };
 
@@ -245,7 +261,6 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     // issued behind the barrier that opens the next unit they had 36 to 56 (8192 x 8192 over K' = 29696 972 -> 944 us, 1777 x
     // 10240 over 8576 129 -> 118, 4096 x 27648 over 5632 1.00 to 1.02 times as fast: the wait for copies is not all that bounds it).
     constexpr int NM = WM * WN;               // MFMAs per k-step
-    constexpr int DIST = C::NUNIT - 1;
     int buf = 0;
     // RAGGED: the wanted scale bytes of unit u+1 are picked out of their windows at the start of k-step 1 (read) and in the
     // middle of it (write).  tail_tag: 1: unit u+1 is the last or the one before, whose windows or blocks may pass the end;
@@ -254,7 +269,8 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     // nothing and, in the last one, reads nothing for a next unit.  (Both used to copy the last unit once more, and the end of the
     // kernel waited for that: 1.0 % of the time on average over 200 problems of 513 to 8192 rows, 1500 x 14336 over K' = 4320 with the
     // quantizer 85.6 -> 84.2 us.)
-    uint3 win[RAG ? C::NSW : 1];
+    uint3 win[RAG ? C::Windows::G : 1];
+    int wchunk = C::Windows::Q == 1 ? 1 : 0, wpart = C::Windows::Q == 1 ? 0 : 1;     // RAGGED: chunk of unit u+1 and its place in it
     auto run_unit = [&](int u, auto tail_tag, auto left_tag) {
         constexpr int NSTEPS = 4;
         constexpr int TAIL = decltype(tail_tag)::value;
@@ -262,10 +278,11 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
         constexpr int LAST_Q = NSTEPS * NM - NM / 2;
         constexpr int COMMIT_Q = LAST_Q - NM / 2;     // REGS: the pieces of unit u+1 go to LDS half a k-step before its barrier
         constexpr int FREE_Q = 2 * NM + (3 * NM) / 8; // EARLY: every fragment of the unit is in registers
-        const uint8_t* st = lds + buf * C::UNIT_BYTES;
+        const uint8_t* st = lds + C::UNITS + buf * C::UNIT_BYTES;
         const int buf1 = buf + 1 == C::NUNIT ? 0 : buf + 1, bufd = EARLY ? buf : buf == 0 ? C::NUNIT - 1 : buf - 1;
         int fetch = u + 2;              // opaque: followed as an induction variable it costs the copies 17 more additions a unit
         asm("" : "+s"(fetch));
+        const uint32_t voffset = lane_offset(fetch);
 #pragma unroll
         for (int t = 0; t < NSTEPS; ++t) {
             if (TAIL == 2 && 8 * u + 2 * t >= nb) break;
@@ -295,20 +312,18 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
                 for (int j = 0; j < WN; ++j) {
                     const int q = t * NM + i * WN + j;
                     if constexpr (RAG && LEFT > 0) {
-                        uint8_t* next = lds + buf1 * C::UNIT_BYTES;
+                        uint8_t* next = lds + C::UNITS + buf1 * C::UNIT_BYTES;
                         if (q == NM) {
-                            // windows of unit u+1: younger are the code copies of that unit and (three ring slots) the
-                            // copies of unit u+2 issued so far
-                            wait_vmcnt<C::NA + C::NW + (EARLY || LEFT < 2 ? 0 : C::NDMA < NM ? C::NDMA : NM)>();
+                            // (windows that have landed before the barrier that opened this unit)
 #pragma unroll
-                            for (int d = 0; d < C::NSW; ++d)
-                                win[d] = windows.gather(d, next + C::WINDOWS, TAIL == 1 && u + 1 >= patch_from, lds + C::PATCH + 8 * (u + 1 - patch_from));
+                            for (int g = 0; g < C::Windows::G; ++g)
+                                win[g] = windows.gather(g, wchunk, wpart, lds, TAIL == 1 && u + 1 >= patch_from, lds + C::PATCH);
                             __builtin_amdgcn_sched_barrier(0);
                         }
                         if (q == NM + NM / 2) {
 #pragma unroll
-                            for (int d = 0; d < C::NSW; ++d)
-                                windows.template put<false>(d, win[d], next + C::A_SCALES, TAIL == 1, u + 1);
+                            for (int g = 0; g < C::Windows::G; ++g)
+                                windows.put(g, win[g], next + C::A_SCALES, TAIL == 1, u + 1);
                             __builtin_amdgcn_sched_barrier(0);
                         }
                     }
@@ -327,9 +342,10 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
                         else wait_vmcnt<LEFT == 2 ? C::NDMA : 0>();
                         if constexpr (RAG) wait_lgkmcnt0();         // this wave's scale bytes of unit u+1 are written
                         wg_barrier();
-                        read_codes(0, 0, lds + buf1 * C::UNIT_BYTES);
-                        read_scales(lds + buf1 * C::UNIT_BYTES, sa_n, sw_n);
+                        read_codes(0, 0, lds + C::UNITS + buf1 * C::UNIT_BYTES);
+                        read_scales(u + 1, buf1, sa_n, sw_n);
                         if constexpr (REG && LEFT == 2) reg_issue(u + 2);
+                        if constexpr (RAG) if (++wpart == C::Windows::Q) wpart = 0, ++wchunk;
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     // weights as the row operand: see store_tile_swapped
@@ -340,16 +356,26 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
                         acc[i][j] = mfma_mx(fw[set][j], fa[set][i], acc[i][j], (int)(t < 2 ? sw[j].x : sw[j].y),
                                             (int)(t < 2 ? sa[i].x : sa[i].y), t & 1);
                     __builtin_amdgcn_sched_barrier(0);
+                    if (C::NG > 0 && LEFT == 2 && q >= LAST_Q) {        // a group of the scale bytes of later units
+#pragma unroll
+                        for (int i = 0; i < C::NG; ++i)
+                            if (i % (NM - NM / 2) == q - LAST_Q) chunks.issue(i, (u - u0 + 1) % C::Chunks::Q, (u - u0 + 1) / C::Chunks::Q + 1, lds0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (C::NWG > 0 && LEFT == 2 && q == LAST_Q) {
+                        windows.issue_group(wpart, wchunk + 1, lds0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                     if constexpr (EARLY) {
                         constexpr int E = LAST_Q - FREE_Q;      // the MFMA slots that the copies of unit u + 2 are spread over
                         if (LEFT == 2 && q >= FREE_Q && q < LAST_Q) {
 #pragma unroll
                             for (int d = 0; d < C::NDMA; ++d)
-                                if (d * E / C::NDMA == q - FREE_Q) issue_one(d, fetch, bufd);
+                                if (d * E / C::NDMA == q - FREE_Q) issue_one(d, fetch, bufd, voffset);
                             __builtin_amdgcn_sched_barrier(0);
                         }
                     } else if (!REG && LEFT == 2 && q < C::NDMA) {
-                        issue_one(q, fetch, bufd);
+                        issue_one(q, fetch, bufd, voffset);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
@@ -364,36 +390,49 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     };
     static_assert(C::NDMA <= 3 * NM, "copies are issued during the first three k-steps of a unit");
 
-    // this workgroup's run of units [u0, u1)
-    const int u0 = (int)((int64_t)split * nunit / splits), u1 = (int)((int64_t)(split + 1) * nunit / splits);
     if constexpr (REG) {
         reg_issue(u0);
         reg_commit(u0, 0);
         reg_issue(min(u0 + 1, nunit - 1));
         wait_lgkmcnt0();
     } else {
+        if constexpr (RAG) {
+            windows.issue_chunk(0, lds0);
+            if (C::Windows::Q == 1) windows.issue_chunk(1, lds0);       // looked at in the first unit
+        } else if constexpr (C::SCALES) {
+            chunks.issue_first((uint32_t)lane, lds0);
+        }
 #pragma unroll
-        for (int u = 0; u < (EARLY ? 2 : DIST); ++u)
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int d = 0; d < C::NDMA; ++d) issue_one(d, min(u0 + u, nunit - 1), u);
-        if constexpr (RAG) windows.fill_patch(lds + C::PATCH);
-        wait_vmcnt<(EARLY ? 1 : DIST - 1) * C::NDMA>();
+            for (int d = 0; d < C::NDMA; ++d) issue_one(d, min(u0 + u, nunit - 1), u, lane_offset(min(u0 + u, nunit - 1)));
+#pragma unroll
+        for (int i = 0; i < C::NG; ++i) chunks.issue(i, 0, 1, lds0);
+        if constexpr (C::NWG > 0 && C::Windows::Q > 1) {
+            windows.issue_group(0, 1, lds0);
+            windows.issue_group(1, 1, lds0);
+        }
+        // (its loads make the first waves wait for every copy so far: 0.3 us)
+        if constexpr (RAG)
+            if (C::Windows::needs_patch(M, N, nb, wg_m0, wg_n0)) C::Windows::fill_patch(a_scales, w_scales, M, N, nb, (uint32_t)tid, lds + C::PATCH);
+        if (C::NG > 0 && !chunks.active) wait_vmcnt<C::NDMA>();
+        else wait_vmcnt<C::NDMA + C::NG + (C::Windows::Q > 1 ? 2 : 0) * C::NWG>();
         if constexpr (RAG) {
             const bool tail = u0 >= patch_from;     // a short run of a split
-            if (tail) {                             // uniform: the patch area is written by the first wave
+            if (tail) {                             // uniform: the patch is written by the first waves
                 wait_lgkmcnt0();
                 wg_barrier();
             }
 #pragma unroll
-            for (int d = 0; d < C::NSW; ++d)
-                windows.template put<false>(d, windows.gather(d, lds + C::WINDOWS, tail, lds + C::PATCH + (tail ? 8 * (u0 - patch_from) : 0)),
-                                            lds + C::A_SCALES, tail, u0);
+            for (int g = 0; g < C::Windows::G; ++g)
+                windows.put(g, windows.gather(g, 0, 0, lds, tail, lds + C::PATCH), lds + C::UNITS + C::A_SCALES, tail, u0);
             wait_lgkmcnt0();
+            if (C::Windows::Q == 1) windows.issue_group(0, 2, lds0);    // into the first chunk's place
         }
     }
     wg_barrier();
-    read_codes(0, 0, lds);
-    read_scales(lds, sa, sw);
+    read_codes(0, 0, lds + C::UNITS);
+    read_scales(u0, 0, sa, sw);
     using Tag0 = std::integral_constant<int, 0>;
     using Tag1 = std::integral_constant<int, 1>;
     using Tag2 = std::integral_constant<int, 2>;
@@ -791,7 +830,7 @@ arcq_status launch_mx_plan(const GemmPlan& plan, const uint8_t* a_codes, const u
     // How the units get into LDS: whole aligned pieces; any K' (a multiple of 32) from 512 on, codes at their minimum alignment;
     // through registers, for scale bytes at odd addresses and short K' (no 192 x 128 tiles there)
     const int mode = (nb & 3) == 0 && aligned16 ? COPIES
-                     : nb >= ScaleWindows<128, 128, 256, 8>::MIN_NB && dword_scales ? RAGGED : REGS;
+                     : nb >= ScaleChunkWindows<128, 128, 256, 3>::MIN_NB && dword_scales ? RAGGED : REGS;
     auto tiled = [&](auto mode_tag) {
         constexpr int MODE = decltype(mode_tag)::value;
         const bool tall = plan.rows == 192 && plan.cols == 128;
