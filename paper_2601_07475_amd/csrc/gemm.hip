@@ -880,35 +880,71 @@ __device__ __forceinline__ void transpose_scale_pairs(uint2 s, uint32_t& even_ch
 // as soon as both have been used.  Two, because a chunk is half a cache line of every row: asking for the halves one by one,
 // each behind a chunk's decode, was 10 to 20 % slower than asking for whole groups between computing them (16 x 8192 over
 // K' = 29696, weights from HBM: 36.4, 31.0 and, by twos, 30.4 us), although it keeps the most loads in flight.
+//
+// The decode of the operands bounds the kernel where it has whole rounds (16 x 28672 over K' = 8464: 131 MB from HBM in 34.6 us), so beyond a
+// round of four weight tiles a wave more tiles (WIDE) cost less than a second round: the decode of the activations is shared by more of them.
+// weight tiles whose partial sums fit the static LDS limit at a time
+constexpr int skinny_batch(int mt, int nt, int waves) { return waves * mt * nt > 64 ? (nt + 1) / 2 : nt; }
+
 template <int MT, int NT, int WAVES, int U, bool GRP, bool ROLL, typename OutT>
-__global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
+__device__ __forceinline__ void skinny_tiles(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N,
-    int nbk, float alpha, OutT* __restrict__ y, int64_t ldy) {
-    __shared__ float red[WAVES][MT * NT][4][64];
-    static_assert(sizeof(float) * WAVES * MT * NT * 256 <= 64 * 1024, "partial tiles must fit the static LDS limit");
+    int nbk, float alpha, OutT* __restrict__ y, int64_t ldy, int n0, float* red_memory) {
+    constexpr int BATCH = skinny_batch(MT, NT, WAVES);
+    auto& red = *reinterpret_cast<float (*)[WAVES][MT * BATCH][4][64]>(red_memory);
+    // WIDE: rows at 32-bit offsets from scalar addresses instead of pointers, and with two row tiles two chunks of activations at a time, loaded again
+    // behind the chunk that used them: 256 registers take seven weight tiles then (four with pointers and whole groups of activations)
+    constexpr bool WIDE = NT > 4, LATE_A = WIDE && MT == 2;
+    static_assert(!WIDE || (GRP && ROLL), "more than four weight tiles: groups only, loaded ahead");
     // the wave number as a scalar: conditions on it become scalar branches (a matrix instruction inside a branch on a
     // vector condition would still execute: it does not honour the lane mask)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int i = lane & 15, q = lane >> 4;
-    const int n0 = blockIdx.x * (16 * NT);
     const int64_t cpitch = (int64_t)nbk * 8, spitch = nbk;
     const int nchunk = (nbk + 7) >> 3;                       // chunks of 8 blocks, the last may be partial
 
-    const uint8_t *ac[MT], *as[MT];
+    const uint8_t* const base_c = w_codes + (WIDE ? n0 * cpitch : 0);
+    const uint8_t* const base_s = w_scales + (WIDE ? n0 * spitch : 0);
+    using Row = std::conditional_t<WIDE, uint32_t, const uint8_t*>;
+    Row ac[MT], as[MT], wc[NT], ws[NT];
 #pragma unroll
     for (int r = 0; r < MT; ++r) {
         const int m = min(16 * r + i, M - 1);
-        ac[r] = a_codes + (int64_t)m * cpitch;
-        as[r] = a_scales + (int64_t)m * spitch;
+        if constexpr (WIDE) {
+            ac[r] = (uint32_t)(m * cpitch) + 16u * q;
+            as[r] = (uint32_t)(m * spitch) + 8u * q;
+        } else {
+            ac[r] = a_codes + (int64_t)m * cpitch;
+            as[r] = a_scales + (int64_t)m * spitch;
+        }
     }
-    const uint8_t *wc[NT], *ws[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int n = min(n0 + 16 * t + i, N - 1);
-        wc[t] = w_codes + n * cpitch;
-        ws[t] = w_scales + n * spitch;
+        if constexpr (WIDE) {
+            wc[t] = (uint32_t)((n - n0) * cpitch) + 16u * q;
+            ws[t] = (uint32_t)((n - n0) * spitch) + 8u * q;
+        } else {
+            wc[t] = w_codes + n * cpitch;
+            ws[t] = w_scales + n * spitch;
+        }
     }
+    auto scale_row = [&](Row codes, Row scales) -> Row {
+        if constexpr (WIDE) { uint32_t o = codes; asm("" : "+v"(o)); return (o >> 3) + 6u * q; }
+        else return scales;
+    };
+    // byte `uniform` + `own` (a lane's) of a row; WIDE: rows come with a lane's place in a group of chunks, `place`, and the offset is opaque, so that no
+    // 64-bit address of a row is kept
+    auto in_row = [](const uint8_t* base, Row row, int64_t uniform, uint32_t own, uint32_t place) -> const uint8_t* {
+        if constexpr (WIDE) {
+            uint32_t offset = row + (own - place);
+            asm("" : "+v"(offset));
+            return base + uniform + offset;
+        } else {
+            return row + (uniform + own);
+        }
+    };
     float4v acc[MT][NT];
 #pragma unroll
     for (int r = 0; r < MT; ++r)
@@ -917,7 +953,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
 
     // ---- operand registers of one group of four whole chunks, and of the U chunks of one pass of the chunk loop
     struct Group {
-        uint4 ca[4][MT], cw[4][NT];
+        uint4 ca[LATE_A ? 2 : 4][MT], cw[4][NT];
         uint2 sa2[MT], sw2[NT];
     };
     struct Chunks {
@@ -930,33 +966,37 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     // save registers, which turns one trip to memory into three; the scheduling barriers behind the calls of
     // these functions keep the loads where they are written.)
     auto load_scales = [&](int g, Group& G) {
-        const int64_t so = 32 * (int64_t)g + 8 * q;
+        const int64_t so = 32 * (int64_t)g;
 #pragma unroll
-        for (int r = 0; r < MT; ++r) G.sa2[r] = load8_a1(as[r] + so);
+        for (int r = 0; r < MT; ++r) G.sa2[r] = load8_a1(in_row(a_scales, scale_row(ac[r], as[r]), so, 8u * q, 8u * q));
 #pragma unroll
-        for (int t = 0; t < NT; ++t) G.sw2[t] = load8_a1(ws[t] + so);
+        for (int t = 0; t < NT; ++t) G.sw2[t] = load8_a1(in_row(base_s, scale_row(wc[t], ws[t]), so, 8u * q, 8u * q));
     };
-    auto load_codes = [&](int g, int m, Group& G) {
-        const int64_t co = 256 * (int64_t)g + 16 * q + 64 * m;
+    auto load_activations = [&](int g, int m, Group& G) {
+        const int64_t co = 256 * (int64_t)g + 64 * m;
 #pragma unroll
-        for (int r = 0; r < MT; ++r) G.ca[m][r] = load16_a8(ac[r] + co);
+        for (int r = 0; r < MT; ++r) G.ca[LATE_A ? m & 1 : m][r] = load16_a8(in_row(a_codes, ac[r], co, 16u * q, 16u * q));
+    };
+    auto load_codes = [&](int g, int m, Group& G, bool activations) {
+        const int64_t co = 256 * (int64_t)g + 64 * m;
+        if (activations) load_activations(g, m, G);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) G.cw[m][t] = load16_a8(wc[t] + co);
+        for (int t = 0; t < NT; ++t) G.cw[m][t] = load16_a8(in_row(base_c, wc[t], co, 16u * q, 16u * q));
     };
     auto load_group = [&](int g, Group& G) {
         load_scales(g, G);
 #pragma unroll
-        for (int m = 0; m < 4; ++m) load_codes(g, m, G);
+        for (int m = 0; m < 4; ++m) load_codes(g, m, G, !LATE_A || m < 2);
     };
-    // next: group whose loads go into the registers that have been used (roll_tag), else not looked at
-    auto compute_group = [&](Group& G, int next, auto roll_tag) {
+    // g: this group; next: group whose loads go into the registers that have been used (roll_tag), else not looked at
+    auto compute_group = [&](Group& G, int g, int next, auto roll_tag) {
         constexpr bool roll = decltype(roll_tag)::value;
         uint32_t ea[2][MT], ew[2][NT];     // [chunk parity][tile]: pairs of chunks (0, 2) / (1, 3)
 #pragma unroll
         for (int r = 0; r < MT; ++r) transpose_scale_pairs(G.sa2[r], ea[0][r], ea[1][r]);
 #pragma unroll
         for (int t = 0; t < NT; ++t) transpose_scale_pairs(G.sw2[t], ew[0][t], ew[1][t]);
-        if constexpr (roll) {
+        if constexpr (roll && !WIDE) {
             __builtin_amdgcn_sched_barrier(0);
             load_scales(next, G);
             __builtin_amdgcn_sched_barrier(0);
@@ -974,7 +1014,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
                 half8 fa[MT];
 #pragma unroll
                 for (int r = 0; r < MT; ++r) {
-                    const uint32_t a32 = k == 0 ? G.ca[m][r].x : k == 1 ? G.ca[m][r].y : k == 2 ? G.ca[m][r].z : G.ca[m][r].w;
+                    const uint4& c4 = G.ca[LATE_A ? m & 1 : m][r];
+                    const uint32_t a32 = k == 0 ? c4.x : k == 1 ? c4.y : k == 2 ? c4.z : c4.w;
                     fa[r] = decode8_half(a32, ha[r], k >> 1);
                 }
 #pragma unroll
@@ -986,10 +1027,17 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
                         acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[r], fw, acc[r][t], 0, 0, 0);
                 }
             }
+            if constexpr (LATE_A)
+                if (m < 2 || roll) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_activations(m < 2 ? g : next, (m + 2) & 3, G);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             if (roll && (m & 1)) {
                 __builtin_amdgcn_sched_barrier(0);
-                load_codes(next, m - 1, G);
-                load_codes(next, m, G);
+                if (WIDE && m == 1) load_scales(next, G);
+                load_codes(next, m - 1, G, !LATE_A);
+                load_codes(next, m, G, !LATE_A);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -1002,16 +1050,16 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
         for (int u = 0; u < U; ++u) {
             const int b0 = 8 * (c0 + u) + 2 * q;
             const bool ok = b0 + 1 < nbk;
-            const int64_t co = ok ? 8 * (int64_t)b0 : 0, so = ok ? b0 : 0;
+            const uint32_t co = ok ? 8u * b0 : 0u, so = ok ? b0 : 0;
 #pragma unroll
             for (int r = 0; r < MT; ++r) {
-                T.ca[u][r] = load16_a8(ac[r] + co);
-                T.sa[u][r] = load2_a1(as[r] + so);
+                T.ca[u][r] = load16_a8(in_row(a_codes, ac[r], 0, co, 16u * q));
+                T.sa[u][r] = load2_a1(in_row(a_scales, scale_row(ac[r], as[r]), 0, so, 8u * q));
             }
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                T.cw[u][t] = load16_a8(wc[t] + co);
-                T.sw[u][t] = load2_a1(ws[t] + so);
+                T.cw[u][t] = load16_a8(in_row(base_c, wc[t], 0, co, 16u * q));
+                T.sw[u][t] = load2_a1(in_row(base_s, scale_row(wc[t], ws[t]), 0, so, 8u * q));
             }
         }
     };
@@ -1060,15 +1108,19 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
                 int g = wave;
                 load_group(g, ga);
                 __builtin_amdgcn_sched_barrier(0);
-                for (; g + WAVES < ngroup; g += WAVES) compute_group(ga, g + WAVES, std::true_type{});
-                compute_group(ga, 0, std::false_type{});
+                for (; g + WAVES < ngroup; g += WAVES) {
+                    int next = g + WAVES;
+                    if (WIDE) asm("" : "+s"(next));     // opaque: followed as induction variables the rows' addresses take two registers each
+                    compute_group(ga, g, next, std::true_type{});
+                }
+                compute_group(ga, g, 0, std::false_type{});
             }
         } else {
             for (int g = wave; g < ngroup; g += WAVES) {
                 Group ga;
                 load_group(g, ga);
                 __builtin_amdgcn_sched_barrier(0);
-                compute_group(ga, 0, std::false_type{});
+                compute_group(ga, g, 0, std::false_type{});
             }
         }
         if (!HOIST && has_tail) load_chunks(tail_c, tail);
@@ -1086,13 +1138,13 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
         uint32_t osa[MT], osw[NT];
 #pragma unroll
         for (int r = 0; r < MT; ++r) {
-            oa[r] = load8_a8(ac[r] + 8 * (int64_t)(nbk - 1));
-            osa[r] = as[r][nbk - 1];
+            oa[r] = load8_a8(in_row(a_codes, ac[r], 8 * (int64_t)(nbk - 1), 0, 16u * q));
+            osa[r] = *in_row(a_scales, scale_row(ac[r], as[r]), nbk - 1, 0, 8u * q);
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            ow[t] = load8_a8(wc[t] + 8 * (int64_t)(nbk - 1));
-            osw[t] = ws[t][nbk - 1];
+            ow[t] = load8_a8(in_row(base_c, wc[t], 8 * (int64_t)(nbk - 1), 0, 16u * q));
+            osw[t] = *in_row(base_s, scale_row(wc[t], ws[t]), nbk - 1, 0, 8u * q);
         }
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
@@ -1109,27 +1161,58 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
         }
     }
 #pragma unroll
-    for (int r = 0; r < MT; ++r)
+    for (int t0 = 0; t0 < NT; t0 += BATCH) {
+        if (t0 > 0) __syncthreads();
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int r = 0; r < MT; ++r)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) red[wave][r * NT + t][e][lane] = acc[r][t][e];
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < MT * NT * 4 * 64; idx += WAVES * 64) {
-        const int rt = idx >> 8, e = (idx >> 6) & 3, l = idx & 63;
-        float sum = 0.f;
+            for (int t = t0; t < (t0 + BATCH < NT ? t0 + BATCH : NT); ++t)
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) sum += red[w][rt][e][l];
-        const int m = 16 * (rt / NT) + 4 * (l >> 4) + e, n = n0 + 16 * (rt % NT) + (l & 15);
-        if (m < M && n < N) store_out(y + (int64_t)m * ldy + n, sum * alpha);
+                for (int e = 0; e < 4; ++e) red[wave][r * BATCH + t - t0][e][lane] = acc[r][t][e];
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < MT * BATCH * 4 * 64; idx += WAVES * 64) {
+            const int rt = idx >> 8, e = (idx >> 6) & 3, l = idx & 63;
+            if (NT % BATCH != 0 && t0 + rt % BATCH >= NT) continue;
+            float sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) sum += red[w][rt][e][l];
+            const int m = 16 * (rt / BATCH) + 4 * (l >> 4) + e, n = n0 + 16 * (t0 + rt % BATCH) + (l & 15);
+            if (m < M && n < N) store_out(y + (int64_t)m * ldy + n, sum * alpha);
+        }
     }
 }
 
-template <int MT, int NT, int WAVES, int U, bool GRP, bool ROLL, typename OutT>
+constexpr int STREAM_ROUND = 256 * 64;      // weight rows of a round of this kernel: a workgroup of four tiles on every compute unit
+
+// BEHIND: weight tiles of the workgroups behind the first STREAM_ROUND weight rows; NT of all others
+template <int MT, int NT, int BEHIND, int WAVES, int U, bool GRP, bool ROLL, typename OutT>
+__global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
+    const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
+    const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N,
+    int nbk, float alpha, OutT* __restrict__ y, int64_t ldy) {
+    constexpr int FLOATS = WAVES * MT * skinny_batch(MT, NT, WAVES) * 256;
+    static_assert(BEHIND <= NT && sizeof(float) * FLOATS <= 64 * 1024, "partial tiles must fit the static LDS limit");
+    __shared__ float red[FLOATS];
+    if constexpr (BEHIND == NT) {
+        skinny_tiles<MT, NT, WAVES, U, GRP, ROLL>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, blockIdx.x * (16 * NT), red);
+    } else {
+        constexpr int FIRST = STREAM_ROUND / (16 * NT);
+        static_assert(FIRST * 16 * NT == STREAM_ROUND, "whole workgroups first");
+        if (blockIdx.x < FIRST)
+            skinny_tiles<MT, NT, WAVES, U, GRP, ROLL>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, blockIdx.x * (16 * NT), red);
+        else
+            skinny_tiles<MT, BEHIND, WAVES, U, GRP, ROLL>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy,
+                                                          STREAM_ROUND + (blockIdx.x - FIRST) * (16 * BEHIND), red);
+    }
+}
+
+template <int MT, int NT, int BEHIND, int WAVES, int U, bool GRP, bool ROLL, typename OutT>
 arcq_status launch_skinny(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                                  const uint8_t* w_scales, int M, int N, int nbk, float alpha, OutT* y, int64_t ldy,
                                  hipStream_t stream) {
-    hipLaunchKernelGGL((gemm_skinny_kernel<MT, NT, WAVES, U, GRP, ROLL, OutT>), dim3((N + 16 * NT - 1) / (16 * NT)),
+    const int rows = BEHIND == NT ? N : std::min(N, STREAM_ROUND), behind = N - rows;
+    const int workgroups = (rows + 16 * NT - 1) / (16 * NT) + (behind + 16 * BEHIND - 1) / (16 * BEHIND);
+    hipLaunchKernelGGL((gemm_skinny_kernel<MT, NT, BEHIND, WAVES, U, GRP, ROLL, OutT>), dim3(workgroups),
                        dim3(WAVES * 64), 0, stream, a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy);
     return check_launch("gemm_skinny_kernel");
 }
@@ -1199,7 +1282,6 @@ static double wide_cost(int64_t M, int64_t N, int rows, double t_stage) {
 }
 
 constexpr int STREAM_WAVES = 8;     // of a workgroup of the weight-streaming kernel (8 x 2 tiles: 4)
-constexpr int STREAM_ROUND = 256 * 64;      // weight rows of a round of that kernel: a workgroup of four tiles on every compute unit
 
 // The weight-streaming kernel's share of the rule: row tiles, weight tiles per wave, and whether the waves load ahead.
 static GemmPlan plan_stream(int64_t M, int64_t N, int64_t Kp) {
@@ -1231,7 +1313,24 @@ static GemmPlan plan_stream(int64_t M, int64_t N, int64_t Kp) {
     else if (mt == 4) ahead = M > 48 ? ngroup >= 12 : ngroup % STREAM_WAVES == 0;
     else if (nt >= 3) ahead = ngroup >= 11 && ngroup % STREAM_WAVES != 1;
     else ahead = mt < 4 && mt * nt != 1 && (mt * nt == 2 || ngroup >= 10);
-    return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, ahead, mt * nt <= 2 ? 2 : 1};
+    GemmPlan plan = {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, ahead, mt * nt <= 2 ? 2 : 1};
+    // Five to seven tiles a wave where they take a round less than four: up to 28672 weight rows in one (from HBM, us: 16 x 22016 over K' = 4352
+    // 18.6 -> 14.4, 16 x 28672 over 8464 38.7 -> 34.6, 32 x 18944 over 2176 14.5 -> 10.3, 32 x 28672 over 4352 24.7 -> 21.1), up to 57344 in two (16 x
+    // 40960 over 4352 28.2 -> 25.0, 32 x 49152 37.6 -> 35.2).  Beyond, rounds overlap so far that it is a draw (16 x 64000 over 4352 39.3 with four, 40.7
+    // with six, 128256 76.6 and 76.1 with seven).  Seven behind two row tiles keep a dozen registers in scratch, which twelve groups pay for too often
+    // (32 x 28672 over 8192 38.0 with four and 41.7; over 5632 29.2 and 28.8): the second round takes three tiles a wave instead of four then, over
+    // 8192 34.7, over 8464 45.8 -> 43.7.  Only where waves load ahead or take one group: they exist in that form alone.
+    const int rounds = tiles <= 7 * 256 ? 1 : 2;
+    if (mt <= 2 && tiles > 4 * 256 * rounds && tiles <= 7 * 256 * rounds && (ahead || ngroup <= STREAM_WAVES)) {
+        const int wide = (int)((tiles + 256 * rounds - 1) / (256 * rounds));
+        if (mt == 1 || wide < 7 || ngroup < 12) {
+            plan.tiles = plan.behind = wide;
+            plan.ahead = true;
+        } else if (rounds == 1) {
+            plan.behind = 3;
+        }
+    }
+    return plan;
 }
 
 // Which kernel serves a problem by rule: a function of the shape alone, so that the workspace a caller sizes beforehand matches what the
@@ -1432,10 +1531,12 @@ arcq_status launch_plan(const GemmPlan& plan, const uint8_t* a_codes, const uint
     const bool aligned16 = ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 && dword_scales;
     if (plan.kernel == ARCQ_ROUTE_STREAM) {
         // (the variants that exist: plan_stream)
-#define ARCQ_STREAM(MT_, NT_, W_, U_, AHEAD_)                                                                                   \
-    if (plan.rows == 16 * MT_ && plan.cols == 16 * NT_ && plan.chunks == U_ && plan.ahead == AHEAD_)                            \
-    return launch_skinny<MT_, NT_, W_, U_, (MT_ <= 4), AHEAD_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, alpha, \
-                                                               y, ldy, stream)
+        const int tiles = plan.tiles ? plan.tiles : plan.cols / 16, behind = plan.behind ? plan.behind : tiles;
+#define ARCQ_STREAM_MIXED(MT_, NT_, BEHIND_, W_, U_, AHEAD_)                                                                      \
+    if (plan.rows == 16 * MT_ && tiles == NT_ && behind == BEHIND_ && plan.chunks == U_ && plan.ahead == AHEAD_)                  \
+    return launch_skinny<MT_, NT_, BEHIND_, W_, U_, (MT_ <= 4), AHEAD_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nbk, \
+                                                                        alpha, y, ldy, stream)
+#define ARCQ_STREAM(MT_, NT_, W_, U_, AHEAD_) ARCQ_STREAM_MIXED(MT_, NT_, NT_, W_, U_, AHEAD_)
         ARCQ_STREAM(1, 1, STREAM_WAVES, 2, false);
         ARCQ_STREAM(1, 1, STREAM_WAVES, 2, true);
         ARCQ_STREAM(1, 2, STREAM_WAVES, 2, true);
@@ -1450,6 +1551,13 @@ arcq_status launch_plan(const GemmPlan& plan, const uint8_t* a_codes, const uint
         ARCQ_STREAM(2, 3, STREAM_WAVES, 1, true);
         ARCQ_STREAM(2, 4, STREAM_WAVES, 1, false);
         ARCQ_STREAM(2, 4, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(1, 5, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(1, 6, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(1, 7, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(2, 5, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(2, 6, STREAM_WAVES, 1, true);
+        ARCQ_STREAM(2, 7, STREAM_WAVES, 1, true);
+        ARCQ_STREAM_MIXED(2, 4, 3, STREAM_WAVES, 1, true);
         ARCQ_STREAM(4, 1, STREAM_WAVES, 1, false);
         ARCQ_STREAM(4, 1, STREAM_WAVES, 1, true);
         ARCQ_STREAM(4, 2, STREAM_WAVES, 1, false);
@@ -1462,6 +1570,7 @@ arcq_status launch_plan(const GemmPlan& plan, const uint8_t* a_codes, const uint
         ARCQ_STREAM(1, 2, STREAM_WAVES, 1, true);
         ARCQ_STREAM(2, 1, STREAM_WAVES, 1, true);
 #undef ARCQ_STREAM
+#undef ARCQ_STREAM_MIXED
         return fail(ARCQ_HIP_ERROR, "no weight-streaming kernel of %d x %d rows, %d chunks, ahead %d", plan.rows, plan.cols, plan.chunks, (int)plan.ahead);
     }
     if (plan.kernel == ARCQ_ROUTE_KSPLIT)

@@ -50,6 +50,8 @@ struct GemmPlan {
     int runs;           // runs of K' across workgroups (ARCQ_ROUTE_TILES)
     bool ahead;         // ARCQ_ROUTE_STREAM: a wave asks for its next group of chunks while it computes one
     int chunks = 1;     // ARCQ_ROUTE_STREAM: left-over chunks (behind the last group) that a wave takes at a time
+    int tiles = 0;      // ARCQ_ROUTE_STREAM: weight tiles of a wave where they are more than four, else 0 (cols / 16 of them)
+    int behind = 0;     // ARCQ_ROUTE_STREAM: weight tiles of a wave behind the first round of workgroups, 0: as in it
 };
 // A problem in one launch, or in two: whole rounds of large tiles over the first `rows` activation rows or the first `cols` weight
 // rows, and the others on whatever is fastest for them.
