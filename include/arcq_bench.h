@@ -42,8 +42,9 @@ arcq_status arcq_ref_gemm_bf16(const void* x, const void* w, int64_t M, int64_t 
  * Which kernel a GEMM problem runs on: a function of its sizes alone (host only, nothing is launched).  Tests ask it, so that
  * a shape written for a tile cannot leave that tile unnoticed when the rule changes; not needed to call the library.
  * ahead: the weight-streaming kernel's waves ask for their next weights while they compute.
- * arcq_gemm_route: the streaming kernel's 64 columns stand for up to 112 where more than 16384 weight rows run in one launch of up to 32
- * rows (64, then 48, where that is the second round); operands whose scale bytes lie at odd addresses run another tile where the one named was taken for its modelled time (with
+ * The streaming kernels' 64 columns stand for up to 112 where more than 16384 weight rows run in one launch of up to 32 rows (64, then 32 or
+ * 48 in the second round, where registers allow no more).
+ * arcq_gemm_route: operands whose scale bytes lie at odd addresses run another tile where the one named was taken for its modelled time (with
  * 65 to 128 rows the streaming kernel), and they, or K' < 256 off the grid of 64, have no 256 x 256 tiles and may run 192 x 256 or
  * 128 x 256 ones instead.  arcq_mx_gemm_route: such operands (or K' < 512 off the grid of 128) run 256-wide
  * or 128 x 128 tiles instead of 192 x 128 ones; with_workspace: as arcq_mx_gemm_ws (non-zero) or arcq_mx_gemm (0).

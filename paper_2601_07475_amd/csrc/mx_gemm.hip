@@ -535,16 +535,18 @@ __device__ __forceinline__ uint32_t transpose_scale_bytes(uint32_t s, uint32_t s
     return __builtin_amdgcn_perm(t[1], t[0], sel_byte);                        // byte q of chunks 0, 1, 2, 3
 }
 
+// weight tiles whose partial sums fit the static LDS limit at a time
+constexpr int mx_skinny_batch(int mt, int nt, int waves) { return waves * mt * nt > 64 ? (nt + 1) / 2 : nt; }
+
 template <int MT, int NT, int WAVES, int U, bool GRP, typename OutT>
-__global__ __launch_bounds__(WAVES * 64) void mx_gemm_skinny_kernel(
+__device__ __forceinline__ void mx_skinny_tiles(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N, int nb,
-    OutT* __restrict__ y, int64_t ldy) {
-    __shared__ float red[WAVES][MT * NT][4][64];
-    static_assert(sizeof(float) * WAVES * MT * NT * 256 <= 64 * 1024, "partial tiles must fit the static LDS limit");
+    OutT* __restrict__ y, int64_t ldy, int n0, float* red_memory) {
+    constexpr int BATCH = mx_skinny_batch(MT, NT, WAVES);
+    auto& red = *reinterpret_cast<float (*)[WAVES][MT * BATCH][4][64]>(red_memory);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // scalar: see gemm.hip
     const int i = lane & 15, q = lane >> 4;
-    const int n0 = blockIdx.x * (16 * NT);
     const int64_t cpitch = (int64_t)nb * 16, spitch = nb;
     const int nchunk = (nb + 3) >> 2;                            // the last chunk may hold fewer than four blocks
 
@@ -651,26 +653,57 @@ __global__ __launch_bounds__(WAVES * 64) void mx_gemm_skinny_kernel(
         }
     }
 #pragma unroll
-    for (int r = 0; r < MT; ++r)
+    for (int t0 = 0; t0 < NT; t0 += BATCH) {
+        if (t0 > 0) __syncthreads();
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int r = 0; r < MT; ++r)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) red[wave][r * NT + t][e][lane] = acc[r][t][e];
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < MT * NT * 4 * 64; idx += WAVES * 64) {
-        const int rt = idx >> 8, e = (idx >> 6) & 3, l = idx & 63;
-        float sum = 0.f;
+            for (int t = t0; t < (t0 + BATCH < NT ? t0 + BATCH : NT); ++t)
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) sum += red[w][rt][e][l];
-        const int m = 16 * (rt / NT) + 4 * (l >> 4) + e, n = n0 + 16 * (rt % NT) + (l & 15);
-        if (m < M && n < N) store_out(y + (int64_t)m * ldy + n, sum);
+                for (int e = 0; e < 4; ++e) red[wave][r * BATCH + t - t0][e][lane] = acc[r][t][e];
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < MT * BATCH * 4 * 64; idx += WAVES * 64) {
+            const int rt = idx >> 8, e = (idx >> 6) & 3, l = idx & 63;
+            if (NT % BATCH != 0 && t0 + rt % BATCH >= NT) continue;
+            float sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) sum += red[w][rt][e][l];
+            const int m = 16 * (rt / BATCH) + 4 * (l >> 4) + e, n = n0 + 16 * (t0 + rt % BATCH) + (l & 15);
+            if (m < M && n < N) store_out(y + (int64_t)m * ldy + n, sum);
+        }
     }
 }
 
-template <int MT, int NT, int WAVES, int U, typename OutT>
+constexpr int MX_STREAM_ROUND = 256 * 64;       // weight rows: a workgroup of eight waves x four tiles on every compute unit
+
+// BEHIND: weight tiles of the workgroups behind the first MX_STREAM_ROUND weight rows; NT of all others
+template <int MT, int NT, int BEHIND, int WAVES, int U, bool GRP, typename OutT>
+__global__ __launch_bounds__(WAVES * 64) void mx_gemm_skinny_kernel(
+    const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
+    const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N, int nb,
+    OutT* __restrict__ y, int64_t ldy) {
+    constexpr int FLOATS = WAVES * MT * mx_skinny_batch(MT, NT, WAVES) * 256;
+    static_assert(BEHIND <= NT && sizeof(float) * FLOATS <= 64 * 1024, "partial tiles must fit the static LDS limit");
+    __shared__ float red[FLOATS];
+    if constexpr (BEHIND == NT) {
+        mx_skinny_tiles<MT, NT, WAVES, U, GRP>(a_codes, a_scales, w_codes, w_scales, M, N, nb, y, ldy, blockIdx.x * (16 * NT), red);
+    } else {
+        constexpr int FIRST = MX_STREAM_ROUND / (16 * NT);
+        static_assert(FIRST * 16 * NT == MX_STREAM_ROUND, "whole workgroups first");
+        if (blockIdx.x < FIRST)
+            mx_skinny_tiles<MT, NT, WAVES, U, GRP>(a_codes, a_scales, w_codes, w_scales, M, N, nb, y, ldy, blockIdx.x * (16 * NT), red);
+        else
+            mx_skinny_tiles<MT, BEHIND, WAVES, U, GRP>(a_codes, a_scales, w_codes, w_scales, M, N, nb, y, ldy,
+                                                       MX_STREAM_ROUND + (blockIdx.x - FIRST) * (16 * BEHIND), red);
+    }
+}
+
+template <int MT, int NT, int BEHIND, int WAVES, int U, typename OutT>
 arcq_status launch_mx_skinny(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes,
                              const uint8_t* w_scales, int M, int N, int nb, OutT* y, int64_t ldy, hipStream_t stream) {
-    hipLaunchKernelGGL((mx_gemm_skinny_kernel<MT, NT, WAVES, U, (MT <= 4), OutT>), dim3((N + 16 * NT - 1) / (16 * NT)),
+    const int rows = BEHIND == NT ? N : std::min(N, MX_STREAM_ROUND), behind = N - rows;
+    const int workgroups = (rows + 16 * NT - 1) / (16 * NT) + (behind + 16 * BEHIND - 1) / (16 * BEHIND);
+    hipLaunchKernelGGL((mx_gemm_skinny_kernel<MT, NT, BEHIND, WAVES, U, (MT <= 4), OutT>), dim3(workgroups),
                        dim3(WAVES * 64), 0, stream, a_codes, a_scales, w_codes, w_scales, M, N, nb, y, ldy);
     return check_launch("mx_gemm_skinny_kernel");
 }
@@ -760,7 +793,18 @@ static GemmPlan plan_mx_stream(int64_t M, int64_t N) {
     const int64_t tiles = (N + 15) / 16;
     const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
     const int nt = tiles <= 256 ? 1 : tiles <= 512 || mt > 2 ? 2 : tiles <= 768 ? 3 : 4;
-    return {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, false, mt * nt <= 2 ? 2 : 1};
+    GemmPlan plan = {ARCQ_ROUTE_STREAM, 16 * mt, 16 * nt, 1, false, mt * nt <= 2 ? 2 : 1};
+    // Five to seven tiles a wave where they take a round less than four: up to 28672 weight rows in one (from HBM, us: 1 x 22016 over K' = 4352 14.4 ->
+    // 11.4, 16 x 28672 over 5632 20.8 -> 17.5, 32 x 18944 over 2176 11.6 -> 8.7), up to 57344 in two (16 x 40960 over 4352 24.1 -> 21.4, 1 x 57344 over
+    // 2176 17.7 -> 16.1).  Two row tiles leave the registers of five; up to 28672 weight rows the second round takes two or three tiles a wave instead
+    // of four (32 x 22016 over 4352 18.7 -> 16.2, 32 x 28672 over 2176 12.2 -> 11.7).
+    const int rounds = tiles <= 7 * 256 ? 1 : 2;
+    if (mt <= 2 && tiles > 4 * 256 * rounds && tiles <= 7 * 256 * rounds) {
+        const int wide = (int)((tiles + 256 * rounds - 1) / (256 * rounds));
+        if (mt == 1 || wide == 5) plan.tiles = plan.behind = wide;
+        else if (rounds == 1) plan.behind = wide - 4;
+    }
+    return plan;
 }
 
 static GemmPlan plan_mx_one(int64_t M, int64_t N, int64_t Kp, bool workspace) {
@@ -777,8 +821,6 @@ static GemmPlan plan_mx_one(int64_t M, int64_t N, int64_t Kp, bool workspace) {
     if (const int rows = mx_wide_rows(M, N)) return {ARCQ_ROUTE_TILES, rows, 256, 1, false};
     return {ARCQ_ROUTE_TILES, 128, 128, workspace ? mx_split_k(M, N, Kp) : 1, false};
 }
-
-constexpr int64_t MX_STREAM_ROUND = 256 * 64;       // weight rows: a workgroup of eight waves x four tiles on every compute unit
 
 GemmParts plan_mx_gemm_parts(int64_t M, int64_t N, int64_t Kp, bool workspace) {
     const GemmPlan one = plan_mx_one(M, N, Kp, workspace);
@@ -807,9 +849,11 @@ arcq_status launch_mx_plan(const GemmPlan& plan, const uint8_t* a_codes, const u
     const bool dword_scales = ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales)) & 3) == 0;
     const bool aligned16 = ((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15) == 0 && dword_scales;
     if (plan.kernel == ARCQ_ROUTE_STREAM) {
-#define ARCQ_MX_STREAM(MT_, NT_, U_)                                           \
-    if (plan.rows == 16 * MT_ && plan.cols == 16 * NT_ && plan.chunks == U_) \
-    return launch_mx_skinny<MT_, NT_, 8, U_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream)
+        const int tiles = plan.tiles ? plan.tiles : plan.cols / 16, behind = plan.behind ? plan.behind : tiles;
+#define ARCQ_MX_STREAM_MIXED(MT_, NT_, BEHIND_, U_)                                                 \
+    if (plan.rows == 16 * MT_ && tiles == NT_ && behind == BEHIND_ && plan.chunks == U_)             \
+    return launch_mx_skinny<MT_, NT_, BEHIND_, 8, U_>(a_codes, a_scales, w_codes, w_scales, (int)M, (int)N, nb, y, ldy, stream)
+#define ARCQ_MX_STREAM(MT_, NT_, U_) ARCQ_MX_STREAM_MIXED(MT_, NT_, NT_, U_)
         ARCQ_MX_STREAM(1, 1, 2);
         ARCQ_MX_STREAM(1, 2, 2);
         ARCQ_MX_STREAM(1, 3, 1);
@@ -818,6 +862,12 @@ arcq_status launch_mx_plan(const GemmPlan& plan, const uint8_t* a_codes, const u
         ARCQ_MX_STREAM(2, 2, 1);
         ARCQ_MX_STREAM(2, 3, 1);
         ARCQ_MX_STREAM(2, 4, 1);
+        ARCQ_MX_STREAM(1, 5, 1);
+        ARCQ_MX_STREAM(1, 6, 1);
+        ARCQ_MX_STREAM(1, 7, 1);
+        ARCQ_MX_STREAM(2, 5, 1);
+        ARCQ_MX_STREAM_MIXED(2, 4, 2, 1);
+        ARCQ_MX_STREAM_MIXED(2, 4, 3, 1);
         ARCQ_MX_STREAM(4, 1, 1);
         ARCQ_MX_STREAM(4, 2, 1);
         // the second launch of two
@@ -825,6 +875,7 @@ arcq_status launch_mx_plan(const GemmPlan& plan, const uint8_t* a_codes, const u
         ARCQ_MX_STREAM(1, 2, 1);
         ARCQ_MX_STREAM(2, 1, 1);
 #undef ARCQ_MX_STREAM
+#undef ARCQ_MX_STREAM_MIXED
         return fail(ARCQ_HIP_ERROR, "no weight-streaming kernel of %d x %d rows, %d chunks", plan.rows, plan.cols, plan.chunks);
     }
     // How the units get into LDS: whole aligned pieces; any K' (a multiple of 32) from 512 on, codes at their minimum alignment;
