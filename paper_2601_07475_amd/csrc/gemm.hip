@@ -907,6 +907,7 @@ __device__ __forceinline__ void skinny_tiles(
     const uint8_t* const base_c = w_codes + (WIDE ? n0 * cpitch : 0);
     const uint8_t* const base_s = w_scales + (WIDE ? n0 * spitch : 0);
     using Row = std::conditional_t<WIDE, uint32_t, const uint8_t*>;
+    using Offset = std::conditional_t<WIDE, uint32_t, int64_t>;
     Row ac[MT], as[MT], wc[NT], ws[NT];
 #pragma unroll
     for (int r = 0; r < MT; ++r) {
@@ -936,7 +937,7 @@ __device__ __forceinline__ void skinny_tiles(
     };
     // byte `uniform` + `own` (a lane's) of a row; WIDE: rows come with a lane's place in a group of chunks, `place`, and the offset is opaque, so that no
     // 64-bit address of a row is kept
-    auto in_row = [](const uint8_t* base, Row row, int64_t uniform, uint32_t own, uint32_t place) -> const uint8_t* {
+    auto in_row = [](const uint8_t* base, Row row, int64_t uniform, Offset own, uint32_t place) -> const uint8_t* {
         if constexpr (WIDE) {
             uint32_t offset = row + (own - place);
             asm("" : "+v"(offset));
@@ -968,20 +969,20 @@ __device__ __forceinline__ void skinny_tiles(
     auto load_scales = [&](int g, Group& G) {
         const int64_t so = 32 * (int64_t)g;
 #pragma unroll
-        for (int r = 0; r < MT; ++r) G.sa2[r] = load8_a1(in_row(a_scales, scale_row(ac[r], as[r]), so, 8u * q, 8u * q));
+        for (int r = 0; r < MT; ++r) G.sa2[r] = load8_a1(in_row(a_scales, scale_row(ac[r], as[r]), so, 8 * q, 8 * q));
 #pragma unroll
-        for (int t = 0; t < NT; ++t) G.sw2[t] = load8_a1(in_row(base_s, scale_row(wc[t], ws[t]), so, 8u * q, 8u * q));
+        for (int t = 0; t < NT; ++t) G.sw2[t] = load8_a1(in_row(base_s, scale_row(wc[t], ws[t]), so, 8 * q, 8 * q));
     };
     auto load_activations = [&](int g, int m, Group& G) {
         const int64_t co = 256 * (int64_t)g + 64 * m;
 #pragma unroll
-        for (int r = 0; r < MT; ++r) G.ca[LATE_A ? m & 1 : m][r] = load16_a8(in_row(a_codes, ac[r], co, 16u * q, 16u * q));
+        for (int r = 0; r < MT; ++r) G.ca[LATE_A ? m & 1 : m][r] = load16_a8(in_row(a_codes, ac[r], co, 16 * q, 16 * q));
     };
     auto load_codes = [&](int g, int m, Group& G, bool activations) {
         const int64_t co = 256 * (int64_t)g + 64 * m;
         if (activations) load_activations(g, m, G);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) G.cw[m][t] = load16_a8(in_row(base_c, wc[t], co, 16u * q, 16u * q));
+        for (int t = 0; t < NT; ++t) G.cw[m][t] = load16_a8(in_row(base_c, wc[t], co, 16 * q, 16 * q));
     };
     auto load_group = [&](int g, Group& G) {
         load_scales(g, G);
@@ -1050,7 +1051,7 @@ __device__ __forceinline__ void skinny_tiles(
         for (int u = 0; u < U; ++u) {
             const int b0 = 8 * (c0 + u) + 2 * q;
             const bool ok = b0 + 1 < nbk;
-            const uint32_t co = ok ? 8u * b0 : 0u, so = ok ? b0 : 0;
+            const Offset co = ok ? 8 * (Offset)b0 : 0, so = ok ? b0 : 0;
 #pragma unroll
             for (int r = 0; r < MT; ++r) {
                 T.ca[u][r] = load16_a8(in_row(a_codes, ac[r], 0, co, 16u * q));
