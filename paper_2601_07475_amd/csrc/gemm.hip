@@ -1475,8 +1475,8 @@ GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
     // in.)  From HBM, us, 1 and 32 rows: 17408 weight rows over K' = 4096 16.2 -> 13.6 and 20.9 -> 18.1, over 14592 44.5 -> 35.8 and 58.0 -> 47.4;
     // 20480 over 4352 17.1 -> 14.9 and 23.0 -> 20.0; 24576 over 6144 22.9 -> 20.7 and 29.7 -> 28.0, over 14592 47.2 -> 42.9 and 60.3 -> 55.0.  Within
     // the limits 84 sizes gain 1.5 us and more, 1.05 to 1.26x.  A pass that runs the second kernel for the first time takes 5 us more, which the
-    // fifth at the latest has made up for.  Less is gained, and one launch kept, with three tiles a wave (32 x 28672 over 8464
-    // 45.0 -> 43.5), few rows behind the round (16 x 16400 over 4352 15.7 -> 15.5) or a shorter K' (16 x 20480 over 2176 12.0 -> 11.5, 16 x 24576 over 4352 19.1 -> 18.0).
+    // fifth at the latest has made up for.  Elsewhere, with three tiles a wave behind the round, few rows there or a shorter
+    // K', a second launch gains less than one of more tiles a wave (plan_stream: 16 x 16400 over 4352 15.7, 15.5 in two, 12.3; 16 x 24576 over 4352 19.1, 18.0 and 15.2).
     const int64_t behind = N - STREAM_ROUND;
     if (rule.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= STREAM_ROUND / 2 &&
         Kp >= (behind > STREAM_ROUND / 4 ? 6144 : 4096)) {

@@ -827,8 +827,8 @@ GemmParts plan_mx_gemm_parts(int64_t M, int64_t N, int64_t Kp, bool workspace) {
     // The streaming kernel with more weight rows than one round of four tiles a wave takes: that round, and the rest with one or two tiles a
     // wave in a launch of its own (see plan_gemm_parts in gemm.hip).  From HBM, us, 1 and 16 rows: 17408 weight rows over K' = 4096 13.5 -> 11.7 and
     // 14.9 -> 13.2, 20480 over 4352 14.2 -> 12.6 and 15.8 -> 14.0, over 8448 24.4 -> 20.2 and 27.7 -> 22.9, 24576 over 6144 19.5 -> 17.9 and 22.4 -> 20.3:
-    // within NVFP4's limits 52 sizes gain 1.3 us and more, 1.07 to 1.22x.  Not worth a launch: few rows behind the round (1 x 16400 over 4352 11.0, 12.0 in two),
-    // three tiles a wave (1 x 28672 over 6400 21.6 and 22.3), a shorter K' (16 x 24576 over 2176 9.9 and 10.4).
+    // within NVFP4's limits 52 sizes gain 1.3 us and more, 1.07 to 1.22x.  Elsewhere a second launch loses to one of more tiles a wave (plan_mx_stream: 1 x 16400
+    // over 4352 11.0, 12.0 in two, 9.5; 1 x 28672 over 6400 21.6, 22.3 and 19.8; 16 x 24576 over 2176 9.9, 10.4 and 8.0).
     const int64_t behind = N - MX_STREAM_ROUND;
     if (one.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= MX_STREAM_ROUND / 2 &&
         Kp >= (behind > MX_STREAM_ROUND / 4 ? 6144 : 4096)) {
