@@ -69,10 +69,12 @@ struct ScaleChunks {
         constexpr int WORDS = CHUNK / 4, RW = 64 / WORDS;           // lanes of a row, rows of a copy: 8 and 8, 4 and 16
         const uint32_t row = lane / WORDS, word = lane % WORDS;
         const uint32_t even = row * (step / R) + 4u * word, odd = row * (step / R) + 4u * (word ^ (LANES == 2 ? 4u : 0u));
+        const uint32_t all = copies * (R / RW);                     // (a wave with fewer than the others repeats its last two, which are unlike each other)
 #pragma unroll
-        for (int k = 0; k < (NA > NW ? NA : NW) * R / RW; ++k)      // (a wave with fewer rows repeats the last ones)
-            copy4(rows, k & 1 ? odd : even, first_byte, min((uint32_t)k, copies * (R / RW) - 1u) * (RW * (step / R)),
-                  ring + to + min((uint32_t)k, copies * (R / RW) - 1u) * (RW * CHUNK));
+        for (int k = 0; k < (NA > NW ? NA : NW) * R / RW; ++k) {
+            const uint32_t i = min((uint32_t)k, all - 2u + (k & 1));
+            copy4(rows, k & 1 ? odd : even, first_byte, i * (RW * (step / R)), ring + to + i * (RW * CHUNK));
+        }
     }
     // copy i of a group of a chunk (a wave with fewer copies than the groups have repeats its last one)
     __device__ __forceinline__ void issue(int i, int group, int chunk, uint32_t ring) const {
