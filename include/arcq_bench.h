@@ -29,6 +29,16 @@ arcq_status arcq_probe_mfma_f16(int iters, float* sink, double* flop_host, void*
 arcq_status arcq_probe_mfma_fp4(int iters, float* sink, double* flop_host, void* stream);
 
 /*
+ * What a copy into LDS through a buffer descriptor does at the end of its buffer, for a test (arcq_mx_gemm's tiles copy rows past the edge of an
+ * operand that way): one wave, each lane `words` words from byte `scalar` + 4 * words * lane of the first `bytes` bytes of src.
+ * src    device, readable for scalar + 1024 bytes whatever `bytes` is, 16-byte aligned
+ * bytes, scalar  multiples of 4, scalar <= bytes       words  1 or 4
+ * out    device, 256 words: what the copy left in LDS, ARCQ_PROBE_UNTOUCHED where it wrote nothing
+ */
+#define ARCQ_PROBE_UNTOUCHED 0xA5A5A5A5u
+arcq_status arcq_probe_buffer_copy(const void* src, uint32_t bytes, uint32_t scalar, int words, uint32_t* out, void* stream);
+
+/*
  * Comparison kernel for measurements (no part of the method): the unquantized linear layer y = x w^T on bf16
  * operands, written on the same tiled skeleton as arcq_mx_gemm (operand rows travel global -> LDS in 128-byte
  * units, v_mfma_f32_32x32x16_bf16, fp32 accumulation), the 16-bit baseline the quantized path is timed against.

@@ -57,6 +57,7 @@ SIGNATURES = {
     "arcq_gemm_noalloc": (ctypes.c_int, [_vp, _vp, _f32, _vp, _vp, _f32, _i64, _i64, _i64, _vp, ctypes.c_int, _i64, _vp]),
     "arcq_probe_mfma_f16": (ctypes.c_int, [ctypes.c_int, _vp, ctypes.POINTER(ctypes.c_double), _vp]),
     "arcq_probe_mfma_fp4": (ctypes.c_int, [ctypes.c_int, _vp, ctypes.POINTER(ctypes.c_double), _vp]),
+    "arcq_probe_buffer_copy": (ctypes.c_int, [_vp, _u32, _u32, ctypes.c_int, _vp, _vp]),
     "arcq_ref_gemm_bf16": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _vp, _i64, _vp]),
     "arcq_gemm_route": (ctypes.c_int, [_i64, _i64, _i64, ctypes.POINTER(Route)]),
     "arcq_mx_gemm_route": (ctypes.c_int, [_i64, _i64, _i64, ctypes.c_int, ctypes.POINTER(Route)]),
@@ -413,6 +414,17 @@ def arcq_probe_mfma_f16(iters, sink=None):
 def arcq_probe_mfma_fp4(iters, sink=None):
     """Enqueues the scaled-FP4 matrix-rate probe; returns the floating-point operations of the launch."""
     return _probe("arcq_probe_mfma_fp4", iters, sink)
+
+
+PROBE_UNTOUCHED = 0xA5A5A5A5
+
+
+def arcq_probe_buffer_copy(src, size, scalar, words):
+    """The 256 words that one wave's copy of `words` words a lane leaves in LDS, from byte `scalar` of the first `size` bytes of src on."""
+    assert src.is_cuda and src.is_contiguous() and src.numel() * src.element_size() >= max(size, scalar + 1024)
+    out = torch.empty(256, dtype=torch.int32, device="cuda")
+    _check(lib().arcq_probe_buffer_copy(_ptr(src), size, scalar, words, _ptr(out), _stream()))
+    return out
 
 
 def arcq_gemm_route(M, N, Kp):

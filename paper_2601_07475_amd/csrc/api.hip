@@ -317,6 +317,15 @@ arcq_status arcq_probe_mfma_fp4(int iters, float* sink, double* flop_host, void*
     return launch_probe_mfma_fp4(iters, sink, flop_host, static_cast<hipStream_t>(stream));
 }
 
+arcq_status arcq_probe_buffer_copy(const void* src, uint32_t bytes, uint32_t scalar, int words, uint32_t* out, void* stream) {
+    clear_error();
+    if (words != 1 && words != 4) return fail(ARCQ_INVALID_ARG, "arcq_probe_buffer_copy: words = %d, not 1 or 4", words);
+    if (scalar > bytes) return fail(ARCQ_INVALID_ARG, "arcq_probe_buffer_copy: scalar offset %u past the buffer's %u bytes", scalar, bytes);
+    if (!src || !out) return fail(ARCQ_INVALID_ARG, "arcq_probe_buffer_copy: null pointer");
+    if (!aligned(src, 16) || !aligned(out, 4) || bytes % 4 || scalar % 4) return fail(ARCQ_BAD_ALIGN, "arcq_probe_buffer_copy: whole words, src 16-byte aligned");
+    return launch_probe_buffer_copy(static_cast<const uint8_t*>(src), bytes, scalar, words, out, static_cast<hipStream_t>(stream));
+}
+
 arcq_status arcq_ref_gemm_bf16(const void* x, const void* w, int64_t M, int64_t N, int64_t K, void* y, int64_t ldy,
                                void* stream) {
     clear_error();

@@ -78,6 +78,7 @@ arcq_status launch_gemm_ksplit(int rows, int cols, const uint8_t* a_codes, const
 
 arcq_status launch_probe_mfma_f16(int iters, float* sink, double* flop_host, hipStream_t stream);
 arcq_status launch_probe_mfma_fp4(int iters, float* sink, double* flop_host, hipStream_t stream);
+arcq_status launch_probe_buffer_copy(const uint8_t* src, uint32_t bytes, uint32_t scalar, int words, uint32_t* out, hipStream_t stream);
 arcq_status launch_ref_gemm_bf16(const void* x, const void* w, int64_t M, int64_t N, int64_t K, _Float16* y, int64_t ldy,
                                  hipStream_t stream);
 arcq_status launch_check_perm(const int32_t* perm, int64_t K, uint8_t* flags,

@@ -38,10 +38,13 @@ __device__ __forceinline__ void dma4(const void* gbase, uint32_t voffset, uint32
                  : "memory", "m0");
 }
 
-// The same through a buffer descriptor: address = base + voffset (a lane's) + soffset0 + soffset1 (scalars), and words at or past `bytes` from the
-// base arrive as zeros and are not read.  A copy then needs no vector instruction: rows a fixed distance apart are a scalar apart, and rows
-// past the edge of an operand need no clamp.  (With addresses of their own a copy costs up to six vector instructions, a 32-bit multiplication
-// among them, where registers are short.)  The addition keeps the distance that M0 needs from its use.
+// The same through a buffer descriptor: address = base + voffset (a lane's) + scalar offset (one, or the sum of two).  Words at or past `bytes` from
+// the base are not read and arrive as zeros, PROVIDED THAT THE SCALAR OFFSET IS AT MOST `bytes`, which the caller sees to: without a stride a
+// word is out of range where voffset >= bytes - scalar offset, and that difference means nothing below zero.  (tests/test_gpu_buffer_copies.py
+// has both copies do it, with the scalar offset below and at `bytes`.)
+// A copy then needs no vector instruction: rows a fixed distance apart are a scalar apart, and rows past the edge of an operand need no clamp per
+// lane.  (With addresses of their own a copy costs up to six vector instructions, a 32-bit multiplication among them, where registers are short.)
+// The addition, or the empty slot, keeps the distance that M0 needs from its use.
 typedef uint32_t buffer_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ buffer_t buffer_of(const uint8_t* base, uint32_t bytes) {
     const uint64_t at = reinterpret_cast<uint64_t>(base);
@@ -54,13 +57,17 @@ __device__ __forceinline__ void copy16(const buffer_t& b, uint32_t voffset, uint
                  : "v"(voffset), "s"(lds_wave_base), "s"(b), "s"(soffset0), "s"(soffset1)
                  : "memory", "m0", "scc");
 }
-
-__device__ __forceinline__ void copy4(const buffer_t& b, uint32_t voffset, uint32_t soffset0, uint32_t soffset1, uint32_t lds_wave_base) {
-    uint32_t sum;
-    asm volatile("s_mov_b32 m0, %2\n\ts_add_u32 %0, %4, %5\n\tbuffer_load_dword %1, %3, %0 offen lds"
-                 : "=&s"(sum)
-                 : "v"(voffset), "s"(lds_wave_base), "s"(b), "s"(soffset0), "s"(soffset1)
-                 : "memory", "m0", "scc");
+__device__ __forceinline__ void copy16(const buffer_t& b, uint32_t voffset, uint32_t soffset, uint32_t lds_wave_base) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, %3 offen lds"
+                 :
+                 : "v"(voffset), "s"(lds_wave_base), "s"(b), "s"(soffset)
+                 : "memory", "m0");
+}
+__device__ __forceinline__ void copy4(const buffer_t& b, uint32_t voffset, uint32_t soffset, uint32_t lds_wave_base) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dword %0, %2, %3 offen lds"
+                 :
+                 : "v"(voffset), "s"(lds_wave_base), "s"(b), "s"(soffset)
+                 : "memory", "m0");
 }
 
 // s_waitcnt on the vector-memory counter only (gfx9 encoding: vmcnt in bits 3:0 and 15:14;

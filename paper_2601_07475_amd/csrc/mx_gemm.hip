@@ -9,6 +9,7 @@
 // No decode: packed operands go global -> LDS -> registers -> matrix core unchanged.
 #include "gemm_epilogue.h"
 #include "internal.h"
+#include "code_rows.h"
 #include "gemm_decode.h"
 #include "lds_dma.h"
 #include "scale_chunks.h"
@@ -143,10 +144,8 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     const typename C::Chunks chunks(a_scales, w_scales, M, N, nb, wg_m0, wg_n0, (uint32_t)lane, wave_slot >> 6, 8 * u0);      // COPIES
     const typename C::Windows windows(a_scales, w_scales, M, N, nb, wg_m0, wg_n0, (uint32_t)tid, wave_slot, 8 * u0);    // RAGGED
     const int patch_from = C::Windows::patch_from(nb);
-    // The offset of this lane's piece of a unit: the same for every copy, whose rows are a scalar apart; rows past the edge of an operand
-    // arrive as zeros (never stored).
-    const buffer_t buf_a = buffer_of(a_codes + (int64_t)wg_m0 * cpitch, (uint32_t)(M - wg_m0) * cpitch);
-    const buffer_t buf_w = buffer_of(w_codes + (int64_t)wg_n0 * cpitch, (uint32_t)(N - wg_n0) * cpitch);
+    // The offset of this lane's piece of a unit: the same for every copy, whose rows are a scalar apart.
+    const CodeRows<C::NT / 8> rows_a(a_codes, M, wg_m0, cpitch), rows_w(w_codes, N, wg_n0, cpitch);
     const uint32_t row_off = (uint32_t)crow * cpitch;
     auto lane_offset = [&](int unit) -> uint32_t {
         if (RAG) return row_off + 16u * (uint32_t)min(8 * unit + (int)lp, nb - 1);
@@ -154,10 +153,10 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
     };
     // copy d of a unit: A code pieces, W code pieces
     auto issue_one = [&](int d, int unit, int buf, uint32_t voffset) {
-        const uint32_t base = lds0 + C::UNITS + buf * C::UNIT_BYTES + 16u * wave_slot, soffset = RAG ? 0u : (uint32_t)unit * 128u;
+        const uint32_t base = lds0 + C::UNITS + buf * C::UNIT_BYTES + 16u * wave_slot, column = RAG ? 0u : (uint32_t)unit * 128u;
         constexpr int NA = C::NA, NT = C::NT;
-        if (d < NA) copy16(buf_a, voffset, soffset, d * (NT / 8) * cpitch, base + C::A_CODES + 16 * d * NT);
-        else copy16(buf_w, voffset, soffset, (d - NA) * (NT / 8) * cpitch, base + C::W_CODES + 16 * (d - NA) * NT);
+        if (d < NA) rows_a.issue(d, voffset, column, base + C::A_CODES + 16 * d * NT);
+        else rows_w.issue(d - NA, voffset, column, base + C::W_CODES + 16 * (d - NA) * NT);
     };
 
     // ---- REGS: the same pieces through registers (piece d of a thread lands where copy d puts it); needs nb >= 4

@@ -3,8 +3,10 @@
 // both operands held in registers and no memory traffic in the loop.  The figures are the practical
 // ceilings the GEMMs' roofline fractions should be read against: under a sustained matrix load the chip
 // clocks below the frequency the published peaks assume.
+// And what a buffer copy into LDS (lds_dma.h) does with words past the end of its buffer, which the MXFP4 tiles' copies of ragged rows rest on.
 #include "internal.h"
 #include "gemm_epilogue.h"
+#include "lds_dma.h"
 
 namespace arcq {
 
@@ -71,7 +73,27 @@ __global__ __launch_bounds__(PROBE_THREADS) void mfma_fp4_rate_kernel(int iters,
     sink[gid] = s;
 }
 
+// One wave, one copy of `words` words a lane; what is in LDS then goes to `out`.
+__global__ __launch_bounds__(64) void buffer_copy_kernel(const uint8_t* __restrict__ src, uint32_t bytes, uint32_t scalar, int words, uint32_t* __restrict__ out) {
+    __shared__ __attribute__((aligned(16))) uint32_t lds[256];
+    const uint32_t lane = threadIdx.x;
+    for (uint32_t i = lane; i < 256; i += 64) lds[i] = ARCQ_PROBE_UNTOUCHED;
+    __syncthreads();
+    const buffer_t b = buffer_of(src, bytes);
+    const uint32_t to = __builtin_amdgcn_readfirstlane(lds_address(lds));
+    if (words == 4) copy16(b, 16u * lane, scalar, to);
+    else copy4(b, 4u * lane, scalar, to);
+    wait_vmcnt<0>();
+    __syncthreads();
+    for (uint32_t i = lane; i < 256; i += 64) out[i] = lds[i];
+}
+
 }  // namespace
+
+arcq_status launch_probe_buffer_copy(const uint8_t* src, uint32_t bytes, uint32_t scalar, int words, uint32_t* out, hipStream_t stream) {
+    hipLaunchKernelGGL(buffer_copy_kernel, dim3(1), dim3(64), 0, stream, src, bytes, scalar, words, out);
+    return check_launch("buffer_copy_kernel");
+}
 
 arcq_status launch_probe_mfma_fp4(int iters, float* sink, double* flop_host, hipStream_t stream) {
     hipLaunchKernelGGL(mfma_fp4_rate_kernel, dim3(PROBE_WGS), dim3(PROBE_THREADS), 0, stream, iters, sink);

@@ -13,6 +13,8 @@
 namespace arcq {
 
 // Units are counted from the first one of the workgroup's run here; `first_byte` is where that one's scale bytes are in a row.
+// Copies of rows past the edge of an operand, and of chunks past the end of its last row, start at its end at the latest: a scalar offset beyond it would
+// leave the range check of a buffer nothing to compare with (lds_dma.h).
 
 // As few copies a wave and group as let `waves` waves with rows of one operand each have all rows.
 constexpr int copies_of_group(int copies_a, int copies_w, int groups, int waves) {
@@ -73,14 +75,14 @@ struct ScaleChunks {
 #pragma unroll
         for (int k = 0; k < (NA > NW ? NA : NW) * R / RW; ++k) {
             const uint32_t i = min((uint32_t)k, all - 2u + (k & 1));
-            copy4(rows, k & 1 ? odd : even, first_byte, i * (RW * (step / R)), ring + to + i * (RW * CHUNK));
+            copy4(rows, k & 1 ? odd : even, min(first_byte + i * (RW * (step / R)), rows[2]), ring + to + i * (RW * CHUNK));
         }
     }
     // copy i of a group of a chunk (a wave with fewer copies than the groups have repeats its last one)
     __device__ __forceinline__ void issue(int i, int group, int chunk, uint32_t ring) const {
         if (!active) return;
         const uint32_t k = min((uint32_t)(group * NG + i), copies - 1u);
-        copy16(rows, voffset, first_byte + (uint32_t)(CHUNK * chunk), k * step, ring + (uint32_t)(chunk & 1) * BYTES + to + k * (R * CHUNK));
+        copy16(rows, voffset, min(first_byte + (uint32_t)(CHUNK * chunk) + k * step, rows[2]), ring + (uint32_t)(chunk & 1) * BYTES + to + k * (R * CHUNK));
     }
 };
 
@@ -130,7 +132,8 @@ struct ScaleChunkWindows {
     __device__ __forceinline__ static int patch_from(int nb) { return (nb - 6) / 8; }
 
     __device__ __forceinline__ void issue(int d, int chunk, uint32_t windows) const {
-        copy16(d < NSA ? a : w, voffset, first_byte + (uint32_t)(8 * Q * chunk), (uint32_t)((d < NSA ? d : d - NSA) * ROWS) * nb,
+        const buffer_t& rows = d < NSA ? a : w;
+        copy16(rows, voffset, min(first_byte + (uint32_t)(8 * Q * chunk) + (uint32_t)((d < NSA ? d : d - NSA) * ROWS) * nb, rows[2]),
                windows + (uint32_t)(chunk & 1) * BYTES + 16u * ((uint32_t)(d * NT) + wave_slot));
     }
     __device__ __forceinline__ void issue_chunk(int chunk, uint32_t windows) const {

@@ -24,7 +24,7 @@ struct Host {
     uint32_t lane = 0;
     int chunk = 0;                          // that copies belong to
     bool eager = false;                     // copies land as soon as they are issued, else in land()
-    long differ = 0;                        // words that copies of one chunk wrote from different places
+    long differ = 0, past = 0;              // words that copies of one chunk wrote from different places; lanes of copies with a scalar offset past the operand
 
     void reset(uint32_t bytes, bool eager_) {
         lds.assign(bytes, 0xA5);
@@ -43,6 +43,8 @@ struct Host {
         flying.erase(flying.begin(), flying.begin() + (long)n);
     }
     void copy(const buffer_t& b, uint32_t words, uint32_t voffset, uint32_t soffset, uint32_t lds_wave_base) {
+        // a word is in range where its lane's offset is below bytes - scalar offset, which is a number only up to the operand's end
+        past += soffset > b.bytes;
         for (uint32_t i = 0; i < words; ++i) {
             const bool in = soffset <= b.bytes && (uint64_t)voffset + 4 * i < b.bytes - soffset;
             const Write w = {lds_wave_base + 4 * words * lane + 4 * i, in ? b.base + soffset + voffset + 4 * i : nullptr, chunk};
@@ -60,8 +62,7 @@ extern Host host;
 inline void copy16(const buffer_t& b, uint32_t voffset, uint32_t soffset0, uint32_t soffset1, uint32_t lds_wave_base) {
     host.copy(b, 4, voffset, soffset0 + soffset1, lds_wave_base);
 }
-inline void copy4(const buffer_t& b, uint32_t voffset, uint32_t soffset0, uint32_t soffset1, uint32_t lds_wave_base) {
-    host.copy(b, 1, voffset, soffset0 + soffset1, lds_wave_base);
-}
+inline void copy16(const buffer_t& b, uint32_t voffset, uint32_t soffset, uint32_t lds_wave_base) { host.copy(b, 4, voffset, soffset, lds_wave_base); }
+inline void copy4(const buffer_t& b, uint32_t voffset, uint32_t soffset, uint32_t lds_wave_base) { host.copy(b, 1, voffset, soffset, lds_wave_base); }
 
 }  // namespace arcq

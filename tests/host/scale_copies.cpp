@@ -1,5 +1,6 @@
-// Runs the copies of scale bytes of the MXFP4 tiles (csrc/scale_chunks.h) on the host, lane by lane and in the order of the kernel's units, and
-// checks them: what lands is what the unit needs, and copies of one chunk never write one place from two.
+// Runs the copies of the MXFP4 tiles (csrc/scale_chunks.h, csrc/code_rows.h) on the host, lane by lane and in the order of the kernel's units, and
+// checks them: what lands is what the unit needs, copies of one chunk never write one place from two, scalar offsets stay within the operand.
+#include "code_rows.h"
 #include "scale_chunks.h"
 
 namespace arcq {
@@ -106,6 +107,31 @@ static void windows(const Problem& p, bool eager) {
     }
 }
 
+// codes of every unit, `column` bytes into the row as with whole rows, or in the lanes' offsets as with rows of any length
+template <int BM>
+static void codes(int rows, int more, int nb, bool whole) {
+    constexpr int NT = 256, ROWS = NT / 8;
+    const int M = BM + rows + more;
+    const uint32_t pitch = 16u * (uint32_t)nb;
+    const std::vector<uint8_t> a = operand(M, (int)pitch, 5u + (uint32_t)nb);
+    const CodeRows<ROWS> c(a.data(), M, BM, pitch);
+    for (int unit = 0; 8 * unit < nb; ++unit) {
+        host.reset(BM * 128, true);
+        for (uint32_t t = 0; t < NT; ++t)
+            for (int d = 0; d < BM / ROWS; ++d) {
+                const uint32_t last = (uint32_t)nb - 1u - 8u * (uint32_t)unit, piece = last < 7 ? min(t & 7u, whole ? 3u : last) : t & 7u;
+                host.lane = t & 63u;
+                c.issue(d, t / 8 * pitch + 16u * piece + (whole ? 0u : 128u * (uint32_t)unit), whole ? 128u * (uint32_t)unit : 0u,
+                        16u * ((uint32_t)(d * NT) + (t & ~63u)));
+            }
+        for (int r = 0; r < BM && BM + r < M; ++r)
+            for (int b = 0; b < 128 && 128 * unit + b < (int)pitch; ++b) {
+                wrong += host.lds[(size_t)(128 * r + b)] != a[(size_t)(BM + r) * pitch + 128 * unit + b];
+                ++checked;
+            }
+    }
+}
+
 template <int BM, int BN>
 static void tile(bool eager) {
     // rows of the tile, and tiles before it; the last tile of an operand whose rows end within it, and a whole one before others
@@ -115,6 +141,8 @@ static void tile(bool eager) {
             Problem p = {BM + s.a + s.more, BN + s.w + s.more, nb, BM, BN, 0, 0, {}, {}};
             p.a = operand(p.M, nb, 1u + (uint32_t)nb);
             p.w = operand(p.N, nb, 77u + (uint32_t)nb);
+            if (nb % 4 == 0) codes<BM>(s.a, s.more, nb, true), codes<BN>(s.w, s.more, nb, true);
+            codes<BM>(s.a, s.more, nb, false), codes<BN>(s.w, s.more, nb, false);
             const int units = (nb + 7) / 8;
             for (int u0 = 0; u0 < units; u0 += 3)
                 for (int u1 : {units, u0 + 1}) {
@@ -134,6 +162,6 @@ int main() {
         tile<192, 256>(eager);
         tile<256, 256>(eager);
     }
-    printf("checked %ld wrong %ld differ %ld\n", checked, wrong, host.differ);
+    printf("checked %ld wrong %ld differ %ld past %ld\n", checked, wrong, host.differ, host.past);
     return 0;
 }

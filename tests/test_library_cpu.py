@@ -327,6 +327,15 @@ def test_probe_argument_errors(name):
     assert probe(10, ctypes.c_void_p(0x10002), ctypes.byref(fl), None) == B.BAD_ALIGN
 
 
+def test_buffer_copy_argument_errors():
+    copy = B.lib().arcq_probe_buffer_copy
+    assert copy(FAKE, 64, 0, 2, FAKE, None) == B.INVALID_ARG
+    assert copy(FAKE, 64, 68, 4, FAKE, None) == B.INVALID_ARG                # a scalar offset past the buffer
+    assert copy(None, 64, 0, 4, FAKE, None) == B.INVALID_ARG and copy(FAKE, 64, 0, 4, None, None) == B.INVALID_ARG
+    assert copy(ctypes.c_void_p(0x10004), 64, 0, 4, FAKE, None) == B.BAD_ALIGN
+    assert copy(FAKE, 62, 0, 4, FAKE, None) == B.BAD_ALIGN and copy(FAKE, 64, 2, 4, FAKE, None) == B.BAD_ALIGN
+
+
 def test_ref_gemm_bf16_argument_errors():
     L = B.lib()
     assert L.arcq_ref_gemm_bf16(FAKE, FAKE, 8, 8, 48, FAKE, 8, None) == B.BAD_SHAPE          # K % 32

@@ -1,5 +1,5 @@
-"""The copies of scale bytes of the MXFP4 tiles, run on the host lane by lane (host/scale_copies.cpp): the header that the kernel includes,
-with the copies themselves recorded instead of done."""
+"""The copies of the MXFP4 tiles, run on the host lane by lane (host/scale_copies.cpp): the headers that the kernel includes, with the copies
+themselves recorded instead of done."""
 import os
 import re
 import shutil
@@ -18,7 +18,7 @@ def counts(tmp_path_factory):
     if not shutil.which("g++"):
         pytest.skip("no host compiler")
     out = tmp_path_factory.mktemp("scale_copies")
-    for name in ("scale_chunks.h",):                    # by themselves, so that they find the host's lds_dma.h
+    for name in ("scale_chunks.h", "code_rows.h"):      # by themselves, so that they find the host's lds_dma.h
         shutil.copy(os.path.join(CSRC, name), out)
     subprocess.run(["g++", "-std=c++17", "-O2", "-Wno-unknown-pragmas", f"-I{out}", f"-I{HOST}", os.path.join(HOST, "scale_copies.cpp"), "-o", out / "run"],
                    check=True, timeout=300)
@@ -34,3 +34,9 @@ def test_a_unit_finds_its_scale_bytes(counts):
 def test_copies_of_a_chunk_agree_where_they_overlap(counts):
     """Copies in flight land in no order that the program may rely on: two that write one place bring the same bytes."""
     assert counts["differ"] == 0
+
+
+def test_scalar_offsets_stay_within_the_operand(counts):
+    """A buffer's range check compares with its length less the scalar offset: rows past the edge of an operand, and chunks past the end of
+    its last row, must not make that negative."""
+    assert counts["past"] == 0
