@@ -886,7 +886,7 @@ __device__ __forceinline__ void transpose_scale_pairs(uint2 s, uint32_t& even_ch
 // weight tiles whose partial sums fit the static LDS limit at a time
 constexpr int skinny_batch(int mt, int nt, int waves) { return waves * mt * nt > 64 ? (nt + 1) / 2 : nt; }
 
-template <int MT, int NT, int WAVES, int U, bool GRP, bool ROLL, typename OutT>
+template <int MT, int NT, int WAVES, int U, bool GRP, bool ROLL, bool TWO_STEPS, typename OutT>
 __device__ __forceinline__ void skinny_tiles(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, int M, int N,
@@ -935,15 +935,26 @@ __device__ __forceinline__ void skinny_tiles(
         if constexpr (WIDE) { uint32_t o = codes; asm("" : "+v"(o)); return (o >> 3) + 6u * q; }
         else return scales;
     };
-    // byte `uniform` + `own` (a lane's) of a row; WIDE: rows come with a lane's place in a group of chunks, `place`, and the offset is opaque, so that no
-    // 64-bit address of a row is kept
-    auto in_row = [](const uint8_t* base, Row row, int64_t uniform, Offset own, uint32_t place) -> const uint8_t* {
+    // Byte `uniform` + `own` (a lane's) of a row.  Up to four tiles one sum for all rows, which has to be one: a sum that is used once is taken apart and added
+    // to every row in two steps (33 to 64 rows, one tile a wave, K' = 1056 to 2880: 4.43 and 4.32 us, 6.64 and 6.52).  TWO_STEPS: in two steps, where that is the
+    // faster one (gemm_skinny_kernel).  WIDE: rows come with a lane's place in a group of chunks, `place`, and the offset is opaque, so that no 64-bit
+    // address of a row is kept.
+    struct Parts { int64_t uniform; Offset own; };
+    using Byte = std::conditional_t<WIDE || TWO_STEPS, Parts, int64_t>;
+    auto byte_at = [](int64_t uniform, Offset own, uint32_t place) -> Byte {
+        if constexpr (WIDE) return Parts{uniform, own - place};
+        else if constexpr (TWO_STEPS) return Parts{uniform, own};
+        else return uniform + own;
+    };
+    auto in_row = [](const uint8_t* base, Row row, Byte at) -> const uint8_t* {
         if constexpr (WIDE) {
-            uint32_t offset = row + (own - place);
+            uint32_t offset = row + at.own;
             asm("" : "+v"(offset));
-            return base + uniform + offset;
+            return base + at.uniform + offset;
+        } else if constexpr (TWO_STEPS) {
+            return row + (at.uniform + at.own);
         } else {
-            return row + (uniform + own);
+            return row + at;
         }
     };
     float4v acc[MT][NT];
@@ -967,22 +978,22 @@ __device__ __forceinline__ void skinny_tiles(
     // save registers, which turns one trip to memory into three; the scheduling barriers behind the calls of
     // these functions keep the loads where they are written.)
     auto load_scales = [&](int g, Group& G) {
-        const int64_t so = 32 * (int64_t)g;
+        const Byte so = byte_at(32 * (int64_t)g, 8 * q, 8 * q);
 #pragma unroll
-        for (int r = 0; r < MT; ++r) G.sa2[r] = load8_a1(in_row(a_scales, scale_row(ac[r], as[r]), so, 8 * q, 8 * q));
+        for (int r = 0; r < MT; ++r) G.sa2[r] = load8_a1(in_row(a_scales, scale_row(ac[r], as[r]), so));
 #pragma unroll
-        for (int t = 0; t < NT; ++t) G.sw2[t] = load8_a1(in_row(base_s, scale_row(wc[t], ws[t]), so, 8 * q, 8 * q));
+        for (int t = 0; t < NT; ++t) G.sw2[t] = load8_a1(in_row(base_s, scale_row(wc[t], ws[t]), so));
     };
-    auto load_activations = [&](int g, int m, Group& G) {
-        const int64_t co = 256 * (int64_t)g + 64 * m;
+    auto load_activations = [&](Byte co, int m, Group& G) {
 #pragma unroll
-        for (int r = 0; r < MT; ++r) G.ca[LATE_A ? m & 1 : m][r] = load16_a8(in_row(a_codes, ac[r], co, 16 * q, 16 * q));
+        for (int r = 0; r < MT; ++r) G.ca[LATE_A ? m & 1 : m][r] = load16_a8(in_row(a_codes, ac[r], co));
     };
+    auto codes_at = [&](int g, int m) { return byte_at(256 * (int64_t)g + 64 * m, 16 * q, 16 * q); };
     auto load_codes = [&](int g, int m, Group& G, bool activations) {
-        const int64_t co = 256 * (int64_t)g + 64 * m;
-        if (activations) load_activations(g, m, G);
+        const Byte co = codes_at(g, m);
+        if (activations) load_activations(co, m, G);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) G.cw[m][t] = load16_a8(in_row(base_c, wc[t], co, 16 * q, 16 * q));
+        for (int t = 0; t < NT; ++t) G.cw[m][t] = load16_a8(in_row(base_c, wc[t], co));
     };
     auto load_group = [&](int g, Group& G) {
         load_scales(g, G);
@@ -1031,7 +1042,7 @@ __device__ __forceinline__ void skinny_tiles(
             if constexpr (LATE_A)
                 if (m < 2 || roll) {
                     __builtin_amdgcn_sched_barrier(0);
-                    load_activations(m < 2 ? g : next, (m + 2) & 3, G);
+                    load_activations(codes_at(m < 2 ? g : next, (m + 2) & 3), (m + 2) & 3, G);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             if (roll && (m & 1)) {
@@ -1051,16 +1062,16 @@ __device__ __forceinline__ void skinny_tiles(
         for (int u = 0; u < U; ++u) {
             const int b0 = 8 * (c0 + u) + 2 * q;
             const bool ok = b0 + 1 < nbk;
-            const Offset co = ok ? 8 * (Offset)b0 : 0, so = ok ? b0 : 0;
+            const Byte co = byte_at(0, ok ? 8 * (Offset)b0 : 0, 16 * q), so = byte_at(0, ok ? b0 : 0, 8 * q);
 #pragma unroll
             for (int r = 0; r < MT; ++r) {
-                T.ca[u][r] = load16_a8(in_row(a_codes, ac[r], 0, co, 16u * q));
-                T.sa[u][r] = load2_a1(in_row(a_scales, scale_row(ac[r], as[r]), 0, so, 8u * q));
+                T.ca[u][r] = load16_a8(in_row(a_codes, ac[r], co));
+                T.sa[u][r] = load2_a1(in_row(a_scales, scale_row(ac[r], as[r]), so));
             }
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                T.cw[u][t] = load16_a8(in_row(base_c, wc[t], 0, co, 16u * q));
-                T.sw[u][t] = load2_a1(in_row(base_s, scale_row(wc[t], ws[t]), 0, so, 8u * q));
+                T.cw[u][t] = load16_a8(in_row(base_c, wc[t], co));
+                T.sw[u][t] = load2_a1(in_row(base_s, scale_row(wc[t], ws[t]), so));
             }
         }
     };
@@ -1137,15 +1148,16 @@ __device__ __forceinline__ void skinny_tiles(
     if ((nbk & 1) != 0 && wave == WAVES - 1) {
         uint2 oa[MT], ow[NT];
         uint32_t osa[MT], osw[NT];
+        const Byte co = byte_at(8 * (int64_t)(nbk - 1), 0, 16 * q), so = byte_at(nbk - 1, 0, 8 * q);
 #pragma unroll
         for (int r = 0; r < MT; ++r) {
-            oa[r] = load8_a8(in_row(a_codes, ac[r], 8 * (int64_t)(nbk - 1), 0, 16u * q));
-            osa[r] = *in_row(a_scales, scale_row(ac[r], as[r]), nbk - 1, 0, 8u * q);
+            oa[r] = load8_a8(in_row(a_codes, ac[r], co));
+            osa[r] = *in_row(a_scales, scale_row(ac[r], as[r]), so);
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            ow[t] = load8_a8(in_row(base_c, wc[t], 8 * (int64_t)(nbk - 1), 0, 16u * q));
-            osw[t] = *in_row(base_s, scale_row(wc[t], ws[t]), nbk - 1, 0, 8u * q);
+            ow[t] = load8_a8(in_row(base_c, wc[t], co));
+            osw[t] = *in_row(base_s, scale_row(wc[t], ws[t]), so);
         }
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
@@ -1185,7 +1197,8 @@ __device__ __forceinline__ void skinny_tiles(
 
 constexpr int STREAM_ROUND = 256 * 64;      // weight rows of a round of this kernel: a workgroup of four tiles on every compute unit
 
-// BEHIND: weight tiles of the workgroups behind the first STREAM_ROUND weight rows; NT of all others
+// BEHIND: weight tiles of the workgroups behind the first STREAM_ROUND weight rows; NT of all others.  (With both, addresses in two steps: 32 x 28672 over
+// K' = 8464 42.1 us, 42.4 with one sum; 20 x 26000 38.5 and 38.8 to 39.1.  All others: one sum.)
 template <int MT, int NT, int BEHIND, int WAVES, int U, bool GRP, bool ROLL, typename OutT>
 __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales,
@@ -1195,15 +1208,15 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
     static_assert(BEHIND <= NT && sizeof(float) * FLOATS <= 64 * 1024, "partial tiles must fit the static LDS limit");
     __shared__ float red[FLOATS];
     if constexpr (BEHIND == NT) {
-        skinny_tiles<MT, NT, WAVES, U, GRP, ROLL>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, blockIdx.x * (16 * NT), red);
+        skinny_tiles<MT, NT, WAVES, U, GRP, ROLL, false>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, blockIdx.x * (16 * NT), red);
     } else {
         constexpr int FIRST = STREAM_ROUND / (16 * NT);
         static_assert(FIRST * 16 * NT == STREAM_ROUND, "whole workgroups first");
         if (blockIdx.x < FIRST)
-            skinny_tiles<MT, NT, WAVES, U, GRP, ROLL>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, blockIdx.x * (16 * NT), red);
+            skinny_tiles<MT, NT, WAVES, U, GRP, ROLL, true>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy, blockIdx.x * (16 * NT), red);
         else
-            skinny_tiles<MT, BEHIND, WAVES, U, GRP, ROLL>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy,
-                                                          STREAM_ROUND + (blockIdx.x - FIRST) * (16 * BEHIND), red);
+            skinny_tiles<MT, BEHIND, WAVES, U, GRP, ROLL, true>(a_codes, a_scales, w_codes, w_scales, M, N, nbk, alpha, y, ldy,
+                                                                STREAM_ROUND + (blockIdx.x - FIRST) * (16 * BEHIND), red);
     }
 }
 
