@@ -52,14 +52,13 @@ arcq_status arcq_ref_gemm_bf16(const void* x, const void* w, int64_t M, int64_t 
  * Which kernel a GEMM problem runs on: a function of its sizes alone (host only, nothing is launched).  Tests ask it, so that
  * a shape written for a tile cannot leave that tile unnoticed when the rule changes; not needed to call the library.
  * ahead: the weight-streaming kernel's waves ask for their next weights while they compute.
- * The streaming kernels' 64 columns stand for up to 112 where more than 16384 weight rows run in one launch of up to 32 rows (64, then 32 or
- * 48 in the second round, where registers allow no more).
+ * The streaming kernels' 64 columns stand for more where a wave takes more than four weight tiles (arcq_gemm_stream_tiles below).
  * arcq_gemm_route: operands whose scale bytes lie at odd addresses run another tile where the one named was taken for its modelled time (with
  * 65 to 128 rows the streaming kernel), and they, or K' < 256 off the grid of 64, have no 256 x 256 tiles and may run 192 x 256 or
  * 128 x 256 ones instead.  arcq_mx_gemm_route: such operands (or K' < 512 off the grid of 128) run 256-wide
  * or 128 x 128 tiles instead of 192 x 128 ones; with_workspace: as arcq_mx_gemm_ws (non-zero) or arcq_mx_gemm (0).
  */
-#define ARCQ_ROUTE_STREAM 0     /* weight-streaming kernel: tile_cols / 16 weight tiles per wave */
+#define ARCQ_ROUTE_STREAM 0     /* weight-streaming kernel: tile_cols / 16 weight tiles per wave, or more than four */
 #define ARCQ_ROUTE_KSPLIT 1     /* tiles whose waves split every stage along k */
 #define ARCQ_ROUTE_TILES 2      /* tiles, K' in `runs` runs across workgroups */
 #define ARCQ_ROUTE_DIRECT 3     /* plain kernel (K' < 128 off the streaming kernel, operands of 4 GiB and more) */
@@ -68,6 +67,13 @@ typedef struct {
 } arcq_route;
 arcq_status arcq_gemm_route(int64_t M, int64_t N, int64_t Kp, arcq_route* route);
 arcq_status arcq_mx_gemm_route(int64_t M, int64_t N, int64_t Kp, int with_workspace, arcq_route* route);
+/*
+ * Weight tiles of 16 rows that a wave takes in the launch that arcq_gemm_route / arcq_mx_gemm_route names, where that is a streaming kernel (else 0):
+ * up to seven where more than 16384 weight rows run in one launch of up to 32 rows.  behind: of the waves behind the first 16384 weight
+ * rows, fewer where registers allow no more than four in the first round; otherwise the same.
+ */
+arcq_status arcq_gemm_stream_tiles(int64_t M, int64_t N, int64_t Kp, int32_t* tiles, int32_t* behind);
+arcq_status arcq_mx_gemm_stream_tiles(int64_t M, int64_t N, int64_t Kp, int with_workspace, int32_t* tiles, int32_t* behind);
 /*
  * Problems whose last round of tiles would leave much of the chip idle run in two launches: the route above for whole rounds, and
  * this one for the last `rows` x `cols` of the output (0 x 0: there is no second launch; else one of the two is M or N).  Operands

@@ -63,6 +63,8 @@ SIGNATURES = {
     "arcq_mx_gemm_route": (ctypes.c_int, [_i64, _i64, _i64, ctypes.c_int, ctypes.POINTER(Route)]),
     "arcq_gemm_rest": (ctypes.c_int, [_i64, _i64, _i64, ctypes.POINTER(Rest)]),
     "arcq_mx_gemm_rest": (ctypes.c_int, [_i64, _i64, _i64, ctypes.c_int, ctypes.POINTER(Rest)]),
+    "arcq_gemm_stream_tiles": (ctypes.c_int, [_i64, _i64, _i64, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]),
+    "arcq_mx_gemm_stream_tiles": (ctypes.c_int, [_i64, _i64, _i64, ctypes.c_int, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]),
     "arcq_tile_order": (ctypes.c_int, [_i64, _i64, _vp, _vp]),
     "arcq_check_perm": (ctypes.c_int, [_vp, _i64, _vp, ctypes.POINTER(ctypes.c_int), _vp]),
 }
@@ -460,6 +462,20 @@ def arcq_mx_gemm_route(M, N, Kp, with_workspace=False):
     r = Route()
     _check(lib().arcq_mx_gemm_route(M, N, Kp, int(with_workspace), ctypes.byref(r)))
     return r.kernel, r.tile_rows, r.tile_cols, r.runs, r.ahead
+
+
+def arcq_gemm_stream_tiles(M, N, Kp):
+    """(weight tiles a wave takes, those of the waves behind the first 16384 weight rows) where arcq_gemm streams, else (0, 0); no GPU needed."""
+    tiles, behind = ctypes.c_int32(), ctypes.c_int32()
+    _check(lib().arcq_gemm_stream_tiles(M, N, Kp, ctypes.byref(tiles), ctypes.byref(behind)))
+    return tiles.value, behind.value
+
+
+def arcq_mx_gemm_stream_tiles(M, N, Kp, with_workspace=False):
+    """The same for arcq_mx_gemm, with or without a workspace."""
+    tiles, behind = ctypes.c_int32(), ctypes.c_int32()
+    _check(lib().arcq_mx_gemm_stream_tiles(M, N, Kp, int(with_workspace), ctypes.byref(tiles), ctypes.byref(behind)))
+    return tiles.value, behind.value
 
 
 def arcq_check_perm(perm):

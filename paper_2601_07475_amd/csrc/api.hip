@@ -206,6 +206,13 @@ arcq_status arcq_gemm_route(int64_t M, int64_t N, int64_t Kp, arcq_route* route)
     return fill_route(plan_gemm(M, N, Kp), route);
 }
 
+static arcq_status fill_tiles(const GemmPlan& p, int32_t* tiles, int32_t* behind) {
+    if (!tiles || !behind) return fail(ARCQ_INVALID_ARG, "null output pointer");
+    *tiles = p.kernel != ARCQ_ROUTE_STREAM ? 0 : p.tiles ? p.tiles : p.cols / 16;
+    *behind = p.behind ? p.behind : *tiles;
+    return ARCQ_OK;
+}
+
 static arcq_status fill_rest(const GemmParts& parts, int64_t M, int64_t N, arcq_rest* rest) {
     const bool two = parts.rows < M || parts.cols < N;
     rest->rows = !two ? 0 : parts.rows < M ? M - parts.rows : M;
@@ -218,6 +225,12 @@ arcq_status arcq_gemm_rest(int64_t M, int64_t N, int64_t Kp, arcq_rest* rest) {
     if (arcq_status st = check_gemm_shape(M, N, Kp)) return st;
     if (!rest) return fail(ARCQ_INVALID_ARG, "null output pointer");
     return fill_rest(plan_gemm_parts(M, N, Kp), M, N, rest);
+}
+
+arcq_status arcq_gemm_stream_tiles(int64_t M, int64_t N, int64_t Kp, int32_t* tiles, int32_t* behind) {
+    clear_error();
+    if (arcq_status st = check_gemm_shape(M, N, Kp)) return st;
+    return fill_tiles(plan_gemm(M, N, Kp), tiles, behind);
 }
 
 arcq_status arcq_tile_order(int64_t tiles_m, int64_t tiles_n, int32_t* rows, int32_t* cols) {
@@ -449,6 +462,12 @@ arcq_status arcq_mx_gemm_rest(int64_t M, int64_t N, int64_t Kp, int with_workspa
     if (arcq_status st = check_mx_gemm_shape(M, N, Kp)) return st;
     if (!rest) return fail(ARCQ_INVALID_ARG, "null output pointer");
     return fill_rest(plan_mx_gemm_parts(M, N, Kp, with_workspace != 0), M, N, rest);
+}
+
+arcq_status arcq_mx_gemm_stream_tiles(int64_t M, int64_t N, int64_t Kp, int with_workspace, int32_t* tiles, int32_t* behind) {
+    clear_error();
+    if (arcq_status st = check_mx_gemm_shape(M, N, Kp)) return st;
+    return fill_tiles(plan_mx_gemm(M, N, Kp, with_workspace != 0), tiles, behind);
 }
 
 arcq_status arcq_mx_gemm_ws(const uint8_t* a_codes, const uint8_t* a_scales, const uint8_t* w_codes, const uint8_t* w_scales,

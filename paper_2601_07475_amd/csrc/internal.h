@@ -46,7 +46,7 @@ arcq_status launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales,
 // every stage along k (NVFP4 only), the tiles whose waves do not, or the plain kernel for what those cannot address.
 struct GemmPlan {
     int kernel;         // ARCQ_ROUTE_*
-    int rows, cols;     // activation and weight rows of a workgroup's tile
+    int rows, cols;     // activation and weight rows of a workgroup's tile (ARCQ_ROUTE_STREAM: weight rows of up to four tiles, see `tiles`)
     int runs;           // runs of K' across workgroups (ARCQ_ROUTE_TILES)
     bool ahead;         // ARCQ_ROUTE_STREAM: a wave asks for its next group of chunks while it computes one
     int chunks = 1;     // ARCQ_ROUTE_STREAM: left-over chunks (behind the last group) that a wave takes at a time

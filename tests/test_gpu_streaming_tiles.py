@@ -9,13 +9,19 @@ from test_gpu_rounds import streamed
 pytestmark = pytest.mark.gpu
 
 
-# first and last weight rows of every number of tiles, in one round and in two; one group per wave and several, left-over chunks, odd block counts
-@pytest.mark.parametrize("M,N,nb", [(1, 16385, 32), (16, 17407, 257), (32, 20480, 129), (16, 20481, 255), (17, 24576, 192), (7, 24577, 353), (16, 28672, 529),
-                                    (32, 28672, 160), (18, 28671, 353), (32, 24577, 384), (31, 28672, 385), (20, 26000, 529), (2, 32769, 64),
-                                    (32, 40960, 71), (16, 40961, 65), (24, 57344, 33), (16, 57344, 97), (32, 57344, 385), (16, 57345, 64), (32, 16400, 1)])
-def test_more_weight_tiles_a_wave(M, N, nb):
+# first and last weight rows of every number of tiles, in one round and in two; one group per wave and several, left-over chunks, odd block counts; the weight
+# tiles a wave takes, and those of a wave behind the first round
+NVFP4 = [(1, 16385, 32, 5, 5), (16, 17407, 257, 5, 5), (32, 20480, 129, 5, 5), (16, 20481, 255, 6, 6), (17, 24576, 192, 6, 6),
+         (7, 24577, 353, 7, 7), (16, 28672, 529, 7, 7), (32, 28672, 160, 7, 7), (18, 28671, 353, 7, 7), (32, 24577, 384, 4, 3),
+         (31, 28672, 385, 4, 3), (20, 26000, 529, 4, 3), (2, 32769, 64, 5, 5), (32, 40960, 71, 5, 5), (16, 40961, 65, 6, 6),
+         (24, 57344, 33, 7, 7), (16, 57344, 97, 7, 7), (32, 57344, 385, 4, 4), (16, 57345, 64, 4, 4), (32, 16400, 1, 5, 5)]
+
+
+@pytest.mark.parametrize("M,N,nb,tiles,behind", NVFP4)
+def test_more_weight_tiles_a_wave(M, N, nb, tiles, behind):
     route = B.arcq_gemm_route(M, N, nb * 16)
     assert route[:4] == (B.ROUTE_STREAM, 16 if M <= 16 else 32, 64, 1) and B.arcq_gemm_rest(M, N, nb * 16) is None
+    assert B.arcq_gemm_stream_tiles(M, N, nb * 16) == (tiles, behind)
     streamed(M, N, nb, 16, lambda a, w, y: B.arcq_gemm(*a, 1.0, *w, 1.0, y=y))
 
 
@@ -30,12 +36,17 @@ def test_more_weight_tiles_a_wave_are_the_same_sum(M, N, nb):
         assert torch.equal(y[:, first:first + 12300], part)
 
 
-@pytest.mark.parametrize("M,N,nb", [(1, 16385, 16), (16, 17407, 129), (32, 20480, 67), (16, 20481, 131), (17, 24576, 130), (7, 24577, 145), (16, 28672, 66),
-                                    (32, 28672, 50), (18, 28671, 67), (32, 20481, 32), (20, 26000, 35), (2, 32769, 33), (32, 40960, 66), (16, 40961, 65),
-                                    (24, 36000, 17), (16, 57344, 50), (16, 57345, 33), (32, 16400, 1)])
-def test_more_mx_weight_tiles_a_wave(M, N, nb):
+MX = [(1, 16385, 16, 5, 5), (16, 17407, 129, 5, 5), (32, 20480, 67, 5, 5), (16, 20481, 131, 6, 6), (17, 24576, 130, 4, 2),
+      (7, 24577, 145, 7, 7), (16, 28672, 66, 7, 7), (32, 28672, 50, 4, 3), (18, 28671, 67, 4, 3), (32, 20481, 32, 4, 2),
+      (20, 26000, 35, 4, 3), (2, 32769, 33, 5, 5), (32, 40960, 66, 5, 5), (16, 40961, 65, 6, 6), (24, 36000, 17, 5, 5),
+      (16, 57344, 50, 7, 7), (16, 57345, 33, 4, 4), (32, 16400, 1, 5, 5)]
+
+
+@pytest.mark.parametrize("M,N,nb,tiles,behind", MX)
+def test_more_mx_weight_tiles_a_wave(M, N, nb, tiles, behind):
     route = B.arcq_mx_gemm_route(M, N, nb * 32)
     assert route[:4] == (B.ROUTE_STREAM, 16 if M <= 16 else 32, 64, 1) and B.arcq_mx_gemm_rest(M, N, nb * 32) is None
+    assert B.arcq_mx_gemm_stream_tiles(M, N, nb * 32) == (tiles, behind)
     streamed(M, N, nb, 32, lambda a, w, y: B.arcq_mx_gemm(*a, *w, y=y))
 
 

@@ -245,6 +245,38 @@ def test_gpu_shape_lists_reach_every_kernel():
     assert (True, True, 16, 16, 1, 0) in routes and (True, True, 16, 32, 1, 1) in routes and (True, True, 32, 16, 1, 1) in routes
 
 
+def test_stream_tiles():
+    t = ctypes.c_int32(0)
+    for fn, head in ((B.lib().arcq_gemm_stream_tiles, ()), (B.lib().arcq_mx_gemm_stream_tiles, (0,))):
+        assert fn(4, 8, 40, *head, ctypes.byref(t), ctypes.byref(t)) == B.BAD_SHAPE
+        assert fn(4, 8, 64, *head, None, ctypes.byref(t)) == B.INVALID_ARG and fn(4, 8, 64, *head, ctypes.byref(t), None) == B.INVALID_ARG
+    for seed, step, route, tiles in ((10, 16, B.arcq_gemm_route, B.arcq_gemm_stream_tiles), (11, 32, B.arcq_mx_gemm_route, B.arcq_mx_gemm_stream_tiles)):
+        streaming = 0
+        for M, N, Kp in random_sizes(seed, 10000, step):
+            kernel, _, cols, _, _ = route(M, N, Kp)
+            got = tiles(M, N, Kp)
+            if kernel != B.ROUTE_STREAM:
+                assert got == (0, 0)
+            elif N <= 16384 or M > 32 or N > 57344:
+                assert got == (cols // 16, cols // 16)
+            else:
+                assert got[0] in (4, 5, 6, 7) and cols == 64 and (got[1] == got[0] or got[0] == 4 and got[1] in (2, 3))
+            streaming += kernel == B.ROUTE_STREAM
+        assert streaming > 200
+
+
+def test_gpu_shape_lists_reach_every_number_of_weight_tiles():
+    """The lists of test_gpu_streaming_tiles.py: every kernel of more than four weight tiles a wave, of four and fewer behind them, and of four."""
+    import test_gpu_streaming_tiles as T
+    rows = lambda M: 1 if M <= 16 else 2
+    nvfp4 = {(rows(M), *B.arcq_gemm_stream_tiles(M, N, 16 * nb)) for M, N, nb, *_ in T.NVFP4}
+    assert nvfp4 == {(1, 4, 4), (1, 5, 5), (1, 6, 6), (1, 7, 7), (2, 4, 4), (2, 5, 5), (2, 6, 6), (2, 7, 7), (2, 4, 3)}
+    mx = {(rows(M), *B.arcq_mx_gemm_stream_tiles(M, N, 32 * nb)) for M, N, nb, *_ in T.MX}
+    assert mx == {(1, 4, 4), (1, 5, 5), (1, 6, 6), (1, 7, 7), (2, 5, 5), (2, 4, 2), (2, 4, 3)}
+    assert all(B.arcq_gemm_stream_tiles(M, N, 16 * nb) == (t, b) for M, N, nb, t, b in T.NVFP4)
+    assert all(B.arcq_mx_gemm_stream_tiles(M, N, 32 * nb) == (t, b) for M, N, nb, t, b in T.MX)
+
+
 def test_check_perm_argument_errors():
     r = ctypes.c_int(0)
     assert B.lib().arcq_check_perm(None, 16, FAKE, ctypes.byref(r), None) == B.INVALID_ARG
