@@ -785,7 +785,7 @@ static int mx_wide_rows(int64_t M, int64_t N) {
     return cost(256) <= cost(192) && cost(256) <= cost(128) ? 256 : cost(192) <= cost(128) ? 192 : 128;
 }
 
-static GemmPlan plan_mx_stream(int64_t M, int64_t N) {
+static GemmPlan plan_mx_stream(int64_t M, int64_t N, int64_t Kp) {
     // weight tiles per wave: as few as keep the launch at one workgroup per compute unit, up to four, two with more than 32
     // rows (measured with weights from HBM, 32 rows: 640 tiles 14.8 us with three per wave against 21.7 with one, 896 tiles
     // 10.4 us with four against 13.0 with two, 320 tiles over K' = 8448 11.2 us with two against 15.2 with one)
@@ -797,8 +797,12 @@ static GemmPlan plan_mx_stream(int64_t M, int64_t N) {
     // 11.4, 16 x 28672 over 5632 20.8 -> 17.5, 32 x 18944 over 2176 11.6 -> 8.7), up to 57344 in two (16 x 40960 over 4352 24.1 -> 21.4, 1 x 57344 over
     // 2176 17.7 -> 16.1).  Two row tiles leave the registers of five; up to 28672 weight rows the second round takes two or three tiles a wave instead
     // of four (32 x 22016 over 4352 18.7 -> 16.2, 32 x 28672 over 2176 12.2 -> 11.7).
+    // One tile behind two whole rounds of four, and from K' = 4096 on two, stay on four: the workgroup that has them costs less than a fifth tile in all
+    // others (four and five tiles a wave, 1 x 32769 over 4352 16.8 and 18.3, 1 x 32800 18.2 and 18.4, 32 x 32769 over 2176 14.3 and 15.4; 1 x 32785 over 2176
+    // 11.5 and 11.3, 1 x 32832 over 4352 20.1 and 18.4).
     const int rounds = tiles <= 7 * 256 ? 1 : 2;
-    if (mt <= 2 && tiles > 4 * 256 * rounds && tiles <= 7 * 256 * rounds) {
+    const int few = rounds == 1 ? 0 : Kp >= 4096 ? 2 : 1;
+    if (mt <= 2 && tiles > 4 * 256 * rounds + few && tiles <= 7 * 256 * rounds) {
         const int wide = (int)((tiles + 256 * rounds - 1) / (256 * rounds));
         if (mt == 1 || wide == 5) plan.tiles = plan.behind = wide;
         else if (rounds == 1) plan.behind = wide - 4;
@@ -809,7 +813,7 @@ static GemmPlan plan_mx_stream(int64_t M, int64_t N) {
 static GemmPlan plan_mx_one(int64_t M, int64_t N, int64_t Kp, bool workspace) {
     const int64_t nb = Kp >> 5;
     // up to 64 rows the tiled kernels only win where they can split K' across workgroups, which needs the workspace
-    if (mx_streaming_shape(M, N, Kp) || (M <= 64 && !workspace && mx_split_k(M, N, Kp) > 1)) return plan_mx_stream(M, N);
+    if (mx_streaming_shape(M, N, Kp) || (M <= 64 && !workspace && mx_split_k(M, N, Kp) > 1)) return plan_mx_stream(M, N, Kp);
     const bool offsets_fit = (uint64_t)M * (uint64_t)nb * 16 < 0xFFFF0000ull && (uint64_t)N * (uint64_t)nb * 16 < 0xFFFF0000ull;
     if (!offsets_fit || (nb < 8 && nb != 4)) return {ARCQ_ROUTE_DIRECT, 128, 128, 1, false};
     // more than 256 tiles of 128 x 128 but at most 256 of 192 x 128: one round of the taller tile instead of two
@@ -831,7 +835,7 @@ GemmParts plan_mx_gemm_parts(int64_t M, int64_t N, int64_t Kp, bool workspace) {
     const int64_t behind = N - MX_STREAM_ROUND;
     if (one.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= MX_STREAM_ROUND / 2 &&
         Kp >= (behind > MX_STREAM_ROUND / 4 ? 6144 : 4096)) {
-        GemmParts parts = {plan_mx_stream(M, MX_STREAM_ROUND), plan_mx_stream(M, behind), M, MX_STREAM_ROUND};
+        GemmParts parts = {plan_mx_stream(M, MX_STREAM_ROUND, Kp), plan_mx_stream(M, behind, Kp), M, MX_STREAM_ROUND};
         parts.rest.chunks = 1;      // K' in the order of four tiles a wave: the same bits as in one launch
         return parts;
     }

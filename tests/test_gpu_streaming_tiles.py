@@ -38,7 +38,7 @@ def test_more_weight_tiles_a_wave_are_the_same_sum(M, N, nb):
 
 MX = [(1, 16385, 16, 5, 5), (16, 17407, 129, 5, 5), (32, 20480, 67, 5, 5), (16, 20481, 131, 6, 6), (17, 24576, 130, 4, 2),
       (7, 24577, 145, 7, 7), (16, 28672, 66, 7, 7), (32, 28672, 50, 4, 3), (18, 28671, 67, 4, 3), (32, 20481, 32, 4, 2),
-      (20, 26000, 35, 4, 3), (2, 32769, 33, 5, 5), (32, 40960, 66, 5, 5), (16, 40961, 65, 6, 6), (24, 36000, 17, 5, 5),
+      (20, 26000, 35, 4, 3), (2, 32769, 33, 4, 4), (2, 32785, 33, 5, 5), (32, 40960, 66, 5, 5), (16, 40961, 65, 6, 6), (24, 36000, 17, 5, 5),
       (16, 57344, 50, 7, 7), (16, 57345, 33, 4, 4), (32, 16400, 1, 5, 5)]
 
 
