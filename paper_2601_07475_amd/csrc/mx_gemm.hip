@@ -395,16 +395,21 @@ __global__ __launch_bounds__(64 * GM * GN) void mx_gemm_staged_kernel(
         reg_issue(min(u0 + 1, nunit - 1));
         wait_lgkmcnt0();
     } else {
+        // Scale bytes go out first (1500 x 14336 over K' = 4320 74.7 us, 75.9 behind the first unit's codes), but with three ring slots and whole rows behind
+        // those: 128 x 128 tiles over short K' wait for little else (128 x 4096 over 512 4.55 -> 4.45 us together with the shares of issue_first).
+        constexpr bool CODES_FIRST = C::SCALES && !RAG && C::NUNIT == 3;
         if constexpr (RAG) {
             windows.issue_chunk(0, lds0);
             if (C::Windows::Q == 1) windows.issue_chunk(1, lds0);       // looked at in the first unit
-        } else if constexpr (C::SCALES) {
-            chunks.issue_first((uint32_t)lane, lds0);
         }
+        if constexpr (C::SCALES && !RAG && !CODES_FIRST) chunks.issue_first((uint32_t)lane, lds0);
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < 2; ++u) {
 #pragma unroll
             for (int d = 0; d < C::NDMA; ++d) issue_one(d, min(u0 + u, nunit - 1), u, lane_offset(min(u0 + u, nunit - 1)));
+            if constexpr (CODES_FIRST)
+                if (u == 0) chunks.issue_first((uint32_t)lane, lds0);
+        }
 #pragma unroll
         for (int i = 0; i < C::NG; ++i) chunks.issue(i, 0, 1, lds0);
         if constexpr (C::NWG > 0 && C::Windows::Q > 1) {

@@ -36,6 +36,7 @@ struct ScaleChunks {
     static constexpr int NG = copies_of_group(TA, TW, Q, WAVES);    // copies of a wave in each group
     static constexpr int WA = (TA + Q * NG - 1) / (Q * NG), WW = (TW + Q * NG - 1) / (Q * NG);      // waves with rows of A, of W
     static constexpr int NA = (TA + WA - 1) / WA, NW = (TW + WW - 1) / WW;          // copies of such a wave
+    static constexpr int SHARE = WAVES >= 2 * (WA + WW) && NA == NW ? 2 : 1;        // waves that share the first chunk's copies of a wave
     static constexpr int W_ROWS = WA * NA * R;                      // row that the W tile's rows start at
     static constexpr int BYTES = (W_ROWS + WW * NW * R) * CHUNK;
 
@@ -44,6 +45,7 @@ struct ScaleChunks {
     uint32_t step, first_byte;
     uint32_t to, copies;        // this wave's place in a chunk, and its copies
     bool active;                // whether it has any
+    uint32_t share;             // of the first chunk
 
     // Words of a row are exchanged by the row's number, so that the eight bytes of 32 rows, which an instruction reads, are on more different banks
     // (8192 x 8192 over K' = 29696, all rows alike 1068 us, every other eight rows exchanged 1012).
@@ -56,6 +58,8 @@ struct ScaleChunks {
     __device__ __forceinline__ ScaleChunks(const uint8_t* a, const uint8_t* w, int M, int N, int nb, int m0, int n0, uint32_t lane, uint32_t wave,
                                            int first_byte_) : step((uint32_t)(R * nb)), first_byte((uint32_t)first_byte_) {
         active = WA + WW == WAVES || wave < (uint32_t)(WA + WW);
+        share = SHARE > 1 && !active ? 1u : 0u;
+        if (SHARE > 1) wave %= (uint32_t)(WA + WW);
         const bool of_a = wave < (uint32_t)WA;
         copies = of_a ? NA : NW;
         const uint32_t in_tile = of_a ? wave * (NA * R) : (wave - WA) * (NW * R);
@@ -65,16 +69,19 @@ struct ScaleChunks {
         rows = buffer_of((of_a ? a : w) + min(start, bytes), bytes - min(start, bytes));
         voffset = lane / LANES * (uint32_t)nb + 16u * (lane % LANES ^ exchanged(lane / LANES));
     }
-    // the first chunk, in words
+    // The first chunk, in words, of which waves without rows take a share (128 x 128 tiles: eight copies a wave instead of sixteen for half of the waves,
+    // each behind four to seven scalar instructions).
     __device__ __forceinline__ void issue_first(uint32_t lane, uint32_t ring) const {
-        if (!active) return;
+        if (SHARE == 1 && !active) return;
         constexpr int WORDS = CHUNK / 4, RW = 64 / WORDS;           // lanes of a row, rows of a copy: 8 and 8, 4 and 16
+        constexpr int MOST = (NA > NW ? NA : NW) * R / RW / SHARE;
+        static_assert(MOST % 2 == 0, "a share begins with an even copy");
         const uint32_t row = lane / WORDS, word = lane % WORDS;
         const uint32_t even = row * (step / R) + 4u * word, odd = row * (step / R) + 4u * (word ^ (LANES == 2 ? 4u : 0u));
         const uint32_t all = copies * (R / RW);                     // (a wave with fewer than the others repeats its last two, which are unlike each other)
 #pragma unroll
-        for (int k = 0; k < (NA > NW ? NA : NW) * R / RW; ++k) {
-            const uint32_t i = min((uint32_t)k, all - 2u + (k & 1));
+        for (int k = 0; k < MOST; ++k) {
+            const uint32_t i = NA == NW ? MOST * share + k : min((uint32_t)k, all - 2u + (k & 1));
             copy4(rows, k & 1 ? odd : even, min(first_byte + i * (RW * (step / R)), rows[2]), ring + to + i * (RW * CHUNK));
         }
     }
