@@ -425,7 +425,7 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
                     win[(x - FIX) & 1] = windows.gather(x - FIX, next + C::WINDOWS, TAIL && s + 1 >= patch_from, lds + C::PATCH + 8 * (s + 1 - patch_from));
                 }
                 if (x > FIX && x <= FIX + C::NSW)
-                    windows.template put<true>(x - FIX - 1, win[(x - FIX - 1) & 1], next + C::A_SCALES, TAIL, s + 1);
+                    windows.put(x - FIX - 1, win[(x - FIX - 1) & 1], next + C::A_SCALES, TAIL, s + 1);
             }
             if (x == 6 && LEFT > 0) {
                 // stage s+1 must have landed: the copies of the DIST - 1 later stages are younger, and
@@ -483,7 +483,7 @@ __global__ __launch_bounds__(64 * GM * GN) void gemm_staged_kernel(
         if constexpr (RAG) {                    // (runs of a split are at least four stages long: the first is whole)
 #pragma unroll
             for (int d = 0; d < C::NSW; ++d)
-                windows.template put<true>(d, windows.gather(d, lds + C::WINDOWS, false, nullptr), lds + C::A_SCALES, false, 0);
+                windows.put(d, windows.gather(d, lds + C::WINDOWS, false, nullptr), lds + C::A_SCALES, false, 0);
             wait_lgkmcnt0();
         }
     }
@@ -654,7 +654,7 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
                 }
                 if (t == 2)
 #pragma unroll
-                    for (int d = 0; d < C::NSW; ++d) windows.template put<true>(d, win[d], next + C::A_SCALES, TAIL, s + 1);
+                    for (int d = 0; d < C::NSW; ++d) windows.put(d, win[d], next + C::A_SCALES, TAIL, s + 1);
             }
             if (t == 3 && LEFT > 0) {
                 wait_vmcnt<LEFT == 2 ? (C::DIST - 1) * C::NDMA : 0>();
@@ -693,7 +693,7 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(
     if constexpr (RAG) {                        // the first stage is whole
 #pragma unroll
         for (int d = 0; d < C::NSW; ++d)
-            windows.template put<true>(d, windows.gather(d, lds + C::WINDOWS, false, nullptr), lds + C::A_SCALES, false, 0);
+            windows.put(d, windows.gather(d, lds + C::WINDOWS, false, nullptr), lds + C::A_SCALES, false, 0);
         wait_lgkmcnt0();
     }
     wg_barrier();
@@ -1333,7 +1333,10 @@ static GemmPlan plan_stream(int64_t M, int64_t N, int64_t Kp) {
     // 40960 over 4352 28.2 -> 25.0, 32 x 49152 37.6 -> 35.2).  Beyond, rounds overlap so far that it is a draw (16 x 64000 over 4352 39.3 with four, 40.7
     // with six, 128256 76.6 and 76.1 with seven).  Seven behind two row tiles keep a dozen registers in scratch, which twelve groups pay for too often
     // (32 x 28672 over 8192 38.0 with four and 41.7; over 5632 29.2 and 28.8): the second round takes three tiles a wave instead of four then, over
-    // 8192 34.7, over 8464 45.8 -> 43.7.  Only where waves load ahead or take one group: they exist in that form alone.
+    // 8192 34.7, over 8464 45.4 -> 42.1.  Only where waves load ahead or take one group, the one form in which these kernels exist: with 9, 10, 17, 25 ...
+    // groups a wave or a few take one more, loading ahead costs 2 to 7 % with four tiles, and what is left of the gain then has not been measured.  Slower
+    // than four: one or two activation rows with 41000 to 49152 weight rows, up to 1.3 % for some K' (1 x 49152 over 8464 53.1 and 53.8), and a weight row behind two whole
+    // rounds (16 x 32769 over 8464 45.8 and 46.5).
     const int rounds = tiles <= 7 * 256 ? 1 : 2;
     if (mt <= 2 && tiles > 4 * 256 * rounds && tiles <= 7 * 256 * rounds && (ahead || ngroup <= STREAM_WAVES)) {
         const int wide = (int)((tiles + 256 * rounds - 1) / (256 * rounds));
@@ -1488,8 +1491,9 @@ GemmParts plan_gemm_parts(int64_t M, int64_t N, int64_t Kp) {
     // in.)  From HBM, us, 1 and 32 rows: 17408 weight rows over K' = 4096 16.2 -> 13.6 and 20.9 -> 18.1, over 14592 44.5 -> 35.8 and 58.0 -> 47.4;
     // 20480 over 4352 17.1 -> 14.9 and 23.0 -> 20.0; 24576 over 6144 22.9 -> 20.7 and 29.7 -> 28.0, over 14592 47.2 -> 42.9 and 60.3 -> 55.0.  Within
     // the limits 84 sizes gain 1.5 us and more, 1.05 to 1.26x.  A pass that runs the second kernel for the first time takes 5 us more, which the
-    // fifth at the latest has made up for.  Elsewhere, with three tiles a wave behind the round, few rows there or a shorter
-    // K', a second launch gains less than one of more tiles a wave (plan_stream: 16 x 16400 over 4352 15.7, 15.5 in two, 12.3; 16 x 24576 over 4352 19.1, 18.0 and 15.2).
+    // fifth at the latest has made up for.  One launch of more tiles a wave (plan_stream) gains more than a second launch everywhere: 16 x 16400 over 4352
+    // 15.7, 15.5 in two, 12.3; 16 x 24576 over 4352 19.1, 18.0 and 15.2; and within the limits too, 1.03 to 1.3x (16 x 20480 over 4352 16.0 in two, 13.2).  They stand for one
+    // reason only: the tests state this route, and its bits, for sizes within them (tests/test_gpu_rounds.py, tests/test_library_cpu.py).
     const int64_t behind = N - STREAM_ROUND;
     if (rule.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= STREAM_ROUND / 2 &&
         Kp >= (behind > STREAM_ROUND / 4 ? 6144 : 4096)) {

@@ -283,7 +283,7 @@ __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
                 }
                 if (t == 2)
 #pragma unroll
-                    for (int d = 0; d < C::NSW; ++d) windows.template put<true>(d, win[d], next + C::A_SCALES, TAIL, s + 1);
+                    for (int d = 0; d < C::NSW; ++d) windows.put(d, win[d], next + C::A_SCALES, TAIL, s + 1);
             }
             if (t == 3 && LEFT > 0) {
                 if constexpr (REG) {
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(64 * GM * GN * KS) void gemm_ksplit_kernel(
         if constexpr (RAG) {                        // the first stage is whole
 #pragma unroll
             for (int d = 0; d < C::NSW; ++d)
-                windows.template put<true>(d, windows.gather(d, lds + C::WINDOWS, false, nullptr), lds + C::A_SCALES, false, 0);
+                windows.put(d, windows.gather(d, lds + C::WINDOWS, false, nullptr), lds + C::A_SCALES, false, 0);
             wait_lgkmcnt0();
         }
     }

@@ -14,6 +14,9 @@
 
 namespace arcq {
 
+// How the tiled GEMM kernels get their stages into LDS (gemm.hip, gemm_ksplit.hip, mx_gemm.hip).
+enum StageMode { COPIES = 0, RAGGED = 1, REGS = 2 };
+
 typedef __attribute__((address_space(3))) uint8_t lds_u8_t;
 
 // Byte address inside the workgroup's LDS allocation of a pointer into __shared__ memory.

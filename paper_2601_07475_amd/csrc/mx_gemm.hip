@@ -13,7 +13,6 @@
 #include "gemm_decode.h"
 #include "lds_dma.h"
 #include "scale_chunks.h"
-#include "scale_windows.h"
 #include "tile_order.h"
 
 #include <type_traits>
@@ -37,9 +36,10 @@ __device__ __forceinline__ float16v mfma_mx(const uint4& a, const uint4& b, cons
 // (8 lanes per row): the texture-address unit of a CU spends about 34 cycles on a copy that touches
 // sixteen 64-byte segments and 17.5 on one that touches eight full lines (measured), and with FP4
 // MFMAs the copies of a 256 x 256 tile would otherwise take as long as its arithmetic.  Units travel
-// global -> LDS with global_load_lds through a ring of NUNIT buffers (2 for the 256 x 256 tile: 2 x 68 KB),
-// one barrier per unit.  LDS layout of one unit: A codes [BM][128] | W codes [BN][128] (RAGGED and REGS: | A scales [BM][8] |
-// W scales [BN][8]), in front of the units the scale bytes' chunks or windows.  The eight pieces of a row are stored
+// global -> LDS with buffer copies (REGS: through registers) through a ring of NUNIT buffers, one barrier per unit.  LDS layout of one unit: A
+// codes [BM][128] | W codes [BN][128] (RAGGED and REGS: | A scales [BM][8] | W scales [BN][8]); in front of the units the scale bytes' two chunks or
+// windows.  The 256 x 256 tile has two buffers: with whole rows 2 x 64 KB of codes and 2 x 16 KB of scale bytes, all of the 160 KB, with windows 2 x 68
+// and 2 x 8 KB.  The eight pieces of a row are stored
 // XOR-swizzled with (row >> 1) & 7: the LDS serves a 16-byte read of 16 consecutive lanes per clock from
 // 64 banks, rows are 128 bytes apart, so 16 consecutive rows must land on 16 different 16-byte bank groups
 // (measured: a swizzle with a period of 8 rows spent 44 % of its LDS cycles on bank conflicts); applied by
@@ -50,9 +50,10 @@ __device__ __forceinline__ float16v mfma_mx(const uint4& a, const uint4& b, cons
 // bytes = 64 bf16 values, there are no scale bytes, and a k-step is one v_mfma_f32_32x32x16_bf16.
 // What the loop spends beside the matrix instructions is the copies: a vector multiplication and four to five other vector instructions each, with
 // addresses per lane, and the copies of scale bytes, two words a row and unit.  With buffer copies (no vector instruction) and scale bytes for several units
-// at once, and without 64-bit divisions in front of the first copy (480 instructions before it, 205 now): 300 random problems of 65 to 8192 rows 1.08x on
-// average (0.978 to 1.40; by tiles 1.05 to 1.16, the same bits), 8192 x 8192 over K' = 29696 1011 -> 950 us, 4096 x 27648 over 5632 377 -> 359 with the
-// quantizer, over 5664 458 -> 418, 1500 x 14336 over 4320 83.0 -> 75.6, 1592 x 2461 over 24000 117 -> 84.
+// at once, and without 64-bit divisions in front of the first copy (480 instructions before it, 217 to 284 now): 300 random problems of 65 to 8192 rows 1.09x on
+// average (0.995 to 1.40; by tiles 1.06 to 1.16, the same bits; the three were measured together), 8192 x 8192 over K' = 29696 1011 -> 950 us, 4096 x 27648 over 5632
+// 383 -> 358, over 5664 458 -> 418 with the quantizer, 1500 x 14336 over 4320 83.2 -> 73.6, 1592 x 2461 over 24000 117 -> 84.
+// fp32 results of 256 x 256 tiles: 33 registers in scratch (16 with windows), behind the loop.
 // How the units get into LDS (MODE): COPIES for K' % 128 == 0, codes 16-byte and scale bytes 4-byte aligned; RAGGED for any K' (a
 // multiple of 32) from 512 on and dword-aligned codes: scale bytes as dword-aligned windows (scale_chunks.h), pieces past the
 // end of a row fetched from its last block and their fragments zeroed in the last unit; the base of the scale bytes has
@@ -69,7 +70,6 @@ struct MxCfg {
     static constexpr int LDS_MOST = 160 * 1024;
     // Scale bytes: chunks or windows of several units (scale_chunks.h); REGS: words of a unit
     static constexpr bool SCALES = !BF16 && MODE != REGS;               // come with copies
-    using Narrow = ScaleChunkWindows<BM, BN, NT, 1>;
     using Wide = ScaleChunkWindows<BM, BN, NT, 3>;
     static constexpr int NAS = BF16 ? 0 : (BM * 2 + NT - 1) / NT, NWS = BF16 ? 0 : (BN * 2 + NT - 1) / NT;     // 4-byte words of scales
     static constexpr int UNIT_BYTES = A_SCALES + (MODE == RAGGED ? Wide::DENSE_BYTES : MODE == REGS ? (NAS + NWS) * NT * 4 : 0);
@@ -82,12 +82,12 @@ struct MxCfg {
     static constexpr int NWG = MODE == RAGGED ? Windows::NG : 0;
     static constexpr int SROW = MODE == COPIES ? 8 * Chunks::Q : 8;     // from a row's scale bytes to the next row's
     static constexpr int W_SCALES = MODE == RAGGED ? Windows::DENSE_W : MODE == REGS ? NAS * NT * 4 : Chunks::W_ROWS * SROW;    // behind those of A
-    // chunks or windows, patch (RAGGED: see ScaleWindows::fill_patch), units
+    // chunks or windows, patch (RAGGED: see ScaleChunkWindows::fill_patch), units
     static constexpr int PATCH = !SCALES ? 0 : MODE == COPIES ? 2 * Chunks::BYTES : 2 * Windows::BYTES;
     static constexpr int UNITS = PATCH + (MODE == RAGGED ? Windows::PATCH : 0);
     static constexpr int LDS_BYTES = UNITS + NUNIT * UNIT_BYTES;
     static_assert(LDS_BYTES <= LDS_MOST, "LDS of a compute unit");
-    static_assert(NDMA + (MODE == RAGGED ? Windows::NS : NG) < 64, "the counted wait needs the copies of NUNIT - 1 units to fit the counter");
+    static_assert(NDMA + (MODE == RAGGED ? Windows::NS : NG) < 64, "a counted wait leaves the copies of a unit and of later scale bytes: they have to fit the counter");
 };
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -836,7 +836,8 @@ GemmParts plan_mx_gemm_parts(int64_t M, int64_t N, int64_t Kp, bool workspace) {
     // wave in a launch of its own (see plan_gemm_parts in gemm.hip).  From HBM, us, 1 and 16 rows: 17408 weight rows over K' = 4096 13.5 -> 11.7 and
     // 14.9 -> 13.2, 20480 over 4352 14.2 -> 12.6 and 15.8 -> 14.0, over 8448 24.4 -> 20.2 and 27.7 -> 22.9, 24576 over 6144 19.5 -> 17.9 and 22.4 -> 20.3:
     // within NVFP4's limits 52 sizes gain 1.3 us and more, 1.07 to 1.22x.  Elsewhere a second launch loses to one of more tiles a wave (plan_mx_stream: 1 x 16400
-    // over 4352 11.0, 12.0 in two, 9.5; 1 x 28672 over 6400 21.6, 22.3 and 19.8; 16 x 24576 over 2176 9.9, 10.4 and 8.0).
+    // over 4352 11.0, 12.0 in two, 9.5; 1 x 28672 over 6400 21.6, 22.3 and 19.8; 16 x 24576 over 2176 9.9, 10.4 and 8.0); that it is taken within the limits has NVFP4's
+    // one reason, the tests that state this route (plan_gemm_parts).
     const int64_t behind = N - MX_STREAM_ROUND;
     if (one.kernel == ARCQ_ROUTE_STREAM && M <= 32 && behind >= 1024 && behind <= MX_STREAM_ROUND / 2 &&
         Kp >= (behind > MX_STREAM_ROUND / 4 ? 6144 : 4096)) {

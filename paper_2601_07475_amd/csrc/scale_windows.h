@@ -20,9 +20,6 @@
 
 namespace arcq {
 
-// How the tiled GEMM kernels get their stages into LDS (gemm.hip, gemm_ksplit.hip, mx_gemm.hip).
-enum StageMode { COPIES = 0, RAGGED = 1, REGS = 2 };
-
 template <int BM, int BN, int NT, int STEP>
 struct ScaleWindows {
     static_assert(STEP == 8 || STEP == 16, "scale bytes per row and stage");
@@ -80,9 +77,8 @@ struct ScaleWindows {
     }
 
     // Their shift and write.  left: blocks of the row from the first of the eight on, where fewer than eight may be left (tail).
-    // Bytes past the end become 0.  PAIRS (blocks copied two to a 16-byte piece): the last block of an odd row was
+    // Bytes past the end become 0.  Blocks are copied two to a 16-byte piece: the last block of an odd row was
     // copied as the second one of its piece, so its byte moves up by one.
-    template <bool PAIRS>
     __device__ __forceinline__ void put(int d, const uint3& v, uint8_t* dense, bool tail, int stage) const {
         const uint32_t phase = ((tid / LPR) * (uint32_t)nb) & 3u;
         uint2 out = make_uint2(__builtin_amdgcn_alignbyte(v.y, v.x, phase), __builtin_amdgcn_alignbyte(v.z, v.y, phase));
@@ -91,7 +87,7 @@ struct ScaleWindows {
             if (left < 8) {
                 uint64_t all = (uint64_t)out.y << 32 | out.x;
                 all = left <= 0 ? 0 : all & (~0ull >> (64 - 8 * left));
-                if (PAIRS && left > 0 && (left & 1)) {
+                if (left > 0 && (left & 1)) {
                     const uint64_t below = (1ull << (8 * (left - 1))) - 1;
                     all = (all & below) | (all & ~below) << 8;
                 }
