@@ -1,7 +1,8 @@
 /*
  * arcq_bench.h -- measurement aids of libarcq (no part of the ARCQuant method; see arcq.h for the method's calls):
  * the matrix-rate probes that give the ceiling a GEMM's roofline fraction is read against on a given machine, and
- * the hand-written bf16 GEMM the quantized linear layer is timed against.  Same conventions as arcq.h: device
+ * the hand-written bf16 GEMM the quantized linear layer is timed against; and what tests ask of the library: routes, tiles,
+ * the end of a buffer copy.  Same conventions as arcq.h: device
  * pointers owned by the caller, work enqueued on `stream`, status codes, arcq_last_error().
  */
 #ifndef ARCQ_BENCH_H
